@@ -1,0 +1,216 @@
+// Per-chunk kernel of the fp32 path (prefill of fp32 inputs and backward pass): everything of a chunk that does
+// not depend on the state, one workgroup of four waves per (chunk, head).
+//
+//   A[r,i] = sum_d k_r,d k_i,d e^(G_r,d - G_i,d), i < r     P[r,i] likewise with q_r, i <= r
+//   Q = A (I + Diag(beta) A)^-1
+//
+// With Y = V - (Gamma.K) S0, the residual R = V - S^T k of the delta rule obeys (I + A Diag(beta)) R = Y, and
+// (I + A Diag(beta))^-1 = I - Q Diag(beta), (I + Diag(beta) A)^-1 = I - Diag(beta) Q with the same Q: the walks
+// (kda_f32_walk.hip) need one C x C matrix for both directions, and no division by beta appears anywhere.
+#include "kda_f32_tile.h"
+
+namespace kda {
+namespace f32 {
+
+constexpr int kPrepThreads = 256;
+constexpr size_t kPrepLds = (size_t)(3 * kC * kLdT + kTri * 64 + kC) * 4;
+
+// Four waves; the channels are taken 64 at a time, 16 per wave.  LDS: Kp = k 2^(G - pref), Qp = q 2^(G - pref) and
+// Kn = k 2^(nref - G) of those 64 channels, 52 KiB, so that two workgroups share a compute unit.
+template <typename Tin, int D>
+__global__ __launch_bounds__(kPrepThreads, 2)
+void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, const Tin *__restrict__ log_alpha,
+                         const Tin *__restrict__ beta, float *__restrict__ slots, const Problem p)
+{
+    using SL = Slot<D>;
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    float *sKp = smem, *sQp = sKp + kC * kLdT, *sKn = sQp + kC * kLdT;
+    float *sF = sKn + kC * kLdT;                             // [kTri][64]: decay between the blocks of a pair
+    float *sBeta = sF + kTri * 64;
+
+    Chunk c;
+    if (!locate(p.cu, p.num_seqs, p.T, p.H, p.chunks_per_seq, blockIdx.x, c)) return;
+    const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t stride = (int64_t)p.H * D, base = (c.tok0 * p.H + c.h) * (int64_t)D + m;
+    float *slot = slots + c.slot * SL::kFloats;
+    if (tid < kC) sBeta[tid] = tid < c.nv ? load_as_float(beta + (c.tok0 + tid) * p.H + c.h) : 0.f;
+
+    // tiles of A (u < 10) and P (u >= 10), five per wave
+    f32x4 acc[5] = {};
+    auto block_of = [](int b, int &R, int &I) { R = b >= 6 ? 3 : b >= 3 ? 2 : b >= 1 ? 1 : 0; I = b - tri(R, 0); };
+    bool strong = false;
+#pragma unroll 1
+    for (int hf = 0; hf < D / 64; ++hf) {
+        const int t = 4 * hf + w;
+        f32x4 kk[4], qq[4];
+        Decay d;
+        load_tile(d.G, log_alpha + base + 16 * t, stride, c.nv, g);
+        load_tile(kk, k + base + 16 * t, stride, c.nv, g);
+        load_tile(qq, q + base + 16 * t, stride, c.nv, g);
+        running_decay(d, lane);
+        strong |= d.strong;
+        if (hf) lds_barrier();                               // the previous channels' tiles are read
+        const float GC = d.E[3];
+#pragma unroll
+        for (int R = 0; R < 4; ++R) {
+            const f32x4 gam = exp2_4(d.G[R]);
+            float *frag = slot + (R * SL::kTiles + t) * kFrag + 4 * lane;
+            st4(frag + SL::kKg, kk[R] * gam);
+            st4(frag + SL::kQg, qq[R] * gam);
+            st4(frag + SL::kKt, kk[R] * exp2_4(GC - d.G[R]));
+            const f32x4 pf = exp2_4(d.G[R] - d.pref[R]), nf = exp2_4(d.nref[R] - d.G[R]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int at = (16 * R + 4 * g + j) * kLdT + 16 * w + m;
+                sKp[at] = kk[R][j] * pf[j];
+                sQp[at] = qq[R][j] * pf[j];
+                sKn[at] = kk[R][j] * nf[j];
+            }
+        }
+        if (g == 0) {
+            slot[SL::kGc + 16 * t + m] = fast_exp2(GC);
+#pragma unroll
+            for (int R = 0; R < 4; ++R)
+#pragma unroll
+                for (int I = 0; I <= R; ++I)
+                    sF[tri(R, I) * 64 + 16 * w + m] = I == R ? d.fdiag[R] : fast_exp2(d.pref[R] - d.nref[I]);
+        }
+        lds_barrier();
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            const int u = w + 4 * i, b = u < 10 ? u : u - 10;
+            int R, I;
+            block_of(b, R, I);
+            const float *pa = (u < 10 ? sKp : sQp) + (16 * R + m) * kLdT + 4 * g, *pb = sKn + (16 * I + m) * kLdT + 4 * g;
+            const float *pF = sF + b * 64 + 4 * g;
+#pragma unroll
+            for (int kt = 0; kt < 4; ++kt) acc[i] = mfma16(ld4(pa + 16 * kt), ld4(pb + 16 * kt) * ld4(pF + 16 * kt), acc[i]);
+        }
+    }
+    if (__syncthreads_or(strong)) {
+        // strong channels inside the diagonal blocks, pair by pair in the log domain (any decay)
+#pragma unroll 1
+        for (int hf = 0; hf < D / 64; ++hf) {
+            const int t = 4 * hf + w;
+            f32x4 kk[4], qq[4];
+            Decay d;
+            load_tile(d.G, log_alpha + base + 16 * t, stride, c.nv, g);
+            load_tile(kk, k + base + 16 * t, stride, c.nv, g);
+            load_tile(qq, q + base + 16 * t, stride, c.nv, g);
+            running_decay(d, lane);
+            __syncthreads();
+#pragma unroll
+            for (int R = 0; R < 4; ++R) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int at = (16 * R + 4 * g + j) * kLdT + 16 * w + m;
+                    sKp[at] = kk[R][j]; sQp[at] = qq[R][j]; sKn[at] = d.G[R][j];
+                }
+                if (g == 0) sF[tri(R, R) * 64 + 16 * w + m] = d.fdiag[R];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 5; ++i) {
+                const int u = w + 4 * i, b = u < 10 ? u : u - 10;
+                int R, I;
+                block_of(b, R, I);
+                if (R != I) continue;
+                const float *row = u < 10 ? sKp : sQp;
+                for (int ch = 0; ch < 64; ++ch) {
+                    if (sF[b * 64 + ch] != 0.f) continue;
+                    const int ci = (16 * R + m) * kLdT + ch;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int ri = (16 * R + 4 * g + j) * kLdT + ch;
+                        acc[i][j] = fmaf(row[ri] * sKp[ci], fast_exp2(fminf(sKn[ri] - sKn[ci], 0.f)), acc[i][j]);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // A as [64][kLdT] (strict lower; the diagonal blocks' upper parts are zero), P straight to the slot
+    float *sA = sKp, *sQ = sQp;
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        const int u = w + 4 * i, b = u < 10 ? u : u - 10;
+        int R, I;
+        block_of(b, R, I);
+        if (R == I) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (m > 4 * g + j || (u < 10 && m == 4 * g + j)) acc[i][j] = 0.f;
+        }
+        if (u >= 10) st4(slot + SL::kP + b * kFrag + 4 * lane, acc[i]);
+        else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) sA[(16 * R + 4 * g + j) * kLdT + 16 * I + m] = acc[i][j];
+        }
+    }
+    lds_barrier();
+    // (I + A Diag(beta)) Q = A by 16 x 16 blocks; wave w takes the column block w.  Diagonal block: substitution,
+    // a lane holds its column.
+    f32x4 Q[4];
+    {
+        float x[16];
+        const float *a = sA + (16 * w) * kLdT + 16 * w;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            float s = a[r * kLdT + m];
+#pragma unroll
+            for (int i = 0; i < r; ++i) s = fmaf(-a[r * kLdT + i], x[i], s);
+            x[r] = s;
+            if (g == (r >> 2)) {
+#pragma unroll
+                for (int ww = 0; ww < 4; ++ww)
+                    if (ww == w) Q[ww][r & 3] = s;
+                sQ[(16 * w + r) * kLdT + 16 * w + m] = s;
+            }
+            x[r] = s * sBeta[16 * w + r];                    // beta_i Q[i][m] is what the rows below take
+        }
+    }
+    lds_barrier();
+    f32x4 bt[4];
+#pragma unroll
+    for (int R = 0; R < 4; ++R) bt[R] = ld4(sBeta + 16 * R + 4 * g);
+    // Q_RI = (I - Q_RR Diag(beta_R)) (A_RI - sum_{I <= J < R} A_RJ Diag(beta_J) Q_JI)
+#pragma unroll
+    for (int R = 1; R < 4; ++R) {
+        if (R <= w) continue;
+        f32x4 s = {0.f, 0.f, 0.f, 0.f}, a;
+#pragma unroll
+        for (int J = 0; J < R; ++J)
+            if (J >= w) s = mfma16(ld4(sA + (16 * R + m) * kLdT + 16 * J + 4 * g), bt[J] * Q[J], s);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[j] = sA[(16 * R + 4 * g + j) * kLdT + 16 * w + m];
+        const f32x4 x = a - s;
+        Q[R] = x - mfma16(ld4(sQ + (16 * R + m) * kLdT + 16 * R + 4 * g), bt[R] * x, f32x4{0.f, 0.f, 0.f, 0.f});
+    }
+#pragma unroll
+    for (int R = 0; R < 4; ++R)
+        if (R >= w) st4(slot + SL::kQ + tri(R, w) * kFrag + 4 * lane, Q[R]);
+}
+
+template <typename Tin, int D>
+kda_status launch_prep(const Problem &p, const Tin *q, const Tin *k, const Tin *log_alpha, const Tin *beta, float *slots,
+                       hipStream_t stream)
+{
+    const int64_t blocks = p.slots * p.H;
+    if (blocks == 0) return KDA_OK;
+    if (blocks > 0x7fffffffLL) return fail(KDA_ERR_UNSUPPORTED, "%lld chunks in one call", (long long)blocks);
+    hipLaunchKernelGGL((kda_f32_prep_kernel<Tin, D>), dim3((unsigned)blocks), dim3(kPrepThreads), kPrepLds, stream, q, k,
+                       log_alpha, beta, slots, p);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? KDA_OK : fail(KDA_ERR_LAUNCH, "kda_f32_prep: %s", hipGetErrorString(e));
+}
+
+#define KDA_PREP(T, DD) template kda_status launch_prep<T, DD>(const Problem &, const T *, const T *, const T *, const T *, float *, hipStream_t)
+KDA_PREP(float, 64);
+KDA_PREP(float, 128);
+KDA_PREP(__hip_bfloat16, 64);
+KDA_PREP(__hip_bfloat16, 128);
+#undef KDA_PREP
+
+}  // namespace f32
+}  // namespace kda

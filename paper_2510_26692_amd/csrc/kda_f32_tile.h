@@ -1,0 +1,214 @@
+// Building blocks of the fp32 kernels (prefill of fp32 inputs, backward pass): 16 x 16 tiles on
+// v_mfma_f32_16x16x4_f32, whose operands are arranged so that four contraction steps take one 16-byte word.
+//
+// With m = lane % 16 and g = lane / 16 the instruction takes A[m][g] and B[g][m] from a lane and leaves
+// D[4 g + j][m] in its register j.  Contraction slot g of step ks (four steps per 16-wide tile) is made to
+// stand for index 4 g + ks of the tile.  Then
+//
+//   - an accumulator tile D is, as it stands, the B operand of the next product (register ks of lane group g is
+//     row 4 g + ks), so states and pseudo-values are fed back with no data movement, and it is also the A
+//     operand of its own transpose;
+//   - an operand with its contraction index along memory is one float4 per lane and tile.
+//
+// A "fragment" is one such tile in memory: 64 lanes x float4 = 1 KiB in lane order.  "Column form" is the
+// accumulator order (lane m holds rows 4 g .. 4 g + 3 of column m); "row form" is its transpose (lane m
+// holds columns 4 g .. 4 g + 3 of row m).  quad_transpose turns one into the other, up to the lane order
+// turned_lane(), while the tile is being loaded or stored.
+#pragma once
+#include "kda_common.h"
+
+namespace kda {
+namespace f32 {
+
+constexpr int kC = kChunk;
+constexpr int kFrag = 256;                                   // floats of a fragment
+constexpr int kTri = 10;                                     // 16 x 16 blocks of a lower-triangular C x C matrix
+__host__ __device__ constexpr int tri(int R, int I) { return R * (R + 1) / 2 + I; }      // block (R, I), I <= R
+
+// What the per-chunk kernel leaves per (chunk, head), in floats: Gamma.K, Gamma^{i->C}.K and Gamma.Q as
+// [token tile][channel tile] fragments, the blocks of Q and Tril(A_qk), all in column form, and e^(G_C).
+template <int D> struct Slot {
+    static constexpr int kTiles = D / 16;
+    static constexpr int kKg = 0;
+    static constexpr int kKt = kKg + 4 * kTiles * kFrag;
+    static constexpr int kQg = kKt + 4 * kTiles * kFrag;
+    static constexpr int kQ = kQg + 4 * kTiles * kFrag;
+    static constexpr int kP = kQ + kTri * kFrag;
+    static constexpr int kGc = kP + kTri * kFrag;
+    static constexpr int kFloats = 3 * kC * D + 2 * kC * (kC + 2) + D;       // (the published size; 13 KiB of it are spare)
+    static_assert(kGc + D <= kFloats && kFloats % 64 == 0, "slots stay 256-byte aligned");
+};
+
+__device__ __forceinline__ f32x4 mfma16(const f32x4 &a, const f32x4 &b, f32x4 acc)      // a 16 x 16 x 16 product
+{
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ks], b[ks], acc, 0, 0, 0);
+    return acc;
+}
+
+// 4 x 4 transpose across the lanes of a quad: lane b register j -> lane j register b.
+template <int kCtrl> __device__ __forceinline__ float quad_swap(float x)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xf, 0xf, true));
+}
+__device__ __forceinline__ f32x4 quad_transpose(f32x4 r, int lane)
+{
+    const bool b0 = lane & 1, b1 = lane & 2;
+    float s, t;
+    s = quad_swap<0xB1>(b0 ? r[0] : r[1]); t = quad_swap<0xB1>(b0 ? r[2] : r[3]);
+    if (b0) { r[0] = s; r[2] = t; } else { r[1] = s; r[3] = t; }
+    s = quad_swap<0x4E>(b1 ? r[0] : r[2]); t = quad_swap<0x4E>(b1 ? r[1] : r[3]);
+    if (b1) { r[0] = s; r[1] = t; } else { r[2] = s; r[3] = t; }
+    return r;
+}
+// The lane of the other form that a lane reads (before the quads turn) or writes (after).
+__device__ __forceinline__ int turned_lane(int lane) { return ((lane >> 2) & 3) * 16 + (lane >> 4) * 4 + (lane & 3); }
+
+__device__ __forceinline__ f32x4 ld4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
+__device__ __forceinline__ void st4(float *p, const f32x4 &v) { *reinterpret_cast<f32x4 *>(p) = v; }
+
+// Workgroup barrier for LDS traffic: global loads and stores stay in flight across it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// R and Z, [tokens x heads x D] floats in all: the rows of a (chunk, head) lie together, token tile by token tile, a tile
+// of n <= 16 valid tokens as [column tile][4 columns][n tokens] float4, which for n = 16 is the fragment in row form.
+__device__ __forceinline__ int64_t token_rows(int64_t tok0, int H, int h, int nv, int D) { return (tok0 * H + (int64_t)h * nv) * D; }
+__device__ __forceinline__ int tile_tokens(int nv, int R) { return nv - 16 * R < 16 ? nv - 16 * R : 16; }
+__device__ __forceinline__ int row_form(int R, int column_tile, int group, int token, int n, int D)
+{
+    return 16 * R * D + ((4 * column_tile + group) * n + token) * 4;
+}
+
+// ---- which chunk a workgroup works on ----
+struct Chunk {
+    int64_t tok0, slot;      // first token; workspace slot (times H + h)
+    int nv, h;               // valid tokens, head
+};
+
+// First slot of sequence n: packed batches floor(cu[n] / C) + n, strictly increasing over (n, chunk) and
+// bounded by floor(total / C) + N.
+__device__ __forceinline__ int64_t first_slot(const int32_t *cu, int64_t n, int64_t chunks_per_seq)
+{
+    return cu ? (int64_t)(cu[n] / kC) + n : n * chunks_per_seq;
+}
+
+// Chunk of workgroup `bid` of a grid of (slots x heads); false: a slot that no chunk uses.
+__device__ __forceinline__ bool locate(const int32_t *cu, int num_seqs, int64_t T, int H, int64_t chunks_per_seq,
+                                       int64_t bid, Chunk &c)
+{
+    const int64_t s = bid / H;
+    c.h = (int)(bid - s * H);
+    c.slot = bid;
+    int64_t len, c0;
+    if (!cu) {
+        const int64_t n = s / chunks_per_seq;
+        c0 = (s - n * chunks_per_seq) * kC; len = T; c.tok0 = n * T + c0;
+    } else {
+        int lo = 0, hi = num_seqs - 1;                       // the last sequence whose first slot is <= s
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (first_slot(cu, mid, 0) <= s) lo = mid; else hi = mid - 1;
+        }
+        c0 = (s - first_slot(cu, lo, 0)) * kC; len = (int64_t)cu[lo + 1] - cu[lo]; c.tok0 = cu[lo] + c0;
+    }
+    c.nv = (int)(len - c0 < kC ? len - c0 : kC);
+    return c0 < len;
+}
+
+// ---- one 16-channel tile of a chunk in column form: register j of [R] is token 16 R + 4 g + j, channel m ----
+// The in-block decay is split between a row factor 2^(G_r - pref_R) and a column factor 2^(nref_I - G_i); a
+// block pair R > I carries 2^(pref_R - nref_I) <= 1 besides, a diagonal pair nothing: pref = nref = the middle
+// of the block's decay.  Both factors then stay within 2^(+-kMaxDecay/2), which fp32 holds with full relative
+// precision.  A channel whose decay inside one 16-token block exceeds 2^-kMaxDecay ("strong") splits at the
+// block's two ends instead (every factor at most 1), contributes nothing to the diagonal products (fdiag = 0)
+// and is added there pair by pair.
+constexpr float kMaxDecay = 100.f;
+
+struct Decay {
+    f32x4 G[4];              // running sum of log2 alpha (tokens past the end repeat the last)
+    float E[4];              // G at the end of each block
+    float pref[4], nref[4], fdiag[4];
+    bool strong;
+};
+
+template <typename T> __device__ __forceinline__ void load_tile(f32x4 (&x)[4], const T *base, int64_t stride, int nv, int g)
+{
+#pragma unroll
+    for (int R = 0; R < 4; ++R)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = 16 * R + 4 * g + j;
+            x[R][j] = load_as_float(base + (int64_t)(r < nv ? r : nv - 1) * stride);
+        }
+    if (nv < kC) {
+#pragma unroll
+        for (int R = 0; R < 4; ++R)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (16 * R + 4 * g + j >= nv) x[R][j] = 0.f;
+    }
+}
+
+__device__ __forceinline__ void running_decay(Decay &d, int lane)     // d.G holds log alpha on entry
+{
+    const int m = lane & 15, g = lane >> 4;
+    float run = 0.f;
+    d.strong = false;
+#pragma unroll
+    for (int R = 0; R < 4; ++R) {
+        f32x4 x = d.G[R] * kLog2e;
+        x[1] += x[0]; x[2] += x[1]; x[3] += x[2];
+        float s = x[3], u = __shfl_up(s, 16);
+        if (g >= 1) s += u;
+        u = __shfl_up(s, 32);
+        if (g >= 2) s += u;
+        u = __shfl_up(s, 16);
+        const float before = run + (g >= 1 ? u : 0.f);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d.G[R][j] = x[j] + before;
+        d.E[R] = __shfl(d.G[R][3], 48 + m);
+        const bool strong = run - d.E[R] > kMaxDecay;
+        d.strong |= strong;
+        const float mid = 0.5f * (run + d.E[R]);
+        d.pref[R] = strong ? run : mid;
+        d.nref[R] = strong ? d.E[R] : mid;
+        d.fdiag[R] = strong ? 0.f : 1.f;
+        run = d.E[R];
+    }
+}
+
+__device__ __forceinline__ f32x4 exp2_4(const f32x4 &x)
+{
+    return f32x4{fast_exp2(x[0]), fast_exp2(x[1]), fast_exp2(x[2]), fast_exp2(x[3])};
+}
+
+constexpr int kLdT = 68;     // row stride of a C x C (or C x 64-channel) tile in LDS: 4 rows apart = 16 banks apart
+
+// ---- launches (one per source file) ----
+struct Problem {
+    const int32_t *cu;
+    int64_t T, chunks_per_seq, slots;      // slots: of the whole call, heads not counted
+    int num_seqs, H;
+    float scale;
+};
+
+template <typename Tin, int D>
+kda_status launch_prep(const Problem &p, const Tin *q, const Tin *k, const Tin *log_alpha, const Tin *beta, float *slots,
+                       hipStream_t stream);
+// Forward walk that writes o and the final states.
+template <typename Tin, int D>
+kda_status launch_forward_walk(const Problem &p, const Tin *v, const Tin *beta, const float *h0, const float *slots, float *o,
+                               float *hT, int compute_units, hipStream_t stream);
+// Forward and backward walks side by side: S0 of every chunk and R = v - S^T k of every token; dS1 of every chunk,
+// Z' = dV / beta of every token, dh0.
+template <typename Tin, typename Tdo, int D>
+kda_status launch_both_walks(const Problem &p, const Tin *v, const Tin *beta, const float *h0, const Tdo *d_o, const float *d_hT,
+                             const float *slots, float *S0, float *R, float *dS1, float *Z, float *dh0, int compute_units,
+                             hipStream_t stream);
+template <typename Tin, typename Tdo, int D>
+kda_status launch_gradients(const Problem &p, const Tin *q, const Tin *k, const Tin *log_alpha, const Tin *beta, const Tdo *d_o,
+                            const float *S0, const float *R, const float *dS1, const float *Z, float *dq, float *dk, float *dv,
+                            float *dla, float *dbeta, hipStream_t stream);
+
+}  // namespace f32
+}  // namespace kda

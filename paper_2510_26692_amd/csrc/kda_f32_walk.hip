@@ -1,0 +1,497 @@
+// The two sequential walks of the fp32 path over the chunks of a (sequence, head), on the operands that
+// kda_f32_prep leaves per chunk (Kg = Gamma.K, Kt = Gamma^{i->C}.K, Qg = Gamma.Q, P = Tril(A_qk), Q):
+//
+//   forward    Y = V - Kg S0,   R = Y - Q (beta Y),   Vn = beta R,   S1 = Diag(e^(G_C)) S0 + Kt^T Vn
+//              (and, for the prefill, O = scale (Qg S0 + P Vn))
+//   backward   dVn = Kt dS1 + P^T dO,   Z = dVn - Q^T (beta dVn),   X = beta Z = dV,
+//              dS0 = Diag(e^(G_C)) dS1 + Qg^T dO - Kg^T X                       (dO carries the scale)
+//
+// The columns of S (and of dS) never mix, so a workgroup owns 16 NC of them.  Its four waves share every product
+// by ROWS: wave w has the token rows 16 w .. and the state rows of D / 64 channel tiles, so an operand fragment is
+// loaded by one wave of the workgroup, from memory straight into registers (no LDS, no second copy), and the
+// right-hand sides (S, Y, Vn: what the waves hand each other) go through LDS in accumulator order, which is B
+// operand order.  Three barriers a chunk.  Each operand's registers are refilled for the next chunk right after
+// their last use, so a load has most of a step to arrive.
+//
+// The two walks do not depend on each other (the backward one needs no forward state): one launch runs both, which
+// doubles the workgroups in flight.
+#include "kda_f32_tile.h"
+
+namespace kda {
+namespace f32 {
+
+constexpr int kWalkThreads = 256;
+
+template <int D, int NC> constexpr size_t walk_lds(bool both) { return (size_t)(NC * (D / 16) + (both ? 4 : 2) * NC * 4) * kFrag * 4; }
+
+struct Where { int64_t tok_base, len, nchunks, slot0, state; };
+
+__device__ __forceinline__ Where where(const Problem &p, int64_t n, int h, int D)
+{
+    Where x;
+    if (p.cu) { x.tok_base = p.cu[n]; x.len = (int64_t)p.cu[n + 1] - x.tok_base; }
+    else      { x.tok_base = n * p.T; x.len = p.T; }
+    x.nchunks = (x.len + kC - 1) / kC;
+    x.slot0 = first_slot(p.cu, n, p.chunks_per_seq) * p.H + h;               // slots of a sequence are H apart
+    x.state = (n * p.H + h) * (int64_t)D * D;
+    return x;
+}
+
+// Rows 16 w + 4 g + j of NC column tiles of a [tokens, H, D] tensor, as they come (rows past nv: clamped).
+template <typename T, int NC>
+__device__ __forceinline__ void load_rows(f32x4 (&x)[NC], const T *base, int64_t stride, int row0, int nv)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int r = row0 + j;
+        const T *p = base + (int64_t)(r < nv ? r : nv - 1) * stride;
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) x[nc][j] = load_as_float(p + 16 * nc);
+    }
+}
+template <typename T>
+__device__ __forceinline__ f32x4 load_beta(const T *base, int64_t H, int row0, int nv)
+{
+    f32x4 b;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) b[j] = load_as_float(base + (int64_t)(row0 + j < nv ? row0 + j : nv - 1) * H);
+    return b;
+}
+template <int NC> __device__ __forceinline__ void mask_rows(f32x4 (&x)[NC], int row0, int nv)
+{
+#pragma unroll
+    for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (row0 + j >= nv) x[nc][j] = 0.f;
+}
+
+template <int D, int NC>
+__device__ __forceinline__ void load_state(f32x4 (&S)[D / 64][NC], const float *src, int t0, int g)
+{
+#pragma unroll
+    for (int tt = 0; tt < D / 64; ++tt)
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) S[tt][nc][j] = src ? src[(int64_t)(16 * (t0 + tt) + 4 * g + j) * D + 16 * nc] : 0.f;
+}
+template <int D, int NC>
+__device__ __forceinline__ void store_state(float *dst, const f32x4 (&S)[D / 64][NC], int t0, int g)
+{
+#pragma unroll
+    for (int tt = 0; tt < D / 64; ++tt)
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) dst[(int64_t)(16 * (t0 + tt) + 4 * g + j) * D + 16 * nc] = S[tt][nc][j];
+}
+
+// One token tile of R or Z, NC column tiles from `tile` on.
+template <int D, int NC>
+__device__ __forceinline__ void store_rows(float *dst, const f32x4 (&x)[NC], int64_t tok0, int H, int h, int nv, int R, int tile, int lane)
+{
+    const int token = 4 * (lane >> 4) + (lane & 3), n = tile_tokens(nv, R);
+    float *p = dst + token_rows(tok0, H, h, nv, D);
+#pragma unroll
+    for (int nc = 0; nc < NC; ++nc) {
+        const f32x4 t = quad_transpose(x[nc], lane);
+        if (token < n) st4(p + row_form(R, tile + nc, (lane >> 2) & 3, token, n, D), t);
+    }
+}
+
+// kOut: o instead of S0 and R.
+template <typename Tin, int D, int NC, bool kOut>
+__device__ __forceinline__ void forward_walk(float *smem, const Problem &p, const Tin *v, const Tin *beta, const float *h0,
+                                             const float *slots, float *S0, float *Rw, float *o, float *hT, int64_t n, int h,
+                                             int slice)
+{
+    using SL = Slot<D>;
+    constexpr int NT = SL::kTiles, TW = NT / 4;
+    float *sS = smem, *sY = sS + NC * NT * kFrag, *sV = sY + NC * 4 * kFrag;
+    const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4, turned = 4 * turned_lane(lane);
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), row0 = 16 * w + 4 * g, t0 = TW * w;
+    const Where x = where(p, n, h, D);
+    const int64_t stride = (int64_t)p.H * D;
+    const int col0 = 16 * NC * slice;
+
+    f32x4 S[TW][NC];
+    load_state<D, NC>(S, h0 ? h0 + x.state + col0 + m : nullptr, t0, g);
+    f32x4 kg[NT], qm[4], kt[TW][4], gam[TW], vv[NC], bt, qg[kOut ? NT : 1], pm[kOut ? 4 : 1];
+    auto load_kg = [&](const float *slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            kg[t] = ld4(slot + SL::kKg + (w * NT + t) * kFrag + turned);
+            if (kOut) qg[t] = ld4(slot + SL::kQg + (w * NT + t) * kFrag + turned);
+        }
+    };
+    auto load_q = [&](const float *slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int J = 0; J < 4; ++J) qm[J] = ld4(slot + SL::kQ + tri(w, J < w ? J : w) * kFrag + turned);
+    };
+    auto load_kt = [&](const float *slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int tt = 0; tt < TW; ++tt) {
+#pragma unroll
+            for (int R = 0; R < 4; ++R) kt[tt][R] = ld4(slot + SL::kKt + (R * NT + t0 + tt) * kFrag + 4 * lane);
+            gam[tt] = ld4(slot + SL::kGc + 16 * (t0 + tt) + 4 * g);
+        }
+        if (kOut) {
+#pragma unroll
+            for (int J = 0; J < 4; ++J) pm[J] = ld4(slot + SL::kP + tri(w, J < w ? J : w) * kFrag + turned);
+        }
+    };
+    auto valid = [&](int64_t ci) { return (int)(x.len - ci * kC < kC ? x.len - ci * kC : kC); };
+    auto load_v = [&](int64_t ci) __attribute__((always_inline)) {
+        const int64_t at = ((x.tok_base + ci * kC) * p.H + h);
+        load_rows<Tin, NC>(vv, v + at * D + col0 + m, stride, row0, valid(ci));
+        bt = load_beta(beta + at, p.H, row0, valid(ci));
+    };
+    auto share_state = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int tt = 0; tt < TW; ++tt)
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) st4(sS + (nc * NT + t0 + tt) * kFrag + 4 * lane, S[tt][nc]);
+    };
+    if (x.nchunks > 0) {
+        const float *slot = slots + x.slot0 * SL::kFloats;
+        load_kg(slot); load_v(0); load_q(slot); load_kt(slot);
+        share_state();
+        lds_barrier();
+    }
+#pragma unroll 1
+    for (int64_t ci = 0; ci < x.nchunks; ++ci) {
+        const int nv = valid(ci);
+        const int64_t cn = ci + 1 < x.nchunks ? ci + 1 : ci;                  // (the last step fetches its own operands again)
+        const float *next = slots + (x.slot0 + cn * p.H) * SL::kFloats;
+        const int64_t sl = x.slot0 + ci * p.H;
+        // Y = V - Kg S0
+        f32x4 y[NC] = {}, oo[kOut ? NC : 1] = {};
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const f32x4 a = quad_transpose(kg[t], lane), aq = kOut ? quad_transpose(qg[kOut ? t : 0], lane) : a;
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) {
+                const f32x4 b = ld4(sS + (nc * NT + t) * kFrag + 4 * lane);
+                y[nc] = mfma16(a, b, y[nc]);
+                if (kOut) oo[kOut ? nc : 0] = mfma16(aq, b, oo[kOut ? nc : 0]);
+            }
+        }
+        load_kg(next);
+        if (nv < kC) mask_rows<NC>(vv, row0, nv);
+        const f32x4 b4 = bt;
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) {
+            y[nc] = vv[nc] - y[nc];
+            st4(sY + (nc * 4 + w) * kFrag + 4 * lane, b4 * y[nc]);
+        }
+        load_v(cn);
+        if (!kOut) {
+#pragma unroll
+            for (int tt = 0; tt < TW; ++tt)
+#pragma unroll
+                for (int nc = 0; nc < NC; ++nc)
+                    st4(S0 + sl * (int64_t)(D * D) + ((t0 + tt) * NT + NC * slice + nc) * kFrag + turned, quad_transpose(S[tt][nc], lane));
+        }
+        lds_barrier();
+        // R = Y - Q (beta Y)
+        f32x4 r[NC] = {};
+#pragma unroll
+        for (int J = 0; J < 4; ++J)
+            if (J <= w) {
+                const f32x4 a = quad_transpose(qm[J], lane);
+#pragma unroll
+                for (int nc = 0; nc < NC; ++nc) r[nc] = mfma16(a, ld4(sY + (nc * 4 + J) * kFrag + 4 * lane), r[nc]);
+            }
+        load_q(next);
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) {
+            r[nc] = y[nc] - r[nc];
+            st4(sV + (nc * 4 + w) * kFrag + 4 * lane, b4 * r[nc]);
+        }
+        if (!kOut) {
+            store_rows<D, NC>(Rw, r, x.tok_base + ci * kC, p.H, h, nv, w, NC * slice, lane);
+        }
+        lds_barrier();
+        // S1 = Diag(e^(G_C)) S0 + Kt^T Vn
+#pragma unroll
+        for (int tt = 0; tt < TW; ++tt)
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) S[tt][nc] *= gam[tt];
+#pragma unroll
+        for (int R = 0; R < 4; ++R)
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) {
+                const f32x4 b = ld4(sV + (nc * 4 + R) * kFrag + 4 * lane);
+#pragma unroll
+                for (int tt = 0; tt < TW; ++tt) S[tt][nc] = mfma16(kt[tt][R], b, S[tt][nc]);
+            }
+        share_state();
+        if (kOut) {
+            // O = scale (Qg S0 + P Vn)
+#pragma unroll
+            for (int J = 0; J < 4; ++J)
+                if (J <= w) {
+                    const f32x4 a = quad_transpose(pm[kOut ? J : 0], lane);
+#pragma unroll
+                    for (int nc = 0; nc < NC; ++nc) oo[kOut ? nc : 0] = mfma16(a, ld4(sV + (nc * 4 + J) * kFrag + 4 * lane), oo[kOut ? nc : 0]);
+                }
+            float *po = o + ((x.tok_base + ci * kC) * p.H + h) * (int64_t)D + col0 + m;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (row0 + j < nv) {
+#pragma unroll
+                    for (int nc = 0; nc < NC; ++nc) po[(row0 + j) * stride + 16 * nc] = p.scale * oo[kOut ? nc : 0][j];
+                }
+        }
+        load_kt(next);
+        lds_barrier();
+    }
+    if (hT) store_state<D, NC>(hT + x.state + col0 + m, S, t0, g);
+}
+
+template <typename Tin, typename Tdo, int D, int NC>
+__device__ __forceinline__ void backward_walk(float *smem, const Problem &p, const Tin *beta, const Tdo *d_o, const float *d_hT,
+                                              const float *slots, float *dS1, float *Zw, float *dh0, int64_t n, int h, int slice)
+{
+    using SL = Slot<D>;
+    constexpr int NT = SL::kTiles, TW = NT / 4;
+    float *sS = smem, *sY = sS + NC * NT * kFrag, *sX = sY + NC * 4 * kFrag, *sO = sX + NC * 4 * kFrag;    // sO: two buffers
+    const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4, turned = 4 * turned_lane(lane);
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), row0 = 16 * w + 4 * g, t0 = TW * w;
+    const Where x = where(p, n, h, D);
+    const int64_t stride = (int64_t)p.H * D;
+    const int col0 = 16 * NC * slice;
+
+    f32x4 S[TW][NC];
+    load_state<D, NC>(S, d_hT ? d_hT + x.state + col0 + m : nullptr, t0, g);
+    f32x4 kt[NT], pm[4], qm[4], kg[TW][4], qg[TW][4], gam[TW], vo[NC], bt;
+    auto load_kt = [&](const float *slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) kt[t] = ld4(slot + SL::kKt + (w * NT + t) * kFrag + turned);
+#pragma unroll
+        for (int R = 0; R < 4; ++R) pm[R] = ld4(slot + SL::kP + tri(R > w ? R : w, w) * kFrag + 4 * lane);
+    };
+    auto load_q = [&](const float *slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int R = 0; R < 4; ++R) qm[R] = ld4(slot + SL::kQ + tri(R > w ? R : w, w) * kFrag + 4 * lane);
+    };
+    auto load_kg = [&](const float *slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int tt = 0; tt < TW; ++tt) {
+#pragma unroll
+            for (int R = 0; R < 4; ++R) {
+                kg[tt][R] = ld4(slot + SL::kKg + (R * NT + t0 + tt) * kFrag + 4 * lane);
+                qg[tt][R] = ld4(slot + SL::kQg + (R * NT + t0 + tt) * kFrag + 4 * lane);
+            }
+            gam[tt] = ld4(slot + SL::kGc + 16 * (t0 + tt) + 4 * g);
+        }
+    };
+    auto valid = [&](int64_t ci) { return (int)(x.len - ci * kC < kC ? x.len - ci * kC : kC); };
+    auto load_o = [&](int64_t ci) __attribute__((always_inline)) {
+        load_rows<Tdo, NC>(vo, d_o + ((x.tok_base + ci * kC) * p.H + h) * (int64_t)D + col0 + m, stride, row0, valid(ci));
+    };
+    auto load_b = [&](int64_t ci) __attribute__((always_inline)) {
+        bt = load_beta(beta + (x.tok_base + ci * kC) * p.H + h, p.H, row0, valid(ci));
+    };
+    auto share_o = [&](int64_t ci) __attribute__((always_inline)) {
+        if (valid(ci) < kC) mask_rows<NC>(vo, row0, valid(ci));
+        float *dst = sO + (ci & 1) * (NC * 4 * kFrag);
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) st4(dst + (nc * 4 + w) * kFrag + 4 * lane, vo[nc] * p.scale);
+    };
+    auto share_state = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int tt = 0; tt < TW; ++tt)
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) st4(sS + (nc * NT + t0 + tt) * kFrag + 4 * lane, S[tt][nc]);
+    };
+    const int64_t last = x.nchunks - 1;
+    if (last >= 0) {
+        const float *slot = slots + (x.slot0 + last * p.H) * SL::kFloats;
+        load_o(last); load_kt(slot); load_b(last); load_q(slot); load_kg(slot);
+        share_state();
+        share_o(last);
+        load_o(last > 0 ? last - 1 : 0);
+        lds_barrier();
+    }
+#pragma unroll 1
+    for (int64_t ci = last; ci >= 0; --ci) {
+        const int64_t cn = ci > 0 ? ci - 1 : 0;
+        const float *next = slots + (x.slot0 + cn * p.H) * SL::kFloats;
+        const int64_t sl = x.slot0 + ci * p.H;
+        const float *so = sO + (ci & 1) * (NC * 4 * kFrag);
+        // dVn = Kt dS1 + P^T dO
+        f32x4 y[NC] = {};
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const f32x4 a = quad_transpose(kt[t], lane);
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) y[nc] = mfma16(a, ld4(sS + (nc * NT + t) * kFrag + 4 * lane), y[nc]);
+        }
+#pragma unroll
+        for (int R = 0; R < 4; ++R)
+            if (R >= w) {
+#pragma unroll
+                for (int nc = 0; nc < NC; ++nc) y[nc] = mfma16(pm[R], ld4(so + (nc * 4 + R) * kFrag + 4 * lane), y[nc]);
+            }
+        load_kt(next);
+        const f32x4 b4 = bt;                                  // (padding rows: dVn is zero there, whatever beta reads)
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) st4(sY + (nc * 4 + w) * kFrag + 4 * lane, b4 * y[nc]);
+        load_b(cn);
+#pragma unroll
+        for (int tt = 0; tt < TW; ++tt)
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc)
+                st4(dS1 + sl * (int64_t)(D * D) + ((t0 + tt) * NT + NC * slice + nc) * kFrag + turned, quad_transpose(S[tt][nc], lane));
+        lds_barrier();
+        // Z = dVn - Q^T (beta dVn)
+        f32x4 z[NC] = {};
+#pragma unroll
+        for (int R = 0; R < 4; ++R)
+            if (R >= w) {
+#pragma unroll
+                for (int nc = 0; nc < NC; ++nc) z[nc] = mfma16(qm[R], ld4(sY + (nc * 4 + R) * kFrag + 4 * lane), z[nc]);
+            }
+        load_q(next);
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) {
+            z[nc] = y[nc] - z[nc];
+            st4(sX + (nc * 4 + w) * kFrag + 4 * lane, -b4 * z[nc]);
+        }
+        store_rows<D, NC>(Zw, z, x.tok_base + ci * kC, p.H, h, valid(ci), w, NC * slice, lane);
+        lds_barrier();
+        // dS0 = Diag(e^(G_C)) dS1 + Qg^T dO - Kg^T X
+#pragma unroll
+        for (int tt = 0; tt < TW; ++tt)
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) S[tt][nc] *= gam[tt];
+#pragma unroll
+        for (int R = 0; R < 4; ++R)
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) {
+                const f32x4 bo = ld4(so + (nc * 4 + R) * kFrag + 4 * lane), bx = ld4(sX + (nc * 4 + R) * kFrag + 4 * lane);
+#pragma unroll
+                for (int tt = 0; tt < TW; ++tt) S[tt][nc] = mfma16(kg[tt][R], bx, mfma16(qg[tt][R], bo, S[tt][nc]));
+            }
+        share_state();
+        load_kg(next);
+        if (ci > 0) {
+            share_o(cn);
+            load_o(cn > 0 ? cn - 1 : 0);
+        }
+        lds_barrier();
+    }
+    if (dh0) store_state<D, NC>(dh0 + x.state + col0 + m, S, t0, g);
+}
+
+// Workgroups are handed to the eight dies in turn: the slices of a (sequence, head), which read the same operands at
+// about the same time, are placed eight workgroups apart, on one die's L2.
+template <int D, int NC>
+__device__ __forceinline__ bool place(const Problem &p, int64_t bid, int64_t &n, int &h, int &slice)
+{
+    constexpr int kSlices = D / (16 * NC);
+    const int64_t rest = bid >> 3, pair = (rest / kSlices) * 8 + (bid & 7);
+    slice = (int)(rest % kSlices);
+    n = pair / p.H;
+    h = (int)(pair - n * p.H);
+    return pair < (int64_t)p.num_seqs * p.H;
+}
+static int64_t walk_workgroups(const Problem &p, int slices) { return ((int64_t)p.num_seqs * p.H + 7) / 8 * 8 * slices; }
+
+template <typename Tin, int D, int NC>
+__global__ __launch_bounds__(kWalkThreads, 2)
+void kda_f32_forward_walk_kernel(const Tin *__restrict__ v, const Tin *__restrict__ beta, const float *__restrict__ h0,
+                                 const float *__restrict__ slots, float *__restrict__ o, float *__restrict__ hT, const Problem p)
+{
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    int64_t n;
+    int h, slice;
+    if (!place<D, NC>(p, blockIdx.x, n, h, slice)) return;
+    forward_walk<Tin, D, NC, true>(smem, p, v, beta, h0, slots, nullptr, nullptr, o, hT, n, h, slice);
+}
+
+// The backward walk, the longer of the two, goes first.
+template <typename Tin, typename Tdo, int D, int NC>
+__global__ __launch_bounds__(kWalkThreads, 2)
+void kda_f32_both_walks_kernel(const Tin *__restrict__ v, const Tin *__restrict__ beta, const float *__restrict__ h0,
+                               const Tdo *__restrict__ d_o, const float *__restrict__ d_hT, const float *__restrict__ slots,
+                               float *__restrict__ S0, float *__restrict__ Rw, float *__restrict__ dS1, float *__restrict__ Zw,
+                               float *__restrict__ dh0, int64_t half, const Problem p)
+{
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    const int64_t bid = blockIdx.x;
+    int64_t n;
+    int h, slice;
+    if (!place<D, NC>(p, bid < half ? bid : bid - half, n, h, slice)) return;
+    if (bid < half) backward_walk<Tin, Tdo, D, NC>(smem, p, beta, d_o, d_hT, slots, dS1, Zw, dh0, n, h, slice);
+    else forward_walk<Tin, D, NC, false>(smem, p, v, beta, h0, slots, S0, Rw, nullptr, nullptr, n, h, slice);
+}
+
+// Column tiles per workgroup: the fewest that still give every compute unit at most two workgroups (more than two
+// would queue; fewer columns than needed load the same operands more often).
+static int column_tiles(const Problem &p, int D, int walks, int compute_units)
+{
+    for (int nc = 1; nc < 4; nc *= 2)
+        if (walks * walk_workgroups(p, D / (16 * nc)) <= 2 * (int64_t)compute_units) return nc;
+    return 4;
+}
+
+template <typename F, typename... Args>
+static kda_status launch_walk(F kern, const char *name, int64_t blocks, size_t lds, hipStream_t stream, Args... args)
+{
+    if (blocks > 0x7fffffffLL) return fail(KDA_ERR_UNSUPPORTED, "%s: %lld workgroups", name, (long long)blocks);
+    hipError_t e = hipSuccess;
+    if (lds > 65536)
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kWalkThreads), lds, stream, args...);
+        e = hipGetLastError();
+    }
+    return e == hipSuccess ? KDA_OK : fail(KDA_ERR_LAUNCH, "%s: %s", name, hipGetErrorString(e));
+}
+
+template <typename Tin, int D>
+kda_status launch_forward_walk(const Problem &p, const Tin *v, const Tin *beta, const float *h0, const float *slots, float *o,
+                               float *hT, int compute_units, hipStream_t stream)
+{
+#define KDA_GO(NC) launch_walk(kda_f32_forward_walk_kernel<Tin, D, NC>, "kda_f32_forward_walk", walk_workgroups(p, D / (16 * NC)), \
+                               walk_lds<D, NC>(false), stream, v, beta, h0, slots, o, hT, p)
+    const int nc = column_tiles(p, D, 1, compute_units);
+    return nc == 1 ? KDA_GO(1) : nc == 2 ? KDA_GO(2) : KDA_GO(4);
+#undef KDA_GO
+}
+
+template <typename Tin, typename Tdo, int D>
+kda_status launch_both_walks(const Problem &p, const Tin *v, const Tin *beta, const float *h0, const Tdo *d_o, const float *d_hT,
+                             const float *slots, float *S0, float *R, float *dS1, float *Z, float *dh0, int compute_units,
+                             hipStream_t stream)
+{
+#define KDA_GO(NC) launch_walk(kda_f32_both_walks_kernel<Tin, Tdo, D, NC>, "kda_f32_both_walks", 2 * walk_workgroups(p, D / (16 * NC)), \
+                               walk_lds<D, NC>(true), stream, v, beta, h0, d_o, d_hT, slots, S0, R, dS1, Z, dh0, \
+                               walk_workgroups(p, D / (16 * NC)), p)
+    const int nc = column_tiles(p, D, 2, compute_units);
+    return nc == 1 ? KDA_GO(1) : nc == 2 ? KDA_GO(2) : KDA_GO(4);
+#undef KDA_GO
+}
+
+#define KDA_FWD(T, DD) template kda_status launch_forward_walk<T, DD>(const Problem &, const T *, const T *, const float *, \
+                                                                      const float *, float *, float *, int, hipStream_t)
+KDA_FWD(float, 64);
+KDA_FWD(float, 128);
+KDA_FWD(__hip_bfloat16, 64);
+KDA_FWD(__hip_bfloat16, 128);
+#define KDA_BOTH(T, O, DD) template kda_status launch_both_walks<T, O, DD>(const Problem &, const T *, const T *, const float *, \
+    const O *, const float *, const float *, float *, float *, float *, float *, float *, int, hipStream_t)
+KDA_BOTH(float, float, 64);
+KDA_BOTH(float, float, 128);
+KDA_BOTH(__hip_bfloat16, float, 64);
+KDA_BOTH(__hip_bfloat16, float, 128);
+KDA_BOTH(__hip_bfloat16, __hip_bfloat16, 64);
+KDA_BOTH(__hip_bfloat16, __hip_bfloat16, 128);
+#undef KDA_FWD
+#undef KDA_BOTH
+
+}  // namespace f32
+}  // namespace kda

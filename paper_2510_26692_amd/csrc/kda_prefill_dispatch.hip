@@ -184,6 +184,8 @@ static int compute_units()
 
 }  // namespace mfma
 
+int current_compute_units() { return mfma::compute_units(); }
+
 size_t chunk_mfma_workspace_size(const kda_dims *d, bool minimal, bool gate)
 {
     if (d->num_seqs == 0 || d->heads == 0 || d->seqlen == 0) return 0;

@@ -1,0 +1,57 @@
+"""The fp32 path (prefill of fp32 inputs, backward pass) where its tiling can go wrong: token tiles of 16 and chunks
+of 64 with one token less and one more, each number of column tiles a workgroup of the walks may own (chosen by the
+number of (sequence, head) pairs), channels whose decay inside 16 tokens is beyond what the factors of the products
+hold next to channels where it is not, and tokens with beta = 0.
+
+Bounds: a factor 2^x of a decay held in fp32 carries a relative error of |x| 2^-24 ln 2 (x in log2 units); with the
+mild decay |x| stays below 60 in a chunk and the bound is the path's 1e-5.  The strong channels reach |x| = 320 and
+more, where the products underflow, but at |x| = 100 they still count: 100 * 2^-24 * ln 2 = 4e-6 per factor, a few of
+them to a term: 4e-5, as for the other strong-decay case of the backward pass."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth_inputs as si
+from helpers import rel_err, to_device
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = [1, 15, 16, 17, 63, 64, 65, 127, 130]
+
+
+def _inputs(lens, H, D, dtype, strong, seed):
+    x = si.make_varlen(lens, H, D, D, dtype, -2.0, seed, 0.05)
+    if strong:                                  # every fifth channel decays by 2^-8 per token and more
+        la = x["log_alpha"].float()
+        la[..., ::5] = la[..., ::5] * 2.0 - 6.0
+        x["log_alpha"] = la.to(x["log_alpha"].dtype)
+    x["beta"][:, ::7] = 0.0
+    return x
+
+
+@pytest.mark.parametrize("strong", [False, True], ids=["mild", "strong"])
+@pytest.mark.parametrize("D,dtype", [(64, "f32"), (128, "f32"), (128, "bf16")])
+@pytest.mark.parametrize("repeat", [1, 5, 9])            # x 9 sequences x 1 head: 9, 45 and 81 pairs
+def test_tiles_of_the_fp32_path(repeat, D, dtype, strong):
+    import paper_2510_26692_amd as kda
+    x = _inputs(LENGTHS * repeat, 1, D, dtype, strong, 1300 + repeat)
+    tol = 4e-5 if strong else 1e-5
+    g = torch.Generator().manual_seed(5)
+    do = torch.randn(x["v"].shape, generator=g)
+    dhT = 0.1 * torch.randn(x["h0"].shape, generator=g)
+    dd = to_device(x)
+    args = [si.to_np32(x[n]) for n in ("q", "k", "v", "log_alpha", "beta")]
+    kw = dict(h0=x["h0"].numpy().astype(np.float64), cu_seqlens=x["cu_seqlens"].numpy().astype(np.int64))
+    dev = [dd[n] for n in ("q", "k", "v", "log_alpha", "beta")]
+    if dtype == "f32":
+        o, hT = kda.kda_chunk_fwd(*dev, h0=dd["h0"], cu_seqlens=dd["cu_seqlens"], max_seqlen=max(LENGTHS))
+        torch.cuda.synchronize()
+        o_ref, h_ref = oracle.kda_forward(*args, **kw)
+        assert rel_err(o.cpu().numpy(), o_ref) <= tol and rel_err(hT.cpu().numpy(), h_ref) <= tol
+    got = kda.kda_chunk_bwd(*dev, do.cuda(), dhT=dhT.cuda(), h0=dd["h0"], cu_seqlens=dd["cu_seqlens"], max_seqlen=max(LENGTHS))
+    torch.cuda.synchronize()
+    ref = oracle.kda_backward(*args, do.numpy(), dhT=dhT.numpy(), **kw)
+    for name in ref:
+        e = rel_err(got[name].cpu().numpy(), ref[name])
+        assert e <= tol, "%s: error %.3e exceeds %.1e" % (name, e, tol)
