@@ -34,7 +34,11 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t stride = (int64_t)p.H * D, base = (c.tok0 * p.H + c.h) * (int64_t)D + m;
     float *slot = slots + c.slot * SL::kFloats;
-    if (tid < kC) sBeta[tid] = tid < c.nv ? load_as_float(beta + (c.tok0 + tid) * p.H + c.h) : 0.f;
+    if (tid < kC) {
+        const float b = tid < c.nv ? load_as_float(beta + (c.tok0 + tid) * p.H + c.h) : 0.f;
+        sBeta[tid] = b;
+        slot[SL::kBeta + tid] = b;
+    }
 
     // tiles of A (u < 10) and P (u >= 10), five per wave
     f32x4 acc[5] = {};

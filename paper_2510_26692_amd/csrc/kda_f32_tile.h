@@ -26,7 +26,8 @@ constexpr int kTri = 10;                                     // 16 x 16 blocks o
 __host__ __device__ constexpr int tri(int R, int I) { return R * (R + 1) / 2 + I; }      // block (R, I), I <= R
 
 // What the per-chunk kernel leaves per (chunk, head), in floats: Gamma.K, Gamma^{i->C}.K and Gamma.Q as
-// [token tile][channel tile] fragments, the blocks of Q and Tril(A_qk), all in column form, and e^(G_C).
+// [token tile][channel tile] fragments, the blocks of Q and Tril(A_qk), all in column form, e^(G_C) and beta (zero past
+// the chunk's end).
 template <int D> struct Slot {
     static constexpr int kTiles = D / 16;
     static constexpr int kKg = 0;
@@ -35,8 +36,9 @@ template <int D> struct Slot {
     static constexpr int kQ = kQg + 4 * kTiles * kFrag;
     static constexpr int kP = kQ + kTri * kFrag;
     static constexpr int kGc = kP + kTri * kFrag;
+    static constexpr int kBeta = kGc + D;
     static constexpr int kFloats = 3 * kC * D + 2 * kC * (kC + 2) + D;       // (the published size; 13 KiB of it are spare)
-    static_assert(kGc + D <= kFloats && kFloats % 64 == 0, "slots stay 256-byte aligned");
+    static_assert(kBeta + kC <= kFloats && kFloats % 64 == 0, "slots stay 256-byte aligned");
 };
 
 __device__ __forceinline__ f32x4 mfma16(const f32x4 &a, const f32x4 &b, f32x4 acc)      // a 16 x 16 x 16 product
@@ -54,11 +56,12 @@ template <int kCtrl> __device__ __forceinline__ float quad_swap(float x)
 __device__ __forceinline__ f32x4 quad_transpose(f32x4 r, int lane)
 {
     const bool b0 = lane & 1, b1 = lane & 2;
-    float s, t;
-    s = quad_swap<0xB1>(b0 ? r[0] : r[1]); t = quad_swap<0xB1>(b0 ? r[2] : r[3]);
-    if (b0) { r[0] = s; r[2] = t; } else { r[1] = s; r[3] = t; }
-    s = quad_swap<0x4E>(b1 ? r[0] : r[2]); t = quad_swap<0x4E>(b1 ? r[1] : r[3]);
-    if (b1) { r[0] = s; r[1] = t; } else { r[2] = s; r[3] = t; }
+    // (the swaps come first: in an arm of a conditional they would run with half of the lanes switched off)
+    const f32x4 s = {quad_swap<0xB1>(r[0]), quad_swap<0xB1>(r[1]), quad_swap<0xB1>(r[2]), quad_swap<0xB1>(r[3])};
+    const f32x4 t = {b0 ? s[1] : r[0], b0 ? r[1] : s[0], b0 ? s[3] : r[2], b0 ? r[3] : s[2]};
+    const f32x4 u = {quad_swap<0x4E>(t[0]), quad_swap<0x4E>(t[1]), quad_swap<0x4E>(t[2]), quad_swap<0x4E>(t[3])};
+    r[0] = b1 ? u[2] : t[0]; r[2] = b1 ? t[2] : u[0];
+    r[1] = b1 ? u[3] : t[1]; r[3] = b1 ? t[3] : u[1];
     return r;
 }
 // The lane of the other form that a lane reads (before the quads turn) or writes (after).
@@ -197,12 +200,12 @@ kda_status launch_prep(const Problem &p, const Tin *q, const Tin *k, const Tin *
                        hipStream_t stream);
 // Forward walk that writes o and the final states.
 template <typename Tin, int D>
-kda_status launch_forward_walk(const Problem &p, const Tin *v, const Tin *beta, const float *h0, const float *slots, float *o,
+kda_status launch_forward_walk(const Problem &p, const Tin *v, const float *h0, const float *slots, float *o,
                                float *hT, int compute_units, hipStream_t stream);
 // Forward and backward walks side by side: S0 of every chunk and R = v - S^T k of every token; dS1 of every chunk,
 // Z' = dV / beta of every token, dh0.
 template <typename Tin, typename Tdo, int D>
-kda_status launch_both_walks(const Problem &p, const Tin *v, const Tin *beta, const float *h0, const Tdo *d_o, const float *d_hT,
+kda_status launch_both_walks(const Problem &p, const Tin *v, const float *h0, const Tdo *d_o, const float *d_hT,
                              const float *slots, float *S0, float *R, float *dS1, float *Z, float *dh0, int compute_units,
                              hipStream_t stream);
 template <typename Tin, typename Tdo, int D>

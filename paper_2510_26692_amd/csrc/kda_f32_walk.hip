@@ -37,33 +37,98 @@ __device__ __forceinline__ Where where(const Problem &p, int64_t n, int h, int D
     return x;
 }
 
-// Rows 16 w + 4 g + j of NC column tiles of a [tokens, H, D] tensor, as they come (rows past nv: clamped).
-template <typename T, int NC>
-__device__ __forceinline__ void load_rows(f32x4 (&x)[NC], const T *base, int64_t stride, int row0, int nv)
-{
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
+// Rows row0 .. row0 + 3 of NC column tiles of a [tokens, H, D] tensor (rows past nv: the last one's, masked when used).
+// They are held as the 32-bit words they lie in and taken apart where they are used, behind an opaque point: left to
+// itself the compiler widens a bf16 value where it is loaded, or at the head of the loop, and waits for it there.
+template <typename T, int NC> struct Rows {
+    uint32_t raw[NC][4];
+    __device__ __forceinline__ void load_row(int j, const T *base, int m, int64_t stride, int row0, int nv)
+    {
         const int r = row0 + j;
-        const T *p = base + (int64_t)(r < nv ? r : nv - 1) * stride;
+        const T *p = base + (int64_t)(r < nv ? r : nv - 1) * stride + (sizeof(T) == 2 ? m & ~1 : m);
 #pragma unroll
-        for (int nc = 0; nc < NC; ++nc) x[nc][j] = load_as_float(p + 16 * nc);
+        for (int nc = 0; nc < NC; ++nc) raw[nc][j] = *reinterpret_cast<const uint32_t *>(p + 16 * nc);
+    }
+    __device__ __forceinline__ f32x4 tile(int nc, int m, int row0, int nv) const
+    {
+        f32x4 x;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            uint32_t u = raw[nc][j];
+            asm volatile("" : "+v"(u));
+            if (sizeof(T) == 2) u = m & 1 ? u & 0xffff0000u : u << 16;
+            x[j] = row0 + j < nv ? __uint_as_float(u) : 0.f;
+        }
+        return x;
+    }
+};
+
+// Loads, stores and LDS accesses stay on their side of this point; arithmetic may cross it.
+__device__ __forceinline__ void pin_memory_order() { __builtin_amdgcn_sched_barrier(0x0f); }
+
+// Four token tiles of B fragments from LDS: all fetched at once, so that one wait covers them, unless that takes more
+// than 32 registers.
+template <int NC> struct Four {
+    static constexpr bool kHeld = NC <= 2;
+    f32x4 b[kHeld ? 4 : 1][kHeld ? NC : 1];
+    const float *p;
+    __device__ __forceinline__ Four(const float *src, int lane) : p(src + 4 * lane)
+    {
+        if constexpr (kHeld) {
+#pragma unroll
+            for (int R = 0; R < 4; ++R)
+#pragma unroll
+                for (int nc = 0; nc < NC; ++nc) b[R][nc] = ld4(p + (nc * 4 + R) * kFrag);
+            pin_memory_order();
+        }
+    }
+    __device__ __forceinline__ f32x4 get(int R, int nc) const
+    {
+        if constexpr (kHeld) return b[R][nc];
+        else return ld4(p + (nc * 4 + R) * kFrag);
+    }
+};
+
+// acc[nc] += A_t B_t over N contraction tiles, B fragments from LDS fetched kAhead tiles ahead of the products.
+// after(t): the loads that refill what tile t has used, and stores.  They go out one or two at a time between the
+// products: a burst of them holds the wave up at issue (the L1 hands a compute unit 64 bytes a clock).
+template <int N, int NC, int kAhead, typename FA, typename FB, typename FH>
+__device__ __forceinline__ void product(f32x4 (&acc)[NC], FA &&a, FB &&b, FH &&after)
+{
+    f32x4 ring[kAhead + 1][NC];
+#pragma unroll
+    for (int t = 0; t < kAhead && t < N; ++t)
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) ring[t][nc] = b(t, nc);
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+        if (t + kAhead < N) {
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) ring[(t + kAhead) % (kAhead + 1)][nc] = b(t + kAhead, nc);
+        }
+        pin_memory_order();
+        const f32x4 at = a(t);
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) acc[nc] = mfma16(at, ring[t % (kAhead + 1)][nc], acc[nc]);
+        after(t);
     }
 }
-template <typename T>
-__device__ __forceinline__ f32x4 load_beta(const T *base, int64_t H, int row0, int nv)
-{
-    f32x4 b;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) b[j] = load_as_float(base + (int64_t)(row0 + j < nv ? row0 + j : nv - 1) * H);
-    return b;
-}
-template <int NC> __device__ __forceinline__ void mask_rows(f32x4 (&x)[NC], int row0, int nv)
+
+// S[tt][nc] += A_tt,R B_R over the four token tiles, likewise.
+template <int TW, int NC, typename FH>
+__device__ __forceinline__ void update_state(f32x4 (&S)[TW][NC], const f32x4 (&a)[TW][4], const Four<NC> &b, FH &&after)
 {
 #pragma unroll
-    for (int nc = 0; nc < NC; ++nc)
+    for (int R = 0; R < 4; ++R) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (row0 + j >= nv) x[nc][j] = 0.f;
+        for (int nc = 0; nc < NC; ++nc) {
+            const f32x4 x = b.get(R, nc);
+#pragma unroll
+            for (int tt = 0; tt < TW; ++tt) S[tt][nc] = mfma16(a[tt][R], x, S[tt][nc]);
+        }
+        pin_memory_order();
+        after(R);
+    }
 }
 
 template <int D, int NC>
@@ -102,7 +167,7 @@ __device__ __forceinline__ void store_rows(float *dst, const f32x4 (&x)[NC], int
 
 // kOut: o instead of S0 and R.
 template <typename Tin, int D, int NC, bool kOut>
-__device__ __forceinline__ void forward_walk(float *smem, const Problem &p, const Tin *v, const Tin *beta, const float *h0,
+__device__ __forceinline__ void forward_walk(float *smem, const Problem &p, const Tin *v, const float *h0,
                                              const float *slots, float *S0, float *Rw, float *o, float *hT, int64_t n, int h,
                                              int slice)
 {
@@ -117,36 +182,21 @@ __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, cons
 
     f32x4 S[TW][NC];
     load_state<D, NC>(S, h0 ? h0 + x.state + col0 + m : nullptr, t0, g);
-    f32x4 kg[NT], qm[4], kt[TW][4], gam[TW], vv[NC], bt, qg[kOut ? NT : 1], pm[kOut ? 4 : 1];
-    auto load_kg = [&](const float *slot) __attribute__((always_inline)) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            kg[t] = ld4(slot + SL::kKg + (w * NT + t) * kFrag + turned);
-            if (kOut) qg[t] = ld4(slot + SL::kQg + (w * NT + t) * kFrag + turned);
-        }
-    };
-    auto load_q = [&](const float *slot) __attribute__((always_inline)) {
-#pragma unroll
-        for (int J = 0; J < 4; ++J) qm[J] = ld4(slot + SL::kQ + tri(w, J < w ? J : w) * kFrag + turned);
-    };
-    auto load_kt = [&](const float *slot) __attribute__((always_inline)) {
-#pragma unroll
-        for (int tt = 0; tt < TW; ++tt) {
-#pragma unroll
-            for (int R = 0; R < 4; ++R) kt[tt][R] = ld4(slot + SL::kKt + (R * NT + t0 + tt) * kFrag + 4 * lane);
-            gam[tt] = ld4(slot + SL::kGc + 16 * (t0 + tt) + 4 * g);
-        }
-        if (kOut) {
-#pragma unroll
-            for (int J = 0; J < 4; ++J) pm[J] = ld4(slot + SL::kP + tri(w, J < w ? J : w) * kFrag + turned);
-        }
-    };
+    constexpr int kAhead = NC == 1 ? 4 : NC == 2 ? 2 : 1;
+    f32x4 kg[NT], qm[4], kt[TW][4], gam[TW], qg[kOut ? NT : 1], pm[kOut ? 4 : 1];
+    f32x4 bt;
+    Rows<Tin, NC> vv;
+    auto load_kg = [&](const float *slot, int t) __attribute__((always_inline)) { kg[t] = ld4(slot + SL::kKg + (w * NT + t) * kFrag + turned); };
+    auto load_qg = [&](const float *slot, int t) __attribute__((always_inline)) { qg[kOut ? t : 0] = ld4(slot + SL::kQg + (w * NT + t) * kFrag + turned); };
+    auto load_q = [&](const float *slot, int J) __attribute__((always_inline)) { qm[J] = ld4(slot + SL::kQ + tri(w, J < w ? J : w) * kFrag + turned); };
+    auto load_p = [&](const float *slot, int J) __attribute__((always_inline)) { pm[kOut ? J : 0] = ld4(slot + SL::kP + tri(w, J < w ? J : w) * kFrag + turned); };
+    auto load_kt = [&](const float *slot, int tt, int R) __attribute__((always_inline)) { kt[tt][R] = ld4(slot + SL::kKt + (R * NT + t0 + tt) * kFrag + 4 * lane); };
+    auto load_gam = [&](const float *slot, int tt) __attribute__((always_inline)) { gam[tt] = ld4(slot + SL::kGc + 16 * (t0 + tt) + 4 * g); };
     auto valid = [&](int64_t ci) { return (int)(x.len - ci * kC < kC ? x.len - ci * kC : kC); };
-    auto load_v = [&](int64_t ci) __attribute__((always_inline)) {
-        const int64_t at = ((x.tok_base + ci * kC) * p.H + h);
-        load_rows<Tin, NC>(vv, v + at * D + col0 + m, stride, row0, valid(ci));
-        bt = load_beta(beta + at, p.H, row0, valid(ci));
+    auto load_v = [&](int64_t ci, int j) __attribute__((always_inline)) {
+        vv.load_row(j, v + ((x.tok_base + ci * kC) * p.H + h) * D + col0, m, stride, row0, valid(ci));
     };
+    auto load_b = [&](const float *slot) __attribute__((always_inline)) { bt = ld4(slot + SL::kBeta + row0); };
     auto share_state = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int tt = 0; tt < TW; ++tt)
@@ -155,7 +205,23 @@ __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, cons
     };
     if (x.nchunks > 0) {
         const float *slot = slots + x.slot0 * SL::kFloats;
-        load_kg(slot); load_v(0); load_q(slot); load_kt(slot);
+        // (in the order of the loop: the compiler's waits take the worse of the two ways into it)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) load_kg(slot, t);
+        if (kOut) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) load_qg(slot, t);
+        }
+        pin_memory_order();
+#pragma unroll
+        for (int R = 0; R < 4; ++R) {
+            load_q(slot, R); load_v(0, R);
+            if (R == 0) load_b(slot);
+#pragma unroll
+            for (int tt = 0; tt < TW; ++tt) load_kt(slot, tt, R);
+            if (R < TW) load_gam(slot, R < TW ? R : 0);
+            pin_memory_order();
+        }
         share_state();
         lds_barrier();
     }
@@ -163,47 +229,46 @@ __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, cons
     for (int64_t ci = 0; ci < x.nchunks; ++ci) {
         const int nv = valid(ci);
         const int64_t cn = ci + 1 < x.nchunks ? ci + 1 : ci;                  // (the last step fetches its own operands again)
-        const float *next = slots + (x.slot0 + cn * p.H) * SL::kFloats;
-        const int64_t sl = x.slot0 + ci * p.H;
+        const float *next = slots + (x.slot0 + cn * p.H) * SL::kFloats, *here = slots + (x.slot0 + ci * p.H) * SL::kFloats;
+        float *s0 = kOut ? nullptr : S0 + (x.slot0 + ci * p.H) * (int64_t)(D * D) + turned;
         // Y = V - Kg S0
         f32x4 y[NC] = {}, oo[kOut ? NC : 1] = {};
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const f32x4 a = quad_transpose(kg[t], lane), aq = kOut ? quad_transpose(qg[kOut ? t : 0], lane) : a;
-#pragma unroll
-            for (int nc = 0; nc < NC; ++nc) {
-                const f32x4 b = ld4(sS + (nc * NT + t) * kFrag + 4 * lane);
-                y[nc] = mfma16(a, b, y[nc]);
-                if (kOut) oo[kOut ? nc : 0] = mfma16(aq, b, oo[kOut ? nc : 0]);
-            }
-        }
-        load_kg(next);
-        if (nv < kC) mask_rows<NC>(vv, row0, nv);
+        product<NT, NC, kAhead>(y, [&](int t) { return quad_transpose(kg[t], lane); },
+                                [&](int t, int nc) { return ld4(sS + (nc * NT + t) * kFrag + 4 * lane); },
+                                [&](int t) {
+                                    load_kg(next, t);
+                                    if (kOut && t < 4) load_p(here, t);
+                                    const int tt = t / NC, nc = t % NC;
+                                    if (!kOut && tt < TW)
+                                        st4(s0 + ((t0 + tt) * NT + NC * slice + nc) * kFrag, quad_transpose(S[tt < TW ? tt : 0][nc], lane));
+                                });
         const f32x4 b4 = bt;
 #pragma unroll
         for (int nc = 0; nc < NC; ++nc) {
-            y[nc] = vv[nc] - y[nc];
+            y[nc] = vv.tile(nc, m, row0, nv) - y[nc];
             st4(sY + (nc * 4 + w) * kFrag + 4 * lane, b4 * y[nc]);
         }
-        load_v(cn);
-        if (!kOut) {
-#pragma unroll
-            for (int tt = 0; tt < TW; ++tt)
-#pragma unroll
-                for (int nc = 0; nc < NC; ++nc)
-                    st4(S0 + sl * (int64_t)(D * D) + ((t0 + tt) * NT + NC * slice + nc) * kFrag + turned, quad_transpose(S[tt][nc], lane));
-        }
+        if constexpr (kOut)                                                   // O = scale (Qg S0 + P Vn), the first half
+            product<NT, NC, kAhead>(oo, [&](int t) { return quad_transpose(qg[t], lane); },
+                                    [&](int t, int nc) { return ld4(sS + (nc * NT + t) * kFrag + 4 * lane); },
+                                    [&](int t) { load_qg(next, t); });
         lds_barrier();
         // R = Y - Q (beta Y)
         f32x4 r[NC] = {};
+        {
+            const Four<NC> by(sY, lane);
 #pragma unroll
-        for (int J = 0; J < 4; ++J)
-            if (J <= w) {
-                const f32x4 a = quad_transpose(qm[J], lane);
+            for (int tt = 0; tt < TW; ++tt)
 #pragma unroll
-                for (int nc = 0; nc < NC; ++nc) r[nc] = mfma16(a, ld4(sY + (nc * 4 + J) * kFrag + 4 * lane), r[nc]);
-            }
-        load_q(next);
+                for (int nc = 0; nc < NC; ++nc) S[tt][nc] *= gam[tt];
+#pragma unroll
+            for (int J = 0; J < 4; ++J)
+                if (J <= w) {
+                    const f32x4 a = quad_transpose(qm[J], lane);
+#pragma unroll
+                    for (int nc = 0; nc < NC; ++nc) r[nc] = mfma16(a, by.get(J, nc), r[nc]);
+                }
+        }
 #pragma unroll
         for (int nc = 0; nc < NC; ++nc) {
             r[nc] = y[nc] - r[nc];
@@ -214,44 +279,41 @@ __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, cons
         }
         lds_barrier();
         // S1 = Diag(e^(G_C)) S0 + Kt^T Vn
+        {
+            const Four<NC> bv(sV, lane);
+            update_state<TW, NC>(S, kt, bv, [&](int R) {
+                load_q(next, R);
+                load_v(cn, R);
+                if (R == 0) load_b(next);
 #pragma unroll
-        for (int tt = 0; tt < TW; ++tt)
+                for (int tt = 0; tt < TW; ++tt) load_kt(next, tt, R);
+                if (R < TW) load_gam(next, R < TW ? R : 0);
+            });
+            share_state();
+            if (kOut) {
 #pragma unroll
-            for (int nc = 0; nc < NC; ++nc) S[tt][nc] *= gam[tt];
+                for (int J = 0; J < 4; ++J)
+                    if (J <= w) {
+                        const f32x4 a = quad_transpose(pm[kOut ? J : 0], lane);
 #pragma unroll
-        for (int R = 0; R < 4; ++R)
+                        for (int nc = 0; nc < NC; ++nc) oo[kOut ? nc : 0] = mfma16(a, bv.get(J, nc), oo[kOut ? nc : 0]);
+                    }
+                float *po = o + ((x.tok_base + ci * kC) * p.H + h) * (int64_t)D + col0 + m;
 #pragma unroll
-            for (int nc = 0; nc < NC; ++nc) {
-                const f32x4 b = ld4(sV + (nc * 4 + R) * kFrag + 4 * lane);
+                for (int j = 0; j < 4; ++j)
+                    if (row0 + j < nv) {
 #pragma unroll
-                for (int tt = 0; tt < TW; ++tt) S[tt][nc] = mfma16(kt[tt][R], b, S[tt][nc]);
+                        for (int nc = 0; nc < NC; ++nc) po[(row0 + j) * stride + 16 * nc] = p.scale * oo[kOut ? nc : 0][j];
+                    }
             }
-        share_state();
-        if (kOut) {
-            // O = scale (Qg S0 + P Vn)
-#pragma unroll
-            for (int J = 0; J < 4; ++J)
-                if (J <= w) {
-                    const f32x4 a = quad_transpose(pm[kOut ? J : 0], lane);
-#pragma unroll
-                    for (int nc = 0; nc < NC; ++nc) oo[kOut ? nc : 0] = mfma16(a, ld4(sV + (nc * 4 + J) * kFrag + 4 * lane), oo[kOut ? nc : 0]);
-                }
-            float *po = o + ((x.tok_base + ci * kC) * p.H + h) * (int64_t)D + col0 + m;
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (row0 + j < nv) {
-#pragma unroll
-                    for (int nc = 0; nc < NC; ++nc) po[(row0 + j) * stride + 16 * nc] = p.scale * oo[kOut ? nc : 0][j];
-                }
         }
-        load_kt(next);
         lds_barrier();
     }
     if (hT) store_state<D, NC>(hT + x.state + col0 + m, S, t0, g);
 }
 
-template <typename Tin, typename Tdo, int D, int NC>
-__device__ __forceinline__ void backward_walk(float *smem, const Problem &p, const Tin *beta, const Tdo *d_o, const float *d_hT,
+template <typename Tdo, int D, int NC>
+__device__ __forceinline__ void backward_walk(float *smem, const Problem &p, const Tdo *d_o, const float *d_hT,
                                               const float *slots, float *dS1, float *Zw, float *dh0, int64_t n, int h, int slice)
 {
     using SL = Slot<D>;
@@ -265,40 +327,24 @@ __device__ __forceinline__ void backward_walk(float *smem, const Problem &p, con
 
     f32x4 S[TW][NC];
     load_state<D, NC>(S, d_hT ? d_hT + x.state + col0 + m : nullptr, t0, g);
-    f32x4 kt[NT], pm[4], qm[4], kg[TW][4], qg[TW][4], gam[TW], vo[NC], bt;
-    auto load_kt = [&](const float *slot) __attribute__((always_inline)) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) kt[t] = ld4(slot + SL::kKt + (w * NT + t) * kFrag + turned);
-#pragma unroll
-        for (int R = 0; R < 4; ++R) pm[R] = ld4(slot + SL::kP + tri(R > w ? R : w, w) * kFrag + 4 * lane);
-    };
-    auto load_q = [&](const float *slot) __attribute__((always_inline)) {
-#pragma unroll
-        for (int R = 0; R < 4; ++R) qm[R] = ld4(slot + SL::kQ + tri(R > w ? R : w, w) * kFrag + 4 * lane);
-    };
-    auto load_kg = [&](const float *slot) __attribute__((always_inline)) {
-#pragma unroll
-        for (int tt = 0; tt < TW; ++tt) {
-#pragma unroll
-            for (int R = 0; R < 4; ++R) {
-                kg[tt][R] = ld4(slot + SL::kKg + (R * NT + t0 + tt) * kFrag + 4 * lane);
-                qg[tt][R] = ld4(slot + SL::kQg + (R * NT + t0 + tt) * kFrag + 4 * lane);
-            }
-            gam[tt] = ld4(slot + SL::kGc + 16 * (t0 + tt) + 4 * g);
-        }
-    };
+    constexpr int kAhead = NC == 1 ? 4 : NC == 2 ? 2 : 1;
+    f32x4 kt[NT], pm[4], qm[4], kg[TW][4], qg[TW][4], gam[TW];
+    f32x4 bt;
+    Rows<Tdo, NC> vo;
+    auto load_kt = [&](const float *slot, int t) __attribute__((always_inline)) { kt[t] = ld4(slot + SL::kKt + (w * NT + t) * kFrag + turned); };
+    auto load_p = [&](const float *slot, int R) __attribute__((always_inline)) { pm[R] = ld4(slot + SL::kP + tri(R > w ? R : w, w) * kFrag + 4 * lane); };
+    auto load_q = [&](const float *slot, int R) __attribute__((always_inline)) { qm[R] = ld4(slot + SL::kQ + tri(R > w ? R : w, w) * kFrag + 4 * lane); };
+    auto load_kg = [&](const float *slot, int tt, int R) __attribute__((always_inline)) { kg[tt][R] = ld4(slot + SL::kKg + (R * NT + t0 + tt) * kFrag + 4 * lane); };
+    auto load_qg = [&](const float *slot, int tt, int R) __attribute__((always_inline)) { qg[tt][R] = ld4(slot + SL::kQg + (R * NT + t0 + tt) * kFrag + 4 * lane); };
+    auto load_gam = [&](const float *slot, int tt) __attribute__((always_inline)) { gam[tt] = ld4(slot + SL::kGc + 16 * (t0 + tt) + 4 * g); };
     auto valid = [&](int64_t ci) { return (int)(x.len - ci * kC < kC ? x.len - ci * kC : kC); };
-    auto load_o = [&](int64_t ci) __attribute__((always_inline)) {
-        load_rows<Tdo, NC>(vo, d_o + ((x.tok_base + ci * kC) * p.H + h) * (int64_t)D + col0 + m, stride, row0, valid(ci));
+    auto load_o = [&](int64_t ci, int j) __attribute__((always_inline)) {
+        vo.load_row(j, d_o + ((x.tok_base + ci * kC) * p.H + h) * (int64_t)D + col0, m, stride, row0, valid(ci));
     };
-    auto load_b = [&](int64_t ci) __attribute__((always_inline)) {
-        bt = load_beta(beta + (x.tok_base + ci * kC) * p.H + h, p.H, row0, valid(ci));
-    };
-    auto share_o = [&](int64_t ci) __attribute__((always_inline)) {
-        if (valid(ci) < kC) mask_rows<NC>(vo, row0, valid(ci));
-        float *dst = sO + (ci & 1) * (NC * 4 * kFrag);
+    auto load_b = [&](const float *slot) __attribute__((always_inline)) { bt = ld4(slot + SL::kBeta + row0); };
+    auto share_o = [&](int64_t ci, int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int nc = 0; nc < NC; ++nc) st4(dst + (nc * 4 + w) * kFrag + 4 * lane, vo[nc] * p.scale);
+        for (int nc = 0; nc < NC; ++nc) st4(sO + ((buf * NC + nc) * 4 + w) * kFrag + 4 * lane, vo.tile(nc, m, row0, valid(ci)) * p.scale);
     };
     auto share_state = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -309,78 +355,104 @@ __device__ __forceinline__ void backward_walk(float *smem, const Problem &p, con
     const int64_t last = x.nchunks - 1;
     if (last >= 0) {
         const float *slot = slots + (x.slot0 + last * p.H) * SL::kFloats;
-        load_o(last); load_kt(slot); load_b(last); load_q(slot); load_kg(slot);
-        share_state();
-        share_o(last);
-        load_o(last > 0 ? last - 1 : 0);
-        lds_barrier();
-    }
-#pragma unroll 1
-    for (int64_t ci = last; ci >= 0; --ci) {
-        const int64_t cn = ci > 0 ? ci - 1 : 0;
-        const float *next = slots + (x.slot0 + cn * p.H) * SL::kFloats;
-        const int64_t sl = x.slot0 + ci * p.H;
-        const float *so = sO + (ci & 1) * (NC * 4 * kFrag);
-        // dVn = Kt dS1 + P^T dO
-        f32x4 y[NC] = {};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) load_o(last, j);
+        share_o(last, 0);
+        // (in the order of the loop: the compiler's waits take the worse of the two ways into it)
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            const f32x4 a = quad_transpose(kt[t], lane);
+            load_kt(slot, t);
+            if (t < 4) load_p(slot, t);
+        }
+        pin_memory_order();
 #pragma unroll
-            for (int nc = 0; nc < NC; ++nc) y[nc] = mfma16(a, ld4(sS + (nc * NT + t) * kFrag + 4 * lane), y[nc]);
+        for (int R = 0; R < 4; ++R) {
+            load_q(slot, R);
+            if (R == 0) load_b(slot);
+            load_o(last > 0 ? last - 1 : 0, R);
+#pragma unroll
+            for (int tt = 0; tt < TW; ++tt) load_qg(slot, tt, R);
+            if (R < TW) load_gam(slot, R < TW ? R : 0);
+            pin_memory_order();
         }
 #pragma unroll
-        for (int R = 0; R < 4; ++R)
-            if (R >= w) {
+        for (int R = 0; R < 4; ++R) {
 #pragma unroll
-                for (int nc = 0; nc < NC; ++nc) y[nc] = mfma16(pm[R], ld4(so + (nc * 4 + R) * kFrag + 4 * lane), y[nc]);
-            }
-        load_kt(next);
-        const f32x4 b4 = bt;                                  // (padding rows: dVn is zero there, whatever beta reads)
+            for (int tt = 0; tt < TW; ++tt) load_kg(slot, tt, R);
+            pin_memory_order();
+        }
+        share_state();
+        lds_barrier();
+    }
+    int buf = 0;
+#pragma unroll 1
+    for (int64_t ci = last; ci >= 0; --ci, buf ^= 1) {
+        const int64_t cn = ci > 0 ? ci - 1 : 0, cnn = cn > 0 ? cn - 1 : 0;
+        const float *next = slots + (x.slot0 + cn * p.H) * SL::kFloats;
+        float *ds1 = dS1 + (x.slot0 + ci * p.H) * (int64_t)(D * D) + turned;
+        const int nv = valid(ci);
+        const float *so = sO + buf * (NC * 4 * kFrag);
+        // dVn = Kt dS1 + P^T dO
+        f32x4 y[NC] = {};
+        {
+            const Four<NC> bo(so, lane);
+#pragma unroll
+            for (int R = 0; R < 4; ++R)
+                if (R >= w) {
+#pragma unroll
+                    for (int nc = 0; nc < NC; ++nc) y[nc] = mfma16(pm[R], bo.get(R, nc), y[nc]);
+                }
+        }
+        product<NT, NC, kAhead>(y, [&](int t) { return quad_transpose(kt[t], lane); },
+                                [&](int t, int nc) { return ld4(sS + (nc * NT + t) * kFrag + 4 * lane); },
+                                [&](int t) {
+                                    load_kt(next, t);
+                                    if (t < 4) load_p(next, t);
+                                    const int tt = t / NC, nc = t % NC;
+                                    if (tt < TW)
+                                        st4(ds1 + ((t0 + tt) * NT + NC * slice + nc) * kFrag, quad_transpose(S[tt < TW ? tt : 0][nc], lane));
+                                });
+        const f32x4 b4 = bt;
 #pragma unroll
         for (int nc = 0; nc < NC; ++nc) st4(sY + (nc * 4 + w) * kFrag + 4 * lane, b4 * y[nc]);
-        load_b(cn);
-#pragma unroll
-        for (int tt = 0; tt < TW; ++tt)
-#pragma unroll
-            for (int nc = 0; nc < NC; ++nc)
-                st4(dS1 + sl * (int64_t)(D * D) + ((t0 + tt) * NT + NC * slice + nc) * kFrag + turned, quad_transpose(S[tt][nc], lane));
+        share_o(cn, buf ^ 1);
         lds_barrier();
         // Z = dVn - Q^T (beta dVn)
         f32x4 z[NC] = {};
+        {
+            const Four<NC> by(sY, lane);
 #pragma unroll
-        for (int R = 0; R < 4; ++R)
-            if (R >= w) {
+            for (int tt = 0; tt < TW; ++tt)
 #pragma unroll
-                for (int nc = 0; nc < NC; ++nc) z[nc] = mfma16(qm[R], ld4(sY + (nc * 4 + R) * kFrag + 4 * lane), z[nc]);
-            }
-        load_q(next);
+                for (int nc = 0; nc < NC; ++nc) S[tt][nc] *= gam[tt];
+#pragma unroll
+            for (int R = 0; R < 4; ++R)
+                if (R >= w) {
+#pragma unroll
+                    for (int nc = 0; nc < NC; ++nc) z[nc] = mfma16(qm[R], by.get(R, nc), z[nc]);
+                }
+        }
 #pragma unroll
         for (int nc = 0; nc < NC; ++nc) {
             z[nc] = y[nc] - z[nc];
             st4(sX + (nc * 4 + w) * kFrag + 4 * lane, -b4 * z[nc]);
         }
-        store_rows<D, NC>(Zw, z, x.tok_base + ci * kC, p.H, h, valid(ci), w, NC * slice, lane);
+        // dS0 = Diag(e^(G_C)) dS1 + Qg^T dO - Kg^T X  (the first product is done while X is on its way)
+        update_state<TW, NC>(S, qg, Four<NC>(so, lane), [&](int R) {
+            load_q(next, R);
+            if (R == 0) load_b(next);
+            load_o(cnn, R);
+#pragma unroll
+            for (int tt = 0; tt < TW; ++tt) load_qg(next, tt, R);
+            if (R < TW) load_gam(next, R < TW ? R : 0);
+        });
+        store_rows<D, NC>(Zw, z, x.tok_base + ci * kC, p.H, h, nv, w, NC * slice, lane);
         lds_barrier();
-        // dS0 = Diag(e^(G_C)) dS1 + Qg^T dO - Kg^T X
+        update_state<TW, NC>(S, kg, Four<NC>(sX, lane), [&](int R) {
 #pragma unroll
-        for (int tt = 0; tt < TW; ++tt)
-#pragma unroll
-            for (int nc = 0; nc < NC; ++nc) S[tt][nc] *= gam[tt];
-#pragma unroll
-        for (int R = 0; R < 4; ++R)
-#pragma unroll
-            for (int nc = 0; nc < NC; ++nc) {
-                const f32x4 bo = ld4(so + (nc * 4 + R) * kFrag + 4 * lane), bx = ld4(sX + (nc * 4 + R) * kFrag + 4 * lane);
-#pragma unroll
-                for (int tt = 0; tt < TW; ++tt) S[tt][nc] = mfma16(kg[tt][R], bx, mfma16(qg[tt][R], bo, S[tt][nc]));
-            }
+            for (int tt = 0; tt < TW; ++tt) load_kg(next, tt, R);
+        });
         share_state();
-        load_kg(next);
-        if (ci > 0) {
-            share_o(cn);
-            load_o(cn > 0 ? cn - 1 : 0);
-        }
         lds_barrier();
     }
     if (dh0) store_state<D, NC>(dh0 + x.state + col0 + m, S, t0, g);
@@ -400,22 +472,25 @@ __device__ __forceinline__ bool place(const Problem &p, int64_t bid, int64_t &n,
 }
 static int64_t walk_workgroups(const Problem &p, int slices) { return ((int64_t)p.num_seqs * p.H + 7) / 8 * 8 * slices; }
 
+// Workgroups a compute unit should hold: two, except the widest, whose registers (and LDS) are a whole one's.
+template <int D, int NC> constexpr int per_cu() { return D * NC == 512 ? 1 : 2; }
+
 template <typename Tin, int D, int NC>
-__global__ __launch_bounds__(kWalkThreads, 2)
-void kda_f32_forward_walk_kernel(const Tin *__restrict__ v, const Tin *__restrict__ beta, const float *__restrict__ h0,
+__global__ __launch_bounds__(kWalkThreads, (per_cu<D, NC>()))
+void kda_f32_forward_walk_kernel(const Tin *__restrict__ v, const float *__restrict__ h0,
                                  const float *__restrict__ slots, float *__restrict__ o, float *__restrict__ hT, const Problem p)
 {
     extern __shared__ __attribute__((aligned(16))) float smem[];
     int64_t n;
     int h, slice;
     if (!place<D, NC>(p, blockIdx.x, n, h, slice)) return;
-    forward_walk<Tin, D, NC, true>(smem, p, v, beta, h0, slots, nullptr, nullptr, o, hT, n, h, slice);
+    forward_walk<Tin, D, NC, true>(smem, p, v, h0, slots, nullptr, nullptr, o, hT, n, h, slice);
 }
 
 // The backward walk, the longer of the two, goes first.
 template <typename Tin, typename Tdo, int D, int NC>
-__global__ __launch_bounds__(kWalkThreads, 2)
-void kda_f32_both_walks_kernel(const Tin *__restrict__ v, const Tin *__restrict__ beta, const float *__restrict__ h0,
+__global__ __launch_bounds__(kWalkThreads, (per_cu<D, NC>()))
+void kda_f32_both_walks_kernel(const Tin *__restrict__ v, const float *__restrict__ h0,
                                const Tdo *__restrict__ d_o, const float *__restrict__ d_hT, const float *__restrict__ slots,
                                float *__restrict__ S0, float *__restrict__ Rw, float *__restrict__ dS1, float *__restrict__ Zw,
                                float *__restrict__ dh0, int64_t half, const Problem p)
@@ -425,8 +500,8 @@ void kda_f32_both_walks_kernel(const Tin *__restrict__ v, const Tin *__restrict_
     int64_t n;
     int h, slice;
     if (!place<D, NC>(p, bid < half ? bid : bid - half, n, h, slice)) return;
-    if (bid < half) backward_walk<Tin, Tdo, D, NC>(smem, p, beta, d_o, d_hT, slots, dS1, Zw, dh0, n, h, slice);
-    else forward_walk<Tin, D, NC, false>(smem, p, v, beta, h0, slots, S0, Rw, nullptr, nullptr, n, h, slice);
+    if (bid < half) backward_walk<Tdo, D, NC>(smem, p, d_o, d_hT, slots, dS1, Zw, dh0, n, h, slice);
+    else forward_walk<Tin, D, NC, false>(smem, p, v, h0, slots, S0, Rw, nullptr, nullptr, n, h, slice);
 }
 
 // Column tiles per workgroup: the fewest that still give every compute unit at most two workgroups (more than two
@@ -453,36 +528,36 @@ static kda_status launch_walk(F kern, const char *name, int64_t blocks, size_t l
 }
 
 template <typename Tin, int D>
-kda_status launch_forward_walk(const Problem &p, const Tin *v, const Tin *beta, const float *h0, const float *slots, float *o,
+kda_status launch_forward_walk(const Problem &p, const Tin *v, const float *h0, const float *slots, float *o,
                                float *hT, int compute_units, hipStream_t stream)
 {
 #define KDA_GO(NC) launch_walk(kda_f32_forward_walk_kernel<Tin, D, NC>, "kda_f32_forward_walk", walk_workgroups(p, D / (16 * NC)), \
-                               walk_lds<D, NC>(false), stream, v, beta, h0, slots, o, hT, p)
+                               walk_lds<D, NC>(false), stream, v, h0, slots, o, hT, p)
     const int nc = column_tiles(p, D, 1, compute_units);
     return nc == 1 ? KDA_GO(1) : nc == 2 ? KDA_GO(2) : KDA_GO(4);
 #undef KDA_GO
 }
 
 template <typename Tin, typename Tdo, int D>
-kda_status launch_both_walks(const Problem &p, const Tin *v, const Tin *beta, const float *h0, const Tdo *d_o, const float *d_hT,
+kda_status launch_both_walks(const Problem &p, const Tin *v, const float *h0, const Tdo *d_o, const float *d_hT,
                              const float *slots, float *S0, float *R, float *dS1, float *Z, float *dh0, int compute_units,
                              hipStream_t stream)
 {
 #define KDA_GO(NC) launch_walk(kda_f32_both_walks_kernel<Tin, Tdo, D, NC>, "kda_f32_both_walks", 2 * walk_workgroups(p, D / (16 * NC)), \
-                               walk_lds<D, NC>(true), stream, v, beta, h0, d_o, d_hT, slots, S0, R, dS1, Z, dh0, \
+                               walk_lds<D, NC>(true), stream, v, h0, d_o, d_hT, slots, S0, R, dS1, Z, dh0, \
                                walk_workgroups(p, D / (16 * NC)), p)
     const int nc = column_tiles(p, D, 2, compute_units);
     return nc == 1 ? KDA_GO(1) : nc == 2 ? KDA_GO(2) : KDA_GO(4);
 #undef KDA_GO
 }
 
-#define KDA_FWD(T, DD) template kda_status launch_forward_walk<T, DD>(const Problem &, const T *, const T *, const float *, \
+#define KDA_FWD(T, DD) template kda_status launch_forward_walk<T, DD>(const Problem &, const T *, const float *, \
                                                                       const float *, float *, float *, int, hipStream_t)
 KDA_FWD(float, 64);
 KDA_FWD(float, 128);
 KDA_FWD(__hip_bfloat16, 64);
 KDA_FWD(__hip_bfloat16, 128);
-#define KDA_BOTH(T, O, DD) template kda_status launch_both_walks<T, O, DD>(const Problem &, const T *, const T *, const float *, \
+#define KDA_BOTH(T, O, DD) template kda_status launch_both_walks<T, O, DD>(const Problem &, const T *, const float *, \
     const O *, const float *, const float *, float *, float *, float *, float *, float *, int, hipStream_t)
 KDA_BOTH(float, float, 64);
 KDA_BOTH(float, float, 128);
