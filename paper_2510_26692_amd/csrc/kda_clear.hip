@@ -1,0 +1,57 @@
+// Zeros for the rows of a packed batch that belong to no sequence: the compute entry points leave them untouched, and a
+// caller that allocates an output has to clear no more than these (usually none) instead of the whole array.
+#include "kda_common.h"
+
+namespace kda {
+namespace {
+
+constexpr int kMaxArrays = 8;
+struct Arrays {
+    float4 *p[kMaxArrays];
+    int64_t row16[kMaxArrays];      // 16-byte units per token; 0: 4-byte units, row4
+    int64_t row4[kMaxArrays];
+};
+
+// One row of workgroups per array; every workgroup reads the number of owned tokens and, as a rule, leaves.
+__global__ void kda_clear_unowned_kernel(const int32_t *cu, int num_seqs, int64_t tokens, const Arrays a)
+{
+    const int64_t owned = cu[num_seqs];
+    if (owned >= tokens) return;
+    const int k = blockIdx.y;
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    if (a.row16[k]) {
+        const int64_t end = tokens * a.row16[k];
+        for (int64_t i = owned * a.row16[k] + i0; i < end; i += step) a.p[k][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    } else {
+        float *p = reinterpret_cast<float *>(a.p[k]);
+        const int64_t end = tokens * a.row4[k];
+        for (int64_t i = owned * a.row4[k] + i0; i < end; i += step) p[i] = 0.f;
+    }
+}
+
+}  // namespace
+}  // namespace kda
+
+using namespace kda;
+
+extern "C" kda_status kda_clear_unowned_rows(const int32_t *cu_seqlens, int32_t num_seqs, int64_t tokens, int32_t num_arrays,
+                                             void *const *arrays, const size_t *row_bytes, void *hip_stream)
+{
+    if (!cu_seqlens || (reinterpret_cast<uintptr_t>(cu_seqlens) & 3u) || num_seqs < 0 || tokens < 0)
+        return fail(KDA_ERR_INVALID_ARG, "kda_clear_unowned_rows: cu_seqlens, num_seqs or tokens");
+    if (num_arrays < 0 || num_arrays > kMaxArrays || (num_arrays && (!arrays || !row_bytes)))
+        return fail(KDA_ERR_INVALID_ARG, "kda_clear_unowned_rows takes up to %d arrays, got %d", kMaxArrays, num_arrays);
+    if (num_arrays == 0 || tokens == 0) return KDA_OK;
+    Arrays a{};
+    for (int k = 0; k < num_arrays; ++k) {
+        if (!arrays[k] || (reinterpret_cast<uintptr_t>(arrays[k]) & 15u) || row_bytes[k] % 4)
+            return fail(KDA_ERR_INVALID_ARG, "kda_clear_unowned_rows: array %d is NULL, misaligned or has rows of %zu bytes", k, row_bytes[k]);
+        a.p[k] = static_cast<float4 *>(arrays[k]);
+        a.row16[k] = row_bytes[k] % 16 ? 0 : (int64_t)(row_bytes[k] / 16);
+        a.row4[k] = (int64_t)(row_bytes[k] / 4);
+    }
+    hipLaunchKernelGGL(kda_clear_unowned_kernel, dim3(64, (unsigned)num_arrays), dim3(256), 0, static_cast<hipStream_t>(hip_stream),
+                       cu_seqlens, num_seqs, tokens, a);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? KDA_OK : fail(KDA_ERR_LAUNCH, "kda_clear_unowned_rows: %s", hipGetErrorString(e));
+}

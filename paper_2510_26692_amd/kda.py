@@ -75,6 +75,9 @@ def load_library():
     lib.kda_chunk_bwd_workspace_size.argtypes = [dp]
     lib.kda_chunk_bwd.restype = ctypes.c_int
     lib.kda_chunk_bwd.argtypes = [dp] + [vp] * 15 + [vp, sz, vp]
+    lib.kda_clear_unowned_rows.restype = ctypes.c_int
+    lib.kda_clear_unowned_rows.argtypes = [vp, ctypes.c_int32, ctypes.c_int64, ctypes.c_int32, ctypes.POINTER(vp),
+                                           ctypes.POINTER(sz), vp]
     lib.kda_static_scratch_size.restype = ctypes.c_size_t
     lib.kda_static_scratch_size.argtypes = []
     lib.kda_chunk_fwd_static_scratch.restype = ctypes.c_int
@@ -226,6 +229,20 @@ def _stream_ptr(dev):
     return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
 
 
+def _clear_unowned(cu_seqlens, tensors):
+    """Zeros in the rows [cu_seqlens[-1], T) of freshly allocated [1,T,...] tensors (the calls write all other rows)."""
+    n = len(tensors)
+    tokens = tensors[0].shape[1]
+    if tokens == 0:
+        return
+    ptrs = (ctypes.c_void_p * n)(*[t.data_ptr() for t in tensors])
+    rows = (ctypes.c_size_t * n)(*[t.numel() // tokens * t.element_size() for t in tensors])
+    st = load_library().kda_clear_unowned_rows(_ptr(cu_seqlens), cu_seqlens.numel() - 1, tokens, n, ptrs, rows,
+                                               _stream_ptr(cu_seqlens.device))
+    if st != 0:
+        raise KdaError(st, kda_last_error())
+
+
 def _out_dtype(o, out_dtype):
     """torch dtype of o: that of a tensor passed in, else `out_dtype`, else fp32."""
     dt = o.dtype if o is not None else (out_dtype or torch.float32)
@@ -334,7 +351,9 @@ def kda_chunk_fwd(q, k, v, log_alpha, beta, h0=None, cu_seqlens=None, scale=1.0,
     if cu_seqlens is not None and cu_seqlens.dtype != torch.int32:
         raise ValueError("cu_seqlens must be int32")
     if o is None:
-        o = torch.zeros(B, T, H, dv, dtype=odt, device=dev)
+        o = torch.empty(B, T, H, dv, dtype=odt, device=dev)
+        if cu_seqlens is not None and H > 0:
+            _clear_unowned(cu_seqlens, [o])
     if hT is None and want_hT:
         hT = torch.empty(N, H, dk, dv, dtype=torch.float32, device=dev)
     if workspace is None:
@@ -394,7 +413,7 @@ def kda_chunk_bwd(q, k, v, log_alpha, beta, do, dhT=None, h0=None, cu_seqlens=No
     """Backward pass of kda_chunk_fwd.  Inputs as there; do [B,T,H,dv] fp32, or bf16 with bf16 inputs;
     dhT fp32 [N,H,dk,dv] or None.  Returns a dict of fp32 tensors dq, dk, dlog_alpha [B,T,H,dk], dv [B,T,H,dv], dbeta [B,T,H]
     and dh0 [N,H,dk,dv] (None unless want_dh0); rows of tokens that belong to no sequence are zero
-    (this wrapper allocates the gradients zero-filled; the library leaves such rows untouched).  `out`:
+    (this wrapper clears them in the gradients it allocates; the library leaves such rows untouched).  `out`:
     the dict an earlier call returned, to be written in place instead of allocating."""
     lib = load_library()
     dev = _check_dev(q, k, v, log_alpha, beta, do, dhT, h0, cu_seqlens, workspace)
@@ -417,7 +436,9 @@ def kda_chunk_bwd(q, k, v, log_alpha, beta, do, dhT=None, h0=None, cu_seqlens=No
     shapes = {"dq": (B, T, H, dk), "dk": (B, T, H, dk), "dv": (B, T, H, dv), "dlog_alpha": (B, T, H, dk),
               "dbeta": (B, T, H), "dh0": (N, H, dk, dv)}
     if out is None:
-        out = {n_: torch.zeros(*sh, **f32) for n_, sh in shapes.items() if n_ != "dh0"}
+        out = {n_: torch.empty(*sh, **f32) for n_, sh in shapes.items() if n_ != "dh0"}
+        if cu_seqlens is not None and H > 0:
+            _clear_unowned(cu_seqlens, list(out.values()))
         out["dh0"] = torch.empty(*shapes["dh0"], **f32) if want_dh0 else None
     else:                                   # the dict of an earlier call with the same shapes, written in place
         for n_, sh in shapes.items():
@@ -508,8 +529,8 @@ def kda_recurrent_steps_pooled(q, k, v, log_alpha, beta, S_pool, state_indices=N
     elif state_indices.dtype != torch.int32 or state_indices.shape != (N,):
         raise ValueError("state_indices must be int32 [N]")
     odt = _out_dtype(o, out_dtype)
-    if o is None:
-        o = torch.zeros(N, Tq, H, dv, dtype=odt, device=dev)
+    if o is None:                           # (with indices: rows of skipped sequences are zero)
+        o = (torch.empty if state_indices is None else torch.zeros)(N, Tq, H, dv, dtype=odt, device=dev)
     elif o.shape != (N, Tq, H, dv):
         raise ValueError("o must have shape [N,Tq,H,dv]")
     dims = KdaDims(batch=N, seqlen=Tq, heads=H, dk=dk, dv=dv, chunk=64, num_seqs=N,

@@ -1,0 +1,41 @@
+"""Outputs that the binding allocates: rows of a packed batch that belong to no sequence are zero (o and every per-token
+gradient), with row sizes that are and are not a multiple of 16 bytes (dbeta has 4 H bytes a row), whether the batch has
+such rows or not, and no row that does belong to a sequence is touched.  The memory is dirtied first."""
+import pytest
+import torch
+
+import synth_inputs as si
+from helpers import to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("lens,stray", [([70, 5], 0), ([70, 5], 1), ([0, 64], 300), ([0], 3)])
+@pytest.mark.parametrize("H,D,dtype", [(3, 64, "f32"), (4, 128, "bf16")])
+def test_unowned_rows_are_zero_and_owned_ones_are_not_touched(lens, stray, H, D, dtype):
+    import paper_2510_26692_amd as kda
+    x = si.make_varlen(lens + [stray], H, D, D, dtype, -2.0, 77, 0.0)
+    T, owned = sum(lens) + stray, sum(lens)
+    x["cu_seqlens"] = x["cu_seqlens"][:-1].contiguous()
+    dd = to_device(x)
+    args = [dd[n] for n in ("q", "k", "v", "log_alpha", "beta")]
+    do = torch.randn(1, T, H, D, device="cuda")
+
+    def both():
+        dirt = [torch.full((1 << 22,), float("nan"), device="cuda") for _ in range(8)]
+        del dirt                                        # (freed blocks that the outputs are likely to be cut from)
+        o, _ = kda.kda_chunk_fwd(*args, cu_seqlens=dd["cu_seqlens"])
+        g = kda.kda_chunk_bwd(*args, do, cu_seqlens=dd["cu_seqlens"], want_dh0=False)
+        torch.cuda.synchronize()
+        return dict(g, o=o)
+
+    got = both()
+    into = {n: torch.full_like(t, 7.0) for n, t in got.items() if t is not None}
+    kda.kda_chunk_fwd(*args, cu_seqlens=dd["cu_seqlens"], o=into["o"])
+    kda.kda_chunk_bwd(*args, do, cu_seqlens=dd["cu_seqlens"], want_dh0=False,
+                      out=dict({n: into[n] for n in into if n != "o"}, dh0=None))
+    torch.cuda.synchronize()
+    for n, t in into.items():
+        assert torch.equal(got[n][:, :owned], t[:, :owned]), n
+        assert bool((got[n][:, owned:] == 0).all()), n
+        assert bool((t[:, owned:] == 7).all()), n       # a caller's own array keeps what it held
