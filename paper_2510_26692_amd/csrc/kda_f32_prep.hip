@@ -13,26 +13,29 @@ namespace kda {
 namespace f32 {
 
 constexpr int kPrepThreads = 256;
-constexpr size_t kPrepLds = (size_t)(3 * kC * kLdT + kTri * 64 + kC) * 4;
+constexpr int kPairs = 6;                                    // pairs of different token blocks
+constexpr size_t kPrepLds = (size_t)(3 * kC * kLdT + kPairs * 64 + kC) * 4;
+static_assert(3 * kPrepLds <= 160 * 1024, "three workgroups share a compute unit");
 
 // Four waves; the channels are taken 64 at a time, 16 per wave.  LDS: Kp = k 2^(G - pref), Qp = q 2^(G - pref) and
-// Kn = k 2^(nref - G) of those 64 channels, 52 KiB, so that two workgroups share a compute unit.
+// Kn = k 2^(nref - G) of those 64 channels, 51 KiB, so that three workgroups share a compute unit.  The inputs of the next
+// 64 channels are on their way while the products of these are formed.
 template <typename Tin, int D>
-__global__ __launch_bounds__(kPrepThreads, 2)
+__global__ __launch_bounds__(kPrepThreads, 3)
 void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, const Tin *__restrict__ log_alpha,
                          const Tin *__restrict__ beta, float *__restrict__ slots, const Problem p)
 {
     using SL = Slot<D>;
     extern __shared__ __attribute__((aligned(16))) float smem[];
     float *sKp = smem, *sQp = sKp + kC * kLdT, *sKn = sQp + kC * kLdT;
-    float *sF = sKn + kC * kLdT;                             // [kTri][64]: decay between the blocks of a pair
-    float *sBeta = sF + kTri * 64;
+    float *sF = sKn + kC * kLdT;                             // [kPairs][64]: decay between the blocks of a pair
+    float *sBeta = sF + kPairs * 64;
 
     Chunk c;
     if (!locate(p.cu, p.num_seqs, p.T, p.H, p.chunks_per_seq, blockIdx.x, c)) return;
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t stride = (int64_t)p.H * D, base = (c.tok0 * p.H + c.h) * (int64_t)D + m;
+    const int64_t stride = (int64_t)p.H * D, base = (c.tok0 * p.H + c.h) * (int64_t)D;
     float *slot = slots + c.slot * SL::kFloats;
     if (tid < kC) {
         const float b = tid < c.nv ? load_as_float(beta + (c.tok0 + tid) * p.H + c.h) : 0.f;
@@ -43,18 +46,27 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
     // tiles of A (u < 10) and P (u >= 10), five per wave
     f32x4 acc[5] = {};
     auto block_of = [](int b, int &R, int &I) { R = b >= 6 ? 3 : b >= 3 ? 2 : b >= 1 ? 1 : 0; I = b - tri(R, 0); };
+    auto pair_of = [](int R, int I) { return R * (R - 1) / 2 + I; };
+    TileFetch<Tin> fg, fk, fq;
+    auto fetch = [&](int t) __attribute__((always_inline)) {
+        fg.fetch(log_alpha + base + 16 * t, stride, c.nv, lane);
+        fk.fetch(k + base + 16 * t, stride, c.nv, lane);
+        fq.fetch(q + base + 16 * t, stride, c.nv, lane);
+    };
+    fetch(w);
     bool strong = false;
 #pragma unroll 1
     for (int hf = 0; hf < D / 64; ++hf) {
         const int t = 4 * hf + w;
         f32x4 kk[4], qq[4];
         Decay d;
-        load_tile(d.G, log_alpha + base + 16 * t, stride, c.nv, g);
-        load_tile(kk, k + base + 16 * t, stride, c.nv, g);
-        load_tile(qq, q + base + 16 * t, stride, c.nv, g);
+        if (hf) lds_barrier();                               // the previous channels' tiles are read
+        fg.turn(d.G, reinterpret_cast<char *>(sKn + 16 * w), 4 * kLdT, c.nv, lane);
+        fk.turn(kk, reinterpret_cast<char *>(sKp + 16 * w), 4 * kLdT, c.nv, lane);
+        fq.turn(qq, reinterpret_cast<char *>(sQp + 16 * w), 4 * kLdT, c.nv, lane);
+        if (4 * hf + 4 < SL::kTiles) fetch(t + 4);
         running_decay(d, lane);
         strong |= d.strong;
-        if (hf) lds_barrier();                               // the previous channels' tiles are read
         const float GC = d.E[3];
 #pragma unroll
         for (int R = 0; R < 4; ++R) {
@@ -75,10 +87,9 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
         if (g == 0) {
             slot[SL::kGc + 16 * t + m] = fast_exp2(GC);
 #pragma unroll
-            for (int R = 0; R < 4; ++R)
+            for (int R = 1; R < 4; ++R)
 #pragma unroll
-                for (int I = 0; I <= R; ++I)
-                    sF[tri(R, I) * 64 + 16 * w + m] = I == R ? d.fdiag[R] : fast_exp2(d.pref[R] - d.nref[I]);
+                for (int I = 0; I < R; ++I) sF[pair_of(R, I) * 64 + 16 * w + m] = fast_exp2(d.pref[R] - d.nref[I]);
         }
         lds_barrier();
 #pragma unroll
@@ -87,32 +98,43 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
             int R, I;
             block_of(b, R, I);
             const float *pa = (u < 10 ? sKp : sQp) + (16 * R + m) * kLdT + 4 * g, *pb = sKn + (16 * I + m) * kLdT + 4 * g;
-            const float *pF = sF + b * 64 + 4 * g;
+            if (R == I) {
 #pragma unroll
-            for (int kt = 0; kt < 4; ++kt) acc[i] = mfma16(ld4(pa + 16 * kt), ld4(pb + 16 * kt) * ld4(pF + 16 * kt), acc[i]);
+                for (int kt = 0; kt < 4; ++kt) acc[i] = mfma16(ld4(pa + 16 * kt), ld4(pb + 16 * kt), acc[i]);
+            } else {
+                const float *pF = sF + pair_of(R, I) * 64 + 4 * g;
+#pragma unroll
+                for (int kt = 0; kt < 4; ++kt) acc[i] = mfma16(ld4(pa + 16 * kt), ld4(pb + 16 * kt) * ld4(pF + 16 * kt), acc[i]);
+            }
         }
     }
     if (__syncthreads_or(strong)) {
-        // strong channels inside the diagonal blocks, pair by pair in the log domain (any decay)
+        // some channel's decay inside a block is beyond the factors' range: the diagonal blocks again, all of them and
+        // all channels, pair by pair in the log domain
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            const int u = w + 4 * i, b = u < 10 ? u : u - 10;
+            int R, I;
+            block_of(b, R, I);
+            if (R == I) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
 #pragma unroll 1
         for (int hf = 0; hf < D / 64; ++hf) {
             const int t = 4 * hf + w;
             f32x4 kk[4], qq[4];
             Decay d;
-            load_tile(d.G, log_alpha + base + 16 * t, stride, c.nv, g);
-            load_tile(kk, k + base + 16 * t, stride, c.nv, g);
-            load_tile(qq, q + base + 16 * t, stride, c.nv, g);
+            load_tile(d.G, log_alpha + base + m + 16 * t, stride, c.nv, g);
+            load_tile(kk, k + base + m + 16 * t, stride, c.nv, g);
+            load_tile(qq, q + base + m + 16 * t, stride, c.nv, g);
             running_decay(d, lane);
             __syncthreads();
 #pragma unroll
-            for (int R = 0; R < 4; ++R) {
+            for (int R = 0; R < 4; ++R)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int at = (16 * R + 4 * g + j) * kLdT + 16 * w + m;
                     sKp[at] = kk[R][j]; sQp[at] = qq[R][j]; sKn[at] = d.G[R][j];
                 }
-                if (g == 0) sF[tri(R, R) * 64 + 16 * w + m] = d.fdiag[R];
-            }
             __syncthreads();
 #pragma unroll
             for (int i = 0; i < 5; ++i) {
@@ -121,8 +143,8 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
                 block_of(b, R, I);
                 if (R != I) continue;
                 const float *row = u < 10 ? sKp : sQp;
+#pragma unroll 1
                 for (int ch = 0; ch < 64; ++ch) {
-                    if (sF[b * 64 + ch] != 0.f) continue;
                     const int ci = (16 * R + m) * kLdT + ch;
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {

@@ -134,6 +134,34 @@ struct Decay {
     bool strong;
 };
 
+// A wave brings such a tile of a [tokens, H, D] tensor in with 16-byte loads (fetch: a lane holds a piece of a row) and
+// turns it through LDS (turn: `at`, rows `ld` bytes apart, belongs to the wave alone for the moment).
+template <typename T> struct TileFetch {
+    static constexpr int kPerRow = (int)sizeof(T);           // 16-byte pieces of a row of 16 channels
+    uint4 raw[kPerRow];
+    __device__ __forceinline__ void fetch(const T *base, int64_t stride, int nv, int lane)
+    {
+#pragma unroll
+        for (int u = 0; u < kPerRow; ++u) {
+            const int r = (lane + 64 * u) / kPerRow, piece = lane % kPerRow;
+            raw[u] = *reinterpret_cast<const uint4 *>(base + (int64_t)(r < nv ? r : nv - 1) * stride + piece * (16 / (int)sizeof(T)));
+        }
+    }
+    __device__ __forceinline__ void turn(f32x4 (&x)[4], char *at, int ld, int nv, int lane) const
+    {
+#pragma unroll
+        for (int u = 0; u < kPerRow; ++u) {
+            const int r = (lane + 64 * u) / kPerRow, piece = lane % kPerRow;
+            *reinterpret_cast<uint4 *>(at + r * ld + piece * 16) = r < nv ? raw[u] : make_uint4(0u, 0u, 0u, 0u);
+        }
+        const int m = lane & 15, g = lane >> 4;
+#pragma unroll
+        for (int R = 0; R < 4; ++R)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[R][j] = load_as_float(reinterpret_cast<const T *>(at + (16 * R + 4 * g + j) * ld) + m);
+    }
+};
+
 template <typename T> __device__ __forceinline__ void load_tile(f32x4 (&x)[4], const T *base, int64_t stride, int nv, int g)
 {
 #pragma unroll
