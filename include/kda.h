@@ -354,9 +354,9 @@ kda_status kda_recurrent_steps_fused(const kda_dims *dims, const kda_prologue *p
                                      void *o, void *hip_stream);
 
 /*
- * Zeros in the rows [cu_seqlens[num_seqs], tokens) of up to eight arrays of `tokens` rows of row_bytes[i] bytes each (a
- * multiple of 4; arrays 16-byte aligned): the tokens of a packed batch that belong to no sequence, which kda_chunk_fwd
- * leaves untouched in o and kda_chunk_bwd in the per-token gradients.  For callers that want them defined.
+ * Zeros in the rows [0, cu_seqlens[0]) and [cu_seqlens[num_seqs], tokens) of up to eight arrays of `tokens` rows of
+ * row_bytes[i] bytes each (a multiple of 4; arrays 16-byte aligned): the tokens of a packed batch that belong to no sequence,
+ * which kda_chunk_fwd leaves untouched in o and kda_chunk_bwd in the per-token gradients.  For callers that want them defined.
  */
 kda_status kda_clear_unowned_rows(const int32_t *cu_seqlens, int32_t num_seqs, int64_t tokens, int32_t num_arrays,
                                   void *const *arrays, const size_t *row_bytes, void *hip_stream);

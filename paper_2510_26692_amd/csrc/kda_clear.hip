@@ -12,20 +12,24 @@ struct Arrays {
     int64_t row4[kMaxArrays];
 };
 
-// One row of workgroups per array; every workgroup reads the number of owned tokens and, as a rule, leaves.
+// Rows [0, cu[0]) and [cu[num_seqs], tokens): one row of workgroups per array; every workgroup reads the two ends and, as a
+// rule, leaves.  (Both ends are clamped to the array, whatever cu holds.)
 __global__ void kda_clear_unowned_kernel(const int32_t *cu, int num_seqs, int64_t tokens, const Arrays a)
 {
-    const int64_t owned = cu[num_seqs];
-    if (owned >= tokens) return;
+    const int64_t low = cu[0], high = cu[num_seqs];
+    const int64_t before = low < 0 ? 0 : low < tokens ? low : tokens, after = high < 0 ? 0 : high < tokens ? high : tokens;
+    if (before == 0 && after == tokens) return;
     const int k = blockIdx.y;
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
-    if (a.row16[k]) {
-        const int64_t end = tokens * a.row16[k];
-        for (int64_t i = owned * a.row16[k] + i0; i < end; i += step) a.p[k][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (const int64_t row = a.row16[k]) {
+        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int64_t i = i0; i < before * row; i += step) a.p[k][i] = zero;
+        for (int64_t i = after * row + i0; i < tokens * row; i += step) a.p[k][i] = zero;
     } else {
         float *p = reinterpret_cast<float *>(a.p[k]);
-        const int64_t end = tokens * a.row4[k];
-        for (int64_t i = owned * a.row4[k] + i0; i < end; i += step) p[i] = 0.f;
+        const int64_t row4 = a.row4[k];
+        for (int64_t i = i0; i < before * row4; i += step) p[i] = 0.f;
+        for (int64_t i = after * row4 + i0; i < tokens * row4; i += step) p[i] = 0.f;
     }
 }
 

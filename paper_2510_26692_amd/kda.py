@@ -230,7 +230,8 @@ def _stream_ptr(dev):
 
 
 def _clear_unowned(cu_seqlens, tensors):
-    """Zeros in the rows [cu_seqlens[-1], T) of freshly allocated [1,T,...] tensors (the calls write all other rows)."""
+    """Zeros in the rows [0, cu_seqlens[0]) and [cu_seqlens[-1], T) of freshly allocated [1,T,...] tensors (the calls write
+    all other rows)."""
     n = len(tensors)
     tokens = tensors[0].shape[1]
     if tokens == 0:

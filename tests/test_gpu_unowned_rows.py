@@ -39,3 +39,21 @@ def test_unowned_rows_are_zero_and_owned_ones_are_not_touched(lens, stray, H, D,
         assert torch.equal(got[n][:, :owned], t[:, :owned]), n
         assert bool((got[n][:, owned:] == 0).all()), n
         assert bool((t[:, owned:] == 7).all()), n       # a caller's own array keeps what it held
+
+
+@pytest.mark.parametrize("cu", [[3, 3], [3, 10], [0, 10], [10, 10], [-5, 12], [0, -1]])
+def test_rows_on_both_sides_of_the_sequences_are_cleared_and_nothing_else(cu):
+    """The clearing call alone, with ends inside, at and beyond those of the array: it never leaves the array."""
+    from paper_2510_26692_amd import kda as binding
+    tokens, guard = 10, 64
+    low, high = min(max(cu[0], 0), tokens), min(max(cu[1], 0), tokens)
+    for width in (3, 8):                                # rows of 12 and of 32 bytes
+        whole = torch.full((tokens * width + 2 * guard,), 7.0, device="cuda")
+        binding._clear_unowned(torch.tensor(cu, dtype=torch.int32, device="cuda"),
+                               [whole[guard:guard + tokens * width].view(1, tokens, width)])
+        got = whole.cpu()
+        rows = got[guard:-guard].view(tokens, width)
+        owned = torch.zeros(tokens, dtype=torch.bool)
+        owned[low:high] = True
+        assert bool((rows[owned] == 7).all()) and bool((rows[~owned] == 0).all())
+        assert bool((got[:guard] == 7).all()) and bool((got[-guard:] == 7).all())
