@@ -16,29 +16,53 @@
 //
 // A wave owns whole 16-channel tiles (all 64 tokens), so everything that is per channel -- the running sum of the
 // decay, the decay factors, the sums over tokens that make dlog alpha -- stays in its registers, and S0 and dS1 are
-// read as B operands straight from memory, once.  Only dO, X and Vn (the operands all waves share) and the two C x C
-// results go through LDS: 48 KiB, half of the value columns at a time, so that two workgroups share a compute unit
-// and one loads while the other multiplies.
+// read as B operands straight from memory, once, a column tile ahead of their products.  Only dO, X and Vn (the operands
+// all waves share) and the two C x C results go through LDS: the former 32 value columns at a time in two buffers, so
+// that one barrier a part is enough and the next part's rows are on their way while this one is multiplied; the latter
+// as fragments in both forms, so that every operand of the second half is one 16-byte read.  The registers (256) allow
+// two workgroups a compute unit.
+//
+// Bounds: at 4 x 4096 tokens x 16 heads 1.5 GB of traffic (0.29 ms at the rate of a large copy) and 41 GFLOP on the fp32 matrix
+// cores (0.27 ms), two workgroups a compute unit to overlap them: 0.49 ms (0.60 with 64 columns a part in one buffer, rows of
+// the results written 4 bytes a lane and the inputs read 2 bytes a lane).  Fetching parts unconditionally, which spares a wait
+// at the loop's end, and unrolling the parts both measured slower (0.51 ms; 470 bytes of scratch a lane).
 #include "kda_f32_tile.h"
 
 namespace kda {
 namespace f32 {
 
 constexpr int kGradThreads = 256;
-constexpr int kPart = 16 * kFrag;                            // one operand, 64 value columns: [token tile][column tile]
-constexpr size_t kGradLds = (size_t)(3 * kPart) * 4;
-static_assert(2 * kC * kLdT <= 3 * kPart, "the C x C tiles take the operands' place");
-
-__device__ __forceinline__ f32x4 load4(const float *p) { return ld4(p); }
-__device__ __forceinline__ f32x4 load4(const __hip_bfloat16 *p)
+constexpr int kCols = 2;                                     // column tiles of a part
+constexpr int kPart = 4 * kCols * kFrag;                     // one operand: [token tile][column tile]
+constexpr int kBoth = 2 * kTri * kFrag;                      // dA or dP: its blocks in row form, then in column form
+// Inputs of a channel tile on their way to column form, per wave: rows 16 bytes longer than they are, so that rows 4
+// apart lie in different banks.
+template <typename T> constexpr int turn_row() { return 16 * (int)sizeof(T) + 16; }
+template <typename T> constexpr size_t grad_lds()
 {
-    const uint2 u = *reinterpret_cast<const uint2 *>(p);
-    f32x4 x;
-    float a, b;
-    unpack_bf16x2(u.x, a, b); x[0] = a; x[1] = b;
-    unpack_bf16x2(u.y, a, b); x[2] = a; x[3] = b;
-    return x;
+    const size_t first = (size_t)2 * 3 * kPart * 4, second = (size_t)2 * kBoth * 4 + 4 * kC * turn_row<T>();
+    return first > second ? first : second;
 }
+static_assert(2 * grad_lds<float>() <= 160 * 1024, "two workgroups share a compute unit");
+
+// Four values of a row as they lie in memory.
+template <typename T> struct Raw4;
+template <> struct Raw4<float> {
+    f32x4 x;
+    __device__ __forceinline__ void load(const float *p) { x = ld4(p); }
+    __device__ __forceinline__ f32x4 get() const { return x; }
+};
+template <> struct Raw4<__hip_bfloat16> {
+    uint2 u;
+    __device__ __forceinline__ void load(const __hip_bfloat16 *p) { u = *reinterpret_cast<const uint2 *>(p); }
+    __device__ __forceinline__ f32x4 get() const
+    {
+        float a, b, c, d;
+        unpack_bf16x2(u.x, a, b);
+        unpack_bf16x2(u.y, c, d);
+        return f32x4{a, b, c, d};
+    }
+};
 
 template <typename Tin, typename Tdo, int D>
 __global__ __launch_bounds__(kGradThreads, 2)
@@ -48,9 +72,8 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
                               float *__restrict__ dq, float *__restrict__ dk, float *__restrict__ dv,
                               float *__restrict__ dla, float *__restrict__ dbeta, const Problem p)
 {
-    constexpr int NT = D / 16, TW = NT / 4, NH = D / 64;
+    constexpr int NT = D / 16, TW = NT / 4, NP = NT / kCols;
     extern __shared__ __attribute__((aligned(16))) float smem[];
-    float *sO = smem, *sX = sO + kPart, *sV = sX + kPart;    // later: dA and dP, [64][kLdT] each
     Chunk c;
     if (!locate(p.cu, p.num_seqs, p.T, p.H, p.chunks_per_seq, blockIdx.x, c)) return;
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
@@ -70,93 +93,121 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
         const int n = tile_tokens(c.nv, w);
         const float *rw = Rw + rows + (live ? row_form(w, 0, g, m, n, D) : 0), *zw = Zw + rows + (live ? row_form(w, 0, g, m, n, D) : 0);
         const int step = live ? 16 * n : 0;                                  // floats from a column tile to the next
-        f32x4 go[4], gz[4], gr[4];
+        Raw4<Tdo> go[kCols];
+        f32x4 gz[kCols], gr[kCols];
         float db = 0.f;
-        auto fetch = [&](int hf) __attribute__((always_inline)) {
+        auto fetch = [&](int pt) __attribute__((always_inline)) {
 #pragma unroll
-            for (int cg = 0; cg < 4; ++cg) {
-                go[cg] = load4(d_o + row + 64 * hf + 16 * cg + 4 * g);
-                gz[cg] = ld4(zw + (4 * hf + cg) * step);
-                gr[cg] = ld4(rw + (4 * hf + cg) * step);
+            for (int cg = 0; cg < kCols; ++cg) {
+                go[cg].load(d_o + row + 16 * (kCols * pt + cg) + 4 * g);
+                gz[cg] = ld4(zw + (kCols * pt + cg) * step);
+                gr[cg] = ld4(rw + (kCols * pt + cg) * step);
+            }
+        };
+        auto commit = [&](int pt, float *buf) __attribute__((always_inline)) {
+#pragma unroll
+            for (int cg = 0; cg < kCols; ++cg) {
+                const f32x4 x = bt * gz[cg], zero = {0.f, 0.f, 0.f, 0.f};
+                float *f = buf + (kCols * w + cg) * kFrag + 4 * lane;
+                st4(f, live ? go[cg].get() * p.scale : zero);
+                st4(f + kPart, live ? x : zero);
+                st4(f + 2 * kPart, live ? bt * gr[cg] : zero);
+                if (live) st4(dv + row + 16 * (kCols * pt + cg) + 4 * g, x);
+                db += gz[cg][0] * gr[cg][0] + gz[cg][1] * gr[cg][1] + gz[cg][2] * gr[cg][2] + gz[cg][3] * gr[cg][3];
+            }
+        };
+        f32x4 bs[kCols][TW], bd[kCols][TW];
+        auto fetch_states = [&](int ct, f32x4 (&s)[TW], f32x4 (&d)[TW]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int tt = 0; tt < TW; ++tt) {
+                const int f = ((4 * tt + w) * NT + ct) * kFrag;
+                s[tt] = ld4(s0 + f); d[tt] = ld4(ds1 + f);
             }
         };
         fetch(0);
+        fetch_states(0, bs[0], bd[0]);
+        pin_memory_order();
+        commit(0, smem);
+        fetch(1);
+        lds_barrier();
 #pragma unroll 1
-        for (int hf = 0; hf < NH; ++hf) {
-            if (hf) lds_barrier();                                           // the previous half is read
+        for (int pt = 0; pt < NP; ++pt) {
+            const float *buf = smem + (pt & 1) * 3 * kPart + 4 * lane;
 #pragma unroll
-            for (int cg = 0; cg < 4; ++cg) {
-                const f32x4 x = bt * gz[cg], zero = {0.f, 0.f, 0.f, 0.f};
-                const int f = (4 * w + cg) * kFrag + 4 * lane;
-                st4(sO + f, live ? go[cg] * p.scale : zero);
-                st4(sX + f, live ? x : zero);
-                st4(sV + f, live ? bt * gr[cg] : zero);
-                if (live) st4(dv + row + 64 * hf + 16 * cg + 4 * g, x);
-                db += gz[cg][0] * gr[cg][0] + gz[cg][1] * gr[cg][1] + gz[cg][2] * gr[cg][2] + gz[cg][3] * gr[cg][3];
-            }
-            lds_barrier();
-            if (hf + 1 < NH) fetch(hf + 1);
-#pragma unroll
-            for (int cg = 0; cg < 4; ++cg) {
-                f32x4 bs[TW], bd[TW];
-#pragma unroll
-                for (int tt = 0; tt < TW; ++tt) {
-                    const int f = ((4 * tt + w) * NT + 4 * hf + cg) * kFrag;
-                    bs[tt] = ld4(s0 + f); bd[tt] = ld4(ds1 + f);
-                }
+            for (int cg = 0; cg < kCols; ++cg) {
+                const int next = kCols * pt + cg + 1;                        // (the last one fetches its own again)
+                fetch_states(next < NT ? next : NT - 1, bs[(cg + 1) % kCols], bd[(cg + 1) % kCols]);
+                pin_memory_order();
 #pragma unroll
                 for (int R = 0; R < 4; ++R) {
-                    const int f = (4 * R + cg) * kFrag + 4 * lane;
-                    const f32x4 ao = ld4(sO + f), ax = ld4(sX + f), av = ld4(sV + f);
+                    const float *f = buf + (kCols * R + cg) * kFrag;
+                    const f32x4 ao = ld4(f), ax = ld4(f + kPart), av = ld4(f + 2 * kPart);
 #pragma unroll
                     for (int tt = 0; tt < TW; ++tt) {
-                        aq[tt][R] = mfma16(ao, bs[tt], aq[tt][R]);
-                        ak[tt][R] = mfma16(ax, bs[tt], ak[tt][R]);
-                        at[tt][R] = mfma16(av, bd[tt], at[tt][R]);
+                        aq[tt][R] = mfma16(ao, bs[cg][tt], aq[tt][R]);
+                        ak[tt][R] = mfma16(ax, bs[cg][tt], ak[tt][R]);
+                        at[tt][R] = mfma16(av, bd[cg][tt], at[tt][R]);
                     }
                 }
 #pragma unroll
                 for (int tt = 0; tt < TW; ++tt)
-                    gc[tt] += bs[tt][0] * bd[tt][0] + bs[tt][1] * bd[tt][1] + bs[tt][2] * bd[tt][2] + bs[tt][3] * bd[tt][3];
+                    gc[tt] += bs[cg][tt][0] * bd[cg][tt][0] + bs[cg][tt][1] * bd[cg][tt][1] + bs[cg][tt][2] * bd[cg][tt][2] + bs[cg][tt][3] * bd[cg][tt][3];
             }
 #pragma unroll
             for (int i = 0; i < 5; ++i) {
                 const int u = w + 4 * i, b = u < 10 ? u : u - 10;
                 const int R = b >= 6 ? 3 : b >= 3 ? 2 : b >= 1 ? 1 : 0, I = b - tri(R, 0);
-                const float *pa = (u < 10 ? sX : sO) + 4 * R * kFrag + 4 * lane, *pb = sV + 4 * I * kFrag + 4 * lane;
+                const float *pa = buf + (u < 10 ? kPart : 0) + kCols * R * kFrag, *pb = buf + 2 * kPart + kCols * I * kFrag;
 #pragma unroll
-                for (int cg = 0; cg < 4; ++cg) tile[i] = mfma16(ld4(pa + cg * kFrag), ld4(pb + cg * kFrag), tile[i]);
+                for (int cg = 0; cg < kCols; ++cg) tile[i] = mfma16(ld4(pa + cg * kFrag), ld4(pb + cg * kFrag), tile[i]);
+            }
+            if (pt + 1 < NP) {
+                commit(pt + 1, smem + ((pt + 1) & 1) * 3 * kPart);           // (last read before the previous barrier)
+                if (pt + 2 < NP) fetch(pt + 2);
+                lds_barrier();
             }
         }
         db += __shfl_xor(db, 16);
         db += __shfl_xor(db, 32);
         if (g == 0 && live) dbeta[(c.tok0 + tok) * p.H + c.h] = db;
     }
+    TileFetch<Tin> fg, fk, fq;
+    auto fetch_inputs = [&](int tt) __attribute__((always_inline)) {
+        const int64_t at0 = base + 16 * (4 * tt + w);
+        fg.fetch(log_alpha + at0, stride, c.nv, lane);
+        fk.fetch(k + at0, stride, c.nv, lane);
+        fq.fetch(q + at0, stride, c.nv, lane);
+    };
+    fetch_inputs(0);
     lds_barrier();
-    float *sA = smem, *sP = smem + kC * kLdT;
+    const int turned = 4 * turned_lane(lane);
+    float *sA = smem, *sP = smem + kBoth;
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
         const int u = w + 4 * i, b = u < 10 ? u : u - 10;
         const int R = b >= 6 ? 3 : b >= 3 ? 2 : b >= 1 ? 1 : 0, I = b - tri(R, 0);
-        float *dst = (u < 10 ? sA : sP) + (16 * R + 4 * g) * kLdT + 16 * I + m;
+        f32x4 x = u < 10 ? -tile[i] : tile[i];
+        if (R == I) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float x = u < 10 ? -tile[i][j] : tile[i][j];
-            if (R == I && (m > 4 * g + j || (u < 10 && m == 4 * g + j))) x = 0.f;
-            dst[j * kLdT] = x;
+            for (int j = 0; j < 4; ++j)
+                if (m > 4 * g + j || (u < 10 && m == 4 * g + j)) x[j] = 0.f;
         }
+        float *dst = (u < 10 ? sA : sP) + b * kFrag;
+        st4(dst + turned, quad_transpose(x, lane));
+        st4(dst + kTri * kFrag + 4 * lane, x);
     }
     lds_barrier();
+    const float *rowA = sA + 4 * lane, *rowP = sP + 4 * lane, *colA = rowA + kTri * kFrag, *colP = rowP + kTri * kFrag;
+    char *turn = reinterpret_cast<char *>(smem + 2 * kBoth) + w * (kC * turn_row<Tin>());
 
     // ---- decay terms and results, a 16-channel tile at a time ----
     auto finish = [&](int tt, f32x4 (&aq)[4], f32x4 (&ak)[4], f32x4 (&at)[4], float gc) __attribute__((always_inline)) {
         asm volatile("" ::: "memory");                                       // (one tile's inputs in registers at a time)
-        const int64_t col = base + 16 * (4 * tt + w) + m;
         f32x4 kk[4], qq[4], pf[4], nf[4];
         Decay d;
-        load_tile(d.G, log_alpha + col, stride, c.nv, g);
-        load_tile(kk, k + col, stride, c.nv, g);
-        load_tile(qq, q + col, stride, c.nv, g);
+        fg.turn(d.G, turn, turn_row<Tin>(), c.nv, lane);
+        fk.turn(kk, turn, turn_row<Tin>(), c.nv, lane);
+        fq.turn(qq, turn, turn_row<Tin>(), c.nv, lane);
         running_decay(d, lane);
         float run = 0.f;
 #pragma unroll
@@ -180,37 +231,40 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
 #pragma unroll
             for (int I = 0; I <= R; ++I) {
                 const f32x4 b = kk[I] * nf[I] * (I == R ? d.fdiag[R] : fast_exp2(d.pref[R] - d.nref[I]));
-                const int f = (16 * R + m) * kLdT + 16 * I + 4 * g;
-                a1 = mfma16(ld4(sA + f), b, a1);
-                a2 = mfma16(ld4(sP + f), b, a2);
+                a1 = mfma16(ld4(rowA + tri(R, I) * kFrag), b, a1);
+                a2 = mfma16(ld4(rowP + tri(R, I) * kFrag), b, a2);
             }
 #pragma unroll
             for (int B = R; B < 4; ++B) {
                 const f32x4 x = pf[B] * (B == R ? d.fdiag[R] : fast_exp2(d.pref[B] - d.nref[R]));
-                const int f = (16 * B + 4 * g) * kLdT + 16 * R + m;
-                b1 = mfma16(f32x4{sA[f], sA[f + kLdT], sA[f + 2 * kLdT], sA[f + 3 * kLdT]}, x * kk[B], b1);
-                b1 = mfma16(f32x4{sP[f], sP[f + kLdT], sP[f + 2 * kLdT], sP[f + 3 * kLdT]}, x * qq[B], b1);
+                b1 = mfma16(ld4(colA + tri(B, R) * kFrag), x * kk[B], b1);
+                b1 = mfma16(ld4(colP + tri(B, R) * kFrag), x * qq[B], b1);
             }
             a1 *= pf[R]; a2 *= pf[R]; b1 *= nf[R];
             if (any_strong) {
-                // strong channels of this block, pair by pair (the products above left their diagonal block out)
+                // strong channels of this block, pair by pair (the products above left their diagonal block out); G again
+                // from the input: kept, it would cost every chunk registers
+                Decay e;
+                load_tile(e.G, log_alpha + base + 16 * (4 * tt + w) + m, stride, c.nv, g);
+                running_decay(e, lane);
                 const bool mine = d.fdiag[R] == 0.f;
 #pragma unroll 1
                 for (int gi = 0; gi < 4; ++gi)
 #pragma unroll
                 for (int ii = 0; ii < 4; ++ii) {
                     const int i = 4 * gi + ii, src = 16 * gi + m;
-                    const float Gi = __shfl(d.G[R][ii], src), ki = __shfl(kk[R][ii], src), qi = __shfl(qq[R][ii], src);
+                    const float Gi = __shfl(e.G[R][ii], src), ki = __shfl(kk[R][ii], src), qi = __shfl(qq[R][ii], src);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const int t = 4 * g + j;
-                        const float e = mine ? fast_exp2(i <= t ? fminf(d.G[R][j] - Gi, 0.f) : fminf(Gi - d.G[R][j], 0.f)) : 0.f;
-                        const float *row = sA + (16 * R + t) * kLdT + 16 * R + i, *cl = sA + (16 * R + i) * kLdT + 16 * R + t;
+                        const float x = mine ? fast_exp2(i <= t ? fminf(e.G[R][j] - Gi, 0.f) : fminf(Gi - e.G[R][j], 0.f)) : 0.f;
+                        const float *row = sA + tri(R, R) * kFrag + 4 * (t + 16 * gi) + ii;      // dA[t][i], dA[i][t] in row form
+                        const float *cl = sA + tri(R, R) * kFrag + 4 * (i + 16 * g) + j;
                         if (i <= t) {                                        // (dA's diagonal is zero)
-                            a1[j] = fmaf(row[0] * ki, e, a1[j]);
-                            a2[j] = fmaf(row[kC * kLdT] * ki, e, a2[j]);
+                            a1[j] = fmaf(row[0] * ki, x, a1[j]);
+                            a2[j] = fmaf(row[kBoth] * ki, x, a2[j]);
                         }
-                        if (i >= t) b1[j] = fmaf(fmaf(cl[0], ki, cl[kC * kLdT] * qi), e, b1[j]);
+                        if (i >= t) b1[j] = fmaf(fmaf(cl[0], ki, cl[kBoth] * qi), x, b1[j]);
                     }
                 }
             }
@@ -225,14 +279,13 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
             u = __shfl_down(tot, 16);
             const float behind = run + (g <= 2 ? u : 0.f);
             run += __shfl(tot, m);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int r = 16 * R + 4 * g + j;
-                if (r < c.nv) {
-                    const int64_t at_ = col + r * stride;
-                    dq[at_] = gq[j]; dk[at_] = gk[j]; dla[at_] = s[j] + behind;
-                }
+            const f32x4 tq = quad_transpose(gq, lane), tk = quad_transpose(gk, lane), tg = quad_transpose(s + behind, lane);
+            const int r = 16 * R + 4 * g + (lane & 3);
+            if (r < c.nv) {
+                const int64_t to = base + r * stride + 16 * (4 * tt + w) + (lane & 12);
+                st4(dq + to, tq); st4(dk + to, tk); st4(dla + to, tg);
             }
+            if (tt + 1 < TW && R == (sizeof(Tin) == 2 ? 2 : 1)) fetch_inputs(tt + 1);    // (into what this tile has freed)
         }
     };
     finish(0, aq[0], ak[0], at[0], gc[0]);
@@ -247,7 +300,7 @@ kda_status launch_gradients(const Problem &p, const Tin *q, const Tin *k, const 
     const int64_t blocks = p.slots * p.H;
     if (blocks == 0) return KDA_OK;
     if (blocks > 0x7fffffffLL) return fail(KDA_ERR_UNSUPPORTED, "%lld chunks in one call", (long long)blocks);
-    hipLaunchKernelGGL((kda_bwd_gradients_kernel<Tin, Tdo, D>), dim3((unsigned)blocks), dim3(kGradThreads), kGradLds, stream, q, k,
+    hipLaunchKernelGGL((kda_bwd_gradients_kernel<Tin, Tdo, D>), dim3((unsigned)blocks), dim3(kGradThreads), grad_lds<Tin>(), stream, q, k,
                        log_alpha, beta, d_o, S0, R, dS1, Z, dq, dk, dv, dla, dbeta, p);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? KDA_OK : fail(KDA_ERR_LAUNCH, "kda_bwd_gradients: %s", hipGetErrorString(e));

@@ -73,6 +73,9 @@ __device__ __forceinline__ void st4(float *p, const f32x4 &v) { *reinterpret_cas
 // Workgroup barrier for LDS traffic: global loads and stores stay in flight across it.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// Loads, stores and LDS accesses stay on their side of this point; arithmetic may cross it.
+__device__ __forceinline__ void pin_memory_order() { __builtin_amdgcn_sched_barrier(0x0f); }
+
 // R and Z, [tokens x heads x D] floats in all: the rows of a (chunk, head) lie together, token tile by token tile, a tile
 // of n <= 16 valid tokens as [column tile][4 columns][n tokens] float4, which for n = 16 is the fragment in row form.
 __device__ __forceinline__ int64_t token_rows(int64_t tok0, int H, int h, int nv, int D) { return (tok0 * H + (int64_t)h * nv) * D; }

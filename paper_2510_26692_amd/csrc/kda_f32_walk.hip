@@ -63,9 +63,6 @@ template <typename T, int NC> struct Rows {
     }
 };
 
-// Loads, stores and LDS accesses stay on their side of this point; arithmetic may cross it.
-__device__ __forceinline__ void pin_memory_order() { __builtin_amdgcn_sched_barrier(0x0f); }
-
 // Four token tiles of B fragments from LDS: all fetched at once, so that one wait covers them, unless that takes more
 // than 32 registers.
 template <int NC> struct Four {
