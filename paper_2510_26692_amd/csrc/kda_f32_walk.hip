@@ -162,13 +162,17 @@ __device__ __forceinline__ void store_rows(float *dst, const f32x4 (&x)[NC], int
     }
 }
 
-// kOut: o instead of S0 and R.
-template <typename Tin, int D, int NC, bool kOut>
+// What the walk leaves besides the final state: o (the prefill), S0 and R (the backward pass), or nothing, where four
+// other waves of the workgroup form o from the S0 and Vn in LDS (output_role).
+enum Leaves { kOutputs, kStates, kNothing };
+
+template <typename Tin, int D, int NC, Leaves kLeaves>
 __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, const Tin *v, const float *h0,
                                              const float *slots, float *S0, float *Rw, float *o, float *hT, int64_t n, int h,
                                              int slice)
 {
     using SL = Slot<D>;
+    constexpr bool kOut = kLeaves == kOutputs;
     constexpr int NT = SL::kTiles, TW = NT / 4;
     float *sS = smem, *sY = sS + NC * NT * kFrag, *sV = sY + NC * 4 * kFrag;
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4, turned = 4 * turned_lane(lane);
@@ -227,7 +231,7 @@ __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, cons
         const int nv = valid(ci);
         const int64_t cn = ci + 1 < x.nchunks ? ci + 1 : ci;                  // (the last step fetches its own operands again)
         const float *next = slots + (x.slot0 + cn * p.H) * SL::kFloats, *here = slots + (x.slot0 + ci * p.H) * SL::kFloats;
-        float *s0 = kOut ? nullptr : S0 + (x.slot0 + ci * p.H) * (int64_t)(D * D) + turned;
+        float *s0 = kLeaves != kStates ? nullptr : S0 + (x.slot0 + ci * p.H) * (int64_t)(D * D) + turned;
         // Y = V - Kg S0
         f32x4 y[NC] = {}, oo[kOut ? NC : 1] = {};
         product<NT, NC, kAhead>(y, [&](int t) { return quad_transpose(kg[t], lane); },
@@ -236,7 +240,7 @@ __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, cons
                                     load_kg(next, t);
                                     if (kOut && t < 4) load_p(here, t);
                                     const int tt = t / NC, nc = t % NC;
-                                    if (!kOut && tt < TW)
+                                    if (kLeaves == kStates && tt < TW)
                                         st4(s0 + ((t0 + tt) * NT + NC * slice + nc) * kFrag, quad_transpose(S[tt < TW ? tt : 0][nc], lane));
                                 });
         const f32x4 b4 = bt;
@@ -271,7 +275,7 @@ __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, cons
             r[nc] = y[nc] - r[nc];
             st4(sV + (nc * 4 + w) * kFrag + 4 * lane, b4 * r[nc]);
         }
-        if (!kOut) {
+        if (kLeaves == kStates) {
             store_rows<D, NC>(Rw, r, x.tok_base + ci * kC, p.H, h, nv, w, NC * slice, lane);
         }
         lds_barrier();
@@ -307,6 +311,60 @@ __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, cons
         lds_barrier();
     }
     if (hT) store_state<D, NC>(hT + x.state + col0 + m, S, t0, g);
+}
+
+// The four waves that form o = scale (Qg S0 + P Vn) beside four that walk (forward_walk of kNothing, one column tile):
+// the products that no later step waits for leave the chain of the steps.  In step with the walk's three barriers a
+// chunk: S0 is read before the second one and Vn between the second and the third, which is when LDS holds them.
+template <int D>
+__device__ __forceinline__ void output_role(const float *smem, const Problem &p, const float *slots, float *o, int64_t n, int h,
+                                            int slice)
+{
+    using SL = Slot<D>;
+    constexpr int NT = SL::kTiles, kAhead = 4;
+    const float *sS = smem, *sV = sS + (NT + 4) * kFrag;
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4, turned = 4 * turned_lane(lane);
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) - 4, row0 = 16 * w + 4 * g;
+    const Where x = where(p, n, h, D);
+    const int64_t stride = (int64_t)p.H * D;
+    f32x4 qg[NT], pm[4];
+    auto load_qg = [&](const float *slot, int t) __attribute__((always_inline)) { qg[t] = ld4(slot + SL::kQg + (w * NT + t) * kFrag + turned); };
+    auto load_p = [&](const float *slot, int J) __attribute__((always_inline)) { pm[J] = ld4(slot + SL::kP + tri(w, J < w ? J : w) * kFrag + turned); };
+    if (x.nchunks > 0) {
+        const float *slot = slots + x.slot0 * SL::kFloats;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) load_qg(slot, t);
+#pragma unroll
+        for (int J = 0; J < 4; ++J) load_p(slot, J);
+        lds_barrier();
+    }
+#pragma unroll 1
+    for (int64_t ci = 0; ci < x.nchunks; ++ci) {
+        const int nv = (int)(x.len - ci * kC < kC ? x.len - ci * kC : kC);
+        const int64_t cn = ci + 1 < x.nchunks ? ci + 1 : ci;
+        const float *next = slots + (x.slot0 + cn * p.H) * SL::kFloats;
+        f32x4 oo[1] = {};
+        auto half = [&](int first) __attribute__((always_inline)) {
+            product<NT / 2, 1, kAhead>(oo, [&](int t) { return quad_transpose(qg[first + t], lane); },
+                                       [&](int t, int) { return ld4(sS + (first + t) * kFrag + 4 * lane); },
+                                       [&](int t) { load_qg(next, first + t); });
+        };
+        half(0);
+        lds_barrier();
+        half(NT / 2);
+        lds_barrier();
+        const Four<1> bv(sV, lane);
+#pragma unroll
+        for (int J = 0; J < 4; ++J)
+            if (J <= w) oo[0] = mfma16(quad_transpose(pm[J], lane), bv.get(J, 0), oo[0]);
+        float *po = o + ((x.tok_base + ci * kC) * p.H + h) * (int64_t)D + 16 * slice + m;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (row0 + j < nv) po[(row0 + j) * stride] = p.scale * oo[0][j];
+#pragma unroll
+        for (int J = 0; J < 4; ++J) load_p(next, J);
+        lds_barrier();
+    }
 }
 
 template <typename Tdo, int D, int NC>
@@ -481,7 +539,24 @@ void kda_f32_forward_walk_kernel(const Tin *__restrict__ v, const float *__restr
     int64_t n;
     int h, slice;
     if (!place<D, NC>(p, blockIdx.x, n, h, slice)) return;
-    forward_walk<Tin, D, NC, true>(smem, p, v, h0, slots, nullptr, nullptr, o, hT, n, h, slice);
+    forward_walk<Tin, D, NC, kOutputs>(smem, p, v, h0, slots, nullptr, nullptr, o, hT, n, h, slice);
+}
+
+template <typename Tin, int D>
+__global__ __launch_bounds__(2 * kWalkThreads, 2)
+void kda_f32_forward_roles_kernel(const Tin *__restrict__ v, const float *__restrict__ h0,
+                                  const float *__restrict__ slots, float *__restrict__ o, float *__restrict__ hT, const Problem p)
+{
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    int64_t n;
+    int h, slice;
+    if (!place<D, 1>(p, blockIdx.x, n, h, slice)) return;
+    if (threadIdx.x < kWalkThreads) {
+        __builtin_amdgcn_s_setprio(1);                                        // the chain first
+        forward_walk<Tin, D, 1, kNothing>(smem, p, v, h0, slots, nullptr, nullptr, nullptr, hT, n, h, slice);
+    } else {
+        output_role<D>(smem, p, slots, o, n, h, slice);
+    }
 }
 
 // The backward walk, the longer of the two, goes first.
@@ -498,7 +573,7 @@ void kda_f32_both_walks_kernel(const Tin *__restrict__ v, const float *__restric
     int h, slice;
     if (!place<D, NC>(p, bid < half ? bid : bid - half, n, h, slice)) return;
     if (bid < half) backward_walk<Tdo, D, NC>(smem, p, d_o, d_hT, slots, dS1, Zw, dh0, n, h, slice);
-    else forward_walk<Tin, D, NC, false>(smem, p, v, h0, slots, S0, Rw, nullptr, nullptr, n, h, slice);
+    else forward_walk<Tin, D, NC, kStates>(smem, p, v, h0, slots, S0, Rw, nullptr, nullptr, n, h, slice);
 }
 
 // Column tiles per workgroup: the fewest that still give every compute unit at most two workgroups (more than two
@@ -511,14 +586,14 @@ static int column_tiles(const Problem &p, int D, int walks, int compute_units)
 }
 
 template <typename F, typename... Args>
-static kda_status launch_walk(F kern, const char *name, int64_t blocks, size_t lds, hipStream_t stream, Args... args)
+static kda_status launch_walk(F kern, const char *name, int64_t blocks, int threads, size_t lds, hipStream_t stream, Args... args)
 {
     if (blocks > 0x7fffffffLL) return fail(KDA_ERR_UNSUPPORTED, "%s: %lld workgroups", name, (long long)blocks);
     hipError_t e = hipSuccess;
     if (lds > 65536)
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kWalkThreads), lds, stream, args...);
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3((unsigned)threads), lds, stream, args...);
         e = hipGetLastError();
     }
     return e == hipSuccess ? KDA_OK : fail(KDA_ERR_LAUNCH, "%s: %s", name, hipGetErrorString(e));
@@ -528,9 +603,15 @@ template <typename Tin, int D>
 kda_status launch_forward_walk(const Problem &p, const Tin *v, const float *h0, const float *slots, float *o,
                                float *hT, int compute_units, hipStream_t stream)
 {
-#define KDA_GO(NC) launch_walk(kda_f32_forward_walk_kernel<Tin, D, NC>, "kda_f32_forward_walk", walk_workgroups(p, D / (16 * NC)), \
+#define KDA_GO(NC) launch_walk(kda_f32_forward_walk_kernel<Tin, D, NC>, "kda_f32_forward_walk", walk_workgroups(p, D / (16 * NC)), kWalkThreads, \
                                walk_lds<D, NC>(false), stream, v, h0, slots, o, hT, p)
     const int nc = column_tiles(p, D, 1, compute_units);
+    // Where every workgroup of one column tile has a compute unit to itself, four more waves share its matrix cores with the
+    // walking ones (16 pairs of 2048 tokens: d 64 112 -> 97 us, d 128 164 -> 141 us; 64 pairs, d 64: 161 -> 155 us).  Two such
+    // workgroups do not fit a compute unit at d 128, and there two plain ones overlap as well.
+    if (walk_workgroups(p, D / 16) <= compute_units)
+        return launch_walk(kda_f32_forward_roles_kernel<Tin, D>, "kda_f32_forward_roles", walk_workgroups(p, D / 16), 2 * kWalkThreads,
+                           walk_lds<D, 1>(false), stream, v, h0, slots, o, hT, p);
     return nc == 1 ? KDA_GO(1) : nc == 2 ? KDA_GO(2) : KDA_GO(4);
 #undef KDA_GO
 }
@@ -540,7 +621,7 @@ kda_status launch_both_walks(const Problem &p, const Tin *v, const float *h0, co
                              const float *slots, float *S0, float *R, float *dS1, float *Z, float *dh0, int compute_units,
                              hipStream_t stream)
 {
-#define KDA_GO(NC) launch_walk(kda_f32_both_walks_kernel<Tin, Tdo, D, NC>, "kda_f32_both_walks", 2 * walk_workgroups(p, D / (16 * NC)), \
+#define KDA_GO(NC) launch_walk(kda_f32_both_walks_kernel<Tin, Tdo, D, NC>, "kda_f32_both_walks", 2 * walk_workgroups(p, D / (16 * NC)), kWalkThreads, \
                                walk_lds<D, NC>(true), stream, v, h0, d_o, d_hT, slots, S0, R, dS1, Z, dh0, \
                                walk_workgroups(p, D / (16 * NC)), p)
     const int nc = column_tiles(p, D, 2, compute_units);
