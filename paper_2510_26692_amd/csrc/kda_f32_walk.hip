@@ -367,13 +367,16 @@ __device__ __forceinline__ void output_role(const float *smem, const Problem &p,
     }
 }
 
-template <typename Tdo, int D, int NC>
+// kHelped (one column tile): four other waves of the workgroup leave P^T dO and Qg^T dO of the chunk in LDS (gradient_role).
+template <typename Tdo, int D, int NC, bool kHelped>
 __device__ __forceinline__ void backward_walk(float *smem, const Problem &p, const Tdo *d_o, const float *d_hT,
                                               const float *slots, float *dS1, float *Zw, float *dh0, int64_t n, int h, int slice)
 {
     using SL = Slot<D>;
     constexpr int NT = SL::kTiles, TW = NT / 4;
     float *sS = smem, *sY = sS + NC * NT * kFrag, *sX = sY + NC * 4 * kFrag, *sO = sX + NC * 4 * kFrag;    // sO: two buffers
+    static_assert(!kHelped || NC == 1, "one column tile");
+    const float *sE = sO + 4 * kFrag;                                         // kHelped: [4] P^T dO, [NT] Qg^T dO
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4, turned = 4 * turned_lane(lane);
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), row0 = 16 * w + 4 * g, t0 = TW * w;
     const Where x = where(p, n, h, D);
@@ -410,23 +413,27 @@ __device__ __forceinline__ void backward_walk(float *smem, const Problem &p, con
     const int64_t last = x.nchunks - 1;
     if (last >= 0) {
         const float *slot = slots + (x.slot0 + last * p.H) * SL::kFloats;
+        if (!kHelped) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) load_o(last, j);
-        share_o(last, 0);
+            for (int j = 0; j < 4; ++j) load_o(last, j);
+            share_o(last, 0);
+        }
         // (in the order of the loop: the compiler's waits take the worse of the two ways into it)
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             load_kt(slot, t);
-            if (t < 4) load_p(slot, t);
+            if (!kHelped && t < 4) load_p(slot, t);
         }
         pin_memory_order();
 #pragma unroll
         for (int R = 0; R < 4; ++R) {
             load_q(slot, R);
             if (R == 0) load_b(slot);
-            load_o(last > 0 ? last - 1 : 0, R);
+            if (!kHelped) {
+                load_o(last > 0 ? last - 1 : 0, R);
 #pragma unroll
-            for (int tt = 0; tt < TW; ++tt) load_qg(slot, tt, R);
+                for (int tt = 0; tt < TW; ++tt) load_qg(slot, tt, R);
+            }
             if (R < TW) load_gam(slot, R < TW ? R : 0);
             pin_memory_order();
         }
@@ -437,6 +444,7 @@ __device__ __forceinline__ void backward_walk(float *smem, const Problem &p, con
             pin_memory_order();
         }
         share_state();
+        if (kHelped) lds_barrier();                                           // (the helpers' own, over the rows of dO)
         lds_barrier();
     }
     int buf = 0;
@@ -449,7 +457,9 @@ __device__ __forceinline__ void backward_walk(float *smem, const Problem &p, con
         const float *so = sO + buf * (NC * 4 * kFrag);
         // dVn = Kt dS1 + P^T dO
         f32x4 y[NC] = {};
-        {
+        if constexpr (kHelped) {
+            y[0] = ld4(sE + w * kFrag + 4 * lane);
+        } else {
             const Four<NC> bo(so, lane);
 #pragma unroll
             for (int R = 0; R < 4; ++R)
@@ -462,7 +472,7 @@ __device__ __forceinline__ void backward_walk(float *smem, const Problem &p, con
                                 [&](int t, int nc) { return ld4(sS + (nc * NT + t) * kFrag + 4 * lane); },
                                 [&](int t) {
                                     load_kt(next, t);
-                                    if (t < 4) load_p(next, t);
+                                    if (!kHelped && t < 4) load_p(next, t);
                                     const int tt = t / NC, nc = t % NC;
                                     if (tt < TW)
                                         st4(ds1 + ((t0 + tt) * NT + NC * slice + nc) * kFrag, quad_transpose(S[tt < TW ? tt : 0][nc], lane));
@@ -470,7 +480,7 @@ __device__ __forceinline__ void backward_walk(float *smem, const Problem &p, con
         const f32x4 b4 = bt;
 #pragma unroll
         for (int nc = 0; nc < NC; ++nc) st4(sY + (nc * 4 + w) * kFrag + 4 * lane, b4 * y[nc]);
-        share_o(cn, buf ^ 1);
+        if (!kHelped) share_o(cn, buf ^ 1);
         lds_barrier();
         // Z = dVn - Q^T (beta dVn)
         f32x4 z[NC] = {};
@@ -493,14 +503,24 @@ __device__ __forceinline__ void backward_walk(float *smem, const Problem &p, con
             st4(sX + (nc * 4 + w) * kFrag + 4 * lane, -b4 * z[nc]);
         }
         // dS0 = Diag(e^(G_C)) dS1 + Qg^T dO - Kg^T X  (the first product is done while X is on its way)
-        update_state<TW, NC>(S, qg, Four<NC>(so, lane), [&](int R) {
+        auto refill = [&](int R) __attribute__((always_inline)) {
             load_q(next, R);
             if (R == 0) load_b(next);
-            load_o(cnn, R);
+            if (!kHelped) {
+                load_o(cnn, R);
 #pragma unroll
-            for (int tt = 0; tt < TW; ++tt) load_qg(next, tt, R);
+                for (int tt = 0; tt < TW; ++tt) load_qg(next, tt, R);
+            }
             if (R < TW) load_gam(next, R < TW ? R : 0);
-        });
+        };
+        if constexpr (kHelped) {
+#pragma unroll
+            for (int tt = 0; tt < TW; ++tt) S[tt][0] += ld4(sE + (4 + t0 + tt) * kFrag + 4 * lane);
+#pragma unroll
+            for (int R = 0; R < 4; ++R) { refill(R); pin_memory_order(); }
+        } else {
+            update_state<TW, NC>(S, qg, Four<NC>(so, lane), refill);
+        }
         store_rows<D, NC>(Zw, z, x.tok_base + ci * kC, p.H, h, nv, w, NC * slice, lane);
         lds_barrier();
         update_state<TW, NC>(S, kg, Four<NC>(sX, lane), [&](int R) {
@@ -511,6 +531,80 @@ __device__ __forceinline__ void backward_walk(float *smem, const Problem &p, con
         lds_barrier();
     }
     if (dh0) store_state<D, NC>(dh0 + x.state + col0 + m, S, t0, g);
+}
+
+// The four waves that leave P^T dO and Qg^T dO of a chunk in LDS while four others walk the chunk before it
+// (backward_walk of kHelped): these products need no state, so they leave the chain of the steps.  In step with the
+// walk's three barriers a chunk: the rows of dO are exchanged before the first; the walk reads the products of its chunk
+// before the second, and the next chunk's replace them between the second and the third.
+template <typename Tdo, int D>
+__device__ __forceinline__ void gradient_role(float *smem, const Problem &p, const Tdo *d_o, const float *slots, int64_t n, int h,
+                                              int slice)
+{
+    using SL = Slot<D>;
+    constexpr int NT = SL::kTiles, TW = NT / 4;
+    float *sO = smem + (NT + 8) * kFrag, *sE = sO + 4 * kFrag;
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) - 4, row0 = 16 * w + 4 * g, t0 = TW * w;
+    const Where x = where(p, n, h, D);
+    const int64_t stride = (int64_t)p.H * D;
+    f32x4 pm[4], qg[TW][4];
+    Rows<Tdo, 1> vo;
+    auto valid = [&](int64_t ci) { return (int)(x.len - ci * kC < kC ? x.len - ci * kC : kC); };
+    auto load_o = [&](int64_t ci) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            vo.load_row(j, d_o + ((x.tok_base + ci * kC) * p.H + h) * (int64_t)D + 16 * slice, m, stride, row0, valid(ci));
+    };
+    auto share_o = [&](int64_t ci) __attribute__((always_inline)) { st4(sO + w * kFrag + 4 * lane, vo.tile(0, m, row0, valid(ci)) * p.scale); };
+    auto load_ops = [&](int64_t ci) __attribute__((always_inline)) {
+        const float *slot = slots + (x.slot0 + ci * p.H) * SL::kFloats;
+#pragma unroll
+        for (int R = 0; R < 4; ++R) {
+            pm[R] = ld4(slot + SL::kP + tri(R > w ? R : w, w) * kFrag + 4 * lane);
+#pragma unroll
+            for (int tt = 0; tt < TW; ++tt) qg[tt][R] = ld4(slot + SL::kQg + (R * NT + t0 + tt) * kFrag + 4 * lane);
+        }
+    };
+    f32x4 y, E[TW][1];
+    auto multiply = [&]() __attribute__((always_inline)) {
+        const Four<1> bo(sO, lane);
+        y = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int R = 0; R < 4; ++R)
+            if (R >= w) y = mfma16(pm[R], bo.get(R, 0), y);
+#pragma unroll
+        for (int tt = 0; tt < TW; ++tt) E[tt][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+        update_state<TW, 1>(E, qg, bo, [](int) {});
+    };
+    auto leave = [&]() __attribute__((always_inline)) {
+        st4(sE + w * kFrag + 4 * lane, y);
+#pragma unroll
+        for (int tt = 0; tt < TW; ++tt) st4(sE + (4 + t0 + tt) * kFrag + 4 * lane, E[tt][0]);
+    };
+    const int64_t last = x.nchunks - 1;
+    if (last < 0) return;
+    load_o(last);
+    load_ops(last);
+    share_o(last);
+    lds_barrier();
+    multiply();
+    leave();
+    load_o(last > 0 ? last - 1 : 0);
+    load_ops(last > 0 ? last - 1 : 0);
+    lds_barrier();
+#pragma unroll 1
+    for (int64_t ci = last; ci >= 0; --ci) {
+        const int64_t cn = ci > 0 ? ci - 1 : 0, cnn = cn > 0 ? cn - 1 : 0;    // (the last ones are formed again, unused)
+        share_o(cn);
+        load_o(cnn);
+        lds_barrier();
+        multiply();
+        load_ops(cnn);
+        lds_barrier();
+        leave();
+        lds_barrier();
+    }
 }
 
 // Workgroups are handed to the eight dies in turn: the slices of a (sequence, head), which read the same operands at
@@ -559,9 +653,10 @@ void kda_f32_forward_roles_kernel(const Tin *__restrict__ v, const float *__rest
     }
 }
 
-// The backward walk, the longer of the two, goes first.
-template <typename Tin, typename Tdo, int D, int NC>
-__global__ __launch_bounds__(kWalkThreads, (per_cu<D, NC>()))
+// The backward walk, the longer of the two, goes first.  kHelped: four waves more, which help the backward walk (and
+// leave at once in the forward one, whose chain holds every product it has).
+template <typename Tin, typename Tdo, int D, int NC, bool kHelped>
+__global__ __launch_bounds__(kHelped ? 2 * kWalkThreads : kWalkThreads, (per_cu<D, NC>()))
 void kda_f32_both_walks_kernel(const Tin *__restrict__ v, const float *__restrict__ h0,
                                const Tdo *__restrict__ d_o, const float *__restrict__ d_hT, const float *__restrict__ slots,
                                float *__restrict__ S0, float *__restrict__ Rw, float *__restrict__ dS1, float *__restrict__ Zw,
@@ -572,7 +667,12 @@ void kda_f32_both_walks_kernel(const Tin *__restrict__ v, const float *__restric
     int64_t n;
     int h, slice;
     if (!place<D, NC>(p, bid < half ? bid : bid - half, n, h, slice)) return;
-    if (bid < half) backward_walk<Tdo, D, NC>(smem, p, d_o, d_hT, slots, dS1, Zw, dh0, n, h, slice);
+    if (kHelped && threadIdx.x >= kWalkThreads) {
+        if (bid < half) gradient_role<Tdo, D>(smem, p, d_o, slots, n, h, slice);
+        return;
+    }
+    if (kHelped) __builtin_amdgcn_s_setprio(1);                               // the chain first
+    if (bid < half) backward_walk<Tdo, D, NC, kHelped>(smem, p, d_o, d_hT, slots, dS1, Zw, dh0, n, h, slice);
     else forward_walk<Tin, D, NC, kStates>(smem, p, v, h0, slots, S0, Rw, nullptr, nullptr, n, h, slice);
 }
 
@@ -621,11 +721,16 @@ kda_status launch_both_walks(const Problem &p, const Tin *v, const float *h0, co
                              const float *slots, float *S0, float *R, float *dS1, float *Z, float *dh0, int compute_units,
                              hipStream_t stream)
 {
-#define KDA_GO(NC) launch_walk(kda_f32_both_walks_kernel<Tin, Tdo, D, NC>, "kda_f32_both_walks", 2 * walk_workgroups(p, D / (16 * NC)), kWalkThreads, \
-                               walk_lds<D, NC>(true), stream, v, h0, d_o, d_hT, slots, S0, R, dS1, Z, dh0, \
+#define KDA_GO(NC, HELPED, THREADS, LDS) launch_walk(kda_f32_both_walks_kernel<Tin, Tdo, D, NC, HELPED>, "kda_f32_both_walks", \
+                               2 * walk_workgroups(p, D / (16 * NC)), THREADS, LDS, stream, v, h0, d_o, d_hT, slots, S0, R, dS1, Z, dh0, \
                                walk_workgroups(p, D / (16 * NC)), p)
     const int nc = column_tiles(p, D, 2, compute_units);
-    return nc == 1 ? KDA_GO(1) : nc == 2 ? KDA_GO(2) : KDA_GO(4);
+    // Where every workgroup of one column tile has a compute unit to itself, four more waves help the backward walks (whole
+    // pass, d 128, 4096 tokens: 4 pairs 271 -> 250 us, 16 pairs 424 -> 399 us; d 64, 32 pairs: 336 -> 326 us).
+    if (2 * walk_workgroups(p, D / 16) <= compute_units)
+        return KDA_GO(1, true, 2 * kWalkThreads, (size_t)(2 * (D / 16) + 16) * kFrag * 4);
+    return nc == 1 ? KDA_GO(1, false, kWalkThreads, (walk_lds<D, 1>(true)))
+         : nc == 2 ? KDA_GO(2, false, kWalkThreads, (walk_lds<D, 2>(true))) : KDA_GO(4, false, kWalkThreads, (walk_lds<D, 4>(true)));
 #undef KDA_GO
 }
 
