@@ -64,7 +64,7 @@ kda_status backward(const kda_dims *dm, const Plan &pl, const void *q, const voi
     auto in = [](const void *x) { return static_cast<const Tin *>(x); };
     auto at = [&](size_t off) { return reinterpret_cast<float *>(ws + off); };
     const Tdo *go = static_cast<const Tdo *>(d_o);
-    kda_status st = f32::launch_prep<Tin, D>(p, in(q), in(k), in(la), in(beta), at(pl.ops), stream);
+    kda_status st = f32::launch_prep<Tin, D, false>(p, in(q), in(k), in(la), in(beta), at(pl.ops), stream);
     if (st == KDA_OK)
         st = f32::launch_both_walks<Tin, Tdo, D>(p, in(v), h0, go, d_hT, at(pl.ops), at(pl.S0), at(pl.R), at(pl.dS1),
                                                  at(pl.Z), dh0, cus, stream);
@@ -81,7 +81,7 @@ kda_status forward(const kda_dims *dm, const Plan &pl, const void *q, const void
     const Problem p = problem(dm, pl, cu);
     auto in = [](const void *x) { return static_cast<const Tin *>(x); };
     float *ops = reinterpret_cast<float *>(ws + pl.ops);
-    const kda_status st = f32::launch_prep<Tin, D>(p, in(q), in(k), in(la), in(beta), ops, stream);
+    const kda_status st = f32::launch_prep<Tin, D, true>(p, in(q), in(k), in(la), in(beta), ops, stream);
     if (st != KDA_OK) return st;
     return f32::launch_forward_walk<Tin, D>(p, in(v), h0, ops, o, hT, cus, stream);
 }

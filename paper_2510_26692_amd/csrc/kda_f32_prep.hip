@@ -20,7 +20,7 @@ static_assert(3 * kPrepLds <= 160 * 1024, "three workgroups share a compute unit
 // Four waves; the channels are taken 64 at a time, 16 per wave.  LDS: Kp = k 2^(G - pref), Qp = q 2^(G - pref) and
 // Kn = k 2^(nref - G) of those 64 channels, 51 KiB, so that three workgroups share a compute unit.  The inputs of the next
 // 64 channels are on their way while the products of these are formed.
-template <typename Tin, int D>
+template <typename Tin, int D, bool kRows>
 __global__ __launch_bounds__(kPrepThreads, 3)
 void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, const Tin *__restrict__ log_alpha,
                          const Tin *__restrict__ beta, float *__restrict__ slots, const Problem p)
@@ -37,6 +37,11 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t stride = (int64_t)p.H * D, base = (c.tok0 * p.H + c.h) * (int64_t)D;
     float *slot = slots + c.slot * SL::kFloats;
+    // (kRows: the operands that the forward walk multiplies from the left, in its order)
+    auto st = [&](float *frag, const f32x4 &x) __attribute__((always_inline)) {
+        if (kRows) st4(frag + 4 * turned_lane(lane), quad_transpose(x, lane));
+        else st4(frag + 4 * lane, x);
+    };
     if (tid < kC) {
         const float b = tid < c.nv ? load_as_float(beta + (c.tok0 + tid) * p.H + c.h) : 0.f;
         sBeta[tid] = b;
@@ -71,10 +76,10 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
 #pragma unroll
         for (int R = 0; R < 4; ++R) {
             const f32x4 gam = exp2_4(d.G[R]);
-            float *frag = slot + (R * SL::kTiles + t) * kFrag + 4 * lane;
-            st4(frag + SL::kKg, kk[R] * gam);
-            st4(frag + SL::kQg, qq[R] * gam);
-            st4(frag + SL::kKt, kk[R] * exp2_4(GC - d.G[R]));
+            float *frag = slot + (R * SL::kTiles + t) * kFrag;
+            st(frag + SL::kKg, kk[R] * gam);
+            st(frag + SL::kQg, qq[R] * gam);
+            st4(frag + SL::kKt + 4 * lane, kk[R] * exp2_4(GC - d.G[R]));
             const f32x4 pf = exp2_4(d.G[R] - d.pref[R]), nf = exp2_4(d.nref[R] - d.G[R]);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -168,7 +173,7 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
             for (int j = 0; j < 4; ++j)
                 if (m > 4 * g + j || (u < 10 && m == 4 * g + j)) acc[i][j] = 0.f;
         }
-        if (u >= 10) st4(slot + SL::kP + b * kFrag + 4 * lane, acc[i]);
+        if (u >= 10) st(slot + SL::kP + b * kFrag, acc[i]);
         else {
 #pragma unroll
             for (int j = 0; j < 4; ++j) sA[(16 * R + 4 * g + j) * kLdT + 16 * I + m] = acc[i][j];
@@ -215,27 +220,32 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
     }
 #pragma unroll
     for (int R = 0; R < 4; ++R)
-        if (R >= w) st4(slot + SL::kQ + tri(R, w) * kFrag + 4 * lane, Q[R]);
+        if (R >= w) st(slot + SL::kQ + tri(R, w) * kFrag, Q[R]);
 }
 
-template <typename Tin, int D>
+template <typename Tin, int D, bool kRows>
 kda_status launch_prep(const Problem &p, const Tin *q, const Tin *k, const Tin *log_alpha, const Tin *beta, float *slots,
                        hipStream_t stream)
 {
     const int64_t blocks = p.slots * p.H;
     if (blocks == 0) return KDA_OK;
     if (blocks > 0x7fffffffLL) return fail(KDA_ERR_UNSUPPORTED, "%lld chunks in one call", (long long)blocks);
-    hipLaunchKernelGGL((kda_f32_prep_kernel<Tin, D>), dim3((unsigned)blocks), dim3(kPrepThreads), kPrepLds, stream, q, k,
+    hipLaunchKernelGGL((kda_f32_prep_kernel<Tin, D, kRows>), dim3((unsigned)blocks), dim3(kPrepThreads), kPrepLds, stream, q, k,
                        log_alpha, beta, slots, p);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? KDA_OK : fail(KDA_ERR_LAUNCH, "kda_f32_prep: %s", hipGetErrorString(e));
 }
 
-#define KDA_PREP(T, DD) template kda_status launch_prep<T, DD>(const Problem &, const T *, const T *, const T *, const T *, float *, hipStream_t)
-KDA_PREP(float, 64);
-KDA_PREP(float, 128);
-KDA_PREP(__hip_bfloat16, 64);
-KDA_PREP(__hip_bfloat16, 128);
+#define KDA_PREP(T, DD, ROWS) template kda_status launch_prep<T, DD, ROWS>(const Problem &, const T *, const T *, const T *, const T *, \
+                                                                             float *, hipStream_t)
+KDA_PREP(float, 64, false);
+KDA_PREP(float, 128, false);
+KDA_PREP(__hip_bfloat16, 64, false);
+KDA_PREP(__hip_bfloat16, 128, false);
+KDA_PREP(float, 64, true);
+KDA_PREP(float, 128, true);
+KDA_PREP(__hip_bfloat16, 64, true);
+KDA_PREP(__hip_bfloat16, 128, true);
 #undef KDA_PREP
 
 }  // namespace f32

@@ -26,8 +26,10 @@ constexpr int kTri = 10;                                     // 16 x 16 blocks o
 __host__ __device__ constexpr int tri(int R, int I) { return R * (R + 1) / 2 + I; }      // block (R, I), I <= R
 
 // What the per-chunk kernel leaves per (chunk, head), in floats: Gamma.K, Gamma^{i->C}.K and Gamma.Q as
-// [token tile][channel tile] fragments, the blocks of Q and Tril(A_qk), all in column form, e^(G_C) and beta (zero past
-// the chunk's end).
+// [token tile][channel tile] fragments, the blocks of Q and Tril(A_qk), e^(G_C) and beta (zero past the chunk's end).  All in
+// column form where both walks read them (one of the two turns each operand as it loads it); for the prefill all but
+// Gamma^{i->C}.K in row form, so that nothing is turned in the walk, whose steps are a chain: a turn is about 100 cycles
+// beside the 128 of a tile's products.
 template <int D> struct Slot {
     static constexpr int kTiles = D / 16;
     static constexpr int kKg = 0;
@@ -226,7 +228,7 @@ struct Problem {
     float scale;
 };
 
-template <typename Tin, int D>
+template <typename Tin, int D, bool kRows>
 kda_status launch_prep(const Problem &p, const Tin *q, const Tin *k, const Tin *log_alpha, const Tin *beta, float *slots,
                        hipStream_t stream);
 // Forward walk that writes o and the final states.

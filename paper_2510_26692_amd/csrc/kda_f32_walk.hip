@@ -172,11 +172,12 @@ __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, cons
                                              int slice)
 {
     using SL = Slot<D>;
-    constexpr bool kOut = kLeaves == kOutputs;
+    constexpr bool kOut = kLeaves == kOutputs, kRows = kLeaves != kStates;      // kRows: the slots are in row form
     constexpr int NT = SL::kTiles, TW = NT / 4;
     float *sS = smem, *sY = sS + NC * NT * kFrag, *sV = sY + NC * 4 * kFrag;
-    const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4, turned = 4 * turned_lane(lane);
+    const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4, turned = 4 * turned_lane(lane), left = kRows ? 4 * lane : turned;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), row0 = 16 * w + 4 * g, t0 = TW * w;
+    auto turn = [&](const f32x4 &a) __attribute__((always_inline)) { return kRows ? a : quad_transpose(a, lane); };
     const Where x = where(p, n, h, D);
     const int64_t stride = (int64_t)p.H * D;
     const int col0 = 16 * NC * slice;
@@ -187,10 +188,10 @@ __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, cons
     f32x4 kg[NT], qm[4], kt[TW][4], gam[TW], qg[kOut ? NT : 1], pm[kOut ? 4 : 1];
     f32x4 bt;
     Rows<Tin, NC> vv;
-    auto load_kg = [&](const float *slot, int t) __attribute__((always_inline)) { kg[t] = ld4(slot + SL::kKg + (w * NT + t) * kFrag + turned); };
-    auto load_qg = [&](const float *slot, int t) __attribute__((always_inline)) { qg[kOut ? t : 0] = ld4(slot + SL::kQg + (w * NT + t) * kFrag + turned); };
-    auto load_q = [&](const float *slot, int J) __attribute__((always_inline)) { qm[J] = ld4(slot + SL::kQ + tri(w, J < w ? J : w) * kFrag + turned); };
-    auto load_p = [&](const float *slot, int J) __attribute__((always_inline)) { pm[kOut ? J : 0] = ld4(slot + SL::kP + tri(w, J < w ? J : w) * kFrag + turned); };
+    auto load_kg = [&](const float *slot, int t) __attribute__((always_inline)) { kg[t] = ld4(slot + SL::kKg + (w * NT + t) * kFrag + left); };
+    auto load_qg = [&](const float *slot, int t) __attribute__((always_inline)) { qg[kOut ? t : 0] = ld4(slot + SL::kQg + (w * NT + t) * kFrag + left); };
+    auto load_q = [&](const float *slot, int J) __attribute__((always_inline)) { qm[J] = ld4(slot + SL::kQ + tri(w, J < w ? J : w) * kFrag + left); };
+    auto load_p = [&](const float *slot, int J) __attribute__((always_inline)) { pm[kOut ? J : 0] = ld4(slot + SL::kP + tri(w, J < w ? J : w) * kFrag + left); };
     auto load_kt = [&](const float *slot, int tt, int R) __attribute__((always_inline)) { kt[tt][R] = ld4(slot + SL::kKt + (R * NT + t0 + tt) * kFrag + 4 * lane); };
     auto load_gam = [&](const float *slot, int tt) __attribute__((always_inline)) { gam[tt] = ld4(slot + SL::kGc + 16 * (t0 + tt) + 4 * g); };
     auto valid = [&](int64_t ci) { return (int)(x.len - ci * kC < kC ? x.len - ci * kC : kC); };
@@ -234,7 +235,7 @@ __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, cons
         float *s0 = kLeaves != kStates ? nullptr : S0 + (x.slot0 + ci * p.H) * (int64_t)(D * D) + turned;
         // Y = V - Kg S0
         f32x4 y[NC] = {}, oo[kOut ? NC : 1] = {};
-        product<NT, NC, kAhead>(y, [&](int t) { return quad_transpose(kg[t], lane); },
+        product<NT, NC, kAhead>(y, [&](int t) { return turn(kg[t]); },
                                 [&](int t, int nc) { return ld4(sS + (nc * NT + t) * kFrag + 4 * lane); },
                                 [&](int t) {
                                     load_kg(next, t);
@@ -250,7 +251,7 @@ __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, cons
             st4(sY + (nc * 4 + w) * kFrag + 4 * lane, b4 * y[nc]);
         }
         if constexpr (kOut)                                                   // O = scale (Qg S0 + P Vn), the first half
-            product<NT, NC, kAhead>(oo, [&](int t) { return quad_transpose(qg[t], lane); },
+            product<NT, NC, kAhead>(oo, [&](int t) { return turn(qg[t]); },
                                     [&](int t, int nc) { return ld4(sS + (nc * NT + t) * kFrag + 4 * lane); },
                                     [&](int t) { load_qg(next, t); });
         lds_barrier();
@@ -265,7 +266,7 @@ __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, cons
 #pragma unroll
             for (int J = 0; J < 4; ++J)
                 if (J <= w) {
-                    const f32x4 a = quad_transpose(qm[J], lane);
+                    const f32x4 a = turn(qm[J]);
 #pragma unroll
                     for (int nc = 0; nc < NC; ++nc) r[nc] = mfma16(a, by.get(J, nc), r[nc]);
                 }
@@ -295,7 +296,7 @@ __device__ __forceinline__ void forward_walk(float *smem, const Problem &p, cons
 #pragma unroll
                 for (int J = 0; J < 4; ++J)
                     if (J <= w) {
-                        const f32x4 a = quad_transpose(pm[kOut ? J : 0], lane);
+                        const f32x4 a = turn(pm[kOut ? J : 0]);
 #pragma unroll
                         for (int nc = 0; nc < NC; ++nc) oo[kOut ? nc : 0] = mfma16(a, bv.get(J, nc), oo[kOut ? nc : 0]);
                     }
@@ -323,13 +324,13 @@ __device__ __forceinline__ void output_role(const float *smem, const Problem &p,
     using SL = Slot<D>;
     constexpr int NT = SL::kTiles, kAhead = 4;
     const float *sS = smem, *sV = sS + (NT + 4) * kFrag;
-    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4, turned = 4 * turned_lane(lane);
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) - 4, row0 = 16 * w + 4 * g;
     const Where x = where(p, n, h, D);
     const int64_t stride = (int64_t)p.H * D;
     f32x4 qg[NT], pm[4];
-    auto load_qg = [&](const float *slot, int t) __attribute__((always_inline)) { qg[t] = ld4(slot + SL::kQg + (w * NT + t) * kFrag + turned); };
-    auto load_p = [&](const float *slot, int J) __attribute__((always_inline)) { pm[J] = ld4(slot + SL::kP + tri(w, J < w ? J : w) * kFrag + turned); };
+    auto load_qg = [&](const float *slot, int t) __attribute__((always_inline)) { qg[t] = ld4(slot + SL::kQg + (w * NT + t) * kFrag + 4 * lane); };
+    auto load_p = [&](const float *slot, int J) __attribute__((always_inline)) { pm[J] = ld4(slot + SL::kP + tri(w, J < w ? J : w) * kFrag + 4 * lane); };
     if (x.nchunks > 0) {
         const float *slot = slots + x.slot0 * SL::kFloats;
 #pragma unroll
@@ -345,7 +346,7 @@ __device__ __forceinline__ void output_role(const float *smem, const Problem &p,
         const float *next = slots + (x.slot0 + cn * p.H) * SL::kFloats;
         f32x4 oo[1] = {};
         auto half = [&](int first) __attribute__((always_inline)) {
-            product<NT / 2, 1, kAhead>(oo, [&](int t) { return quad_transpose(qg[first + t], lane); },
+            product<NT / 2, 1, kAhead>(oo, [&](int t) { return qg[first + t]; },
                                        [&](int t, int) { return ld4(sS + (first + t) * kFrag + 4 * lane); },
                                        [&](int t) { load_qg(next, first + t); });
         };
@@ -356,7 +357,7 @@ __device__ __forceinline__ void output_role(const float *smem, const Problem &p,
         const Four<1> bv(sV, lane);
 #pragma unroll
         for (int J = 0; J < 4; ++J)
-            if (J <= w) oo[0] = mfma16(quad_transpose(pm[J], lane), bv.get(J, 0), oo[0]);
+            if (J <= w) oo[0] = mfma16(pm[J], bv.get(J, 0), oo[0]);
         float *po = o + ((x.tok_base + ci * kC) * p.H + h) * (int64_t)D + 16 * slice + m;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -707,7 +708,7 @@ kda_status launch_forward_walk(const Problem &p, const Tin *v, const float *h0, 
                                walk_lds<D, NC>(false), stream, v, h0, slots, o, hT, p)
     const int nc = column_tiles(p, D, 1, compute_units);
     // Where every workgroup of one column tile has a compute unit to itself, four more waves share its matrix cores with the
-    // walking ones (16 pairs of 2048 tokens: d 64 112 -> 97 us, d 128 164 -> 141 us; 64 pairs, d 64: 161 -> 155 us).  Two such
+    // walking ones (16 pairs of 2048 tokens, whole call: d 64 112 -> 97 us, d 128 164 -> 141 us; 64 pairs, d 64: 161 -> 155 us).  Two such
     // workgroups do not fit a compute unit at d 128, and there two plain ones overlap as well.
     if (walk_workgroups(p, D / 16) <= compute_units)
         return launch_walk(kda_f32_forward_roles_kernel<Tin, D>, "kda_f32_forward_roles", walk_workgroups(p, D / 16), 2 * kWalkThreads,
