@@ -189,8 +189,9 @@ kda_status kda_chunk_fwd_static_scratch(const kda_dims *dims,
  *   workspace                  at least kda_chunk_bwd_workspace_size(dims) bytes, 256-byte
  *                              aligned: the state at the start of every chunk and the
  *                              gradient of the state at its end (2 * dk * dv floats per chunk
- *                              and head), three [tokens, H, dv] arrays and four C x C tiles
- *                              per chunk and head; it is not bounded by time segments
+ *                              and head), two [tokens, H, dv] arrays, the decay-scaled
+ *                              operands and two triangular C x C matrices per chunk and head,
+ *                              and room that is spare; it is not bounded by time segments
  * No gradient may alias an input or another gradient.  Sequences of more than 65535 * 64
  * tokens are KDA_ERR_UNSUPPORTED.  Everything runs on `hip_stream`.
  */
