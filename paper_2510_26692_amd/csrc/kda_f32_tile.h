@@ -100,7 +100,8 @@ __device__ __forceinline__ int64_t first_slot(const int32_t *cu, int64_t n, int6
     return cu ? (int64_t)(cu[n] / kC) + n : n * chunks_per_seq;
 }
 
-// Chunk of workgroup `bid` of a grid of (slots x heads); false: a slot that no chunk uses.
+// Chunk of workgroup `bid` of a grid of (slots x heads); false: a slot that no chunk uses (past a sequence's last chunk, or
+// ahead of the first sequence where that does not start at token 0).
 __device__ __forceinline__ bool locate(const int32_t *cu, int num_seqs, int64_t T, int H, int64_t chunks_per_seq,
                                        int64_t bid, Chunk &c)
 {
@@ -120,7 +121,7 @@ __device__ __forceinline__ bool locate(const int32_t *cu, int num_seqs, int64_t 
         c0 = (s - first_slot(cu, lo, 0)) * kC; len = (int64_t)cu[lo + 1] - cu[lo]; c.tok0 = cu[lo] + c0;
     }
     c.nv = (int)(len - c0 < kC ? len - c0 : kC);
-    return c0 < len;
+    return c0 >= 0 && c0 < len;
 }
 
 // ---- one 16-channel tile of a chunk in column form: register j of [R] is token 16 R + 4 g + j, channel m ----

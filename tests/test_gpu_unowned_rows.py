@@ -57,3 +57,42 @@ def test_rows_on_both_sides_of_the_sequences_are_cleared_and_nothing_else(cu):
         owned[low:high] = True
         assert bool((rows[owned] == 7).all()) and bool((rows[~owned] == 0).all())
         assert bool((got[:guard] == 7).all()) and bool((got[-guard:] == 7).all())
+
+
+@pytest.mark.parametrize("lead", [63, 64, 200])
+@pytest.mark.parametrize("H,D,dtype", [(3, 64, "f32"), (2, 128, "f32"), (4, 128, "bf16")])
+def test_rows_ahead_of_the_first_sequence_take_no_part(lead, H, D, dtype):
+    """cu_seqlens that starts past token 0, by less than a chunk, a whole one and several: the rows ahead (and those
+    behind) are zero in outputs that the binding allocates and as they were in a caller's own, whatever the inputs hold
+    there, and the sequences' rows are bit for bit those of the same sequences alone."""
+    import paper_2510_26692_amd as kda
+    lens, tail = [70, 0, 5, 129], 90
+    x = si.make_varlen([lead] + lens + [tail], H, D, D, dtype, -2.0, 78, 0.05)
+    end = lead + sum(lens)
+    x["cu_seqlens"], x["h0"] = x["cu_seqlens"][1:-1].contiguous(), x["h0"][1:-1].contiguous()
+    names = ("q", "k", "v", "log_alpha", "beta")
+    for n in names:
+        x[n][:, :lead], x[n][:, end:] = float("nan"), float("nan")
+    dd = to_device(x)
+    do = torch.randn(1, end + tail, H, D, device="cuda")
+    dhT = 0.1 * torch.randn(len(lens), H, D, D, device="cuda")
+
+    def both(part, cu, o=None, hT=None, out=None):
+        args = [dd[n][:, part].clone() for n in names]
+        o, hT = kda.kda_chunk_fwd(*args, h0=dd["h0"], cu_seqlens=cu, o=o, hT=hT)
+        g = kda.kda_chunk_bwd(*args, do[:, part].clone(), dhT=dhT, h0=dd["h0"], cu_seqlens=cu, out=out)
+        torch.cuda.synchronize()
+        return dict(g, o=o, hT=hT)
+
+    whole, owned = slice(0, end + tail), slice(lead, end)
+    alone = both(owned, dd["cu_seqlens"] - lead)
+    got = both(whole, dd["cu_seqlens"])
+    into = {n: torch.full_like(t, 7.0) for n, t in got.items()}
+    both(whole, dd["cu_seqlens"], into["o"], into["hT"], {n: into[n] for n in into if n not in ("o", "hT")})
+    for n in got:
+        if n in ("hT", "dh0"):
+            assert torch.equal(got[n], alone[n]) and torch.equal(into[n], alone[n]), n
+            continue
+        for t, rest in ((got[n], 0.0), (into[n], 7.0)):
+            assert torch.equal(t[:, owned], alone[n]), n
+            assert bool((t[:, :lead] == rest).all()) and bool((t[:, end:] == rest).all()), n
