@@ -60,27 +60,26 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
     };
     fetch(w);
     bool strong = false;
-#pragma unroll 1
+#pragma unroll
     for (int hf = 0; hf < D / 64; ++hf) {
         const int t = 4 * hf + w;
         f32x4 kk[4], qq[4];
         Decay d;
         if (hf) lds_barrier();                               // the previous channels' tiles are read
-        fg.turn(d.G, reinterpret_cast<char *>(sKn + 16 * w), 4 * kLdT, c.nv, lane);
+        fg.turn(d.x, reinterpret_cast<char *>(sKn + 16 * w), 4 * kLdT, c.nv, lane);
         fk.turn(kk, reinterpret_cast<char *>(sKp + 16 * w), 4 * kLdT, c.nv, lane);
         fq.turn(qq, reinterpret_cast<char *>(sQp + 16 * w), 4 * kLdT, c.nv, lane);
-        if (4 * hf + 4 < SL::kTiles) fetch(t + 4);
-        running_decay(d, lane);
-        strong |= d.strong;
-        const float GC = d.E[3];
+        sum_decay(d, lane);
+        strong |= d.strong();
 #pragma unroll
         for (int R = 0; R < 4; ++R) {
-            const f32x4 gam = exp2_4(d.G[R]);
+            const Exponents x(d, R);
+            const f32x4 gam = exp2_4(x.start);
             float *frag = slot + (R * SL::kTiles + t) * kFrag;
             st(frag + SL::kKg, kk[R] * gam);
             st(frag + SL::kQg, qq[R] * gam);
-            st4(frag + SL::kKt + 4 * lane, kk[R] * exp2_4(GC - d.G[R]));
-            const f32x4 pf = exp2_4(d.G[R] - d.pref[R]), nf = exp2_4(d.nref[R] - d.G[R]);
+            st4(frag + SL::kKt + 4 * lane, kk[R] * exp2_4(x.end));
+            const f32x4 pf = exp2_4(x.row), nf = exp2_4(x.column);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int at = (16 * R + 4 * g + j) * kLdT + 16 * w + m;
@@ -88,13 +87,20 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
                 sQp[at] = qq[R][j] * pf[j];
                 sKn[at] = kk[R][j] * nf[j];
             }
+            __builtin_amdgcn_sched_barrier(0);               // (one block's values in registers at a time)
         }
         if (g == 0) {
-            slot[SL::kGc + 16 * t + m] = fast_exp2(GC);
+            slot[SL::kGc + 16 * t + m] = fast_exp2(d.whole());
 #pragma unroll
             for (int R = 1; R < 4; ++R)
 #pragma unroll
-                for (int I = 0; I < R; ++I) sF[pair_of(R, I) * 64 + 16 * w + m] = fast_exp2(d.pref[R] - d.nref[I]);
+                for (int I = 0; I < R; ++I) sF[pair_of(R, I) * 64 + 16 * w + m] = fast_exp2(d.across(R, I));
+        }
+        pin_memory_order();
+        if (4 * hf + 4 < SL::kTiles) {                       // (no earlier: this tile's values need the registers)
+            int next = t + 4;
+            asm volatile("" : "+s"(next));                   // (nor its addresses)
+            fetch(next);
         }
         lds_barrier();
 #pragma unroll
@@ -128,18 +134,20 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
             const int t = 4 * hf + w;
             f32x4 kk[4], qq[4];
             Decay d;
-            load_tile(d.G, log_alpha + base + m + 16 * t, stride, c.nv, g);
+            load_tile(d.x, log_alpha + base + m + 16 * t, stride, c.nv, g);
             load_tile(kk, k + base + m + 16 * t, stride, c.nv, g);
             load_tile(qq, q + base + m + 16 * t, stride, c.nv, g);
-            running_decay(d, lane);
+            sum_decay(d, lane);
             __syncthreads();
 #pragma unroll
-            for (int R = 0; R < 4; ++R)
+            for (int R = 0; R < 4; ++R) {
+                const f32x4 L = d.in_block(R);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int at = (16 * R + 4 * g + j) * kLdT + 16 * w + m;
-                    sKp[at] = kk[R][j]; sQp[at] = qq[R][j]; sKn[at] = d.G[R][j];
+                    sKp[at] = kk[R][j]; sQp[at] = qq[R][j]; sKn[at] = L[j];
                 }
+            }
             __syncthreads();
 #pragma unroll
             for (int i = 0; i < 5; ++i) {

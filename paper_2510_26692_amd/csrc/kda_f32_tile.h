@@ -125,19 +125,71 @@ __device__ __forceinline__ bool locate(const int32_t *cu, int num_seqs, int64_t 
 }
 
 // ---- one 16-channel tile of a chunk in column form: register j of [R] is token 16 R + 4 g + j, channel m ----
-// The in-block decay is split between a row factor 2^(G_r - pref_R) and a column factor 2^(nref_I - G_i); a
-// block pair R > I carries 2^(pref_R - nref_I) <= 1 besides, a diagonal pair nothing: pref = nref = the middle
-// of the block's decay.  Both factors then stay within 2^(+-kMaxDecay/2), which fp32 holds with full relative
-// precision.  A channel whose decay inside one 16-token block exceeds 2^-kMaxDecay ("strong") splits at the
-// block's two ends instead (every factor at most 1), contributes nothing to the diagonal products (fdiag = 0)
-// and is added there pair by pair.
-constexpr float kMaxDecay = 100.f;
+// Every decay is summed from the log alpha it consists of, never taken as a difference of running sums (whose rounding, 2^-24
+// of the decay since the chunk's start, is that of the result).  The in-block decay of a pair r >= i is split in the
+// middle of the 16-token block, between its tokens 7 and 8: a row factor 2^row(R), the decay from there to token r, and a
+// column factor 2^column(I), from token i to there, each below 1 on one side of the middle and above it on the other;
+// a block pair R > I carries 2^across(R, I) <= 1 besides.  Both factors stay within 2^(+-kMaxDecay): nothing overflows or
+// underflows, and a factor 2^x is off by |x| 2^-24 ln 2 (its exponent's rounding) and the exponential's own.  A channel
+// that decays by more than 2^-kMaxDecay in one half of a block ("strong") splits at the block's two ends instead (every
+// factor at most 1), contributes nothing to the diagonal products and is added there pair by pair.
+// (2-norm errors at log alpha = -softplus(normal - 2), d 128, against running sums over the chunk split at half of a block's
+// decay: dq 3.4e-7 -> 2.3e-7, dk 3.8e-7 -> 2.4e-7, o 3.4e-7 -> 2.3e-7, hT 3.1e-7 -> 0.9e-7; 2.1 times less at a mean of 0.)
+constexpr float kMaxDecay = 50.f;
 
 struct Decay {
-    f32x4 G[4];              // running sum of log2 alpha (tokens past the end repeat the last)
-    float E[4];              // G at the end of each block
-    float pref[4], nref[4], fdiag[4];
-    bool strong;
+    f32x4 x[4];                              // log alpha (0 past the end); sums are natural ones, scaled when used
+    float nb[4], h1[4], h2[4];               // sums over the block's tokens: the neighbouring lane group's, either half's
+    bool weak[4];                            // the channel is not strong in this block
+    bool second, odd;                        // this lane's tokens lie in the block's second half; in a half's second group
+    __device__ __forceinline__ f32x4 prefix(int R) const         // over the lane's own tokens: up to each, behind each
+    {
+        const float a = x[R][0] + x[R][1], b = a + x[R][2];
+        return f32x4{x[R][0], a, b, b + x[R][3]};
+    }
+    __device__ __forceinline__ f32x4 suffix(int R) const
+    {
+        const float a = x[R][2] + x[R][3];
+        return f32x4{x[R][1] + a, a, x[R][3], 0.f};
+    }
+    __device__ __forceinline__ float up(int R) const         // the block's groups ahead of this one
+    {
+        const float n = odd ? nb[R] : 0.f, h = second ? h1[R] : 0.f;
+        return n + h;
+    }
+    __device__ __forceinline__ float before(int R) const { float s = 0.f; for (int b = 0; b < R; ++b) s += h1[b] + h2[b]; return s; }
+    __device__ __forceinline__ float after(int R) const { float s = 0.f; for (int b = 3; b > R; --b) s += h1[b] + h2[b]; return s; }
+    __device__ __forceinline__ f32x4 in_block(int R) const { return (prefix(R) + up(R)) * kLog2e; }
+    __device__ __forceinline__ float across(int R, int I) const
+    {
+        const float r = weak[R] ? h1[R] : 0.f, i = weak[I] ? h2[I] : 0.f;
+        float s = r + i;
+        for (int b = I + 1; b < R; ++b) s += h1[b] + h2[b];
+        return s * kLog2e;
+    }
+    __device__ __forceinline__ float whole() const { return before(4) * kLog2e; }
+    __device__ __forceinline__ bool strong() const { return !(weak[0] && weak[1] && weak[2] && weak[3]); }
+};
+
+// The four exponents of a block, in log2 units: from the chunk's start to each token and from each to the chunk's end, and
+// those of its row and column factors.
+struct Exponents {
+    f32x4 start, end, row, column;
+    __device__ __forceinline__ Exponents(const Decay &d, int R)
+    {
+        const f32x4 p = d.prefix(R), e = d.suffix(R);
+        const float up = d.up(R), dn = d.odd ? 0.f : d.nb[R], dh = d.second ? 0.f : d.h2[R], down = dn + dh;
+        const float n = d.second == d.odd ? d.nb[R] : 0.f, mid = d.second ? n : -n;              // from the middle to this group
+        const bool r = d.second || !d.weak[R], c = !d.second || !d.weak[R];
+        const float ro = d.weak[R] ? mid : up, co = d.weak[R] ? -mid : down;
+        start = (p + (up + d.before(R))) * kLog2e;
+        end = (e + (down + d.after(R))) * kLog2e;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            row[j] = ((r ? p[j] : -e[j]) + ro) * kLog2e;
+            column[j] = ((c ? e[j] : -p[j]) + co) * kLog2e;
+        }
+    }
 };
 
 // A wave brings such a tile of a [tokens, H, D] tensor in with 16-byte loads (fetch: a lane holds a piece of a row) and
@@ -145,12 +197,14 @@ struct Decay {
 template <typename T> struct TileFetch {
     static constexpr int kPerRow = (int)sizeof(T);           // 16-byte pieces of a row of 16 channels
     uint4 raw[kPerRow];
+    // (the base is the workgroup's, so that the lanes' 32-bit offsets serve every tensor; 64 rows of 65535 heads fit them)
     __device__ __forceinline__ void fetch(const T *base, int64_t stride, int nv, int lane)
     {
 #pragma unroll
         for (int u = 0; u < kPerRow; ++u) {
-            const int r = (lane + 64 * u) / kPerRow, piece = lane % kPerRow;
-            raw[u] = *reinterpret_cast<const uint4 *>(base + (int64_t)(r < nv ? r : nv - 1) * stride + piece * (16 / (int)sizeof(T)));
+            const uint32_t r = (lane + 64 * u) / kPerRow, piece = lane % kPerRow, last = nv - 1;
+            const uint32_t off = (r < last ? r : last) * (uint32_t)(stride * sizeof(T)) + 16 * piece;
+            raw[u] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(base) + off);
         }
     }
     __device__ __forceinline__ void turn(f32x4 (&x)[4], char *at, int ld, int nv, int lane) const
@@ -186,31 +240,18 @@ template <typename T> __device__ __forceinline__ void load_tile(f32x4 (&x)[4], c
     }
 }
 
-__device__ __forceinline__ void running_decay(Decay &d, int lane)     // d.G holds log alpha on entry
+__device__ __forceinline__ void sum_decay(Decay &d, int lane)     // d.x holds log alpha on entry
 {
-    const int m = lane & 15, g = lane >> 4;
-    float run = 0.f;
-    d.strong = false;
+    d.second = lane & 32;
+    d.odd = lane & 16;
 #pragma unroll
     for (int R = 0; R < 4; ++R) {
-        f32x4 x = d.G[R] * kLog2e;
-        x[1] += x[0]; x[2] += x[1]; x[3] += x[2];
-        float s = x[3], u = __shfl_up(s, 16);
-        if (g >= 1) s += u;
-        u = __shfl_up(s, 32);
-        if (g >= 2) s += u;
-        u = __shfl_up(s, 16);
-        const float before = run + (g >= 1 ? u : 0.f);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) d.G[R][j] = x[j] + before;
-        d.E[R] = __shfl(d.G[R][3], 48 + m);
-        const bool strong = run - d.E[R] > kMaxDecay;
-        d.strong |= strong;
-        const float mid = 0.5f * (run + d.E[R]);
-        d.pref[R] = strong ? run : mid;
-        d.nref[R] = strong ? d.E[R] : mid;
-        d.fdiag[R] = strong ? 0.f : 1.f;
-        run = d.E[R];
+        const float own = d.prefix(R)[3];
+        d.nb[R] = __shfl_xor(own, 16);
+        const float mine = own + d.nb[R], other = __shfl_xor(mine, 32);
+        d.h1[R] = d.second ? other : mine;
+        d.h2[R] = d.second ? mine : other;
+        d.weak[R] = fminf(d.h1[R], d.h2[R]) >= -kMaxDecay / kLog2e;
     }
 }
 

@@ -1,0 +1,52 @@
+"""Size of the rounding errors of the fp32 path (prefill of fp32 inputs, backward pass) at slow and at moderate decay.
+
+Bounds: the 2-norm errors of a chunkwise evaluation in fp32 that keeps every decay inside a 16-token block as an exponential of
+its own and adds each product's 128 terms in a sum of its own, measured on these inputs against the fp64 oracle (mean over
+the seeds).  A sum taken at the size of something larger, or a decay taken as the difference of long running sums, shows here
+long before it reaches the 1e-5 of the parity tests.  The path is deterministic, and so are its errors."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth_inputs as si
+from helpers import to_device
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = [200, 70, 129, 257]
+BOUNDS = {      # (head dim, mean of the decay's argument): units of 1e-7
+    (128, -2.0): dict(dq=3.13, dk=3.32, dv=3.67, dlog_alpha=5.59, dbeta=4.43, o=3.11, hT=2.68),
+    (64, -2.0): dict(dq=2.79, dk=3.00, dv=3.40, dlog_alpha=5.55, dbeta=3.98, o=2.77, hT=2.52),
+    (128, 0.0): dict(dq=6.26, dk=6.33, dv=6.54, dlog_alpha=13.9, dbeta=6.87, o=6.37, hT=4.99),
+    (64, 0.0): dict(dq=5.84, dk=5.93, dv=6.07, dlog_alpha=13.5, dbeta=6.22, o=5.90, hT=3.90),
+}
+
+
+@pytest.mark.parametrize("mean", [-2.0, 0.0])
+@pytest.mark.parametrize("D,dtype", [(64, "f32"), (128, "f32"), (128, "bf16")])
+@pytest.mark.parametrize("H", [2, 24])                   # 8 and 96 pairs: few and many columns to a workgroup of the walks
+def test_errors_of_the_fp32_path_stay_as_small_as_they_can_be(H, D, dtype, mean):
+    import paper_2510_26692_amd as kda
+    errors = {}
+    for seed in range(4000, 4003):
+        x = si.make_varlen(LENGTHS, H, D, D, dtype, mean, seed, 0.05)
+        g = torch.Generator().manual_seed(seed)
+        do = torch.randn(x["v"].shape, generator=g)
+        dhT = 0.1 * torch.randn(x["h0"].shape, generator=g)
+        args = [si.to_np32(x[n]) for n in ("q", "k", "v", "log_alpha", "beta")]
+        kw = dict(h0=x["h0"].numpy().astype(np.float64), cu_seqlens=x["cu_seqlens"].numpy().astype(np.int64))
+        ref = dict(oracle.kda_backward(*args, do.numpy(), dhT=dhT.numpy(), **kw))
+        dd = to_device(x)
+        dev = [dd[n] for n in ("q", "k", "v", "log_alpha", "beta")]
+        got = kda.kda_chunk_bwd(*dev, do.cuda(), dhT=dhT.cuda(), h0=dd["h0"], cu_seqlens=dd["cu_seqlens"])
+        if dtype == "f32":
+            got["o"], got["hT"] = kda.kda_chunk_fwd(*dev, h0=dd["h0"], cu_seqlens=dd["cu_seqlens"])
+            ref["o"], ref["hT"] = oracle.kda_forward(*args, **kw)
+        torch.cuda.synchronize()
+        for n in BOUNDS[D, mean]:
+            if n in got:
+                e = got[n].cpu().numpy().astype(np.float64) - ref[n]
+                errors.setdefault(n, []).append(np.linalg.norm(e) / np.linalg.norm(ref[n]))
+    for n, e in errors.items():
+        assert np.mean(e) <= 1e-7 * BOUNDS[D, mean][n], "%s: error %.3e exceeds %.2fe-7" % (n, np.mean(e), BOUNDS[D, mean][n])
