@@ -13,7 +13,8 @@ struct Arrays {
 };
 
 // Rows [0, cu[0]) and [cu[num_seqs], tokens): one row of workgroups per array; every workgroup reads the two ends and, as a
-// rule, leaves.  (Both ends are clamped to the array, whatever cu holds.)
+// rule, leaves.  (Both ends are clamped to the array, whatever cu holds.)  256 workgroups of 256 threads: 3.2 GB in 0.50 ms
+// (64: 0.52, 512: 0.61, 1024: 0.66 ms; a plain fill 0.48 ms), 67 MB in 11.6 us (64: 14.0 us; a plain fill 10.4 us).
 __global__ void kda_clear_unowned_kernel(const int32_t *cu, int num_seqs, int64_t tokens, const Arrays a)
 {
     const int64_t low = cu[0], high = cu[num_seqs];
@@ -54,7 +55,7 @@ extern "C" kda_status kda_clear_unowned_rows(const int32_t *cu_seqlens, int32_t 
         a.row16[k] = row_bytes[k] % 16 ? 0 : (int64_t)(row_bytes[k] / 16);
         a.row4[k] = (int64_t)(row_bytes[k] / 4);
     }
-    hipLaunchKernelGGL(kda_clear_unowned_kernel, dim3(64, (unsigned)num_arrays), dim3(256), 0, static_cast<hipStream_t>(hip_stream),
+    hipLaunchKernelGGL(kda_clear_unowned_kernel, dim3(256, (unsigned)num_arrays), dim3(256), 0, static_cast<hipStream_t>(hip_stream),
                        cu_seqlens, num_seqs, tokens, a);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? KDA_OK : fail(KDA_ERR_LAUNCH, "kda_clear_unowned_rows: %s", hipGetErrorString(e));

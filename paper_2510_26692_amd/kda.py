@@ -229,13 +229,19 @@ def _stream_ptr(dev):
     return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
 
 
+def _mostly_unowned(cu_seqlens, tokens, max_seqlen):
+    """Whether max_seqlen tells that most rows of a packed call belong to no sequence.  Fresh outputs are then filled with zeros
+    whole, at the rate of a plain fill (200000 rows x 32 heads, 2048 of them owned: 0.48 against 0.50 ms)."""
+    return 0 < 2 * max_seqlen * (cu_seqlens.numel() - 1) < tokens
+
+
 def _clear_unowned(cu_seqlens, tensors):
     """Zeros in the rows [0, cu_seqlens[0]) and [cu_seqlens[-1], T) of freshly allocated [1,T,...] tensors (the calls write
     all other rows)."""
-    n = len(tensors)
-    tokens = tensors[0].shape[1]
-    if tokens == 0:
+    tensors = [t for t in tensors if t.numel()]
+    if not tensors:
         return
+    n, tokens = len(tensors), tensors[0].shape[1]
     ptrs = (ctypes.c_void_p * n)(*[t.data_ptr() for t in tensors])
     rows = (ctypes.c_size_t * n)(*[t.numel() // tokens * t.element_size() for t in tensors])
     st = load_library().kda_clear_unowned_rows(_ptr(cu_seqlens), cu_seqlens.numel() - 1, tokens, n, ptrs, rows,
@@ -351,10 +357,13 @@ def kda_chunk_fwd(q, k, v, log_alpha, beta, h0=None, cu_seqlens=None, scale=1.0,
         raise ValueError("h0 must be fp32 [N,H,dk,dv]")
     if cu_seqlens is not None and cu_seqlens.dtype != torch.int32:
         raise ValueError("cu_seqlens must be int32")
+    clear = False
     if o is None:
-        o = torch.empty(B, T, H, dv, dtype=odt, device=dev)
-        if cu_seqlens is not None and H > 0:
-            _clear_unowned(cu_seqlens, [o])
+        # (up to 8 MiB the fill costs less than the clearing call: 12 tokens x 2 heads, bf16, 24.5 against 26.3 us in all)
+        packed = cu_seqlens is not None
+        filled = packed and (T * H * dv * odt.itemsize <= 8 << 20 or _mostly_unowned(cu_seqlens, T, max_seqlen))
+        o = (torch.zeros if filled else torch.empty)(B, T, H, dv, dtype=odt, device=dev)
+        clear = packed and not filled
     if hT is None and want_hT:
         hT = torch.empty(N, H, dk, dv, dtype=torch.float32, device=dev)
     if workspace is None:
@@ -372,6 +381,8 @@ def kda_chunk_fwd(q, k, v, log_alpha, beta, h0=None, cu_seqlens=None, scale=1.0,
                                      *tail)
     if st != 0:
         raise KdaError(st, kda_last_error())
+    if clear:                               # (behind the call, whose launch need not wait for this one's)
+        _clear_unowned(cu_seqlens, [o])
     if check:
         kda_chunk_fwd_check(dims, workspace)
     return o, hT
@@ -434,12 +445,16 @@ def kda_chunk_bwd(q, k, v, log_alpha, beta, do, dhT=None, h0=None, cu_seqlens=No
     if cu_seqlens is not None and cu_seqlens.dtype != torch.int32:
         raise ValueError("cu_seqlens must be int32")
     f32 = dict(dtype=torch.float32, device=dev)
+    clear = None
     shapes = {"dq": (B, T, H, dk), "dk": (B, T, H, dk), "dv": (B, T, H, dv), "dlog_alpha": (B, T, H, dk),
               "dbeta": (B, T, H), "dh0": (N, H, dk, dv)}
     if out is None:
-        out = {n_: torch.empty(*sh, **f32) for n_, sh in shapes.items() if n_ != "dh0"}
-        if cu_seqlens is not None and H > 0:
-            _clear_unowned(cu_seqlens, list(out.values()))
+        # (five fills are five launches, which gradients of up to 64 MiB do not repay: 8192 rows x 16 heads x 64, 64 against 72 us in all)
+        packed = cu_seqlens is not None
+        filled = packed and T * H * dk * 4 > 64 << 20 and _mostly_unowned(cu_seqlens, T, max_seqlen)
+        out = {n_: (torch.zeros if filled else torch.empty)(*sh, **f32) for n_, sh in shapes.items() if n_ != "dh0"}
+        if packed and not filled:
+            clear = list(out.values())
         out["dh0"] = torch.empty(*shapes["dh0"], **f32) if want_dh0 else None
     else:                                   # the dict of an earlier call with the same shapes, written in place
         for n_, sh in shapes.items():
@@ -459,6 +474,8 @@ def kda_chunk_bwd(q, k, v, log_alpha, beta, do, dhT=None, h0=None, cu_seqlens=No
                            _ptr(workspace), ctypes.c_size_t(ws_bytes), _stream_ptr(dev))
     if st != 0:
         raise KdaError(st, kda_last_error())
+    if clear:                               # (behind the call, as in kda_chunk_fwd)
+        _clear_unowned(cu_seqlens, clear)
     return out
 
 

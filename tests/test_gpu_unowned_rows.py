@@ -10,9 +10,12 @@ from helpers import to_device
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("lens,stray", [([70, 5], 0), ([70, 5], 1), ([0, 64], 300), ([0], 3)])
+@pytest.mark.parametrize("bound", [False, True], ids=["unbounded", "bounded"])
+@pytest.mark.parametrize("lens,stray", [([70, 5], 0), ([70, 5], 1), ([0, 64], 300), ([0], 3), ([9000, 900], 700), ([200], 32900)])
 @pytest.mark.parametrize("H,D,dtype", [(3, 64, "f32"), (4, 128, "bf16")])
-def test_unowned_rows_are_zero_and_owned_ones_are_not_touched(lens, stray, H, D, dtype):
+def test_unowned_rows_are_zero_and_owned_ones_are_not_touched(lens, stray, H, D, dtype, bound):
+    # (outputs of more than 8 and gradients of more than 64 MiB at four heads, mostly owned and mostly not, with the longest length given or not)
+    more = dict(max_seqlen=max(lens)) if bound else {}
     import paper_2510_26692_amd as kda
     x = si.make_varlen(lens + [stray], H, D, D, dtype, -2.0, 77, 0.0)
     T, owned = sum(lens) + stray, sum(lens)
@@ -24,15 +27,15 @@ def test_unowned_rows_are_zero_and_owned_ones_are_not_touched(lens, stray, H, D,
     def both():
         dirt = [torch.full((1 << 22,), float("nan"), device="cuda") for _ in range(8)]
         del dirt                                        # (freed blocks that the outputs are likely to be cut from)
-        o, _ = kda.kda_chunk_fwd(*args, cu_seqlens=dd["cu_seqlens"])
-        g = kda.kda_chunk_bwd(*args, do, cu_seqlens=dd["cu_seqlens"], want_dh0=False)
+        o, _ = kda.kda_chunk_fwd(*args, cu_seqlens=dd["cu_seqlens"], **more)
+        g = kda.kda_chunk_bwd(*args, do, cu_seqlens=dd["cu_seqlens"], want_dh0=False, **more)
         torch.cuda.synchronize()
         return dict(g, o=o)
 
     got = both()
     into = {n: torch.full_like(t, 7.0) for n, t in got.items() if t is not None}
-    kda.kda_chunk_fwd(*args, cu_seqlens=dd["cu_seqlens"], o=into["o"])
-    kda.kda_chunk_bwd(*args, do, cu_seqlens=dd["cu_seqlens"], want_dh0=False,
+    kda.kda_chunk_fwd(*args, cu_seqlens=dd["cu_seqlens"], o=into["o"], **more)
+    kda.kda_chunk_bwd(*args, do, cu_seqlens=dd["cu_seqlens"], want_dh0=False, **more,
                       out=dict({n: into[n] for n in into if n != "o"}, dh0=None))
     torch.cuda.synchronize()
     for n, t in into.items():
@@ -96,3 +99,17 @@ def test_rows_ahead_of_the_first_sequence_take_no_part(lead, H, D, dtype):
         for t, rest in ((got[n], 0.0), (into[n], 7.0)):
             assert torch.equal(t[:, owned], alone[n]), n
             assert bool((t[:, :lead] == rest).all()) and bool((t[:, end:] == rest).all()), n
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_a_refused_packed_call_says_why_whatever_its_outputs(dtype):
+    """Head dims outside the built set are refused as that (a row of such an output need not be a multiple of 4 bytes)."""
+    import paper_2510_26692_amd as kda
+    q, b = torch.zeros(1, 1 << 23, 1, 1, dtype=dtype, device="cuda"), torch.zeros(1, 1 << 23, 1, dtype=dtype, device="cuda")
+    cu = torch.tensor([0, 5], dtype=torch.int32, device="cuda")
+    args, unsupported = (q, q, q, q, b), 2                 # KDA_ERR_UNSUPPORTED
+    for call in (lambda: kda.kda_chunk_fwd(*args, cu_seqlens=cu, out_dtype=dtype),
+                 lambda: kda.kda_chunk_bwd(*args, q, cu_seqlens=cu)):
+        with pytest.raises(kda.KdaError) as e:
+            call()
+        assert e.value.status == unsupported
