@@ -66,9 +66,16 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
         f32x4 kk[4], qq[4];
         Decay d;
         if (hf) lds_barrier();                               // the previous channels' tiles are read
-        fg.turn(d.x, reinterpret_cast<char *>(sKn + 16 * w), 4 * kLdT, c.nv, lane);
-        fk.turn(kk, reinterpret_cast<char *>(sKp + 16 * w), 4 * kLdT, c.nv, lane);
-        fq.turn(qq, reinterpret_cast<char *>(sQp + 16 * w), 4 * kLdT, c.nv, lane);
+        char *pg = reinterpret_cast<char *>(sKn + 16 * w), *pk = reinterpret_cast<char *>(sKp + 16 * w),
+             *pq = reinterpret_cast<char *>(sQp + 16 * w);
+        fg.put(pg, 4 * kLdT, c.nv, lane);
+        fk.put(pk, 4 * kLdT, c.nv, lane);
+        fq.put(pq, 4 * kLdT, c.nv, lane);
+        wave_lds_fence();
+        fg.get(d.x, pg, 4 * kLdT, lane);
+        fk.get(kk, pk, 4 * kLdT, lane);
+        fq.get(qq, pq, 4 * kLdT, lane);
+        wave_lds_fence();
         sum_decay(d, lane);
         strong |= d.strong();
 #pragma unroll

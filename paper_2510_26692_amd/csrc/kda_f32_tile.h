@@ -72,6 +72,15 @@ __device__ __forceinline__ int turned_lane(int lane) { return ((lane >> 2) & 3) 
 __device__ __forceinline__ f32x4 ld4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
 __device__ __forceinline__ void st4(float *p, const f32x4 &v) { *reinterpret_cast<f32x4 *>(p) = v; }
 
+// Between the LDS accesses of one wave whose lanes hand each other values: the hardware keeps a wave's LDS accesses in order,
+// and this keeps the compiler from moving them across (it sees each lane's addresses, not who reads what).  No instruction.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // Workgroup barrier for LDS traffic: global loads and stores stay in flight across it.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
@@ -193,7 +202,7 @@ struct Exponents {
 };
 
 // A wave brings such a tile of a [tokens, H, D] tensor in with 16-byte loads (fetch: a lane holds a piece of a row) and
-// turns it through LDS (turn: `at`, rows `ld` bytes apart, belongs to the wave alone for the moment).
+// turns it through LDS (put, a fence, get: `at`, rows `ld` bytes apart, belongs to the wave alone for the moment).
 template <typename T> struct TileFetch {
     static constexpr int kPerRow = (int)sizeof(T);           // 16-byte pieces of a row of 16 channels
     uint4 raw[kPerRow];
@@ -207,18 +216,28 @@ template <typename T> struct TileFetch {
             raw[u] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(base) + off);
         }
     }
-    __device__ __forceinline__ void turn(f32x4 (&x)[4], char *at, int ld, int nv, int lane) const
+    __device__ __forceinline__ void put(char *at, int ld, int nv, int lane) const
     {
 #pragma unroll
         for (int u = 0; u < kPerRow; ++u) {
             const int r = (lane + 64 * u) / kPerRow, piece = lane % kPerRow;
             *reinterpret_cast<uint4 *>(at + r * ld + piece * 16) = r < nv ? raw[u] : make_uint4(0u, 0u, 0u, 0u);
         }
+    }
+    static __device__ __forceinline__ void get(f32x4 (&x)[4], const char *at, int ld, int lane)
+    {
         const int m = lane & 15, g = lane >> 4;
 #pragma unroll
         for (int R = 0; R < 4; ++R)
 #pragma unroll
             for (int j = 0; j < 4; ++j) x[R][j] = load_as_float(reinterpret_cast<const T *>(at + (16 * R + 4 * g + j) * ld) + m);
+    }
+    __device__ __forceinline__ void turn(f32x4 (&x)[4], char *at, int ld, int nv, int lane) const
+    {
+        put(at, ld, nv, lane);
+        wave_lds_fence();
+        get(x, at, ld, lane);
+        wave_lds_fence();                                    // (the next tile comes through the same place)
     }
 };
 
