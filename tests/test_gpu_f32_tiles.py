@@ -1,6 +1,6 @@
 """The fp32 path (prefill of fp32 inputs, backward pass) where its tiling can go wrong: token tiles of 16 and chunks
-of 64 with one token less and one more, each number of column tiles a workgroup of the walks may own (chosen by the
-number of (sequence, head) pairs), channels whose decay inside 16 tokens is beyond what the factors of the products
+of 64 with one token less and one more, each form of the walks (a helped workgroup of one column tile, or 1, 2 or 4 tiles to
+a workgroup, chosen by the number of (sequence, head) pairs and by the device's compute units), channels whose decay inside 16 tokens is beyond what the factors of the products
 hold next to channels where it is not, and tokens with beta = 0.
 
 Bounds: a factor 2^x of a decay held in fp32 carries a relative error of |x| 2^-24 ln 2 (x in log2 units); with the
@@ -18,6 +18,22 @@ from helpers import rel_err, to_device
 pytestmark = pytest.mark.gpu
 
 LENGTHS = [1, 15, 16, 17, 63, 64, 65, 127, 130]
+REPEATS = [1, 3, 5, 9, 15, 30]                            # x 9 sequences x 1 head: 9, 27, 45, 81, 135 and 270 pairs
+
+
+def _walk_form(D, walks, pairs, compute_units):
+    """The rule of kda_f32_walk.hip: workgroups of a compute unit each are helped, then the fewest tiles that leave two."""
+    groups = lambda tiles: walks * -(-pairs // 8) * 8 * (D // (16 * tiles))
+    if groups(1) <= compute_units:
+        return "helped"
+    return next((n for n in (1, 2) if groups(n) <= 2 * compute_units), 4)
+
+
+def test_the_pair_counts_below_reach_every_form_of_the_walks():
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    for D in (64, 128):
+        for walks in (1, 2):                              # the prefill's; the backward pass's two side by side
+            assert {_walk_form(D, walks, 9 * r, units) for r in REPEATS} == {"helped", 1, 2, 4}, (D, walks, units)
 
 
 def _inputs(lens, H, D, dtype, strong, seed):
@@ -31,27 +47,28 @@ def _inputs(lens, H, D, dtype, strong, seed):
 
 
 @pytest.mark.parametrize("strong", [False, True], ids=["mild", "strong"])
-@pytest.mark.parametrize("D,dtype", [(64, "f32"), (128, "f32"), (128, "bf16")])
-@pytest.mark.parametrize("repeat", [1, 5, 9])            # x 9 sequences x 1 head: 9, 45 and 81 pairs
-def test_tiles_of_the_fp32_path(repeat, D, dtype, strong):
+@pytest.mark.parametrize("D,dtype,do_dtype", [(64, "f32", "f32"), (128, "f32", "f32"), (128, "bf16", "f32"), (128, "bf16", "bf16"),
+                                              (64, "bf16", "f32"), (64, "bf16", "bf16")])
+@pytest.mark.parametrize("repeat", REPEATS)
+def test_tiles_of_the_fp32_path(repeat, D, dtype, do_dtype, strong):
     import paper_2510_26692_amd as kda
     x = _inputs(LENGTHS * repeat, 1, D, dtype, strong, 1300 + repeat)
     tol = 4e-5 if strong else 1e-5
     g = torch.Generator().manual_seed(5)
-    do = torch.randn(x["v"].shape, generator=g)
+    do = torch.randn(x["v"].shape, generator=g).to(torch.bfloat16 if do_dtype == "bf16" else torch.float32)
     dhT = 0.1 * torch.randn(x["h0"].shape, generator=g)
     dd = to_device(x)
     args = [si.to_np32(x[n]) for n in ("q", "k", "v", "log_alpha", "beta")]
     kw = dict(h0=x["h0"].numpy().astype(np.float64), cu_seqlens=x["cu_seqlens"].numpy().astype(np.int64))
     dev = [dd[n] for n in ("q", "k", "v", "log_alpha", "beta")]
-    if dtype == "f32":
+    if do_dtype == "f32" and (dtype == "f32" or D == 64):      # (bf16 inputs with d 128 take other kernels)
         o, hT = kda.kda_chunk_fwd(*dev, h0=dd["h0"], cu_seqlens=dd["cu_seqlens"], max_seqlen=max(LENGTHS))
         torch.cuda.synchronize()
         o_ref, h_ref = oracle.kda_forward(*args, **kw)
         assert rel_err(o.cpu().numpy(), o_ref) <= tol and rel_err(hT.cpu().numpy(), h_ref) <= tol
     got = kda.kda_chunk_bwd(*dev, do.cuda(), dhT=dhT.cuda(), h0=dd["h0"], cu_seqlens=dd["cu_seqlens"], max_seqlen=max(LENGTHS))
     torch.cuda.synchronize()
-    ref = oracle.kda_backward(*args, do.numpy(), dhT=dhT.numpy(), **kw)
+    ref = oracle.kda_backward(*args, do.float().numpy(), dhT=dhT.numpy(), **kw)
     for name in ref:
         e = rel_err(got[name].cpu().numpy(), ref[name])
         assert e <= tol, "%s: error %.3e exceeds %.1e" % (name, e, tol)

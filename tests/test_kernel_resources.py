@@ -45,3 +45,19 @@ def test_prefill_kernels_use_no_scratch_outside_the_gated_variants(resources):
 def test_decode_kernels_use_no_scratch(resources):
     for name, r in _kernels(resources, "kda_step_kernel").items():
         assert r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0, (name, r)
+
+
+def test_fp32_kernels_use_no_scratch_beyond_a_few_dwords_of_the_gradients_kernel(resources):
+    # The walks are chains of steps, and the per-chunk kernel is short: neither has anything to hide a reload behind.  The
+    # gradients kernel keeps two workgroups a compute unit (256 registers); at d 128 a few values wait in scratch between
+    # its two halves.
+    walks = _kernels(resources, "kda_f32_forward_walk") | _kernels(resources, "kda_f32_forward_roles") | \
+        _kernels(resources, "kda_f32_both_walks")
+    prep, gradients = _kernels(resources, "kda_f32_prep_kernel"), _kernels(resources, "kda_bwd_gradients_kernel")
+    assert len(walks) == 12 + 4 + 24 and len(prep) == 8 and len(gradients) == 6
+    for name, r in (walks | prep).items():
+        assert r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0, (name, r)
+    for name, r in prep.items():
+        assert r["Occupancy [waves/SIMD]"] >= 3, (name, r)
+    for name, r in gradients.items():
+        assert r["Occupancy [waves/SIMD]"] >= 2 and r["VGPRs Spill"] <= (8 if "Li128E" in name else 0), (name, r)
