@@ -625,11 +625,8 @@ __device__ __forceinline__ bool place(const Problem &p, int64_t bid, int64_t &n,
 }
 static int64_t walk_workgroups(const Problem &p, int slices) { return ((int64_t)p.num_seqs * p.H + 7) / 8 * 8 * slices; }
 
-// Workgroups a compute unit should hold: two, except the widest, whose registers (and LDS) are a whole one's.
-template <int D, int NC> constexpr int per_cu() { return D * NC == 512 ? 1 : 2; }
-
 template <typename Tin, int D, int NC>
-__global__ __launch_bounds__(kWalkThreads, (per_cu<D, NC>()))
+__global__ __launch_bounds__(kWalkThreads, 2)
 void kda_f32_forward_walk_kernel(const Tin *__restrict__ v, const float *__restrict__ h0,
                                  const float *__restrict__ slots, float *__restrict__ o, float *__restrict__ hT, const Problem p)
 {
@@ -660,7 +657,7 @@ void kda_f32_forward_roles_kernel(const Tin *__restrict__ v, const float *__rest
 // The backward walk, the longer of the two, goes first.  kHelped: four waves more, which help the backward walk (and
 // leave at once in the forward one, whose chain holds every product it has).
 template <typename Tin, typename Tdo, int D, int NC, bool kHelped>
-__global__ __launch_bounds__(kHelped ? 2 * kWalkThreads : kWalkThreads, (per_cu<D, NC>()))
+__global__ __launch_bounds__(kHelped ? 2 * kWalkThreads : kWalkThreads, 2)
 void kda_f32_both_walks_kernel(const Tin *__restrict__ v, const float *__restrict__ h0,
                                const Tdo *__restrict__ d_o, const float *__restrict__ d_hT, const float *__restrict__ slots,
                                float *__restrict__ S0, float *__restrict__ Rw, float *__restrict__ dS1, float *__restrict__ Zw,
@@ -681,12 +678,19 @@ void kda_f32_both_walks_kernel(const Tin *__restrict__ v, const float *__restric
 }
 
 // Column tiles per workgroup: the fewest that still give every compute unit at most two workgroups (more than two
-// would queue; fewer columns than needed load the same operands more often).
+// would queue; fewer columns than needed load the same operands more often), and at most 2 tiles at d 128, 4 at d 64: two
+// workgroups of the widest fit a compute unit with their registers.  (Four tiles at d 128 take a whole one, and were never faster:
+// 2048 tokens, fp32 inputs, 2 against 4 tiles, backward pass 96 pairs 975 / 1077 us, 128 pairs 1252 / 1247, 136 pairs
+// 1389 / 1515, 256 pairs 2454 / 2458; prefill 136 pairs 638 / 800, 256 pairs 947 / 972.  The other lines, 1 against 2 tiles:
+// backward pass d 128, 32 pairs 373 / 396, 48 pairs 563 / 568, 64 pairs 717 / 659; d 64, 64 pairs 312 / 308, 96 pairs 452 / 452,
+// 128 pairs 586 / 538; prefill d 128, 32 pairs 159 / 217, 64 pairs 291 / 273, 128 pairs 550 / 489; d 64, 128 pairs 266 / 249, 256
+// pairs 506 / 460.  2 against 4 tiles, d 64: backward pass 128 pairs 538 / 570, 256 pairs 1034 / 1017; prefill 256 pairs 460 / 470.)
 static int column_tiles(const Problem &p, int D, int walks, int compute_units)
 {
-    for (int nc = 1; nc < 4; nc *= 2)
+    const int widest = D == 128 ? 2 : 4;
+    for (int nc = 1; nc < widest; nc *= 2)
         if (walks * walk_workgroups(p, D / (16 * nc)) <= 2 * (int64_t)compute_units) return nc;
-    return 4;
+    return widest;
 }
 
 template <typename F, typename... Args>
@@ -716,7 +720,9 @@ kda_status launch_forward_walk(const Problem &p, const Tin *v, const float *h0, 
     if (walk_workgroups(p, D / 16) <= compute_units)
         return launch_walk(kda_f32_forward_roles_kernel<Tin, D>, "kda_f32_forward_roles", walk_workgroups(p, D / 16), 2 * kWalkThreads,
                            walk_lds<D, 1>(false), stream, v, h0, slots, o, hT, p);
-    return nc == 1 ? KDA_GO(1) : nc == 2 ? KDA_GO(2) : KDA_GO(4);
+    if constexpr (D == 64)
+        if (nc == 4) return KDA_GO(4);
+    return nc == 1 ? KDA_GO(1) : KDA_GO(2);
 #undef KDA_GO
 }
 
@@ -733,8 +739,9 @@ kda_status launch_both_walks(const Problem &p, const Tin *v, const float *h0, co
     // pass, d 128, 4096 tokens: 4 pairs 271 -> 250 us, 16 pairs 424 -> 399 us; d 64, 32 pairs: 336 -> 326 us).
     if (2 * walk_workgroups(p, D / 16) <= compute_units)
         return KDA_GO(1, true, 2 * kWalkThreads, (size_t)(2 * (D / 16) + 16) * kFrag * 4);
-    return nc == 1 ? KDA_GO(1, false, kWalkThreads, (walk_lds<D, 1>(true)))
-         : nc == 2 ? KDA_GO(2, false, kWalkThreads, (walk_lds<D, 2>(true))) : KDA_GO(4, false, kWalkThreads, (walk_lds<D, 4>(true)));
+    if constexpr (D == 64)
+        if (nc == 4) return KDA_GO(4, false, kWalkThreads, (walk_lds<D, 4>(true)));
+    return nc == 1 ? KDA_GO(1, false, kWalkThreads, (walk_lds<D, 1>(true))) : KDA_GO(2, false, kWalkThreads, (walk_lds<D, 2>(true)));
 #undef KDA_GO
 }
 
