@@ -5,9 +5,9 @@ inside 16 tokens is beyond what the factors of the products hold next to channel
 beta = 0.
 
 Bounds: a factor 2^x of a decay held in fp32 carries a relative error of |x| 2^-24 ln 2 (x in log2 units); with the
-mild decay |x| stays below 60 in a chunk and the bound is the path's 1e-5.  The strong channels reach |x| = 320 and
-more, where the products underflow, but at |x| = 100 they still count: 100 * 2^-24 * ln 2 = 4e-6 per factor, a few of
-them to a term: 4e-5, as for the other strong-decay case of the backward pass."""
+mild decay |x| stays below 60 in a chunk and the bound is the path's 1e-5.  The strong channels, and those with single strong
+tokens, reach |x| = 320 and more, where the products underflow, but at |x| = 100 they still count:
+100 * 2^-24 * ln 2 = 4e-6 per factor, a few of them to a term: 4e-5, as for the other strong-decay case of the backward pass."""
 import numpy as np
 import pytest
 import torch
@@ -40,24 +40,34 @@ def test_the_pair_counts_below_reach_every_form_of_the_walks():
             assert forms == ({"helped", 1, 2} if D == 128 else {"helped", 1, 2, 4}), (D, walks, units, forms)
 
 
-def _inputs(lens, H, D, dtype, strong, seed):
+def _inputs(lens, H, D, dtype, decay, seed):
     x = si.make_varlen(lens, H, D, D, dtype, -2.0, seed, 0.05)
-    if strong:                                  # every fifth channel decays by 2^-8 per token and more
-        la = x["log_alpha"].float()
+    la = x["log_alpha"].float()
+    if decay == "strong":                       # every fifth channel decays by 2^-8 per token and more
         la[..., ::5] = la[..., ::5] * 2.0 - 6.0
-        x["log_alpha"] = la.to(x["log_alpha"].dtype)
+    elif decay == "spikes":                     # single tokens around 2^-60, where a channel turns strong, and beyond
+        size = torch.tensor([-30.0, -41.25, -41.5, -41.75, -60.0, -100.0])
+        # (the first and last tokens of the halves of a 16-token block; both halves that meet at a block's end and around its
+        # middle, with tokens between them that see each other almost undecayed)
+        for at, tokens in enumerate([(0,), (7,), (8, 14), (1, 14), (6, 9)]):
+            for token in tokens:
+                part = la[:, token::16, :, at::5]
+                part[:] = size[torch.arange(part.shape[-1]) % 6]
+    elif decay == "steep":                      # every token alike, around where a half of a block turns strong
+        la[..., ::2] = la[..., ::2] * 0.5 - torch.linspace(4.0, 5.5, la[..., ::2].shape[-1])
+    x["log_alpha"] = la.to(x["log_alpha"].dtype)
     x["beta"][:, ::7] = 0.0
     return x
 
 
-@pytest.mark.parametrize("strong", [False, True], ids=["mild", "strong"])
+@pytest.mark.parametrize("decay", ["mild", "strong", "spikes", "steep"])
 @pytest.mark.parametrize("D,dtype,do_dtype", [(64, "f32", "f32"), (128, "f32", "f32"), (128, "bf16", "f32"), (128, "bf16", "bf16"),
                                               (64, "bf16", "f32"), (64, "bf16", "bf16")])
 @pytest.mark.parametrize("repeat", REPEATS)
-def test_tiles_of_the_fp32_path(repeat, D, dtype, do_dtype, strong):
+def test_tiles_of_the_fp32_path(repeat, D, dtype, do_dtype, decay):
     import paper_2510_26692_amd as kda
-    x = _inputs(LENGTHS * repeat, 1, D, dtype, strong, 1300 + repeat)
-    tol = 4e-5 if strong else 1e-5
+    x = _inputs(LENGTHS * repeat, 1, D, dtype, decay, 1300 + repeat)
+    tol = 1e-5 if decay == "mild" else 4e-5
     g = torch.Generator().manual_seed(5)
     do = torch.randn(x["v"].shape, generator=g).to(torch.bfloat16 if do_dtype == "bf16" else torch.float32)
     dhT = 0.1 * torch.randn(x["h0"].shape, generator=g)
