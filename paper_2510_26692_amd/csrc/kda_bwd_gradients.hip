@@ -8,7 +8,7 @@
 //   dq_r = Gamma_r dQg_r + a2_r             a2_r = sum_{i<=r} dP[r,i] k_i e^(G_r - G_i)
 //   up_r = Gamma_r dKg_r + a1_r             a1_r = sum_{i<r}  dA[r,i] k_i e^(G_r - G_i)
 //   dn_t = e^(G_C - G_t) dKt_t + b1_t       b1_t = sum_{r>t} dA[r,t] k_r e^(G_r - G_t) + sum_{r>=t} dP[r,t] q_r e^(G_r - G_t)
-//   dk = up + dn,   dG = q dq + k (up - dn),   dG_C = e^(G_C) rowsum(dS1 . S0) + sum_t k_t e^(G_C - G_t) dKt_t
+//   dk = up + dn,   dG = q dq + k (up - dn)  (r = t taken out of a2 and b1, where it cancels),   dG_C = e^(G_C) rowsum(dS1 . S0) + sum_t k_t e^(G_C - G_t) dKt_t
 //   dlog alpha_t = sum_{r>=t} dG_r + dG_C
 //
 // (dA needs no product with the inverse: with T = (I + Diag(beta) A)^-1 the chain rule through it,
@@ -40,7 +40,7 @@ constexpr int kBoth = 2 * kTri * kFrag;                      // dA or dP: its bl
 template <typename T> constexpr int turn_row() { return 16 * (int)sizeof(T) + 16; }
 template <typename T> constexpr size_t grad_lds()
 {
-    const size_t first = (size_t)2 * 3 * kPart * 4, second = (size_t)2 * kBoth * 4 + 4 * kC * turn_row<T>();
+    const size_t first = (size_t)2 * 3 * kPart * 4, second = (size_t)(2 * kBoth + kC) * 4 + 4 * kC * turn_row<T>();
     return first > second ? first : second;
 }
 static_assert(2 * grad_lds<float>() <= 160 * 1024, "two workgroups share a compute unit");
@@ -174,23 +174,26 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
     TileFetch<Tin> fg, fk, fq;
     auto fetch_inputs = [&](int tt) __attribute__((always_inline)) {
         const int64_t at0 = base + 16 * (4 * tt + w);
-        fg.fetch(log_alpha + at0, stride, c.nv, lane);
-        fk.fetch(k + at0, stride, c.nv, lane);
-        fq.fetch(q + at0, stride, c.nv, lane);
+        int l = lane;
+        asm volatile("" : "+v"(l));                                          // (addresses formed here, not kept from the first tile)
+        fg.fetch(log_alpha + at0, stride, c.nv, l);
+        fk.fetch(k + at0, stride, c.nv, l);
+        fq.fetch(q + at0, stride, c.nv, l);
     };
     fetch_inputs(0);
     lds_barrier();
     const int turned = 4 * turned_lane(lane);
-    float *sA = smem, *sP = smem + kBoth;
+    float *sA = smem, *sP = smem + kBoth, *sD = smem + 2 * kBoth;            // sD: the diagonal of dP
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
         const int u = w + 4 * i, b = u < 10 ? u : u - 10;
         const int R = b >= 6 ? 3 : b >= 3 ? 2 : b >= 1 ? 1 : 0, I = b - tri(R, 0);
         f32x4 x = u < 10 ? -tile[i] : tile[i];
         if (R == I) {
+            const float d01 = m & 1 ? x[1] : x[0], d23 = m & 1 ? x[3] : x[2];
+            if (u >= 10 && m >> 2 == g) sD[16 * R + m] = m & 2 ? d23 : d01;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (m > 4 * g + j || (u < 10 && m == 4 * g + j)) x[j] = 0.f;
+            for (int j = 0; j < 4; ++j) x[j] = m >= 4 * g + j ? 0.f : x[j];
         }
         float *dst = (u < 10 ? sA : sP) + b * kFrag;
         st4(dst + turned, quad_transpose(x, lane));
@@ -198,7 +201,7 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
     }
     lds_barrier();
     const float *rowA = sA + 4 * lane, *rowP = sP + 4 * lane, *colA = rowA + kTri * kFrag, *colP = rowP + kTri * kFrag;
-    char *turn = reinterpret_cast<char *>(smem + 2 * kBoth) + w * (kC * turn_row<Tin>());
+    char *turn = reinterpret_cast<char *>(sD + kC) + w * (kC * turn_row<Tin>());
 
     // ---- decay terms and results, a 16-channel tile at a time ----
     auto finish = [&](int tt, f32x4 (&aq)[4], f32x4 (&ak)[4], f32x4 (&at)[4], float gc) __attribute__((always_inline)) {
@@ -225,6 +228,13 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
         run = fmaf(gc, fast_exp2(d.whole()), run);
         run += __shfl_xor(run, 16);
         run += __shfl_xor(run, 32);                                          // dG_C
+        float across[6];                                                     // decay between the blocks of a pair
+#pragma unroll
+        for (int R = 1; R < 4; ++R)
+#pragma unroll
+            for (int I = 0; I < R; ++I) across[R * (R - 1) / 2 + I] = fast_exp2(d.across(R, I));
+#pragma unroll
+        for (int i = 0; i < 6; ++i) asm volatile("" : "+v"(across[i]));          // (kept, not formed again from the sums at each use)
         const bool any_strong = __any(d.strong());
 #pragma unroll
         for (int R = 3; R >= 0; --R) {
@@ -234,7 +244,7 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
             f32x4 a1 = none, a2 = none, b1 = none, a1d = none, a2d = none, b1d = none;
 #pragma unroll
             for (int I = 0; I < R; ++I) {
-                const f32x4 b = kk[I] * nf[I] * fast_exp2(d.across(R, I));
+                const f32x4 b = kk[I] * nf[I] * across[R * (R - 1) / 2 + I];
                 a1 = mfma16(ld4(rowA + tri(R, I) * kFrag), b, a1);
                 a2 = mfma16(ld4(rowP + tri(R, I) * kFrag), b, a2);
             }
@@ -247,7 +257,7 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
             }
 #pragma unroll
             for (int B = R + 1; B < 4; ++B) {
-                const f32x4 x = pf[B] * fast_exp2(d.across(B, R));
+                const f32x4 x = pf[B] * across[B * (B - 1) / 2 + R];
                 b1 = mfma16(ld4(colA + tri(B, R) * kFrag), x * kk[B], b1);
                 b1 = mfma16(ld4(colP + tri(B, R) * kFrag), x * qq[B], b1);
             }
@@ -272,7 +282,7 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
                         const float x = mine ? fast_exp2(i <= t ? fminf(eL[j] - Gi, 0.f) : fminf(Gi - eL[j], 0.f)) : 0.f;
                         const float *row = sA + tri(R, R) * kFrag + 4 * (t + 16 * gi) + ii;      // dA[t][i], dA[i][t] in row form
                         const float *cl = sA + tri(R, R) * kFrag + 4 * (i + 16 * g) + j;
-                        if (i <= t) {                                        // (dA's diagonal is zero)
+                        if (i <= t) {                                        // (the diagonals are zero)
                             a1[j] = fmaf(row[0] * ki, x, a1[j]);
                             a2[j] = fmaf(row[kBoth] * ki, x, a2[j]);
                         }
@@ -280,8 +290,15 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
                     }
                 }
             }
-            const f32x4 gq = aq[R] + a2, up = ak[R] + a1, dn = at[R] + b1, gk = up + dn;
-            f32x4 s = qq[R] * gq + kk[R] * (up - dn);
+            // (dP's diagonal stays out of s: q_r (dP_rr k_r) - k_r (dP_rr q_r) is nothing, and its rounding is most of dlog alpha's
+            // error where the decay is fast: 2.7e-6 -> 0.7e-6 at a mean log alpha of -2.1, 5.3e-7 -> 4.8e-7 at -0.18)
+            f32x4 gq = aq[R] + a2;
+            const f32x4 up = ak[R] + a1, dn = at[R] + b1;
+            f32x4 s = qq[R] * gq + kk[R] * (up - dn), gk = up + dn;
+            pin_memory_order();
+            const f32x4 diag = ld4(sD + 16 * R + 4 * g);
+            gq += diag * kk[R];
+            gk += diag * qq[R];
             // dlog alpha: sums over the tokens behind, inside the lane, across the four lane groups, over the blocks
             s[2] += s[3]; s[1] += s[2]; s[0] += s[1];
             float tot = s[0], u = __shfl_down(tot, 16);
