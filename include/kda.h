@@ -100,9 +100,11 @@ typedef struct {
  * unsupported or malformed `dims`, and for problems that need no workspace.
  * KDA_F32 inputs: the minimum is 0 (one sequential kernel per sequence, head and
  * 32 state columns); with kda_chunk_fwd_workspace_size(dims) bytes (per chunk and
- * head two 64 x 66 and three 64 x dk fp32 tiles) a parallel per-chunk kernel and a
- * matrix-core walk run instead, about sixteen times faster at 4 x 4096 tokens x 16
- * heads; anything in between runs the sequential kernel.
+ * head three 64 x dk fp32 operand tiles, the lower triangles of two 64 x 64
+ * matrices, dk + 64 floats, and 13 KiB that the size has always held and nothing
+ * uses) a parallel per-chunk kernel and a matrix-core walk run instead, some thirty
+ * times faster at 4 x 4096 tokens x 16 heads; anything in between runs the
+ * sequential kernel.
  */
 size_t kda_chunk_fwd_workspace_size(const kda_dims *dims);
 size_t kda_chunk_fwd_min_workspace_size(const kda_dims *dims);
@@ -173,8 +175,9 @@ kda_status kda_chunk_fwd_static_scratch(const kda_dims *dims,
  * with the general DPLR one for exactly that purpose) but derives no backward algorithm; what
  * is computed here is the chain rule applied to Eq. (1), organised chunk by chunk through the
  * quantities of Section 3.1 (A_kk, A_qk, the UT transform, the chunk state update), in fp32
- * throughout, every decay kept as a pairwise difference of cumulative log decays so that it
- * cannot overflow.
+ * throughout.  A decay between two tokens of a chunk is the product of two or three factors,
+ * each within 2^(+-60), so that nothing overflows; a channel that decays by more than 2^-60
+ * within 8 tokens is added pair by pair where it still counts.
  *
  *   q, k, v, log_alpha, beta, h0, cu_seqlens   as for kda_chunk_fwd (in_dtype KDA_F32 or
  *                              KDA_BF16, dk == dv in {64, 128})
@@ -191,7 +194,9 @@ kda_status kda_chunk_fwd_static_scratch(const kda_dims *dims,
  *                              gradient of the state at its end (2 * dk * dv floats per chunk
  *                              and head), two [tokens, H, dv] arrays, the decay-scaled
  *                              operands and two triangular C x C matrices per chunk and head,
- *                              and room that is spare; it is not bounded by time segments
+ *                              and a fifth that is spare (the size is part of the interface:
+ *                              callers keep it with their plans and buffers); it is not
+ *                              bounded by time segments
  * No gradient may alias an input or another gradient.  Sequences of more than 65535 * 64
  * tokens are KDA_ERR_UNSUPPORTED.  Everything runs on `hip_stream`.
  */

@@ -20,8 +20,9 @@ struct Plan {
     size_t S0, dS1, R, Z, ops, total;
 };
 
-// backward: all areas; forward: the per-chunk operands only.  (The sizes are the published ones; the backward pass leaves
-// a [tokens, H, D] array and 2 C^2 + D floats per chunk and head of its own unused.)
+// backward: all areas; forward: the per-chunk operands only.  (The sizes are the published ones, which callers keep with their
+// plans and buffers; the backward pass leaves a [tokens, H, D] array and 2 C^2 + D floats per chunk and head of its own
+// unused, the slots 13 KiB each.)
 Plan make_plan(const kda_dims *d, bool packed, bool backward)
 {
     Plan p{};
