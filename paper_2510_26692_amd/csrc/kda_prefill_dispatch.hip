@@ -284,7 +284,7 @@ kda_status chunk_mfma_dispatch(const kda_dims *d, const kda_prologue *pro, const
         a.producers = g_producers; a.raw = raw;
         // packed sequences in more than one batch of pairs: longest first
         const bool ordered = cu != nullptr && parts == 1 && d->num_seqs > 1 && d->num_seqs <= kMaxOrderedSeqs &&
-                             streams > fused_batch_pairs(streams, cus);
+                             streams > fused_batch_pairs(streams, cus, 0);
         a.order = ordered ? reinterpret_cast<const int32_t *>(base + 256) : nullptr;
         L.order_out = (ordered && seg == 0) ? reinterpret_cast<int32_t *>(base + 256) : nullptr;
         L.num_seqs = (int)d->num_seqs;

@@ -7,13 +7,25 @@ namespace mfma {
 
 // (sequence, head) pairs per batch of the grid: the scan workgroups of a batch wait for the per-chunk
 // workgroups behind them, and about two batches' worth of them are resident at a time, each on half a
-// compute unit.  128 scan workgroups in flight is where an MI355X does best (64 cannot take the slots as fast
-// as the per-chunk role makes them, 256 leave that role too little of the device); a device with fewer compute
-// units gets batches of a quarter of its workgroup slots, so that two batches never take more than half.
-constexpr int kMaxBatchPairs = 128;
+// compute unit.  Up to 128 pairs make one batch (128 pairs x 64 chunks: 376 us, as two batches of 64 421 us).  More are
+// dealt out evenly in batches of at most 96, which is where two batches in flight do best (64 scan workgroups cannot take
+// the slots as fast as the per-chunk role makes them, 192 and more leave that role too little of the device), and an
+// uneven last batch is a chain with little beside it: us with batches of at most 128 / of at most 96, evenly: 144 pairs
+// x 32 chunks 287 / 224, 160 x 128 1049 / 935, 192 x 64 597 / 556, 192 packed with the output gate (7200 chunks in all) 512 / 458,
+// 256 x 64 751 / 740, 256 x 16 223 / 203, 256 x 512 5691 / 5713, 384 x 64 1114 / 1093.  Packed sequences, longest first, go
+// whole into a batch, as many as fit (256 pairs in all, 20000 chunks: 968 us as two batches, 967 as three of 86 pairs, 946 as 96, 96 and
+// the 64 pairs of the two shortest).  A device with fewer compute units gets batches of a quarter of its workgroup slots, so
+// that two batches never take more than half.
+constexpr int kMaxSingleBatchPairs = 128, kMaxBatchPairs = 96;
 
-// Chunks one workgroup of the per-chunk role works through (the fetch of each hides behind the one before).
+// Chunks a workgroup of the per-chunk role works through.  Four: the fetch of each hides behind the one before, which is
+// what counts where the per-chunk role sets the pace (a batch of 96 pairs or more on its own, ranges of a time split: 2^17
+// tokens x 32 heads 2972 us, with one 3108) and in short calls (64 pairs x 16 chunks 56 us, with one 58).  One: the
+// chunks are finished in just the order the scan wants them, which is what counts where its steps set the pace: several
+// batches (192 x 64: 595 us with four, 556 with one), or one of fewer than 96 pairs and 32 chunks a pair or more (64 x 64:
+// 233 and 217 us, 88 x 128: 549 and 504, 64 x 32: 114.5 and 112.5; at 24 chunks equal).
 constexpr int kItemsPerWorkgroup = 4;
+constexpr int kOrderedPairs = 96, kOrderedChunks = 32;
 
 // Time-split scan (kda_scan4_split.h): workspace areas and the cut of the chunk axis.
 struct SplitArgs {
@@ -64,7 +76,8 @@ struct FusedLaunch {
     int compute_units;              // of the device the launch goes to
 };
 
-int fused_batch_pairs(int64_t pairs, int compute_units);
+// heads: of a packed call whose sequences are taken longest first, else 0
+int fused_batch_pairs(int64_t pairs, int compute_units, int heads);
 kda_status launch_prefill_fused(const FusedLaunch &L, hipStream_t stream);
 
 }  // namespace mfma

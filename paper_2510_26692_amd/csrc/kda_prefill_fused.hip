@@ -9,7 +9,7 @@
 // Workgroups are dispatched in index order.  A scan workgroup walks the chunks of its pair and
 // takes each slot when the per-chunk workgroup that produces it has raised the slot's flag; the
 // per-chunk workgroups wait for nothing.  Every producer a scan workgroup depends on follows it
-// in the grid within its own batch, a batch holds at most kMaxBatchPairs scan workgroups, and
+// in the grid within its own batch, a batch holds at most kMaxBatchPairs scan workgroups (a call's only one kMaxSingleBatchPairs), and
 // the scan workgroups of the next batch start only when the per-chunk workgroups of this one
 // have all been placed: at no time do waiting workgroups hold more than a fraction of the
 // device, whatever the number of pairs, so the producers always find room and every wait ends.
@@ -203,12 +203,16 @@ static bool reserve_fused_lds()
     return ok;
 }
 
-int fused_batch_pairs(int64_t pairs, int compute_units)
+int fused_batch_pairs(int64_t pairs, int compute_units, int heads)
 {
     int most = compute_units / 2;                             // a quarter of the two slots per compute unit
-    if (most > kMaxBatchPairs) most = kMaxBatchPairs;
+    if (most > kMaxSingleBatchPairs) most = kMaxSingleBatchPairs;
     if (most < 1) most = 1;
-    return (int)(pairs < most ? pairs : most);
+    if (pairs <= most) return (int)pairs;
+    if (most > kMaxBatchPairs) most = kMaxBatchPairs;
+    if (heads > 0 && heads <= most) return most / heads * heads;
+    const int64_t batches = (pairs + most - 1) / most;
+    return (int)((pairs + batches - 1) / batches);
 }
 
 kda_status launch_prefill_fused(const FusedLaunch &L, hipStream_t stream)
@@ -216,7 +220,7 @@ kda_status launch_prefill_fused(const FusedLaunch &L, hipStream_t stream)
     if (!reserve_fused_lds())
         return fail(KDA_ERR_LAUNCH, "cannot reserve %d bytes of LDS for the prefill kernel", scan4::kLds);
     FusedArgs a = L.args;
-    a.nb = fused_batch_pairs(a.pairs, L.compute_units);
+    a.nb = fused_batch_pairs(a.pairs, L.compute_units, a.order ? a.H : 0);
     int64_t blocks;
     // chunks per workgroup of the per-chunk role, and the workgroups of that role expected to be resident
     // together: two per compute unit, less the scan workgroups beside them (two batches' worth, or all of them)
@@ -229,6 +233,7 @@ kda_status launch_prefill_fused(const FusedLaunch &L, hipStream_t stream)
         blocks = nscan + intra_workgroups(items, a.per_wg, a.window);
     } else {
         const int64_t nbatches = (a.pairs + a.nb - 1) / a.nb;
+        if (nbatches > 1 || (a.pairs < kOrderedPairs && a.launch_chunks >= kOrderedChunks)) a.per_wg = 1;
         const int64_t beside = nbatches > 1 ? 2 * a.nb : a.nb;
         a.window = (int)(slots - beside > 64 ? slots - beside : 64);
         blocks = nbatches * (a.nb + intra_workgroups((int64_t)a.nb * a.launch_chunks, a.per_wg, a.window));

@@ -135,6 +135,15 @@ def test_bf16_packed_in_several_batches_of_pairs_takes_the_longest_sequences_fir
         assert torch.equal(o1, o[:, sl]) and torch.equal(h1[0], hT[n]), n
 
 
+@pytest.mark.parametrize("B,T,H", [(1, 130, 128), (3, 130, 43), (5, 70, 29), (7, 64, 28), (5, 31 * 64, 13), (5, 31 * 64 + 1, 13),
+                                   (5, 32 * 64, 19), (6, 32 * 64, 16)])
+def test_bf16_batches_of_pairs_and_chunks_per_workgroup(B, T, H):
+    """Both sides of the lines of the launch rule: 128 pairs (one batch) and 129 (two of 65 and 64), 145 (73 and 72), 196 (three:
+    66, 66, 64); 65 pairs at 31 and at 32 chunks, 95 and 96 pairs at 32 chunks (four and one chunk per workgroup)."""
+    eo, eh = check_prefill(si.make_prefill(B, T, H, 128, 128, "bf16", -2.0, B * T + H, 0.02), TOL_BF16)
+    print("bf16 %dx%dx%d: err_o %.2e err_hT %.2e" % (B, T, H, eo, eh))
+
+
 def test_bf16_strong_decay_takes_the_exact_subchunk_path():
     """Gates far stronger than the fast operands allow (sub-chunk decay below 2^-11 on
     most channels, log alpha down to about -20 per token)."""
