@@ -17,51 +17,66 @@
 // A wave owns whole 16-channel tiles (all 64 tokens), so everything that is per channel -- the running sum of the
 // decay, the decay factors, the sums over tokens that make dlog alpha -- stays in its registers, and S0 and dS1 are
 // read as B operands straight from memory, once, a column tile ahead of their products.  Only dO, X and Vn (the operands
-// all waves share) and the two C x C results go through LDS: the former 32 value columns at a time in two buffers, so
+// all waves share) and the two C x C results go through LDS: the former 16 value columns at a time in two buffers, so
 // that one barrier a part is enough and the next part's rows are on their way while this one is multiplied; the latter
 // as fragments in both forms, so that every operand of the second half is one 16-byte read.  The registers (256) allow
 // two workgroups a compute unit.
 //
-// Bounds: at 4 x 4096 tokens x 16 heads 1.5 GB of traffic (0.29 ms at the rate of a large copy) and 41 GFLOP on the fp32 matrix
-// cores (0.27 ms), two workgroups a compute unit to overlap them: 0.49 ms (0.60 with 64 columns a part in one buffer, rows of
-// the results written 4 bytes a lane and the inputs read 2 bytes a lane).  Fetching parts unconditionally, which spares a wait
-// at the loop's end, and unrolling the parts both measured slower (0.51 ms; 470 bytes of scratch a lane).
+// The products with S0 and dS1 and the two C x C ones, three quarters of the kernel's, are formed from bf16 pieces (kda_f32_tile.h):
+// a state's fragment meets four token tiles in one or two products and a row's eight channel tiles, so the splitting is spread
+// over 192 to 384 cycles of products; dO, X and Vn are split once, by the wave that stages them.  The products of the second half,
+// whose factors are formed for one or two uses, stay on the fp32 instruction.
+//
+// Bounds: at 4 x 4096 tokens x 16 heads 1.5 GB of traffic (0.29 ms at the rate of a large copy), and per wave 25 of the 40 thousand
+// cycles of matrix products that the fp32 instruction takes for all of them: 0.49 -> 0.44 ms (two workgroups a compute unit overlap
+// the two), 9 x 1 tokens x 32 heads 55 -> 45 us; 2-norm errors of dq 0.75, dk 0.80 and dlog alpha 0.95 of what they were (bf16 inputs and dO,
+// mean log alpha -0.18; fp32 0.89, 0.91, 0.98).  32 columns a part leave 30 registers in scratch memory.
 #include "kda_f32_tile.h"
 
 namespace kda {
 namespace f32 {
 
 constexpr int kGradThreads = 256;
-constexpr int kCols = 2;                                     // column tiles of a part
-constexpr int kPart = 4 * kCols * kFrag;                     // one operand: [token tile][column tile]
+constexpr int kCols = 1;                                     // column tiles of a part
+// One operand of a part, [token tile][column tile]: in pieces (X, Vn and an fp32 dO), or bf16 as it stands (a bf16 dO).
+constexpr int kPart = 4 * kCols * kSplitFrag;
+template <typename T> constexpr int kRowFrag = sizeof(T) == 2 ? kFrag / 2 : kSplitFrag;
+template <typename T> constexpr int part_floats() { return 2 * kPart + 4 * kCols * kRowFrag<T>; }
 constexpr int kBoth = 2 * kTri * kFrag;                      // dA or dP: its blocks in row form, then in column form
 // Inputs of a channel tile on their way to column form, per wave: rows 16 bytes longer than they are, so that rows 4
 // apart lie in different banks.
 template <typename T> constexpr int turn_row() { return 16 * (int)sizeof(T) + 16; }
-template <typename T> constexpr size_t grad_lds()
+template <typename T, typename O> constexpr size_t grad_lds()
 {
-    const size_t first = (size_t)2 * 3 * kPart * 4, second = (size_t)(2 * kBoth + kC) * 4 + 4 * kC * turn_row<T>();
+    const size_t first = (size_t)2 * part_floats<O>() * 4, second = (size_t)(2 * kBoth + kC) * 4 + 4 * kC * turn_row<T>();
     return first > second ? first : second;
 }
-static_assert(2 * grad_lds<float>() <= 160 * 1024, "two workgroups share a compute unit");
+static_assert(2 * grad_lds<float, float>() <= 160 * 1024, "two workgroups share a compute unit");
 
-// Four values of a row as they lie in memory.
-template <typename T> struct Raw4;
-template <> struct Raw4<float> {
+// dO: four values of a row as they lie in memory, what of them goes to LDS, and the left factor read from there.  fp32 rows carry
+// the scale there; bf16 ones stay as they are, which spares a third of their products, and the scale comes behind the products.
+template <typename T> struct RowsOfO;
+template <> struct RowsOfO<float> {
+    using Factor = Left;
     f32x4 x;
     __device__ __forceinline__ void load(const float *p) { x = ld4(p); }
-    __device__ __forceinline__ f32x4 get() const { return x; }
-};
-template <> struct Raw4<__hip_bfloat16> {
-    uint2 u;
-    __device__ __forceinline__ void load(const __hip_bfloat16 *p) { u = *reinterpret_cast<const uint2 *>(p); }
-    __device__ __forceinline__ f32x4 get() const
+    __device__ __forceinline__ void put(float *frag, bool live, float scale, int lane) const
     {
-        float a, b, c, d;
-        unpack_bf16x2(u.x, a, b);
-        unpack_bf16x2(u.y, c, d);
-        return f32x4{a, b, c, d};
+        put_pieces(frag, split(live ? x * scale : f32x4{0.f, 0.f, 0.f, 0.f}), lane);
     }
+    static __device__ __forceinline__ Factor get(const float *frag, int lane) { Factor f; f.set(get_pieces(frag, lane)); return f; }
+    static __device__ __forceinline__ f32x4 scaled(const f32x4 &x, float) { return x; }
+};
+template <> struct RowsOfO<__hip_bfloat16> {
+    using Factor = LeftExact;
+    u32x2 x;
+    __device__ __forceinline__ void load(const __hip_bfloat16 *p) { x = *reinterpret_cast<const u32x2 *>(p); }
+    __device__ __forceinline__ void put(float *frag, bool live, float, int lane) const
+    {
+        *reinterpret_cast<u32x2 *>(frag + 2 * lane) = live ? x : u32x2{0u, 0u};
+    }
+    static __device__ __forceinline__ Factor get(const float *frag, int lane) { Factor f; f.set(*reinterpret_cast<const u32x2 *>(frag + 2 * lane)); return f; }
+    static __device__ __forceinline__ f32x4 scaled(const f32x4 &x, float scale) { return x * scale; }
 };
 
 template <typename Tin, typename Tdo, int D>
@@ -93,7 +108,10 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
         const int n = tile_tokens(c.nv, w);
         const float *rw = Rw + rows + (live ? row_form(w, 0, g, m, n, D) : 0), *zw = Zw + rows + (live ? row_form(w, 0, g, m, n, D) : 0);
         const int step = live ? 16 * n : 0;                                  // floats from a column tile to the next
-        Raw4<Tdo> go[kCols];
+        using RowO = RowsOfO<Tdo>;
+        using FactorO = typename RowO::Factor;
+        constexpr int kRowO = kRowFrag<Tdo>, kParts = part_floats<Tdo>();
+        RowO go[kCols];
         f32x4 gz[kCols], gr[kCols];
         float db = 0.f;
         auto fetch = [&](int pt) __attribute__((always_inline)) {
@@ -104,69 +122,110 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
                 gr[cg] = ld4(rw + (kCols * pt + cg) * step);
             }
         };
+        // (in a buffer: X, Vn, dO)
         auto commit = [&](int pt, float *buf) __attribute__((always_inline)) {
 #pragma unroll
             for (int cg = 0; cg < kCols; ++cg) {
                 const f32x4 x = bt * gz[cg], zero = {0.f, 0.f, 0.f, 0.f};
-                float *f = buf + (kCols * w + cg) * kFrag + 4 * lane;
-                st4(f, live ? go[cg].get() * p.scale : zero);
-                st4(f + kPart, live ? x : zero);
-                st4(f + 2 * kPart, live ? bt * gr[cg] : zero);
+                float *f = buf + (kCols * w + cg) * kSplitFrag;
+                put_pieces(f, split(live ? x : zero), lane);
+                put_pieces(f + kPart, split(live ? bt * gr[cg] : zero), lane);
+                go[cg].put(buf + 2 * kPart + (kCols * w + cg) * kRowO, live, p.scale, lane);
                 if (live) st4(dv + row + 16 * (kCols * pt + cg) + 4 * g, x);
                 db += gz[cg][0] * gr[cg][0] + gz[cg][1] * gr[cg][1] + gz[cg][2] * gr[cg][2] + gz[cg][3] * gr[cg][3];
             }
         };
-        f32x4 bs[kCols][TW], bd[kCols][TW];
-        auto fetch_states = [&](int ct, f32x4 (&s)[TW], f32x4 (&d)[TW]) __attribute__((always_inline)) {
+        f32x4 bs[TW], bd[TW];
+        auto fetch_states = [&](f32x4 (&to)[TW], const float *from, int ct) __attribute__((always_inline)) {
 #pragma unroll
-            for (int tt = 0; tt < TW; ++tt) {
-                const int f = ((4 * tt + w) * NT + ct) * kFrag;
-                s[tt] = ld4(s0 + f); d[tt] = ld4(ds1 + f);
-            }
+            for (int tt = 0; tt < TW; ++tt) to[tt] = ld4(from + ((4 * tt + w) * NT + ct) * kFrag);
         };
         fetch(0);
-        fetch_states(0, bs[0], bd[0]);
+        fetch_states(bs, s0, 0);
+        fetch_states(bd, ds1, 0);
         pin_memory_order();
         commit(0, smem);
         fetch(1);
         lds_barrier();
 #pragma unroll 1
         for (int pt = 0; pt < NP; ++pt) {
-            const float *buf = smem + (pt & 1) * 3 * kPart + 4 * lane;
+            const float *buf = smem + (pt & 1) * kParts;
 #pragma unroll
             for (int cg = 0; cg < kCols; ++cg) {
-                const int next = kCols * pt + cg + 1;                        // (the last one fetches its own again)
-                fetch_states(next < NT ? next : NT - 1, bs[(cg + 1) % kCols], bd[(cg + 1) % kCols]);
+                const int next = kCols * pt + cg + 1 < NT ? kCols * pt + cg + 1 : NT - 1;    // (the last one fetches its own again)
+                Right b[TW];
+#pragma unroll
+                for (int tt = 0; tt < TW; ++tt) {
+                    gc[tt] += bs[tt][0] * bd[tt][0] + bs[tt][1] * bd[tt][1] + bs[tt][2] * bd[tt][2] + bs[tt][3] * bd[tt][3];
+                    b[tt].set(split(bs[tt]));
+                }
+                fetch_states(bs, s0, next);
                 pin_memory_order();
 #pragma unroll
                 for (int R = 0; R < 4; ++R) {
-                    const float *f = buf + (kCols * R + cg) * kFrag;
-                    const f32x4 ao = ld4(f), ax = ld4(f + kPart), av = ld4(f + 2 * kPart);
+                    pin_memory_order();
+                    Left ax;
+                    ax.set(get_pieces(buf + (kCols * R + cg) * kSplitFrag, lane));
+                    const FactorO ao = RowO::get(buf + 2 * kPart + (kCols * R + cg) * kRowO, lane);
 #pragma unroll
-                    for (int tt = 0; tt < TW; ++tt) {
-                        aq[tt][R] = mfma16(ao, bs[cg][tt], aq[tt][R]);
-                        ak[tt][R] = mfma16(ax, bs[cg][tt], ak[tt][R]);
-                        at[tt][R] = mfma16(av, bd[cg][tt], at[tt][R]);
+                    for (int k = 0; k < Left::kSteps; ++k) {
+#pragma unroll
+                        for (int tt = 0; tt < TW; ++tt) ak[tt][R] = ax.step(k, b[tt], ak[tt][R]);
+                        if (k < FactorO::kSteps) {
+#pragma unroll
+                            for (int tt = 0; tt < TW; ++tt) aq[tt][R] = ao.step(k, b[tt], aq[tt][R]);
+                        }
                     }
                 }
 #pragma unroll
-                for (int tt = 0; tt < TW; ++tt)
-                    gc[tt] += bs[cg][tt][0] * bd[cg][tt][0] + bs[cg][tt][1] * bd[cg][tt][1] + bs[cg][tt][2] * bd[cg][tt][2] + bs[cg][tt][3] * bd[cg][tt][3];
+                for (int tt = 0; tt < TW; ++tt) b[tt].set(split(bd[tt]));
+                fetch_states(bd, ds1, next);
+                pin_memory_order();
+#pragma unroll
+                for (int R = 0; R < 4; ++R) {
+                    pin_memory_order();
+                    Left av;
+                    av.set(get_pieces(buf + kPart + (kCols * R + cg) * kSplitFrag, lane));
+#pragma unroll
+                    for (int k = 0; k < Left::kSteps; ++k)
+#pragma unroll
+                        for (int tt = 0; tt < TW; ++tt) at[tt][R] = av.step(k, b[tt], at[tt][R]);
+                }
             }
 #pragma unroll
-            for (int i = 0; i < 5; ++i) {
-                const int u = w + 4 * i, b = u < 10 ? u : u - 10;
-                const int R = b >= 6 ? 3 : b >= 3 ? 2 : b >= 1 ? 1 : 0, I = b - tri(R, 0);
-                const float *pa = buf + (u < 10 ? kPart : 0) + kCols * R * kFrag, *pb = buf + 2 * kPart + kCols * I * kFrag;
+            for (int cg = 0; cg < kCols; ++cg)
 #pragma unroll
-                for (int cg = 0; cg < kCols; ++cg) tile[i] = mfma16(ld4(pa + cg * kFrag), ld4(pb + cg * kFrag), tile[i]);
-            }
+                for (int i = 0; i < 5; ++i) {
+                    const bool inA = i < 2 || (i == 2 && w < 2);             // u < 10
+                    const int u = w + 4 * i, bl = inA ? u : u - 10;
+                    const int R = bl >= 6 ? 3 : bl >= 3 ? 2 : bl >= 1 ? 1 : 0, I = bl - tri(R, 0);
+                    pin_memory_order();
+                    Right bv;
+                    bv.set(get_pieces(buf + kPart + (kCols * I + cg) * kSplitFrag, lane));
+                    if (inA) {
+                        Left ax;
+                        ax.set(get_pieces(buf + (kCols * R + cg) * kSplitFrag, lane));
+#pragma unroll
+                        for (int k = 0; k < Left::kSteps; ++k) tile[i] = ax.step(k, bv, tile[i]);
+                    } else {
+                        const FactorO ao = RowO::get(buf + 2 * kPart + (kCols * R + cg) * kRowO, lane);
+#pragma unroll
+                        for (int k = 0; k < FactorO::kSteps; ++k) tile[i] = ao.step(k, bv, tile[i]);
+                    }
+                }
             if (pt + 1 < NP) {
-                commit(pt + 1, smem + ((pt + 1) & 1) * 3 * kPart);           // (last read before the previous barrier)
+                commit(pt + 1, smem + ((pt + 1) & 1) * kParts);              // (last read before the previous barrier)
                 if (pt + 2 < NP) fetch(pt + 2);
                 lds_barrier();
             }
         }
+#pragma unroll
+        for (int tt = 0; tt < TW; ++tt)
+#pragma unroll
+            for (int R = 0; R < 4; ++R) aq[tt][R] = RowO::scaled(aq[tt][R], p.scale);
+#pragma unroll
+        for (int i = 0; i < 5; ++i)
+            if (i > 2 || (i == 2 && w >= 2)) tile[i] = RowO::scaled(tile[i], p.scale);
         db += __shfl_xor(db, 16);
         db += __shfl_xor(db, 32);
         if (g == 0 && live) dbeta[(c.tok0 + tok) * p.H + c.h] = db;
@@ -329,7 +388,7 @@ kda_status launch_gradients(const Problem &p, const Tin *q, const Tin *k, const 
     const int64_t blocks = p.slots * p.H;
     if (blocks == 0) return KDA_OK;
     if (blocks > 0x7fffffffLL) return fail(KDA_ERR_UNSUPPORTED, "%lld chunks in one call", (long long)blocks);
-    hipLaunchKernelGGL((kda_bwd_gradients_kernel<Tin, Tdo, D>), dim3((unsigned)blocks), dim3(kGradThreads), grad_lds<Tin>(), stream, q, k,
+    hipLaunchKernelGGL((kda_bwd_gradients_kernel<Tin, Tdo, D>), dim3((unsigned)blocks), dim3(kGradThreads), (grad_lds<Tin, Tdo>()), stream, q, k,
                        log_alpha, beta, d_o, S0, R, dS1, Z, dq, dk, dv, dla, dbeta, p);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? KDA_OK : fail(KDA_ERR_LAUNCH, "kda_bwd_gradients: %s", hipGetErrorString(e));

@@ -96,6 +96,23 @@ def test_backward_parity(case):
         assert e <= TOL, "%s: %s error %.3e exceeds %.1e" % (case, name, e, TOL)
 
 
+@pytest.mark.parametrize("shift", [-40, 40])
+@pytest.mark.parametrize("D,dtype,do_dtype", [(128, "bf16", "bf16"), (128, "bf16", "f32"), (64, "f32", "f32")])
+def test_gradients_scale_bit_for_bit_with_powers_of_two(D, dtype, do_dtype, shift):
+    """The gradients are linear in (d_o, d_hT), and a power of two moves through every product, sum and splitting into pieces
+    unrounded as long as nothing leaves the range of normal numbers: no part of the path has a range of its own."""
+    import paper_2510_26692_amd as kda
+    x = si.make_prefill(1, 145, 2, D, D, dtype, -2.0, 1220, 0.05)
+    do, dhT = _grad_inputs(x, 81)
+    dd = to_device(x)
+    do = do.to(torch.bfloat16 if do_dtype == "bf16" else torch.float32).cuda()
+    args = [dd[n] for n in ("q", "k", "v", "log_alpha", "beta")]
+    one = kda.kda_chunk_bwd(*args, do, dhT=dhT.cuda(), h0=dd["h0"])
+    two = kda.kda_chunk_bwd(*args, do * 2.0 ** shift, dhT=dhT.cuda() * 2.0 ** shift, h0=dd["h0"])
+    for name in NAMES:
+        assert torch.equal(one[name] * 2.0 ** shift, two[name]), name
+
+
 def test_backward_strong_decay_stays_finite_and_close():
     """Decays of e^-5 per token and channel and more: every decay is a pairwise difference, so nothing
     overflows.  The cumulative log decay reaches a few hundred here and is held in fp32, so a decay
