@@ -7,6 +7,8 @@
 // With Y = V - (Gamma.K) S0, the residual R = V - S^T k of the delta rule obeys (I + A Diag(beta)) R = Y, and
 // (I + A Diag(beta))^-1 = I - Q Diag(beta), (I + Diag(beta) A)^-1 = I - Diag(beta) Q with the same Q: the walks
 // (kda_f32_walk.hip) need one C x C matrix for both directions, and no division by beta appears anywhere.
+#include <type_traits>
+
 #include "kda_f32_tile.h"
 
 namespace kda {
@@ -110,21 +112,30 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
             fetch(next);
         }
         lds_barrier();
+        // (three tiles side by side, then two: the products of one are a chain, in which each waits half as long again as it takes, and
+        // for its operands.  With the substitution's reads ahead of its chain, below: a chunk on its own 15.6 -> 14.6 us at d 128)
+        auto multiply = [&](auto first, auto count) __attribute__((always_inline)) {
+            constexpr int i0 = decltype(first)::value, N = decltype(count)::value;
 #pragma unroll
-        for (int i = 0; i < 5; ++i) {
-            const int u = w + 4 * i, b = u < 10 ? u : u - 10;
-            int R, I;
-            block_of(b, R, I);
-            const float *pa = (u < 10 ? sKp : sQp) + (16 * R + m) * kLdT + 4 * g, *pb = sKn + (16 * I + m) * kLdT + 4 * g;
-            if (R == I) {
+            for (int kt = 0; kt < 4; ++kt) {
+                f32x4 fa[N], fb[N];
 #pragma unroll
-                for (int kt = 0; kt < 4; ++kt) acc[i] = mfma16(ld4(pa + 16 * kt), ld4(pb + 16 * kt), acc[i]);
-            } else {
-                const float *pF = sF + pair_of(R, I) * 64 + 4 * g;
+                for (int i = 0; i < N; ++i) {
+                    const int u = w + 4 * (i0 + i), b = u < 10 ? u : u - 10;
+                    int R, I;
+                    block_of(b, R, I);
+                    fa[i] = ld4((u < 10 ? sKp : sQp) + (16 * R + m) * kLdT + 4 * g + 16 * kt);
+                    fb[i] = ld4(sKn + (16 * I + m) * kLdT + 4 * g + 16 * kt);
+                    if (R > I) fb[i] *= ld4(sF + pair_of(R, I) * 64 + 4 * g + 16 * kt);
+                }
 #pragma unroll
-                for (int kt = 0; kt < 4; ++kt) acc[i] = mfma16(ld4(pa + 16 * kt), ld4(pb + 16 * kt) * ld4(pF + 16 * kt), acc[i]);
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int i = 0; i < N; ++i) acc[i0 + i] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][ks], fb[i][ks], acc[i0 + i], 0, 0, 0);
             }
-        }
+        };
+        multiply(std::integral_constant<int, 0>{}, std::integral_constant<int, 3>{});
+        multiply(std::integral_constant<int, 3>{}, std::integral_constant<int, 2>{});
     }
     if (__syncthreads_or(strong)) {
         // some channel's decay inside a block is beyond the factors' range: the diagonal blocks again, all of them and
@@ -199,22 +210,27 @@ void kda_f32_prep_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, c
     // a lane holds its column.
     f32x4 Q[4];
     {
-        float x[16];
+        // (the rows of A are read ahead of the chain: nothing is stored between them)
+        float x[16], q[16];
         const float *a = sA + (16 * w) * kLdT + 16 * w;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             float s = a[r * kLdT + m];
 #pragma unroll
             for (int i = 0; i < r; ++i) s = fmaf(-a[r * kLdT + i], x[i], s);
-            x[r] = s;
-            if (g == (r >> 2)) {
-#pragma unroll
-                for (int ww = 0; ww < 4; ++ww)
-                    if (ww == w) Q[ww][r & 3] = s;
-                sQ[(16 * w + r) * kLdT + 16 * w + m] = s;
-            }
+            q[r] = s;
             x[r] = s * sBeta[16 * w + r];                    // beta_i Q[i][m] is what the rows below take
         }
+        f32x4 own;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float q0 = q[j], q1 = q[4 + j], q2 = q[8 + j], q3 = q[12 + j], lo = g & 1 ? q1 : q0, hi = g & 1 ? q3 : q2;
+            own[j] = g & 2 ? hi : lo;
+            sQ[(16 * w + 4 * g + j) * kLdT + 16 * w + m] = own[j];
+        }
+#pragma unroll
+        for (int ww = 0; ww < 4; ++ww)
+            if (ww == w) Q[ww] = own;
     }
     lds_barrier();
     f32x4 bt[4];
