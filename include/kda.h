@@ -360,6 +360,16 @@ kda_status kda_recurrent_steps_fused(const kda_dims *dims, const kda_prologue *p
                                      void *o, void *hip_stream);
 
 /*
+ * The decode entry points above in one, with two choices in `flags`: KDA_STEPS_SCALAR_GATE, log_alpha is [N,Tq,H] (prologue and
+ * epilogue must then be NULL); KDA_STEPS_ZERO_SKIPPED, the rows of o of a skipped sequence are written as zeros instead of left
+ * untouched, for callers that want all of a fresh o defined.
+ */
+enum { KDA_STEPS_SCALAR_GATE = 1, KDA_STEPS_ZERO_SKIPPED = 2 };
+kda_status kda_recurrent_steps(const kda_dims *dims, const kda_prologue *prologue, const kda_epilogue *epilogue,
+                               const void *q, const void *k, const void *v, const void *log_alpha, const void *beta,
+                               float *S_pool, const int32_t *state_indices, void *o, uint32_t flags, void *hip_stream);
+
+/*
  * Zeros in the rows [0, cu_seqlens[0]) and [cu_seqlens[num_seqs], tokens) of up to eight arrays of `tokens` rows of
  * row_bytes[i] bytes each (a multiple of 4; arrays 16-byte aligned): the tokens of a packed batch that belong to no sequence,
  * which kda_chunk_fwd leaves untouched in o and kda_chunk_bwd in the per-token gradients.  For callers that want them defined.

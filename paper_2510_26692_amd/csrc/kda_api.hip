@@ -26,7 +26,7 @@ kda_status fail(kda_status code, const char *fmt, ...)
 // Kernel-side entry points (one per source file).
 kda_status recurrent_step_dispatch(const kda_dims *, const kda_prologue *, const kda_epilogue *, const void *, const void *,
                                    const void *, const void *, const void *, float *, void *,
-                                   const int32_t *, bool scalar_gate, hipStream_t);
+                                   const int32_t *, bool scalar_gate, bool zero_skipped, hipStream_t);
 int recurrent_max_steps();
 kda_status chunk_f32_dispatch(const kda_dims *, const void *, const void *, const void *,
                               const void *, const void *, const float *, const int32_t *, void *,
@@ -431,7 +431,7 @@ kda_status kda_recurrent_step(const kda_dims *d, const void *q, const void *k, c
     if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(log_alpha) || !aligned16(S) ||
         !aligned16(o) || (reinterpret_cast<uintptr_t>(beta) & 1u))
         return fail(KDA_ERR_INVALID_ARG, "tensor pointers must be 16-byte aligned");
-    return recurrent_step_dispatch(d, nullptr, nullptr, q, k, v, log_alpha, beta, S, o, nullptr, false,
+    return recurrent_step_dispatch(d, nullptr, nullptr, q, k, v, log_alpha, beta, S, o, nullptr, false, false,
                                    static_cast<hipStream_t>(hip_stream));
 }
 
@@ -439,7 +439,7 @@ static kda_status steps_pooled_impl(const kda_dims *d, const kda_prologue *pro, 
                                     const void *q, const void *k,
                                     const void *v, const void *log_alpha, const void *beta, float *S_pool,
                                     const int32_t *state_indices, void *o, void *hip_stream,
-                                    bool scalar_gate = false)
+                                    bool scalar_gate = false, bool zero_skipped = false)
 {
     kda_status st = check_dims(d, false);
     if (st != KDA_OK) return st;
@@ -453,7 +453,7 @@ static kda_status steps_pooled_impl(const kda_dims *d, const kda_prologue *pro, 
         !aligned16(o) || (reinterpret_cast<uintptr_t>(beta) & 1u) || (reinterpret_cast<uintptr_t>(log_alpha) & 1u) ||
         (reinterpret_cast<uintptr_t>(state_indices) & 3u))
         return fail(KDA_ERR_INVALID_ARG, "tensor pointers must be 16-byte aligned (state_indices: 4)");
-    return recurrent_step_dispatch(d, pro, epi, q, k, v, log_alpha, beta, S_pool, o, state_indices, scalar_gate,
+    return recurrent_step_dispatch(d, pro, epi, q, k, v, log_alpha, beta, S_pool, o, state_indices, scalar_gate, zero_skipped,
                                    static_cast<hipStream_t>(hip_stream));
 }
 
@@ -484,6 +484,22 @@ kda_status kda_recurrent_steps_fused(const kda_dims *d, const kda_prologue *pro,
     if (st == KDA_OK) st = check_epilogue(epi);
     if (st != KDA_OK) return st;
     return steps_pooled_impl(d, pro, epi, q_raw, k_raw, v, gate, beta_logit, S_pool, state_indices, o, hip_stream);
+}
+
+kda_status kda_recurrent_steps(const kda_dims *d, const kda_prologue *pro, const kda_epilogue *epi,
+                               const void *q, const void *k, const void *v, const void *log_alpha, const void *beta,
+                               float *S_pool, const int32_t *state_indices, void *o, uint32_t flags, void *hip_stream)
+{
+    g_last_error[0] = 0;
+    if (flags & ~(uint32_t)(KDA_STEPS_SCALAR_GATE | KDA_STEPS_ZERO_SKIPPED))
+        return fail(KDA_ERR_INVALID_ARG, "unknown flags %u", (unsigned)flags);
+    const bool scalar_gate = (flags & KDA_STEPS_SCALAR_GATE) != 0;
+    if (scalar_gate && (pro || epi)) return fail(KDA_ERR_UNSUPPORTED, "the scalar-gate decode has no fused stages");
+    kda_status st = check_prologue(pro);
+    if (st == KDA_OK) st = check_epilogue(epi);
+    if (st != KDA_OK) return st;
+    return steps_pooled_impl(d, pro, epi, q, k, v, log_alpha, beta, S_pool, state_indices, o, hip_stream, scalar_gate,
+                             (flags & KDA_STEPS_ZERO_SKIPPED) != 0);
 }
 
 }  // extern "C"

@@ -15,6 +15,7 @@ _lib = None
 
 KDA_F32, KDA_BF16 = 0, 1
 _DTYPE_CODE = {torch.float32: KDA_F32, torch.bfloat16: KDA_BF16}
+_SCALAR_GATE, _ZERO_SKIPPED = 1, 2        # flags of kda_recurrent_steps
 
 
 class KdaError(RuntimeError):
@@ -116,6 +117,8 @@ def load_library():
     lib.kda_recurrent_steps_pooled_scalar_gate.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
     lib.kda_recurrent_steps_fused.restype = ctypes.c_int
     lib.kda_recurrent_steps_fused.argtypes = [dp, pp, ep, vp, vp, vp, vp, vp, vp, vp, vp, vp]
+    lib.kda_recurrent_steps.restype = ctypes.c_int
+    lib.kda_recurrent_steps.argtypes = [dp, pp, ep, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_uint32, vp]
     _lib = lib
     return lib
 
@@ -547,21 +550,18 @@ def kda_recurrent_steps_pooled(q, k, v, log_alpha, beta, S_pool, state_indices=N
     elif state_indices.dtype != torch.int32 or state_indices.shape != (N,):
         raise ValueError("state_indices must be int32 [N]")
     odt = _out_dtype(o, out_dtype)
+    flags = _SCALAR_GATE if _scalar_gate else 0
     if o is None:                           # (with indices: rows of skipped sequences are zero)
-        o = (torch.empty if state_indices is None else torch.zeros)(N, Tq, H, dv, dtype=odt, device=dev)
+        o = torch.empty(N, Tq, H, dv, dtype=odt, device=dev)
+        flags |= _ZERO_SKIPPED
     elif o.shape != (N, Tq, H, dv):
         raise ValueError("o must have shape [N,Tq,H,dv]")
     dims = KdaDims(batch=N, seqlen=Tq, heads=H, dk=dk, dv=dv, chunk=64, num_seqs=N,
                    in_dtype=_DTYPE_CODE[q.dtype], out_dtype=_DTYPE_CODE[odt], scale=float(scale), max_seqlen=0)
-    tail = (_ptr(q), _ptr(k), _ptr(v), _ptr(log_alpha), _ptr(beta), _ptr(S_pool), _ptr(state_indices), _ptr(o),
-            _stream_ptr(dev))
-    if _scalar_gate:
-        st = lib.kda_recurrent_steps_pooled_scalar_gate(ctypes.byref(dims), *tail)
-    elif _fused is None:
-        st = lib.kda_recurrent_steps_pooled(ctypes.byref(dims), *tail)
-    else:
-        st = lib.kda_recurrent_steps_fused(ctypes.byref(dims),
-                                           *[None if f is None else ctypes.byref(f) for f in _fused], *tail)
+    pro, epi = _fused or (None, None)
+    st = lib.kda_recurrent_steps(ctypes.byref(dims), None if pro is None else ctypes.byref(pro), None if epi is None else ctypes.byref(epi),
+                                 _ptr(q), _ptr(k), _ptr(v), _ptr(log_alpha), _ptr(beta), _ptr(S_pool), _ptr(state_indices), _ptr(o),
+                                 flags, _stream_ptr(dev))
     if st != 0:
         raise KdaError(st, kda_last_error())
     return o

@@ -133,3 +133,17 @@ def test_pooled_decode_without_indices_equals_the_plain_step_and_rejects_bad_siz
     with pytest.raises(kda.KdaError) as ei:
         kda.kda_recurrent_steps_pooled(gb["q"], gb["k"], gb["v"], gb["log_alpha"], gb["beta"], S2)
     assert ei.value.status == 1
+
+
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+def test_rows_of_skipped_sequences_are_zero_in_a_fresh_output(out_dtype):
+    import paper_2510_26692_amd as kda
+    N, H, d, Tq = 4, 3, 128, 5
+    g = {k_: v_.cuda() for k_, v_ in _stack_tokens(N, H, d, "bf16", Tq, 74).items()}
+    idx = torch.tensor([-1, 3, -2, 0], dtype=torch.int32, device="cuda")
+    args = [g[n] for n in ("q", "k", "v", "log_alpha", "beta")]
+    torch.full((N, Tq, H, d), 7.0, device="cuda")                   # (what a fresh output is likely to lie on)
+    o = kda.kda_recurrent_steps_pooled(*args, si.make_state(5, H, d, d, 0.02, 75).cuda(), idx, out_dtype=out_dtype)
+    given = torch.full((N, Tq, H, d), 7.0, dtype=out_dtype, device="cuda")
+    kda.kda_recurrent_steps_pooled(*args, si.make_state(5, H, d, d, 0.02, 75).cuda(), idx, o=given)
+    assert (o[[0, 2]] == 0).all() and (given[[0, 2]] == 7).all() and torch.equal(o[[1, 3]], given[[1, 3]])
