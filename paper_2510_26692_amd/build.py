@@ -31,6 +31,11 @@ _REMARK = re.compile(r"remark:\s+(Function Name|TotalSGPRs|VGPRs|AGPRs|ScratchSi
                      r"|Occupancy \[waves/SIMD\]|LDS Size \[bytes/block\]|Dynamic Stack):\s+(\S+)")
 
 
+# The Python binding's decode calls, marshalled natively (csrc/kda_host.cpp): an extension module beside the library.
+HOST_SOURCE = os.path.join(CSRC, "kda_host.cpp")
+HOST_LIB = os.path.join(HERE, "_kda_host.so")
+
+
 def parse_resources(text):
     """{mangled kernel name: {figure: value}} from the compiler's kernel-resource-usage remarks."""
     out, cur = {}, None
@@ -80,5 +85,28 @@ def build(verbose=True, extra_flags=()):
     return LIB
 
 
+def build_host(verbose=True):
+    """Compile csrc/kda_host.cpp against this interpreter and its torch; raises on failure."""
+    import sysconfig
+
+    from torch.utils import cpp_extension
+    tmp = HOST_LIB + ".tmp.%d" % os.getpid()
+    # (include_paths and library_paths of a plain C++ extension: no HIP header or library is needed here)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-o", tmp, HOST_SOURCE, "-I", os.path.join(ROOT, "include"),
+           "-isystem", sysconfig.get_paths()["include"]]
+    for p in cpp_extension.include_paths():
+        cmd += ["-isystem", p]
+    cmd += ["-D_GLIBCXX_USE_CXX11_ABI=%d" % int(__import__("torch")._C._GLIBCXX_USE_CXX11_ABI)]
+    for p in cpp_extension.library_paths():
+        cmd += ["-L", p]
+    cmd += ["-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, HOST_LIB)
+    return HOST_LIB
+
+
 if __name__ == "__main__":
     build(extra_flags=sys.argv[1:])
+    build_host()

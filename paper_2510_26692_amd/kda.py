@@ -12,10 +12,12 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 # KDA_LIBRARY_PATH lets a developer point the binding at another build of the same library.
 _LIB_PATH = os.environ.get("KDA_LIBRARY_PATH") or os.path.join(_HERE, "libkda.so")
 _lib = None
+_native = None                            # decode calls marshalled natively (csrc/kda_host.cpp); None: not built, everything goes the general way
 
 KDA_F32, KDA_BF16 = 0, 1
 _DTYPE_CODE = {torch.float32: KDA_F32, torch.bfloat16: KDA_BF16}
 _SCALAR_GATE, _ZERO_SKIPPED = 1, 2        # flags of kda_recurrent_steps
+_STEPS_OPTIONS = {"scale", "o", "out_dtype"}
 
 
 class KdaError(RuntimeError):
@@ -51,7 +53,7 @@ def library_path():
 
 def load_library():
     """Load libkda.so; raises if it has not been built (no fallback exists)."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -119,6 +121,12 @@ def load_library():
     lib.kda_recurrent_steps_fused.argtypes = [dp, pp, ep, vp, vp, vp, vp, vp, vp, vp, vp, vp]
     lib.kda_recurrent_steps.restype = ctypes.c_int
     lib.kda_recurrent_steps.argtypes = [dp, pp, ep, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_uint32, vp]
+    try:
+        from . import _kda_host
+        _kda_host.bind(*[ctypes.cast(f, vp).value for f in (lib.kda_recurrent_step, lib.kda_recurrent_steps)], _raw_stream)
+        _native = _kda_host
+    except ImportError:
+        pass
     _lib = lib
     return lib
 
@@ -228,8 +236,23 @@ def _check_dev(*tensors):
     return dev
 
 
+def _raw_stream(index):
+    return torch.cuda.current_stream(index).cuda_stream
+
+
+# (the same number without a Stream object around it: 0.1 instead of 2 us)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _raw_stream)
+
+
 def _stream_ptr(dev):
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+    return ctypes.c_void_p(_raw_stream(dev.index))
+
+
+def _result(done):
+    """What the native way returned: the tensor, or the status of a call the library refused."""
+    if type(done) is int:
+        raise KdaError(done, kda_last_error())
+    return done
 
 
 def _mostly_unowned(cu_seqlens, tokens, max_seqlen):
@@ -493,6 +516,10 @@ def kda_recurrent_step(q, k, v, log_alpha, beta, S, scale=1.0, o=None, out_dtype
     S fp32 [N,H,dk,dv], updated in place.  Returns o [N,H,dv] (fp32, or bf16 on request as in
     kda_chunk_fwd)."""
     lib = load_library()
+    if _native is not None:
+        done = _native.step(q, k, v, log_alpha, beta, S, scale, o, out_dtype)
+        if done is not None:
+            return _result(done)
     dev = _check_dev(q, k, v, log_alpha, beta, S, o)
     N, H, dk = q.shape
     dv = v.shape[-1]
@@ -517,6 +544,12 @@ def kda_recurrent_step(q, k, v, log_alpha, beta, S, scale=1.0, o=None, out_dtype
 def kda_recurrent_steps_fused(q, k, v, gate, beta, S_pool, state_indices=None, prologue=True, l2norm_eps=1e-6,
                               a_scale=None, dt_bias=None, out_gate=None, norm_weight=None, rms_eps=1e-6, **kw):
     """kda_recurrent_steps_pooled with the fused stages (see kda_chunk_fwd_fused)."""
+    load_library()
+    if _native is not None and kw.keys() <= _STEPS_OPTIONS:
+        done = _native.steps(q, k, v, gate, beta, S_pool, state_indices, kw.get("scale", 1.0), kw.get("o"), kw.get("out_dtype"),
+                             2 if prologue else 3, l2norm_eps, a_scale, dt_bias, out_gate, norm_weight, rms_eps)
+        if done is not None:
+            return _result(done)
     pro = _make_prologue(q.shape[2], q.shape[3], l2norm_eps, a_scale, dt_bias) if prologue else None
     return kda_recurrent_steps_pooled(q, k, v, gate, beta, S_pool, state_indices,
                                       _fused=(pro, _make_epilogue(v, out_gate, norm_weight, rms_eps)), **kw)
@@ -534,6 +567,11 @@ def kda_recurrent_steps_pooled(q, k, v, log_alpha, beta, S_pool, state_indices=N
     device (negative = skip) or None for 0..N-1.  Returns o [N,Tq,H,dv] (fp32, or bf16 on request as in
     kda_chunk_fwd)."""
     lib = load_library()
+    if _native is not None and _fused is None:
+        done = _native.steps(q, k, v, log_alpha, beta, S_pool, state_indices, scale, o, out_dtype, int(bool(_scalar_gate)), 0.0, None, None,
+                             None, None, 0.0)
+        if done is not None:
+            return _result(done)
     dev = _check_dev(q, k, v, log_alpha, beta, S_pool, state_indices, o)
     N, Tq, H, dk = q.shape
     dv = v.shape[-1]

@@ -147,3 +147,81 @@ def test_rows_of_skipped_sequences_are_zero_in_a_fresh_output(out_dtype):
     given = torch.full((N, Tq, H, d), 7.0, dtype=out_dtype, device="cuda")
     kda.kda_recurrent_steps_pooled(*args, si.make_state(5, H, d, d, 0.02, 75).cuda(), idx, o=given)
     assert (o[[0, 2]] == 0).all() and (given[[0, 2]] == 7).all() and torch.equal(o[[1, 3]], given[[1, 3]])
+
+
+def _decode_call(form, dtype, d, out_dtype, given, indices, Tq, seed):
+    """(function of the binding, arguments, keywords) of a decode call on fresh tensors, the states last among the arguments."""
+    import paper_2510_26692_amd as kda
+    N, H, P = 5, 3, 7
+    g = torch.Generator().manual_seed(seed)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rn = lambda *s: torch.randn(*s, generator=g).to(dt).cuda()
+    lead = (N, H) if form == "step" else (N, Tq, H)
+    q, k, v = rn(*lead, d) * 0.1, rn(*lead, d) * 0.1, rn(*lead, d)
+    la = rn(*lead) if form == "scalar" else rn(*lead, d)
+    la, beta = -la.abs(), rn(*lead).abs().clamp(max=1.0)
+    S = 0.1 * torch.randn(N if form == "step" else P, H, d, d, generator=g).cuda()
+    kw = dict(scale=0.7, out_dtype=out_dtype)
+    if given:
+        kw["o"] = torch.full(lead + (d,), 3.0, dtype=out_dtype or torch.float32, device="cuda")
+    if form != "step" and indices:
+        kw["state_indices"] = torch.tensor([6, -1, 0, 3, -7], dtype=torch.int32, device="cuda")
+    if form.startswith("fused"):
+        kw.update(prologue=form != "fused_gate", out_gate=rn(*lead, d) if "gate" in form else None)
+        if form == "fused_all_gate":
+            kw.update(a_scale=torch.rand(H, generator=g).cuda(), dt_bias=torch.randn(H, d, generator=g).cuda(),
+                      norm_weight=torch.randn(d, generator=g).cuda(), l2norm_eps=1e-5, rms_eps=1e-4)
+    call = {"step": kda.kda_recurrent_step, "plain": kda.kda_recurrent_steps_pooled, "scalar": kda.kda_recurrent_steps_pooled_scalar_gate}
+    return call.get(form, kda.kda_recurrent_steps_fused), [q, k, v, la, beta, S], kw
+
+
+@pytest.mark.parametrize("form", ["step", "plain", "scalar", "fused", "fused_gate", "fused_all_gate"])
+@pytest.mark.parametrize("dtype,d,out_dtype", [("bf16", 128, None), ("bf16", 128, torch.bfloat16), ("bf16", 64, None), ("f32", 128, torch.float32)])
+@pytest.mark.parametrize("given,indices", [(False, True), (True, True), (False, False)])
+def test_native_marshalling_is_the_general_one(form, dtype, d, out_dtype, given, indices, monkeypatch):
+    """Every form of the decode calls, marshalled natively and by the general path: the same outputs and states bit for bit,
+    rows of skipped sequences zero in a fresh o and untouched in a given one."""
+    import paper_2510_26692_amd as kda
+    assert kda.kda._native is not None
+    results = []
+    for general in (False, True):
+        call, args, kw = _decode_call(form, dtype, d, out_dtype, given, indices, 3, 71)
+        if general:
+            monkeypatch.setattr(kda.kda, "_native", None)
+        o = call(*args, **kw)
+        assert not given or o is kw["o"]
+        results.append((o, args[-1]))
+    (o0, S0), (o1, S1) = results
+    assert o0.dtype == o1.dtype and torch.equal(o0, o1) and torch.equal(S0, S1)
+    if form != "step" and indices:
+        assert (o0[[1, 4]].float() == (3.0 if given else 0.0)).all()
+
+
+@pytest.mark.parametrize("form", ["step", "plain", "fused_all_gate"])
+def test_irregular_decode_calls_are_still_refused(form):
+    import paper_2510_26692_amd as kda
+
+    def refused(error, at=None, to=None, **more):
+        call, args, kw = _decode_call(form, "bf16", 128, None, False, False, 2, 72)
+        if at is not None:
+            args[at] = to(args[at])
+        with pytest.raises(error):
+            call(*args, **{**kw, **more})
+    wide = lambda t: torch.cat([t, t], dim=-1)[..., :t.shape[-1]]
+    for at in range(6):
+        refused(ValueError, at, lambda t: t.cpu())
+        if at != 4:
+            refused(ValueError, at, wide)
+        refused(ValueError, at, lambda t: t.to(torch.float16))
+    refused(ValueError, 5, lambda t: t[:, :-1].contiguous())
+    refused(ValueError, o=torch.empty(3, device="cuda"))
+    refused(ValueError, out_dtype=torch.float16)
+    refused(ValueError, o=torch.empty(3, device="cuda"), out_dtype=torch.bfloat16)
+    if form != "step":
+        refused(ValueError, state_indices=torch.zeros(5, dtype=torch.int64, device="cuda"))
+        refused(ValueError, state_indices=torch.zeros(4, dtype=torch.int32, device="cuda"))
+        refused(ValueError, 1, lambda t: t[:, :, :-1].contiguous())
+        refused(TypeError, nonsense=1)
+        with pytest.raises(kda.KdaError):                           # nine tokens: refused by the library, on either way
+            call, args, kw = _decode_call(form, "bf16", 128, None, False, False, 9, 73)
+            call(*args, **kw)
