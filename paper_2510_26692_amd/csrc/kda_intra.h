@@ -420,35 +420,57 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
             }
             __syncthreads();                                                               // B6
 
-            // ---- UT transform, off-diagonal blocks: X_RI = -X_RR sum_{I<=J<R} L_RJ X_JI (fp32 MFMA) ----
+            // ---- UT transform, off-diagonal blocks (fp32 MFMA).  First X_10 and X_32, then the lower left quarter of blocks:
+            // X_RI = -sum_{2<=K<=R} X_RK T_KI, T_KI = sum_{I<=J<=1} L_KJ X_JI, each wave one of them with the T it needs.  (Block row by
+            // block row is three rounds, each waiting for the one before, 3100 cycles of the 24 000 of a chunk: 8 packed sequences, 20 000
+            // chunks, 946 -> 923 us, 2^17 tokens x 32 heads 2979 -> 2926, 333 tokens x 32 heads 32.0 -> 31.4) ----
             {
                 const float *sLT = reinterpret_cast<const float *>(lds + kL);
                 float *sX = reinterpret_cast<float *>(lds + kX);
-                for (int Rr = 1; Rr < 4; ++Rr) {
-                    if (wave < Rr) {
-                        const int Ii = wave;
-                        f32x4 t = {0.f, 0.f, 0.f, 0.f};
-                        for (int J = Ii; J < Rr; ++J) {
+                // operands: L_RJ with contraction slot (ks, g) standing for its column 4 ks + g and X_JI with it for its row; and X_RK with
+                // the slot standing for its column 4 g + ks, so that register ks of an accumulator is the other operand as it stands
+                auto left = [&](int R, int J) __attribute__((always_inline)) {
+                    f32x4 a;
 #pragma unroll
-                            for (int ks = 0; ks < 4; ++ks) {
-                                const float a = sLT[(16 * J + 4 * ks + g) * kLdF + 16 * Rr + m];   // L[16 Rr + m][16 J + 4 ks + g]
-                                const float b = sX[(16 * J + 4 * ks + g) * kLdF + 16 * Ii + m];
-                                t = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, t, 0, 0, 0);
-                            }
-                        }
-                        // second product with contraction slot (ks, g) standing for index 4 g + ks, so
-                        // that register ks of the accumulator t is the B operand as it stands
-                        f32x4 r = {0.f, 0.f, 0.f, 0.f};
+                    for (int ks = 0; ks < 4; ++ks) a[ks] = sLT[(16 * J + 4 * ks + g) * kLdF + 16 * R + m];
+                    return a;
+                };
+                auto right = [&](int J, int I) __attribute__((always_inline)) {
+                    f32x4 b;
 #pragma unroll
-                        for (int ks = 0; ks < 4; ++ks) {
-                            const float a = sX[(16 * Rr + m) * kLdF + 16 * Rr + 4 * g + ks];
-                            r = __builtin_amdgcn_mfma_f32_16x16x4f32(a, t[ks], r, 0, 0, 0);
-                        }
+                    for (int ks = 0; ks < 4; ++ks) b[ks] = sX[(16 * J + 4 * ks + g) * kLdF + 16 * I + m];
+                    return b;
+                };
+                auto row = [&](int R, int K) __attribute__((always_inline)) { return *reinterpret_cast<const f32x4 *>(sX + (16 * R + m) * kLdF + 16 * K + 4 * g); };
+                auto put = [&](int R, int I, const f32x4 &v) __attribute__((always_inline)) {
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) sX[(16 * Rr + 4 * g + j) * kLdF + 16 * Ii + m] = -r[j];
-                    }
-                    __syncthreads();                                                       // B7
+                    for (int z = 0; z < 4; ++z) sX[(16 * R + 4 * g + z) * kLdF + 16 * I + m] = -v[z];
+                };
+                auto mul = [&](const f32x4 &a, const f32x4 &b, f32x4 acc) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ks], b[ks], acc, 0, 0, 0);
+                    return acc;
+                };
+                const f32x4 none = {0.f, 0.f, 0.f, 0.f};
+                if (wave >= 2) {
+                    const int I = 2 * (wave - 2);                           // 0 and 2
+                    const f32x4 d = row(I + 1, I + 1);
+                    put(I + 1, I, mul(d, mul(left(I + 1, I), right(I, I), none), none));
                 }
+                __syncthreads();                                                           // B7
+                const int I = wave & 1;
+                const f32x4 x0 = right(0, 0), x1 = right(1, I), l21 = left(2, 1), l20 = left(2, 0);
+                f32x4 t2 = mul(l21, x1, none);
+                if (I == 0) t2 = mul(l20, x0, t2);
+                if (wave >= 2) {
+                    put(2, I, mul(row(2, 2), t2, none));
+                } else {
+                    const f32x4 l31 = left(3, 1), l30 = left(3, 0), x32 = row(3, 2), x33 = row(3, 3);
+                    f32x4 t3 = mul(l31, x1, none);
+                    if (I == 0) t3 = mul(l30, x0, t3);
+                    put(3, I, mul(x33, t3, mul(x32, t2, none)));
+                }
+                __syncthreads();
             }
             // ---- M = X Diag(beta) as fp16 (over the dead K' tile); Tril(A_qk) out; V tile (over L) ----
             {
