@@ -79,18 +79,19 @@ template <> struct RowsOfO<__hip_bfloat16> {
     static __device__ __forceinline__ f32x4 scaled(const f32x4 &x, float scale) { return x * scale; }
 };
 
-template <typename Tin, typename Tdo, int D>
-__global__ __launch_bounds__(kGradThreads, 2)
-void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, const Tin *__restrict__ log_alpha,
-                              const Tin *__restrict__ beta, const Tdo *__restrict__ d_o, const float *__restrict__ S0,
-                              const float *__restrict__ Rw, const float *__restrict__ dS1, const float *__restrict__ Zw,
-                              float *__restrict__ dq, float *__restrict__ dk, float *__restrict__ dv,
-                              float *__restrict__ dla, float *__restrict__ dbeta, const Problem p)
+// kHalves: two workgroups a chunk, each with half of the channel tiles (and the C x C results for itself).
+template <typename Tin, typename Tdo, int D, bool kHalves>
+__device__ __forceinline__ void gradients(const Tin *__restrict__ q, const Tin *__restrict__ k, const Tin *__restrict__ log_alpha,
+                                          const Tin *__restrict__ beta, const Tdo *__restrict__ d_o, const float *__restrict__ S0,
+                                          const float *__restrict__ Rw, const float *__restrict__ dS1, const float *__restrict__ Zw,
+                                          float *__restrict__ dq, float *__restrict__ dk, float *__restrict__ dv,
+                                          float *__restrict__ dla, float *__restrict__ dbeta, const Problem &p)
 {
-    constexpr int NT = D / 16, TW = NT / 4, NP = NT / kCols;
+    constexpr int NT = D / 16, TW = NT / 4 / (kHalves ? 2 : 1), NP = NT / kCols;
+    const int half = kHalves ? (int)(blockIdx.x & 1) : 0, tile0 = 4 * TW * half;   // its channel tiles: tile0 + 4 tt + w
     extern __shared__ __attribute__((aligned(16))) float smem[];
     Chunk c;
-    if (!locate(p.cu, p.num_seqs, p.T, p.H, p.chunks_per_seq, blockIdx.x, c)) return;
+    if (!locate(p.cu, p.num_seqs, p.T, p.H, p.chunks_per_seq, kHalves ? blockIdx.x >> 1 : blockIdx.x, c)) return;
     const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t stride = (int64_t)p.H * D, base = (c.tok0 * p.H + c.h) * (int64_t)D;
@@ -131,14 +132,14 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
                 put_pieces(f, split(live ? x : zero), lane);
                 put_pieces(f + kPart, split(live ? bt * gr[cg] : zero), lane);
                 go[cg].put(buf + 2 * kPart + (kCols * w + cg) * kRowO, live, p.scale, lane);
-                if (live) st4(dv + row + 16 * (kCols * pt + cg) + 4 * g, x);
+                if (live && half == 0) st4(dv + row + 16 * (kCols * pt + cg) + 4 * g, x);
                 db += gz[cg][0] * gr[cg][0] + gz[cg][1] * gr[cg][1] + gz[cg][2] * gr[cg][2] + gz[cg][3] * gr[cg][3];
             }
         };
         f32x4 bs[TW], bd[TW];
         auto fetch_states = [&](f32x4 (&to)[TW], const float *from, int ct) __attribute__((always_inline)) {
 #pragma unroll
-            for (int tt = 0; tt < TW; ++tt) to[tt] = ld4(from + ((4 * tt + w) * NT + ct) * kFrag);
+            for (int tt = 0; tt < TW; ++tt) to[tt] = ld4(from + ((tile0 + 4 * tt + w) * NT + ct) * kFrag);
         };
         fetch(0);
         fetch_states(bs, s0, 0);
@@ -228,11 +229,11 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
             if (i > 2 || (i == 2 && w >= 2)) tile[i] = RowO::scaled(tile[i], p.scale);
         db += __shfl_xor(db, 16);
         db += __shfl_xor(db, 32);
-        if (g == 0 && live) dbeta[(c.tok0 + tok) * p.H + c.h] = db;
+        if (g == 0 && live && half == 0) dbeta[(c.tok0 + tok) * p.H + c.h] = db;
     }
     TileFetch<Tin> fg, fk, fq;
     auto fetch_inputs = [&](int tt) __attribute__((always_inline)) {
-        const int64_t at0 = base + 16 * (4 * tt + w);
+        const int64_t at0 = base + 16 * (tile0 + 4 * tt + w);
         int l = lane;
         asm volatile("" : "+v"(l));                                          // (addresses formed here, not kept from the first tile)
         fg.fetch(log_alpha + at0, stride, c.nv, l);
@@ -325,7 +326,7 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
                 // strong channels of this block, pair by pair (the products above left their diagonal block out); G again
                 // from the input: kept, it would cost every chunk registers
                 Decay e;
-                load_tile(e.x, log_alpha + base + 16 * (4 * tt + w) + m, stride, c.nv, g);
+                load_tile(e.x, log_alpha + base + 16 * (tile0 + 4 * tt + w) + m, stride, c.nv, g);
                 sum_decay(e, lane);
                 const f32x4 eL = e.in_block(R);
                 const bool mine = !d.weak[R];
@@ -370,7 +371,7 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
             const f32x4 tq = quad_transpose(gq, lane), tk = quad_transpose(gk, lane), tg = quad_transpose(s + behind, lane);
             const int r = 16 * R + 4 * g + (lane & 3);
             if (r < c.nv) {
-                const int64_t to = base + r * stride + 16 * (4 * tt + w) + (lane & 12);
+                const int64_t to = base + r * stride + 16 * (tile0 + 4 * tt + w) + (lane & 12);
                 st4(dq + to, tq); st4(dk + to, tk); st4(dla + to, tg);
             }
             if (tt + 1 < TW && R == (sizeof(Tin) == 2 ? 2 : 1)) fetch_inputs(tt + 1);    // (into what this tile has freed)
@@ -381,21 +382,51 @@ void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__
 }
 
 template <typename Tin, typename Tdo, int D>
+__global__ __launch_bounds__(kGradThreads, 2)
+void kda_bwd_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, const Tin *__restrict__ log_alpha,
+                              const Tin *__restrict__ beta, const Tdo *__restrict__ d_o, const float *__restrict__ S0,
+                              const float *__restrict__ Rw, const float *__restrict__ dS1, const float *__restrict__ Zw,
+                              float *__restrict__ dq, float *__restrict__ dk, float *__restrict__ dv,
+                              float *__restrict__ dla, float *__restrict__ dbeta, const Problem p)
+{
+    gradients<Tin, Tdo, D, false>(q, k, log_alpha, beta, d_o, S0, Rw, dS1, Zw, dq, dk, dv, dla, dbeta, p);
+}
+
+template <typename Tin, typename Tdo, int D>
+__global__ __launch_bounds__(kGradThreads, 2)
+void kda_bwd_half_gradients_kernel(const Tin *__restrict__ q, const Tin *__restrict__ k, const Tin *__restrict__ log_alpha,
+                                   const Tin *__restrict__ beta, const Tdo *__restrict__ d_o, const float *__restrict__ S0,
+                                   const float *__restrict__ Rw, const float *__restrict__ dS1, const float *__restrict__ Zw,
+                                   float *__restrict__ dq, float *__restrict__ dk, float *__restrict__ dv,
+                                   float *__restrict__ dla, float *__restrict__ dbeta, const Problem p)
+{
+    gradients<Tin, Tdo, D, true>(q, k, log_alpha, beta, d_o, S0, Rw, dS1, Zw, dq, dk, dv, dla, dbeta, p);
+}
+
+template <typename Tin, typename Tdo, int D>
 kda_status launch_gradients(const Problem &p, const Tin *q, const Tin *k, const Tin *log_alpha, const Tin *beta, const Tdo *d_o,
                             const float *S0, const float *R, const float *dS1, const float *Z, float *dq, float *dk, float *dv,
-                            float *dla, float *dbeta, hipStream_t stream)
+                            float *dla, float *dbeta, int compute_units, hipStream_t stream)
 {
     const int64_t blocks = p.slots * p.H;
     if (blocks == 0) return KDA_OK;
     if (blocks > 0x7fffffffLL) return fail(KDA_ERR_UNSUPPORTED, "%lld chunks in one call", (long long)blocks);
-    hipLaunchKernelGGL((kda_bwd_gradients_kernel<Tin, Tdo, D>), dim3((unsigned)blocks), dim3(kGradThreads), (grad_lds<Tin, Tdo>()), stream, q, k,
-                       log_alpha, beta, d_o, S0, R, dS1, Z, dq, dk, dv, dla, dbeta, p);
-    const hipError_t e = hipGetLastError();
-    return e == hipSuccess ? KDA_OK : fail(KDA_ERR_LAUNCH, "kda_bwd_gradients: %s", hipGetErrorString(e));
+    auto launch = [&](auto kern, int64_t workgroups) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)workgroups), dim3(kGradThreads), (grad_lds<Tin, Tdo>()), stream, q, k, log_alpha, beta,
+                           d_o, S0, R, dS1, Z, dq, dk, dv, dla, dbeta, p);
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess ? KDA_OK : fail(KDA_ERR_LAUNCH, "kda_bwd_gradients: %s", hipGetErrorString(e));
+    };
+    // Up to one chunk a compute unit the time is that of one workgroup, half of which is spent on its channel tiles one after the
+    // other: two share them (whole pass, d 128, whole / halves: 8 chunks 51.7 / 43.2 us, 32 57.7 / 48.7, 64 64.6 / 54.1, 128 76.8 / 67.6, 256
+    // 103.9 / 101.9; beyond, what both do twice counts: 384 149.9 / 150.9, 512 171.6 / 175.8).  At d 64 a wave has one tile as it is.
+    if constexpr (D == 128)
+        if (blocks <= compute_units) return launch(kda_bwd_half_gradients_kernel<Tin, Tdo, D>, 2 * blocks);
+    return launch(kda_bwd_gradients_kernel<Tin, Tdo, D>, blocks);
 }
 
 #define KDA_GRAD(T, O, DD) template kda_status launch_gradients<T, O, DD>(const Problem &, const T *, const T *, const T *, const T *, \
-    const O *, const float *, const float *, const float *, const float *, float *, float *, float *, float *, float *, hipStream_t)
+    const O *, const float *, const float *, const float *, const float *, float *, float *, float *, float *, float *, int, hipStream_t)
 KDA_GRAD(float, float, 64);
 KDA_GRAD(float, float, 128);
 KDA_GRAD(__hip_bfloat16, float, 64);

@@ -71,7 +71,7 @@ kda_status backward(const kda_dims *dm, const Plan &pl, const void *q, const voi
                                                  at(pl.Z), dh0, cus, stream);
     if (st == KDA_OK)
         st = f32::launch_gradients<Tin, Tdo, D>(p, in(q), in(k), in(la), in(beta), go, at(pl.S0), at(pl.R), at(pl.dS1),
-                                                at(pl.Z), dq, dk, dv, dla, dbeta, stream);
+                                                at(pl.Z), dq, dk, dv, dla, dbeta, cus, stream);
     return st;
 }
 

@@ -387,7 +387,7 @@ kda_status launch_both_walks(const Problem &p, const Tin *v, const float *h0, co
 template <typename Tin, typename Tdo, int D>
 kda_status launch_gradients(const Problem &p, const Tin *q, const Tin *k, const Tin *log_alpha, const Tin *beta, const Tdo *d_o,
                             const float *S0, const float *R, const float *dS1, const float *Z, float *dq, float *dk, float *dv,
-                            float *dla, float *dbeta, hipStream_t stream);
+                            float *dla, float *dbeta, int compute_units, hipStream_t stream);
 
 }  // namespace f32
 }  // namespace kda

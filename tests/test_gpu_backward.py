@@ -113,6 +113,18 @@ def test_gradients_scale_bit_for_bit_with_powers_of_two(D, dtype, do_dtype, shif
         assert torch.equal(one[name] * 2.0 ** shift, two[name]), name
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T,H", [(1, 3), (256, 64), (257, 52)])
+def test_gradients_of_one_chunk_a_compute_unit_and_of_more(T, H, dtype):
+    """Up to as many chunks as the device has compute units two workgroups share a chunk (1 and 256 chunks), beyond that one has it
+    to itself (260)."""
+    x = si.make_prefill(1, T, H, 128, 128, dtype, -2.0, 1230 + T, 0.05)
+    do, dhT = _grad_inputs(x, 82)
+    got, ref, cu = _run(x, do, dhT)
+    for name, e in _errors(got, ref, cu, 1, H).items():
+        assert e <= TOL, "%s error %.3e exceeds %.1e" % (name, e, TOL)
+
+
 def test_backward_strong_decay_stays_finite_and_close():
     """Decays of e^-5 per token and channel and more: every decay is a pairwise difference, so nothing
     overflows.  The cumulative log decay reaches a few hundred here and is held in fp32, so a decay
