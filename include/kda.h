@@ -175,9 +175,10 @@ kda_status kda_chunk_fwd_static_scratch(const kda_dims *dims,
  * with the general DPLR one for exactly that purpose) but derives no backward algorithm; what
  * is computed here is the chain rule applied to Eq. (1), organised chunk by chunk through the
  * quantities of Section 3.1 (A_kk, A_qk, the UT transform, the chunk state update), in fp32
- * throughout.  A decay between two tokens of a chunk is the product of two or three factors,
- * each within 2^(+-60), so that nothing overflows; a channel that decays by more than 2^-60
- * within 8 tokens is added pair by pair where it still counts.
+ * throughout (some products are formed from the exact bf16 pieces of their fp32 operands and
+ * accumulated in fp32, no less precisely).  A decay between two tokens of a chunk is the
+ * product of two or three factors, each within 2^(+-60), so that nothing overflows; a channel
+ * that decays by more than 2^-60 within 8 tokens is added pair by pair where it still counts.
  *
  *   q, k, v, log_alpha, beta, h0, cu_seqlens   as for kda_chunk_fwd (in_dtype KDA_F32 or
  *                              KDA_BF16, dk == dv in {64, 128})
