@@ -206,15 +206,17 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
 
     // own state tiles in accumulator order: S[t][j] = S(dk = 32 t + acc_row(j, hh), dv = 32 c + x)
     f32x16 S[4];
+    auto fill_state = [&](auto value) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int row = 32 * t + acc_row(j, hh);
-            if (kRole == kRoleT)      S[t][j] = (row == 32 * c + x) ? 1.f : 0.f;
-            else if (kRole == kRoleB) S[t][j] = 0.f;
-            else                      S[t][j] = poisoned ? __builtin_nanf("") : (state_in ? state_in[st_base + (int64_t)row * D] : 0.f);
-        }
+            for (int j = 0; j < 16; ++j) S[t][j] = value(32 * t + acc_row(j, hh));
+    };
+    if constexpr (kRole == kRoleT)      fill_state([&](int row) { return (row == 32 * c + x) ? 1.f : 0.f; });
+    else if constexpr (kRole == kRoleB) fill_state([](int) { return 0.f; });
+    // (one branch around all of the loads: asked element by element, some variants of the kernel wait for each load before the next)
+    else if (state_in && !poisoned)     fill_state([&](int row) { return state_in[st_base + (int64_t)row * D]; });
+    else                                fill_state([fill = poisoned ? __builtin_nanf("") : 0.f](int) { return fill; });
 
     if (c_begin < c_end) {
         const uint32_t lds0 = (uint32_t)(uintptr_t)lds;          // LDS byte address of the ring

@@ -5,6 +5,8 @@ prefill a scratch access waits behind the write-through slot stores in the same 
 places in scratch, cost the 2^20-token workload 5 % before it was noticed."""
 import json
 import os
+import re
+import subprocess
 
 import pytest
 
@@ -63,3 +65,52 @@ def test_fp32_kernels_use_no_scratch_beyond_a_few_dwords_of_the_gradients_kernel
         assert r["Occupancy [waves/SIMD]"] >= 3, (name, r)
     for name, r in gradients.items():
         assert r["Occupancy [waves/SIMD]"] >= 2 and r["VGPRs Spill"] <= (8 if "Li128E" in name else 0), (name, r)
+
+
+_OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+def _kernel_code(lib, folder, fragment):
+    """{kernel name: [instruction, ..]} of the kernels of `lib` whose name holds `fragment`, as the compiler left them."""
+    here = os.path.join(str(folder), "lib.so")
+    os.symlink(lib, here)                                    # (the code objects are written beside the file)
+    subprocess.run([_OBJDUMP, "--offloading", here], check=True, capture_output=True, cwd=str(folder))
+    code = {}
+    for name in os.listdir(str(folder)):
+        path = os.path.join(str(folder), name)
+        if "gfx950" not in name or fragment.encode() not in open(path, "rb").read():
+            continue
+        text = subprocess.run([_OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", path], check=True, capture_output=True, text=True).stdout
+        kernel = None
+        for ln in text.splitlines():
+            m = re.match(r"(?:[0-9a-f]+ )?<(\w+)>:", ln)
+            if m:
+                kernel = code.setdefault(m.group(1), []) if fragment in m.group(1) else None
+            elif kernel is not None and ln.strip():
+                kernel.append(ln.split("//")[0].strip())
+    return code
+
+
+@pytest.mark.skipif(not os.path.exists(_OBJDUMP), reason="needs llvm-objdump")
+def test_no_prefill_kernel_waits_for_each_load_of_a_state_before_the_next(tmp_path):
+    """A scan workgroup starts from 64 loads a lane.  Asked one by one whether there is a state to load, two of the kernels waited for
+    each (4 pairs of 4023 tokens, gate and bf16 output: 156 instead of 140 us).  The longest run of loads with a wait for all memory
+    between any two and no store and no product: the copy of a range's final state, which waits for each, stores each."""
+    lib = os.path.join(ROOT, "paper_2510_26692_amd", "libkda.so")
+    if not os.path.exists(lib):
+        pytest.skip("no library: build it first (python -m paper_2510_26692_amd.build)")
+    kernels = _kernel_code(lib, tmp_path, "kda_prefill_kernel")
+    kernels = {k: v for k, v in kernels.items() if len(v) > 1000}        # (descriptors of the same name are data)
+    assert len(kernels) == 10
+    for name, code in kernels.items():
+        longest = run = 0
+        waited = False
+        for ins in code:
+            if ins.startswith("global_load_dword "):
+                run = run + 1 if waited else 0
+                longest, waited = max(longest, run), False
+            elif ins.startswith("s_waitcnt") and "vmcnt(0)" in ins:
+                waited = True
+            elif ins.startswith(("global_store", "flat_store", "v_mfma", "s_barrier", "ds_")):
+                run, waited = 0, False
+        assert longest < 8, (name, longest)
