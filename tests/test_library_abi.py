@@ -52,6 +52,23 @@ def test_library_imports_no_allocating_or_stream_creating_runtime_call():
                    "hipPeekAtLastError"}, hip
 
 
+def test_extension_module_has_no_thread_local_storage():
+    """A module with thread-local storage that its code never touches slows down every access to such storage in the process after it
+    is loaded (glibc compares generations and finds no newer one to move to): it showed in every launch and every torch call."""
+    import struct
+
+    from paper_2510_26692_amd import build
+    if not os.path.exists(build.HOST_LIB):
+        build.build_host(verbose=False)
+    with open(build.HOST_LIB, "rb") as f:
+        elf = f.read()
+    assert elf[:6] == b"\x7fELF\x02\x01"                              # 64 bits, little endian
+    table, = struct.unpack_from("<Q", elf, 32)
+    size, count = struct.unpack_from("<HH", elf, 54)
+    kinds = [struct.unpack_from("<I", elf, table + i * size)[0] for i in range(count)]
+    assert 1 in kinds and 7 not in kinds                              # PT_LOAD, PT_TLS
+
+
 def test_dims_struct_layout_matches_header():
     kda, _ = _lib()
     # int32, pad, int64, 4 x int32, int32, 2 x enum, float, pad, int64 -> 56 bytes on LP64
