@@ -51,6 +51,13 @@ kda_status kda_debug_chunk_fwd_plan(const kda_dims *dims, size_t workspace_bytes
                                     int64_t out[5]);
 
 /*
+ * The grid of kda_chunk_fwd's first launch with the workspace of kda_chunk_fwd_workspace_size and no time split, on a device of
+ * `compute_units` compute units (256 on MI355X; no device is asked): out[0] (sequence, head) pairs per batch, out[1] chunks a
+ * workgroup of the per-chunk role works through, out[2] workgroups.  packed: the call has cu_seqlens.  Launches nothing.
+ */
+kda_status kda_debug_prefill_grid(const kda_dims *dims, int packed, int compute_units, int64_t out[3]);
+
+/*
  * The raw status word that a bf16 prefill call left in `workspace` (same dims, workspace and size as
  * that call), after waiting for `hip_stream`.  Bits 1, 2, 4: the failures kda_chunk_fwd_check reports.
  * Bits 256 and 512 report, for a call whose scan was split into ranges, that some (sequence, head)

@@ -37,6 +37,7 @@ kda_status chunk_mfma_dispatch(const kda_dims *, const kda_prologue *, const kda
 size_t chunk_mfma_workspace_size(const kda_dims *, bool minimal, bool output_gate);
 size_t chunk_mfma_status_offset(const kda_dims *, size_t workspace_bytes);
 kda_status chunk_mfma_plan(const kda_dims *, size_t workspace_bytes, bool gate, int64_t out[5]);
+void chunk_mfma_grid(const kda_dims *, bool packed, int compute_units, int64_t out[3]);
 size_t chunk_bwd_workspace_size(const kda_dims *);
 size_t chunk_f32_fast_workspace_size(const kda_dims *);
 kda_status chunk_f32_fast_dispatch(const kda_dims *, const void *, const void *, const void *, const void *,
@@ -170,6 +171,20 @@ kda_status kda_debug_chunk_fwd_plan(const kda_dims *d, size_t workspace_bytes, i
     if (!mfma_path(d)) return fail(KDA_ERR_UNSUPPORTED, "only the matrix-core prefill (bf16 inputs, dk = dv = 128) has a plan");
     if (d->seqlen == 0 || d->num_seqs == 0 || d->heads == 0) { out[0] = out[1] = out[3] = out[4] = 0; out[2] = 1; return KDA_OK; }
     return chunk_mfma_plan(d, workspace_bytes, output_gate != 0, out);
+}
+
+kda_status kda_debug_prefill_grid(const kda_dims *d, int packed, int compute_units, int64_t out[3])
+{
+    g_last_error[0] = 0;
+    if (!d || !out) return fail(KDA_ERR_INVALID_ARG, "dims or out is NULL");
+    if (d->chunk != kChunk) return fail(KDA_ERR_UNSUPPORTED, "chunk must be %d, got %d", kChunk, d->chunk);
+    if (compute_units < 1) return fail(KDA_ERR_INVALID_ARG, "%d compute units", compute_units);
+    const kda_status st = check_dims(d, packed != 0);
+    if (st != KDA_OK) return st;
+    if (!mfma_path(d)) return fail(KDA_ERR_UNSUPPORTED, "only the matrix-core prefill (bf16 inputs, dk = dv = 128) has a grid of batches");
+    if (d->seqlen == 0 || d->num_seqs == 0 || d->heads == 0) { out[0] = out[1] = out[2] = 0; return KDA_OK; }
+    chunk_mfma_grid(d, packed != 0, compute_units, out);
+    return KDA_OK;
 }
 
 const char *kda_last_error(void) { return g_last_error; }

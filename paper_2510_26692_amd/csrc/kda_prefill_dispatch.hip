@@ -33,6 +33,24 @@ static int64_t max_chunks_per_seq(const kda_dims *d)
     return (longest + kChunk - 1) / kChunk;
 }
 
+// Of the pairs * launch_chunks places a launch has for a chunk, those that may hold one: all, but in a packed call, where a sequence's
+// bound is that of the longest (or of the whole stream), no more than the stream's tokens fill, spread evenly over the call's launches.
+static int64_t live_chunks(const kda_dims *d, bool packed, int64_t launch_chunks)
+{
+    const int64_t places = (int64_t)d->num_seqs * d->heads * launch_chunks, maxc = max_chunks_per_seq(d);
+    if (!packed || maxc == 0) return places;
+    const int64_t all = (int64_t)d->heads * (d->seqlen / kChunk + d->num_seqs);
+    const int64_t live = (int64_t)((double)all * (double)launch_chunks / (double)maxc);
+    return live < places ? live : places;
+}
+
+// Packed sequences in more than one batch of pairs go longest first.
+static bool takes_longest_first(const kda_dims *d, bool packed, int parts, int cus)
+{
+    const int64_t pairs = (int64_t)d->num_seqs * d->heads;
+    return packed && parts == 1 && d->num_seqs > 1 && d->num_seqs <= kMaxOrderedSeqs && pairs > fused_batch_pairs(pairs, cus, 0);
+}
+
 static size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Workspace: [status word, 256 B; sequence order, 1 KiB][slots of one segment, pair by pair][state carry][ready flags, one per slot]
@@ -216,6 +234,20 @@ kda_status chunk_mfma_plan(const kda_dims *d, size_t workspace_bytes, bool gate,
     return KDA_OK;
 }
 
+// The grid of the first launch of a call that has the workspace of kda_chunk_fwd_workspace_size and is not split in time, on a device
+// of `cus` compute units: out[0] pairs per batch, [1] chunks a workgroup of the per-chunk role works through, [2] workgroups.
+void chunk_mfma_grid(const kda_dims *d, bool packed, int cus, int64_t out[3])
+{
+    using namespace mfma;
+    FusedArgs a{};
+    a.pairs = (int64_t)d->num_seqs * d->heads;
+    a.launch_chunks = make_plan(d, 0, true, false).seg_chunks;
+    a.split.parts = 1;
+    a.nb = fused_batch_pairs(a.pairs, cus, takes_longest_first(d, packed, 1, cus) ? d->heads : 0);
+    out[2] = fused_workgroups(a, live_chunks(d, packed, a.launch_chunks), cus);
+    out[0] = a.nb; out[1] = a.per_wg;
+}
+
 kda_status chunk_mfma_dispatch(const kda_dims *d, const kda_prologue *pro, const kda_epilogue *epi,
                                const void *q, const void *k,
                                const void *v, const void *log_alpha, const void *beta, const float *h0,
@@ -282,9 +314,7 @@ kda_status chunk_mfma_dispatch(const kda_dims *d, const kda_prologue *pro, const
         a.launch_chunks = left < plan.seg_chunks ? left : plan.seg_chunks;
         a.wait_limit = g_wait_limit; a.H = d->heads; a.scale = d->scale; a.epoch = (uint32_t)(seg + 1);
         a.producers = g_producers; a.raw = raw;
-        // packed sequences in more than one batch of pairs: longest first
-        const bool ordered = cu != nullptr && parts == 1 && d->num_seqs > 1 && d->num_seqs <= kMaxOrderedSeqs &&
-                             streams > fused_batch_pairs(streams, cus, 0);
+        const bool ordered = takes_longest_first(d, cu != nullptr, parts, cus);
         a.order = ordered ? reinterpret_cast<const int32_t *>(base + 256) : nullptr;
         L.order_out = (ordered && seg == 0) ? reinterpret_cast<int32_t *>(base + 256) : nullptr;
         L.num_seqs = (int)d->num_seqs;
@@ -303,6 +333,7 @@ kda_status chunk_mfma_dispatch(const kda_dims *d, const kda_prologue *pro, const
         L.num_flags = parts > 1 ? (int64_t)((plan.split_offset + kSplitFlagBytes - plan.flags_offset) / 4)
                                 : (int64_t)plan.seg_chunks * streams;
         L.reset_split = parts > 1 && seg > 0;
+        L.live_chunks = live_chunks(d, cu != nullptr, a.launch_chunks);
         L.compute_units = cus;
         const kda_status st = launch_prefill_fused(L, stream);
         if (st != KDA_OK) return st;

@@ -24,8 +24,15 @@ constexpr int kMaxSingleBatchPairs = 128, kMaxBatchPairs = 96;
 // chunks are finished in just the order the scan wants them, which is what counts where its steps set the pace: several
 // batches (192 x 64: 595 us with four, 556 with one), or one of fewer than 96 pairs and 32 chunks a pair or more (64 x 64:
 // 233 and 217 us, 88 x 128: 549 and 504, 64 x 32: 114.5 and 112.5; at 24 chunks equal).
+// But the grid of a packed call has a place for as many chunks of every sequence as the longest may have, and a workgroup that finds
+// nothing at its place costs its launch, about 2 ns each, with batches of them ahead of the next batch's scan workgroups.  One chunk a
+// workgroup means four times as many, so it is taken only while such places are at most half of all and at most kMostEmptyPlaces.
+// us with four / with one: eight sequences of 5000 tokens x 32 heads 946 / 894, and without max_seqlen, 140 000 empty places, 1282 /
+// 1538; twelve of 500 to 3000 without it 830 / 1016; forty of 100 to 300 x 2 heads without it 48 / 62; with it, of 512 to 8192 tokens
+// x 32 heads: eight (11 500 empty) 972 / 925, nine (14 200) 998 / 972 and (15 000) 771 / 773, ten (16 700) 1047 / 1074 and (15 900) 885 / 908.
 constexpr int kItemsPerWorkgroup = 4;
 constexpr int kOrderedPairs = 96, kOrderedChunks = 32;
+constexpr int64_t kMostEmptyPlaces = 14 * 1024;
 
 // Time-split scan (kda_scan4_split.h): workspace areas and the cut of the chunk axis.
 struct SplitArgs {
@@ -73,11 +80,17 @@ struct FusedLaunch {
     int32_t *order_out;             // the first launch of such a call (the one that resets the flags) writes the order here, else NULL
     int num_seqs;
     bool reset_split;               // clear the counters of the time-split scan first (segments after the first)
+    int64_t live_chunks;            // of the pairs * launch_chunks places for a chunk, how many hold one, as far as the host can tell (at least)
     int compute_units;              // of the device the launch goes to
 };
 
+// Plain scan: pairs per batch, and chunks a workgroup of the per-chunk role works through.
 // heads: of a packed call whose sequences are taken longest first, else 0
 int fused_batch_pairs(int64_t pairs, int compute_units, int heads);
+int fused_chunks_per_workgroup(int64_t pairs, int batch_pairs, int64_t launch_chunks, int64_t live_chunks);
+// Workgroups of a launch, and the two figures the kernel lays them out by (a.per_wg, a.window); a.nb, a.pairs, a.launch_chunks and
+// a.split are given.
+int64_t fused_workgroups(FusedArgs &a, int64_t live_chunks, int compute_units);
 kda_status launch_prefill_fused(const FusedLaunch &L, hipStream_t stream);
 
 }  // namespace mfma

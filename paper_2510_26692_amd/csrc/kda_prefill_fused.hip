@@ -215,29 +215,39 @@ int fused_batch_pairs(int64_t pairs, int compute_units, int heads)
     return (int)((pairs + batches - 1) / batches);
 }
 
+int fused_chunks_per_workgroup(int64_t pairs, int batch_pairs, int64_t launch_chunks, int64_t live_chunks)
+{
+    const int64_t places = pairs * launch_chunks;
+    const bool by_steps = pairs > batch_pairs || (pairs < kOrderedPairs && launch_chunks >= kOrderedChunks);
+    return by_steps && places <= 2 * live_chunks && places - live_chunks <= kMostEmptyPlaces ? 1 : kItemsPerWorkgroup;
+}
+
+int64_t fused_workgroups(FusedArgs &a, int64_t live_chunks, int compute_units)
+{
+    // window: the workgroups of the per-chunk role expected to be resident together, two per compute unit, less the scan workgroups
+    // beside them (two batches' worth, or all of them)
+    const int slots = 2 * compute_units;
+    if (a.split.parts > 1) {
+        a.per_wg = kItemsPerWorkgroup;
+        const int64_t nscan = a.pairs * (int64_t)(2 * a.split.parts - 1);
+        a.window = (int)(slots - nscan > 64 ? slots - nscan : 64);
+        const int64_t items = a.pairs * ((a.split.parts - 1) * a.split.tail + (int64_t)a.split.parts * a.split.part_len);
+        return nscan + intra_workgroups(items, a.per_wg, a.window);
+    }
+    a.per_wg = fused_chunks_per_workgroup(a.pairs, a.nb, a.launch_chunks, live_chunks);
+    const int64_t nbatches = (a.pairs + a.nb - 1) / a.nb;
+    const int64_t beside = nbatches > 1 ? 2 * a.nb : a.nb;
+    a.window = (int)(slots - beside > 64 ? slots - beside : 64);
+    return nbatches * (a.nb + intra_workgroups((int64_t)a.nb * a.launch_chunks, a.per_wg, a.window));
+}
+
 kda_status launch_prefill_fused(const FusedLaunch &L, hipStream_t stream)
 {
     if (!reserve_fused_lds())
         return fail(KDA_ERR_LAUNCH, "cannot reserve %d bytes of LDS for the prefill kernel", scan4::kLds);
     FusedArgs a = L.args;
     a.nb = fused_batch_pairs(a.pairs, L.compute_units, a.order ? a.H : 0);
-    int64_t blocks;
-    // chunks per workgroup of the per-chunk role, and the workgroups of that role expected to be resident
-    // together: two per compute unit, less the scan workgroups beside them (two batches' worth, or all of them)
-    const int slots = 2 * L.compute_units;
-    a.per_wg = kItemsPerWorkgroup;
-    if (a.split.parts > 1) {
-        const int64_t nscan = a.pairs * (int64_t)(2 * a.split.parts - 1);
-        a.window = (int)(slots - nscan > 64 ? slots - nscan : 64);
-        const int64_t items = a.pairs * ((a.split.parts - 1) * a.split.tail + (int64_t)a.split.parts * a.split.part_len);
-        blocks = nscan + intra_workgroups(items, a.per_wg, a.window);
-    } else {
-        const int64_t nbatches = (a.pairs + a.nb - 1) / a.nb;
-        if (nbatches > 1 || (a.pairs < kOrderedPairs && a.launch_chunks >= kOrderedChunks)) a.per_wg = 1;
-        const int64_t beside = nbatches > 1 ? 2 * a.nb : a.nb;
-        a.window = (int)(slots - beside > 64 ? slots - beside : 64);
-        blocks = nbatches * (a.nb + intra_workgroups((int64_t)a.nb * a.launch_chunks, a.per_wg, a.window));
-    }
+    const int64_t blocks = fused_workgroups(a, L.live_chunks, L.compute_units);
     if (blocks > 0x7fffffffLL)
         return fail(KDA_ERR_UNSUPPORTED, "%lld workgroups in one launch: use a smaller workspace (shorter time segments)",
                     (long long)blocks);

@@ -92,6 +92,8 @@ def load_library():
     lib.kda_debug_chunk_fwd_plan.restype = ctypes.c_int
     lib.kda_debug_chunk_fwd_plan.argtypes = [ctypes.POINTER(KdaDims), ctypes.c_size_t, ctypes.c_int,
                                              ctypes.POINTER(ctypes.c_int64)]
+    lib.kda_debug_prefill_grid.restype = ctypes.c_int
+    lib.kda_debug_prefill_grid.argtypes = [ctypes.POINTER(KdaDims), ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int64)]
     lib.kda_debug_chunk_fwd_status.restype = ctypes.c_int
     lib.kda_debug_chunk_fwd_status.argtypes = [ctypes.POINTER(KdaDims), vp, sz, vp, ctypes.POINTER(ctypes.c_uint)]
     lib.kda_debug_stream_probe.restype = ctypes.c_int
@@ -155,6 +157,15 @@ def kda_debug_chunk_fwd_plan(dims, workspace_bytes, output_gate=False):
     out = (ctypes.c_int64 * 5)()
     st = load_library().kda_debug_chunk_fwd_plan(ctypes.byref(dims), ctypes.c_size_t(int(workspace_bytes)),
                                                  int(bool(output_gate)), out)
+    if st != 0:
+        raise KdaError(st, kda_last_error())
+    return tuple(int(x) for x in out)
+
+
+def kda_debug_prefill_grid(dims, packed, compute_units=256):
+    """(pairs per batch, chunks a per-chunk workgroup works through, workgroups) of a bf16 prefill's first launch (kda_debug.h)."""
+    out = (ctypes.c_int64 * 3)()
+    st = load_library().kda_debug_prefill_grid(ctypes.byref(dims), int(bool(packed)), int(compute_units), out)
     if st != 0:
         raise KdaError(st, kda_last_error())
     return tuple(int(x) for x in out)

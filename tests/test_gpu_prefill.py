@@ -135,6 +135,26 @@ def test_bf16_packed_in_several_batches_of_pairs_takes_the_longest_sequences_fir
         assert torch.equal(o1, o[:, sl]) and torch.equal(h1[0], hT[n]), n
 
 
+@pytest.mark.parametrize("H,batch", [(32, 96)])
+def test_bf16_packed_results_do_not_depend_on_the_bound_of_the_lengths(H, batch):
+    """Seven packed sequences in several batches of pairs: with their longest length given a per-chunk workgroup takes one chunk,
+    without it, when most places of the grid are empty, four.  The same bits, and right ones."""
+    import paper_2510_26692_amd as kda
+    lens = [300, 290, 0, 257, 311, 320, 256]
+    x = si.make_varlen(lens, H, 128, 128, "bf16", -2.0, 12, 0.05)
+    eo, eh = check_prefill(x, TOL_BF16)
+    print("bf16 packed, %d heads: err_o %.2e err_hT %.2e" % (H, eo, eh))
+    dd = to_device(x)
+    results = []
+    for bound, per_workgroup in ((max(lens), 1), (0, 4)):
+        dims = kda.kda.make_chunk_dims(dd["q"], dd["v"], dd["cu_seqlens"], max_seqlen=bound)
+        assert kda.kda.kda_debug_prefill_grid(dims, True, torch.cuda.get_device_properties(0).multi_processor_count)[:2] == (batch, per_workgroup)
+        results.append(kda.kda_chunk_fwd(dd["q"], dd["k"], dd["v"], dd["log_alpha"], dd["beta"], h0=dd["h0"], cu_seqlens=dd["cu_seqlens"],
+                                         max_seqlen=bound, check=True))
+    (o0, h0), (o1, h1) = results
+    assert torch.equal(o0, o1) and torch.equal(h0, h1)
+
+
 @pytest.mark.parametrize("B,T,H", [(1, 130, 128), (3, 130, 43), (5, 70, 29), (7, 64, 28), (5, 31 * 64, 13), (5, 31 * 64 + 1, 13),
                                    (5, 32 * 64, 19), (6, 32 * 64, 16)])
 def test_bf16_batches_of_pairs_and_chunks_per_workgroup(B, T, H):

@@ -114,6 +114,26 @@ def test_workspace_sizes_are_consistent():
     assert kda.kda_chunk_fwd_workspace_size(_dims(kda, seqlen=0)) == 0
 
 
+@pytest.mark.parametrize("N,tokens,heads,bound,per_workgroup", [
+    (8, 40000, 32, 5000, 1), (8, 40000, 32, 0, 4),               # eight like prompts; without max_seqlen every one may be all of the stream
+    (4, 9000, 40, 4608, 1), (4, 9000, 40, 4609, 4),              # 72 and 73 places a pair, 36 of which can hold a chunk
+    (8, 40000, 32, 8640, 1), (8, 40000, 32, 8641, 4),            # 14 304 and 14 560 places without a chunk
+    (40, 8000, 2, 0, 4), (40, 8000, 2, 300, 4), (4, 9000, 16, 2496, 1), (4, 9000, 16, 0, 4), (4, 4000, 16, 1900, 4),   # one batch of pairs
+])
+def test_grid_of_a_packed_prefill_follows_its_tokens_not_a_loose_bound(N, tokens, heads, bound, per_workgroup):
+    """One chunk a workgroup only where most places of the grid hold a chunk: the workgroups of the per-chunk role stay within
+    about twice the chunks there can be, or within a quarter of the places."""
+    kda, _ = _lib()
+    d = _dims(kda, num_seqs=N, seqlen=tokens, heads=heads, max_seqlen=bound)
+    batch, per, workgroups = kda.kda.kda_debug_prefill_grid(d, packed=True)
+    assert per == per_workgroup
+    places = N * heads * -(-(bound or tokens) // 64)
+    assert workgroups <= 1.1 * places / per + 2 * N * heads + 4 * 512
+    # rows of one length have no empty places
+    rows = _dims(kda, batch=N, num_seqs=N, seqlen=max(1, tokens // N), heads=heads, max_seqlen=0)
+    assert kda.kda.kda_debug_prefill_grid(rows, packed=False)[1] == (1 if N * heads > 128 or tokens // N > 31 * 64 else 4)
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(dk=96, dv=96), 2), (dict(chunk=32), 2), (dict(out_dtype=1, in_dtype=0), 2), (dict(out_dtype=5), 1),
     (dict(seqlen=-1), 1),
