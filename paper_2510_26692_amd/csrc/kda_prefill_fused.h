@@ -13,9 +13,12 @@ namespace mfma {
 // uneven last batch is a chain with little beside it: us with batches of at most 128 / of at most 96, evenly: 144 pairs
 // x 32 chunks 287 / 224, 160 x 128 1049 / 935, 192 x 64 597 / 556, 192 packed with the output gate (7200 chunks in all) 512 / 458,
 // 256 x 64 751 / 740, 256 x 16 223 / 203, 256 x 512 5691 / 5713, 384 x 64 1114 / 1093.  Packed sequences, longest first, go
-// whole into a batch, as many as fit (256 pairs in all, 20000 chunks: 968 us as two batches, 967 as three of 86 pairs, 946 as 96, 96 and
-// the 64 pairs of the two shortest).  A device with fewer compute units gets batches of a quarter of its workgroup slots, so
-// that two batches never take more than half.
+// whole into a batch, as many as fit, where that comes to five sixths of the 96 or more (32 heads, sequences of 512 to 8192 tokens, us as
+// batches of 128 pairs / evenly / whole: eight sequences 958 / 944 / 925, 764 / 801 / 784 and 865 / 844 / 849 for three draws of
+// their lengths, six 616 / - / 610 and 597 / - / 560, ten 1063 / 1056 / 1047 and 897 / 899 / 885; 40 heads, which make 80: four
+// 770 / 697 / 695).  Otherwise evenly, too: with 64 heads whole sequences make batches of 64 (four sequences 1032 / 1020 / 1066 and 658 /
+// 650 / 668; eight shorter ones 942 / 919 / 912 and 714 / 694 / 698).  A device with fewer compute units gets batches of a quarter of
+// its workgroup slots, so that two batches never take more than half.
 constexpr int kMaxSingleBatchPairs = 128, kMaxBatchPairs = 96;
 
 // Chunks a workgroup of the per-chunk role works through.  Four: the fetch of each hides behind the one before, which is

@@ -210,7 +210,8 @@ int fused_batch_pairs(int64_t pairs, int compute_units, int heads)
     if (most < 1) most = 1;
     if (pairs <= most) return (int)pairs;
     if (most > kMaxBatchPairs) most = kMaxBatchPairs;
-    if (heads > 0 && heads <= most) return most / heads * heads;
+    const int whole = heads > 0 ? most / heads * heads : 0;
+    if (6 * whole >= 5 * most) return whole;
     const int64_t batches = (pairs + most - 1) / most;
     return (int)((pairs + batches - 1) / batches);
 }

@@ -135,7 +135,7 @@ def test_bf16_packed_in_several_batches_of_pairs_takes_the_longest_sequences_fir
         assert torch.equal(o1, o[:, sl]) and torch.equal(h1[0], hT[n]), n
 
 
-@pytest.mark.parametrize("H,batch", [(32, 96)])
+@pytest.mark.parametrize("H,batch", [(32, 96), (40, 80), (64, 90), (100, 88)])
 def test_bf16_packed_results_do_not_depend_on_the_bound_of_the_lengths(H, batch):
     """Seven packed sequences in several batches of pairs: with their longest length given a per-chunk workgroup takes one chunk,
     without it, when most places of the grid are empty, four.  The same bits, and right ones."""

@@ -134,6 +134,16 @@ def test_grid_of_a_packed_prefill_follows_its_tokens_not_a_loose_bound(N, tokens
     assert kda.kda.kda_debug_prefill_grid(rows, packed=False)[1] == (1 if N * heads > 128 or tokens // N > 31 * 64 else 4)
 
 
+@pytest.mark.parametrize("N,heads,batch", [
+    (8, 16, 128), (8, 32, 96), (9, 19, 95), (10, 24, 96), (8, 40, 80), (6, 48, 96), (2, 96, 96),     # whole sequences
+    (10, 26, 87), (4, 49, 66), (4, 64, 86), (8, 64, 86), (3, 79, 79), (3, 100, 75), (2, 200, 80),    # 78, 49, 64 .. would be too few: evenly
+])
+def test_batches_of_packed_sequences_are_whole_sequences_only_where_that_fills_them(N, heads, batch):
+    kda, _ = _lib()
+    d = _dims(kda, num_seqs=N, seqlen=500 * N, heads=heads, max_seqlen=600)
+    assert kda.kda.kda_debug_prefill_grid(d, packed=True)[0] == batch
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(dk=96, dv=96), 2), (dict(chunk=32), 2), (dict(out_dtype=1, in_dtype=0), 2), (dict(out_dtype=5), 1),
     (dict(seqlen=-1), 1),
