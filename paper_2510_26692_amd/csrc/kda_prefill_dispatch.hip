@@ -120,7 +120,9 @@ static SplitCut split_cut(const SegPlan &plan, const kda_dims *d, int cus, int f
     const double step = 3.0, item = 17.0, item_full = 21.2;
     const double items = (double)pairs * (double)maxc;
     // the plain scan: the chain of one pair, the per-chunk stage beside the scan workgroups, or what all scan
-    // workgroups together get done (with 64 of them on a busy device a step takes 3.6)
+    // workgroups together get done (with 64 of them on a busy device a step takes 3.5; the 3.6 stands for what the estimate of two
+    // ranges adds to theirs.  64 pairs, us plain / two ranges: 96 chunks 340 / 351, 128 444 / 447, 192 673 / 618, 256 895 / 783, 512 1808 /
+    // 1490.  The estimate of two ranges is 11 to 19 % high there and puts the line between 192 and 256; 3.5 would move it past 256)
     const double t_scan = (double)maxc * step, t_intra1 = items * item / (double)(slots - pairs);
     const double t_steps = items * (pairs >= 64 ? 3.6 : step) / (double)pairs;
     double best = t_scan > t_intra1 ? t_scan : t_intra1, ratio = 1.0;
