@@ -52,3 +52,30 @@ def test_errors_of_the_fp32_path_stay_as_small_as_they_can_be(H, D, dtype, mean)
                 errors.setdefault(n, []).append(np.linalg.norm(e) / np.linalg.norm(ref[n]))
     for n, e in errors.items():
         assert np.mean(e) <= 1e-7 * BOUNDS[D, mean][n], "%s: error %.3e exceeds %.2fe-7" % (n, np.mean(e), BOUNDS[D, mean][n])
+
+
+def _sums(d_o, S0):
+    """sum_v S0[k][v] d_o[v], as dq of one token with k = v = beta = log alpha = 0, and the same in 64 bits."""
+    import paper_2510_26692_amd as kda
+    N, H, D, _ = S0.shape
+    zero = torch.zeros(N, 1, H, D, device="cuda")
+    got = kda.kda_chunk_bwd(zero, zero, zero, zero, zero[..., 0].contiguous(), d_o.cuda(), h0=S0.cuda(), want_dh0=False)
+    torch.cuda.synchronize()
+    return got["dq"][:, 0].cpu().double(), torch.einsum("nhkv,nhv->nhk", S0.double(), d_o[:, 0].double())
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("value", ["0x1.fep+127", "0x1.fefffep+127", "0x1.ffp+127", "0x1.fffffep+127", "-0x1.fffffep+127"])
+def test_products_from_pieces_take_every_finite_value(D, value):
+    """The gradients kernel forms products from bf16 pieces of their operands.  The largest numbers lie above the largest finite bf16 (the
+    first of these values), by as much as the second piece holds: the result stays finite, and right to the bound below."""
+    S0 = torch.randn(2, 2, D, D, generator=torch.Generator().manual_seed(1)) * 2.0 ** -8
+    d_o = torch.zeros(2, 1, 2, D)
+    d_o[1, 0, 0, D // 2 + 3] = float.fromhex(value)
+    got, ref = _sums(d_o, S0)
+    # (one product: the pieces left out, 2^-24 of it, the sum of those kept, and what the state's pieces round)
+    assert ((got - ref).abs() <= 2.0 ** -22 * ref.abs()).all()
+    S0[1, 1, 5, 9] = float.fromhex(value)                             # and a state's
+    d_o = torch.full((2, 1, 2, D), 2.0 ** -9)
+    got, ref = _sums(d_o, S0)
+    assert torch.isfinite(got).all() and ((got - ref).norm() <= 1e-6 * ref.norm())
