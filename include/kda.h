@@ -175,10 +175,15 @@ kda_status kda_chunk_fwd_static_scratch(const kda_dims *dims,
  * with the general DPLR one for exactly that purpose) but derives no backward algorithm; what
  * is computed here is the chain rule applied to Eq. (1), organised chunk by chunk through the
  * quantities of Section 3.1 (A_kk, A_qk, the UT transform, the chunk state update), in fp32
- * throughout (some products are formed from the exact bf16 pieces of their fp32 operands and
- * accumulated in fp32, no less precisely).  A decay between two tokens of a chunk is the
- * product of two or three factors, each within 2^(+-60), so that nothing overflows; a channel
- * that decays by more than 2^-60 within 8 tokens is added pair by pair where it still counts.
+ * throughout.  Some products are formed from three bf16 pieces of their fp32 operands, which
+ * hold them exactly, and accumulated in fp32: what is left out is at most 1.01 * 2^-24 of a
+ * product, and the 2-norm errors of sums are smaller than with fp32 products (1.6e-7 against
+ * 2.05e-7 at 128 terms).  That holds for values of d_o, the states and what is formed from them
+ * down to 2^-110 (7.7e-34); smaller ones are rounded to multiples of 2^-133 there.  An infinity
+ * in d_o, h0 or d_hT comes back as NaN in the gradients of its (sequence, head).
+ * A decay between two tokens of a chunk is the product of two or three factors, each within
+ * 2^(+-60), so that nothing overflows; a channel that decays by more than 2^-60 within 8 tokens
+ * is added pair by pair where it still counts.
  *
  *   q, k, v, log_alpha, beta, h0, cu_seqlens   as for kda_chunk_fwd (in_dtype KDA_F32 or
  *                              KDA_BF16, dk == dv in {64, 128})

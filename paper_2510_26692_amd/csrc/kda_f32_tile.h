@@ -51,13 +51,15 @@ __device__ __forceinline__ f32x4 mfma16(const f32x4 &a, const f32x4 &b, f32x4 ac
 }
 
 // ---- fp32 products on the bf16 matrix cores ----
-// A value is the exact sum of three bf16 pieces, x = h + m + l (each the rest rounded to nearest: 8 bits a piece, and |m| <= 2^-9 |x|,
-// |l| <= 2^-18 |x|).  Of the nine products of two such sums the six down to 2^-18 are formed, two at a time in the 32
-// contraction slots of one 16x16x32 instruction (slots 8 g .. 8 g + 3 are one piece of the values 4 g .. 4 g + 3 of the tile, slots
-// 8 g + 4 .. 8 g + 7 another); the three left out are 2^-26 of the product and less.  Three instructions of 16 cycles for a
-// 16 x 16 x 16 product against four of 32 (measured: 386 against 142 TFLOP/s), fp32 accumulation, and rounded less often: 2-norm error of a sum
-// of 128 products of normal values 1.7e-7, on the fp32 instruction 2.05e-7.  Splitting a fragment costs 26 vector instructions,
-// so it pays where a fragment meets several others.  (A value that is not finite becomes NaN in its pieces.)
+// A value is the exact sum of three bf16 pieces, x = h + m + l (each the rest rounded to nearest: 8 bits a piece, and |m| <= 2^-8 |x|,
+// |l| <= 2^-17 |x|).  Of the nine products of two such sums six are formed, two at a time in the 32 contraction slots of one 16x16x32
+// instruction (slots 8 g .. 8 g + 3 are one piece of the values 4 g .. 4 g + 3 of the tile, slots 8 g + 4 .. 8 g + 7 another); the three
+// left out, m l', l m' and l l', come to at most 2^-24 of the product (and a little: 2^-24.007), the rounding of one fp32 multiplication.
+// Three instructions of 16 cycles for a 16 x 16 x 16 product against four of 32 (measured: 386 against 142 TFLOP/s), fp32
+// accumulation, and sums rounded less often: 2-norm error of a sum of 128 products of normal values 1.6e-7, on the fp32 instruction 2.05e-7,
+// down to values of 2^-110.  Below, l (and from 2^-118 m) is a subnormal bf16, which ends at 2^-133: 2^-116 2e-6, 2^-122 1.3e-4.  Above,
+// every finite value is taken; one that is not finite becomes NaN in its pieces.  Splitting a fragment costs 26 vector instructions, so it
+// pays where a fragment meets several others.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));

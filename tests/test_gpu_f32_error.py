@@ -79,3 +79,37 @@ def test_products_from_pieces_take_every_finite_value(D, value):
     d_o = torch.full((2, 1, 2, D), 2.0 ** -9)
     got, ref = _sums(d_o, S0)
     assert torch.isfinite(got).all() and ((got - ref).norm() <= 1e-6 * ref.norm())
+
+
+def test_products_from_pieces_of_the_worst_significands():
+    """Operands whose left-out products are largest and of one sign (2^-24.01 of each product): with the sum's own roundings, 24
+    additions of positive terms of up to half a unit of 2^-23, the result stays within 2^-24 + 24 * 2^-24."""
+    value = float.fromhex("0x1.00ff8p+0")
+    got, ref = _sums(torch.full((1, 1, 1, 128), value), torch.full((1, 1, 128, 128), value))
+    assert ((got - ref).abs() <= 25 * 2.0 ** -24 * ref).all()
+
+
+@pytest.mark.parametrize("exponent", [-100, -110, -113, -116, -122, -126])
+@pytest.mark.parametrize("of_state", [False, True])
+def test_products_from_pieces_of_the_smallest_values(exponent, of_state):
+    """Down to 2^-110 as precise as ever; below, operands (of size 2^exponent) are rounded to multiples of 2^-133, a bf16's last."""
+    g = torch.Generator().manual_seed(7)
+    d_o, S0 = torch.randn(3, 1, 2, 128, generator=g), torch.randn(3, 2, 128, 128, generator=g)
+    if of_state:
+        S0 *= 2.0 ** exponent
+    else:
+        d_o *= 2.0 ** exponent
+    got, ref = _sums(d_o, S0)
+    bound = 3e-7 if exponent >= -110 else 3e-7 + 2.0 ** (-134 - exponent)
+    assert (got - ref).norm() <= bound * ref.norm()
+
+
+def test_an_infinite_gradient_stays_with_its_sequence_and_head():
+    g = torch.Generator().manual_seed(8)
+    d_o, S0 = torch.randn(3, 1, 2, 128, generator=g), torch.randn(3, 2, 128, 128, generator=g)
+    finite, _ = _sums(d_o, S0)
+    d_o[1, 0, 0, 17] = float("inf")
+    got, _ = _sums(d_o, S0)
+    assert not torch.isfinite(got[1, 0]).any()
+    got[1, 0], finite[1, 0] = 0.0, 0.0
+    assert torch.equal(got, finite)
