@@ -538,6 +538,8 @@ def kda_recurrent_step(q, k, v, log_alpha, beta, S, scale=1.0, o=None, out_dtype
         raise ValueError("S must be fp32 [N,H,dk,dv]")
     if q.dtype not in _DTYPE_CODE or not (q.dtype == k.dtype == v.dtype == log_alpha.dtype == beta.dtype):
         raise ValueError("q, k, v, log_alpha, beta must share a supported dtype")
+    if min(k.numel(), log_alpha.numel()) < N * H * dk or v.numel() < N * H * dv or beta.numel() < N * H:
+        raise ValueError("inconsistent input shapes")
     odt = _out_dtype(o, out_dtype)
     if o is None:
         o = torch.empty(N, H, dv, dtype=odt, device=dev)

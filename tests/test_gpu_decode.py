@@ -225,3 +225,13 @@ def test_irregular_decode_calls_are_still_refused(form):
         with pytest.raises(kda.KdaError):                           # nine tokens: refused by the library, on either way
             call, args, kw = _decode_call(form, "bf16", 128, None, False, False, 9, 73)
             call(*args, **kw)
+
+
+@pytest.mark.parametrize("at", [1, 2, 3, 4])
+@pytest.mark.parametrize("shorter", [lambda t: t[:-1].contiguous(), lambda t: t[:, :-1].contiguous()])
+def test_a_step_with_too_short_an_input_is_refused(at, shorter):
+    """k, v, log alpha and beta hold a row for every row of q, or nothing is launched: the kernel reads them all."""
+    call, args, kw = _decode_call("step", "bf16", 128, None, False, False, 1, 74)
+    args[at] = shorter(args[at])
+    with pytest.raises(ValueError):
+        call(*args, **kw)
