@@ -401,6 +401,8 @@ def kda_chunk_fwd(q, k, v, log_alpha, beta, h0=None, cu_seqlens=None, scale=1.0,
         filled = packed and (T * H * dv * odt.itemsize <= 8 << 20 or _mostly_unowned(cu_seqlens, T, max_seqlen))
         o = (torch.zeros if filled else torch.empty)(B, T, H, dv, dtype=odt, device=dev)
         clear = packed and not filled
+    if hT is not None and hT.numel() * hT.element_size() < N * H * dk * dv * 4:
+        raise ValueError("hT must be fp32 [N,H,dk,dv]")
     if hT is None and want_hT:
         hT = torch.empty(N, H, dk, dv, dtype=torch.float32, device=dev)
     if workspace is None:

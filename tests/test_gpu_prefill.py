@@ -646,3 +646,11 @@ def test_bf16_thousands_of_short_packed_sequences():
     # (max_seqlen bounds the workspace: without it every sequence is sized as if it held all tokens)
     eo, eh = check_prefill(x, TOL_BF16, max_seqlen=int(lens.max()))
     print("bf16 3000 short sequences (%d tokens): err_o %.2e err_hT %.2e" % (int(lens.sum()), eo, eh))
+
+
+@pytest.mark.parametrize("shape,dtype", [((1, 2, 128, 128), torch.float32), ((3, 2, 128, 128), torch.bfloat16), ((3, 2, 128), torch.float32)])
+def test_an_array_too_small_for_the_final_states_is_refused(shape, dtype):
+    import paper_2510_26692_amd as kda
+    dd = to_device(si.make_prefill(3, 70, 2, 128, 128, "bf16", -2.0, 90, 0.05))
+    with pytest.raises(ValueError):
+        kda.kda_chunk_fwd(dd["q"], dd["k"], dd["v"], dd["log_alpha"], dd["beta"], hT=torch.empty(shape, dtype=dtype, device="cuda"))
