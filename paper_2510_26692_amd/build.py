@@ -9,6 +9,7 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -31,9 +32,10 @@ _REMARK = re.compile(r"remark:\s+(Function Name|TotalSGPRs|VGPRs|AGPRs|ScratchSi
                      r"|Occupancy \[waves/SIMD\]|LDS Size \[bytes/block\]|Dynamic Stack):\s+(\S+)")
 
 
-# The Python binding's decode calls, marshalled natively (csrc/kda_host.cpp): an extension module beside the library.
+# The Python binding's decode calls, marshalled natively (csrc/kda_host.cpp): an extension module beside the library, under a name that
+# no other interpreter loads.
 HOST_SOURCE = os.path.join(CSRC, "kda_host.cpp")
-HOST_LIB = os.path.join(HERE, "_kda_host.so")
+HOST_LIB = os.path.join(HERE, "_kda_host" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 
 def parse_resources(text):
@@ -87,8 +89,6 @@ def build(verbose=True, extra_flags=()):
 
 def build_host(verbose=True):
     """Compile csrc/kda_host.cpp against this interpreter and its torch; raises on failure."""
-    import sysconfig
-
     from torch.utils import cpp_extension
     tmp = HOST_LIB + ".tmp.%d" % os.getpid()
     # (include_paths and library_paths of a plain C++ extension: no HIP header or library is needed here.  NDEBUG, as torch itself is

@@ -5,6 +5,7 @@ handles (``data_ptr()``), the stream is torch's current HIP stream.
 """
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -127,8 +128,9 @@ def load_library():
         from . import _kda_host
         _kda_host.bind(*[ctypes.cast(f, vp).value for f in (lib.kda_recurrent_step, lib.kda_recurrent_steps)], _raw_stream)
         _native = _kda_host
-    except ImportError:
-        pass
+    except ImportError as e:                # (missing, or built for another torch or interpreter: right all the same, but no secret)
+        warnings.warn("decode calls are marshalled in Python, at about twice the host time: %s (build it with "
+                      "python -m paper_2510_26692_amd.build)" % e, RuntimeWarning, stacklevel=2)
     _lib = lib
     return lib
 

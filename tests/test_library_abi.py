@@ -258,6 +258,29 @@ def test_binding_fails_loudly_without_the_library(monkeypatch):
         binding.load_library()
 
 
+def test_a_missing_extension_module_is_told(monkeypatch):
+    """Without it decode calls go the general way, right but slower: loading the library says so."""
+    import sys
+
+    import paper_2510_26692_amd as kda
+    binding = kda.kda
+    _lib()
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_native", None)
+    monkeypatch.delattr(kda, "_kda_host", raising=False)
+    monkeypatch.setitem(sys.modules, kda.__name__ + "._kda_host", None)
+    with pytest.warns(RuntimeWarning, match="host time"):
+        binding.load_library()
+    assert binding._lib is not None and binding._native is None
+
+
+def test_extension_module_is_named_for_this_interpreter():
+    import sysconfig
+
+    from paper_2510_26692_amd import build
+    assert build.HOST_LIB.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+
+
 def test_bench_flop_model_matches_the_papers_formula():
     """bench.py's FLOP-per-token constant against the hand-evaluated values of the paper's
     formula (Section 6.3, "Training flops") stored in tests/golden/flops_model.txt."""
