@@ -235,3 +235,84 @@ def test_a_step_with_too_short_an_input_is_refused(at, shorter):
     args[at] = shorter(args[at])
     with pytest.raises(ValueError):
         call(*args, **kw)
+
+
+@pytest.mark.parametrize("form", ["step", "plain", "fused_all_gate"])
+def test_irregular_decode_calls_that_are_valid_are_still_taken(form):
+    """What the native marshalling hands back and the general path accepts: the same outputs and states as the plain call's."""
+    import numpy as np
+
+    import paper_2510_26692_amd as kda
+
+    class Tagged(torch.Tensor):
+        pass
+
+    class Recording:
+        """The native functions, and for each call whether it was taken."""
+        def __init__(self, native):
+            self.taken = []
+
+            def recorded(f):
+                def g(*a):
+                    r = f(*a)
+                    self.taken.append(r is not None)
+                    return r
+                return g
+            self.step, self.steps = recorded(native.step), recorded(native.steps)
+
+    def results(change_args=lambda a: a, **change_kw):
+        call, args, kw = _decode_call(form, "bf16", 128, None, False, form != "step", 2, 76)
+        args = change_args(args)
+        with pytest.MonkeyPatch.context() as m:
+            recording = Recording(kda.kda._native)
+            m.setattr(kda.kda, "_native", recording)
+            o = call(*args, **{**kw, **change_kw})
+        return o, args[5], recording.taken
+    o, S, taken = results()
+    assert taken == [True]
+    irregular = [
+        (lambda a: [t.as_subclass(Tagged) for t in a], {}),                           # a tensor subclass
+        (lambda a: [torch.nn.Parameter(t, requires_grad=False) for t in a], {}),
+        (lambda a: a, dict(scale=np.float32(0.7))),                                   # a number of another kind
+        (lambda a: a, dict(scale=torch.tensor(0.7))),
+    ]
+    if form == "step":
+        irregular.append((lambda a: a[:4] + [a[4][..., None]] + a[5:], {}))           # beta [N,H,1]
+    every = []
+    for change_args, change_kw in irregular:
+        o1, S1, taken = results(change_args, **change_kw)
+        every += taken
+        assert torch.equal(o, o1) and torch.equal(S, S1)
+    assert every.count(False) >= len(irregular) - 1                                   # (a Parameter is a plain tensor)
+
+
+def test_c_entry_points_for_decode_agree():
+    """kda_recurrent_steps_pooled, _pooled_scalar_gate and _fused against kda_recurrent_steps, which the binding calls: the same bits,
+    rows of skipped sequences untouched."""
+    import ctypes
+
+    import paper_2510_26692_amd as kda
+    lib, binding = kda.load_library(), kda.kda
+
+    def run(entry, form, flags=None):
+        call, (q, k, v, la, beta, S), kw = _decode_call(form, "bf16", 128, None, True, True, 3, 77)
+        N, T, H, D = q.shape
+        dims = binding.KdaDims(batch=N, seqlen=T, heads=H, dk=D, dv=D, chunk=64, num_seqs=N, in_dtype=1, out_dtype=0, scale=0.7, max_seqlen=0)
+        ref = ctypes.byref
+        stages = []
+        if form.startswith("fused"):
+            pro = binding._make_prologue(H, D, kw["l2norm_eps"], kw["a_scale"], kw["dt_bias"])
+            epi = binding._make_epilogue(v, kw["out_gate"], kw["norm_weight"], kw["rms_eps"])
+            stages = [ref(pro), ref(epi)]
+        elif flags is not None:
+            stages = [None, None]
+        ptrs = [t.data_ptr() for t in (q, k, v, la, beta, S, kw["state_indices"], kw["o"])]
+        more = [] if flags is None else [flags]
+        assert entry(ref(dims), *stages, *ptrs, *more, torch.cuda.current_stream().cuda_stream) == 0, kda.kda_last_error()
+        torch.cuda.synchronize()
+        return kw["o"], S
+    for form, entry, flags in (("plain", lib.kda_recurrent_steps_pooled, 0), ("scalar", lib.kda_recurrent_steps_pooled_scalar_gate, 1),
+                               ("fused_all_gate", lib.kda_recurrent_steps_fused, 0)):
+        (o0, S0), (o1, S1) = run(entry, form), run(lib.kda_recurrent_steps, form, flags)
+        assert torch.equal(o0, o1) and torch.equal(S0, S1), form
+        assert (o0[[1, 4]] == 3.0).all() and not (o0[[0, 2, 3]] == 3.0).any(), form

@@ -56,10 +56,11 @@ def test_fp32_kernels_use_no_scratch_beyond_a_few_dwords_of_the_gradients_kernel
     walks = _kernels(resources, "kda_f32_forward_walk") | _kernels(resources, "kda_f32_forward_roles") | \
         _kernels(resources, "kda_f32_both_walks")
     prep, gradients = _kernels(resources, "kda_f32_prep_kernel"), _kernels(resources, "kda_bwd_gradients_kernel")
-    assert len(walks) == 10 + 4 + 21 and len(prep) == 8 and len(gradients) == 6
-    for name, r in (walks | prep).items():
+    halves = _kernels(resources, "kda_bwd_half_gradients_kernel")
+    assert len(walks) == 10 + 4 + 21 and len(prep) == 8 and len(gradients) == 6 and len(halves) == 3
+    for name, r in (walks | prep | halves).items():          # (a half has one channel tile a wave, and registers to spare)
         assert r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0, (name, r)
-    for name, r in walks.items():                            # the dispatch counts on two workgroups a compute unit
+    for name, r in (walks | halves).items():                 # the dispatch counts on two workgroups a compute unit
         assert r["Occupancy [waves/SIMD]"] >= 2, (name, r)
     for name, r in prep.items():
         assert r["Occupancy [waves/SIMD]"] >= 3, (name, r)

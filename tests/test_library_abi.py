@@ -241,6 +241,22 @@ def test_recurrent_step_rejects_bad_calls():
     assert lib.kda_recurrent_step(ctypes.byref(d), fake, fake, fake, fake, fake, fake, fake, None) == 2
 
 
+def test_recurrent_steps_rejects_unknown_flags_and_a_scalar_gate_with_fused_stages():
+    kda, lib = _lib()
+    binding = kda.kda
+    d = _dims(kda, seqlen=2)
+    fake = ctypes.c_void_p(0x1000)
+    pro, epi = ctypes.byref(binding.KdaPrologue(l2norm_eps=1e-6)), ctypes.byref(binding.KdaEpilogue(rms_eps=1e-6, gate=0x1000))
+
+    def call(flags, pro=None, epi=None, S=fake):
+        return lib.kda_recurrent_steps(ctypes.byref(d), pro, epi, fake, fake, fake, fake, fake, S, None, fake, flags, None)
+    for flags in (4, 8, 5, 0x80000000):
+        assert call(flags) == 1 and "flags" in kda.kda_last_error()
+    assert call(1, pro=pro) == 2 and call(1, epi=epi) == 2 and call(3, pro=pro, epi=epi) == 2
+    assert call(0, epi=ctypes.byref(binding.KdaEpilogue(rms_eps=1e-6))) == 1           # a gate stage without a gate
+    assert call(0, S=None) == 1 and call(1, S=None) == 1 and call(2, S=ctypes.c_void_p(0x1004)) == 1
+
+
 def test_empty_problems_are_ok_and_launch_nothing():
     kda, lib = _lib()
     d = _dims(kda, heads=0)
