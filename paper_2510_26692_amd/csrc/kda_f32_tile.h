@@ -74,7 +74,8 @@ __device__ __forceinline__ uint32_t round_pair(float a, float b)
     return u;
 }
 // The largest finite bf16 for anything larger: rounded up, the first piece of the largest fp32 values would be an infinity, and what is
-// left of them no number.  (Backward pass at 4 x 4096 tokens x 16 heads 1.18 ms as without it, 9 x 1 tokens x 32 heads 111.6 -> 112.1 us.)
+// left of them no number.  (Backward pass at 4 x 4096 tokens x 16 heads 1.19 ms as without it, five packed sequences of 100 to 3000 tokens x 16
+// heads 487.7 -> 491, 9 x 1 tokens x 32 heads 111.6 -> 112.2 us; clamping d_o alone costs as much.)
 __device__ __forceinline__ float within_bf16(float x)
 {
     constexpr float most = 0x1.fep127f;
