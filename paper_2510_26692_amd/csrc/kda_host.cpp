@@ -1,6 +1,6 @@
 // The decode calls of the Python binding (kda.py), marshalled natively: a decode step of one sequence takes the device 4 us, and the
 // checks, descriptors and ctypes of the general path 10 us of the host (measured in a loop of kda_recurrent_step, 1 sequence x 32
-// heads: 9.9 us a call through kda.py alone, 5.4 here).
+// heads: 9.9 us a call through kda.py alone, 4.2 to 5.0 here).
 //
 // Only calls that are regular in every respect are taken: plain contiguous device tensors of the expected types and shapes on
 // one device.  For anything else, and for whatever cannot be told here, the functions return None, and kda.py's own path decides
