@@ -1,9 +1,9 @@
 // kda_intra: the per-chunk stage of the matrix-core prefill (Section 3.1), as a device function
 // that a kernel calls with the (head, sequence, chunk) of its workgroup.  It forms the running
 // log-decay G, the two intra-chunk matrices A_kk and A_qk, the UT transform
-// M = (I + StrictTril(Diag(beta) A_kk))^-1 Diag(beta) by forward substitution, W = M (Gamma.K),
-// U = M V and the decay-scaled operands Gamma.Q and Gamma^{i->C}.K, and leaves them in the chunk's
-// workspace slot in MFMA register order (kda_mfma_layout.h).
+// M = (I + StrictTril(Diag(beta) A_kk))^-1 Diag(beta) by forward substitution and the decay-scaled operands
+// Gamma.K, Gamma.Q and Gamma^{i->C}.K, and leaves them in the chunk's workspace slot in MFMA register order
+// (kda_mfma_layout.h).  V is not touched: the sequential stage reads it where it stands.
 //
 // Matrix-core operands are fp16 (unit roundoff 2^-11), accumulation is fp32.  bf16 inputs convert
 // to fp16 exactly while their magnitude lies in [2^-14, 65504] (or is zero); derived operands are rounded.
@@ -55,16 +55,13 @@ constexpr int kFix = kTab + 7 * 2048;                   //   early alias: scratc
 constexpr int kL = kX + kTileF;                         // fp32 L = StrictTril(Diag(beta) A_kk), stored transposed
 constexpr int kAq = kL + kTileF;                        // fp16 Tril(A_qk), stored transposed
 constexpr int kColS = kL;                               //   early alias: column operands [6 tiles][4][64] x 16 B
-constexpr int kV = kL;                                  //   late alias: fp16 V tile
-constexpr int kGK = kAq + kTileM;                       // fp16 Gamma.K
-constexpr int kKp = kGK + kTileH;                       // fp16 Gamma^{i->C}.K
-constexpr int kM = kKp;                                 //   late alias: fp16 M
+constexpr int kKp = kAq + kTileM;                       // fp16 Gamma^{i->C}.K
 constexpr int kTot = kKp + kTileH;                      // fp32 [4][128] sub-chunk log2-decay totals
 constexpr int kBeta = kTot + 4 * 128 * 4;               // fp32 [64]
 constexpr int kStrong = kBeta + 64 * 4;                 // u32 [4][4] strong-channel masks per (sub-chunk, g)
 constexpr int kIntraLds = kStrong + 64;
 static_assert(kFix + 4 * 4 * 16 * 3 * 4 <= kL, "early aliases must fit under X");
-static_assert(kColS + 6 * 4 * 64 * 16 <= kGK, "early aliases must fit under L and A_qk");
+static_assert(kColS + 6 * 4 * 64 * 16 <= kKp, "early aliases must fit under L and A_qk");
 static_assert(kIntraLds <= 80 * 1024, "kda_intra must leave room for two workgroups per CU");
 
 // Half of a sub-chunk's log2 decay `tot` (<= 0), as a non-negative shift; 0 for a strong channel.
@@ -175,7 +172,7 @@ __device__ __forceinline__ float log2_alpha_from_gate(float x, float a)
 
 // What the per-chunk stage reads and writes, the same for every chunk of a launch.
 struct IntraArgs {
-    const uint16_t *q, *k, *v, *log_alpha, *beta;    // bf16 inputs (log_alpha: [B,T,H,128], or [B,T,H] with kScalar)
+    const uint16_t *q, *k, *log_alpha, *beta;        // bf16 inputs (log_alpha: [B,T,H,128], or [B,T,H] with kScalar)
     const int32_t *cu_seqlens;                       // NULL: sequences of T tokens
     uint8_t *ws;                                     // slots
     int64_t T;
@@ -209,7 +206,7 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
     // (the wave index is the same in all lanes: telling the compiler so turns the per-wave cases
     // below into scalar branches instead of masked vector code)
     constexpr int kPolicy = kHandoff ? kCacheDevice : 0;
-    const uint16_t *__restrict__ q = A.q, *__restrict__ k = A.k, *__restrict__ v = A.v;
+    const uint16_t *__restrict__ q = A.q, *__restrict__ k = A.k;
     const uint16_t *__restrict__ log_alpha = A.log_alpha, *__restrict__ beta = A.beta, *__restrict__ out_gate = A.out_gate;
     uint8_t *__restrict__ ws = A.ws, *__restrict__ gate_ws = A.gate_ws;
     const int H = A.H;
@@ -275,6 +272,18 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
         beta_raw = rows_load2(rows_resource(beta + (L.tok0 * H + L.h), L.head_bytes), (tid & 63) * H * 2);
     };
 
+    // Eight values of this lane's token, channels 32 ks + 8 g + 0..7, to the workspace in MFMA register order as fp16: lanes g and
+    // g ^ 1 swap one 4-channel piece each so that every lane ends up with a complete 16-byte slot.  off: kOffKg or kOffQp.
+    auto put_frag = [&](const __amdgpu_buffer_rsrc_t &out, const int off, const int ks, const int tok, const int g, const float (&f)[8]) __attribute__((always_inline)) {
+        const uint32_t a0 = pack_h2(f[0], f[1]), a1 = pack_h2(f[2], f[3]), b0 = pack_h2(f[4], f[5]), b1 = pack_h2(f[6], f[7]);
+        const bool odd = g & 1;
+        const uint32_t r0 = __shfl_xor(odd ? a0 : b0, 16), r1 = __shfl_xor(odd ? a1 : b1, 16);
+        u32x4 o4;
+        if (odd) { o4[0] = r0; o4[1] = r1; o4[2] = b0; o4[3] = b1; }
+        else     { o4[0] = a0; o4[1] = a1; o4[2] = r0; o4[3] = r1; }
+        slot_store16<kPolicy>(out, off + frag_rts(tok >> 5, ks, g >> 1) * kFragBytes + ((tok & 31) + 32 * (g & 1)) * 16, o4);
+    };
+
     // Each item is computed in two halves, and the loop is rotated by one half: a pass fetches the inputs of
     // its item, finishes the item before it (which does not touch them) and then computes the first half of
     // its own, so a fetch has the second half of an item, a third of the whole, to arrive, and no register
@@ -298,10 +307,9 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
 
 
         if (prev.valid) {                                        // ---- second half of the item before ----
-            const int h = prev.h, nv = prev.nv, row_bytes = prev.row_bytes;
+            const int row_bytes = prev.row_bytes;
             const int64_t slot = prev.slot, row0 = prev.row0;
             const __amdgpu_buffer_rsrc_t out = slot_resource(ws + slot * (int64_t)kSlotBytes);
-            (void)h;
             // ---- output gate (fused epilogue): the chunk's gate factors go out in the accumulator order of the
             // sequential stage, which reads them like any other part of the slot.  Done first thing in the second half
             // of the chunk, where few registers are in use, and fenced off from the scheduler so that it stays there.
@@ -343,7 +351,7 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
                 __builtin_amdgcn_sched_barrier(0);
             }
 
-            // ---- L and Tril(A_qk) tiles of row R; fp16 V tile ----
+            // ---- L and Tril(A_qk) tiles of row R ----
             {
                 // (L is kept transposed, sLT[column][row]: a lane's four rows of a column are contiguous, one
                 // 16-byte store per tile, and the substitution below reads a column of L as a row)
@@ -371,14 +379,6 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
                 }
             }
             __syncthreads();                                                               // B5
-
-            // V is fetched now; its latency hides behind the UT transform
-            u32x4 vraw[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int u = tid + 256 * i, tokv = u >> 4, cg = u & 15;
-                vraw[i] = rows_load16(rows_resource(v + row0, row_bytes), tokv * row_pitch + 16 * cg);
-            }
 
             // ---- UT transform, diagonal 16x16 blocks: column j of (I + L_ww)^-1 per lane ----
             {
@@ -472,94 +472,39 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
                 }
                 __syncthreads();
             }
-            // ---- M = X Diag(beta) as fp16 (over the dead K' tile); Tril(A_qk) out; V tile (over L) ----
+            // ---- M = X Diag(beta) and Tril(A_qk) out in MFMA register order, three fragments a wave ----
             {
+                // lane (x, hh) of fragment (rr, ri, s): row token 32 rr + x, column tokens 32 ri + 16 s + 4 hh + 0..3 and + 8..11
                 const float *sX = reinterpret_cast<const float *>(lds + kX);
-                _Float16 *sM = reinterpret_cast<_Float16 *>(lds + kM);
-                // four consecutive columns per thread and pass: 16-byte reads, 8-byte writes
-#pragma unroll
-                for (int pass = 0; pass < 4; ++pass) {
-                    const int idx = tid + 256 * pass, r = idx >> 4, j0 = 4 * (idx & 15);
-                    const f32x4 xr = *reinterpret_cast<const f32x4 *>(sX + r * kLdF + j0);
-                    const f32x4 br = *reinterpret_cast<const f32x4 *>(sBeta + j0);
-                    float val[4];
-#pragma unroll
-                    for (int z = 0; z < 4; ++z) {
-                        const int j = j0 + z;
-                        val[z] = (j < r) ? xr[z] * br[z] : ((j == r) ? br[z] : 0.f);
-                    }
-                    u32x2 w2 = {pack_h2(val[0], val[1]), pack_h2(val[2], val[3])};
-                    *reinterpret_cast<u32x2 *>(sM + r * kLdM + j0) = w2;
-                }
-                // lane (x, hh) of fragment (rr, ri, s): row token 32 rr + x, column tokens 32 ri + 16 s + 4 hh + 0..3
-                // and + 8..11, which are rows of the transposed tile
-                const int hh = lane >> 5, xb = 16 * ((lane >> 4) & 1);
+                const int x = lane & 31, hh = lane >> 5, xb = 16 * ((lane >> 4) & 1);
+                auto tile = [](int idx, int &rr, int &ri, int &s) { const int p = idx >> 1; s = idx & 1; rr = (p == 0) ? 0 : 1; ri = (p == 2) ? 1 : 0; };
                 for (int idx = wave; idx < 6; idx += 4) {
-                    const int p = idx >> 1, s = idx & 1;
-                    const int rr = (p == 0) ? 0 : 1, ri = (p == 2) ? 1 : 0;
+                    int rr, ri, s;
+                    tile(idx, rr, ri, s);
+                    const int r = 32 * rr + x, j0 = 32 * ri + 16 * s + 4 * hh;
+                    u32x4 o4;
+#pragma unroll
+                    for (int half = 0; half < 2; ++half) {
+                        const f32x4 xr = *reinterpret_cast<const f32x4 *>(sX + r * kLdF + j0 + 8 * half);
+                        const f32x4 br = *reinterpret_cast<const f32x4 *>(sBeta + j0 + 8 * half);
+                        float val[4];
+#pragma unroll
+                        for (int z = 0; z < 4; ++z) {
+                            const int j = j0 + 8 * half + z;
+                            val[z] = (j < r) ? xr[z] * br[z] : ((j == r) ? br[z] : 0.f);
+                        }
+                        o4[2 * half] = pack_h2(val[0], val[1]); o4[2 * half + 1] = pack_h2(val[2], val[3]);
+                    }
+                    slot_store16<kPolicy>(out, kOffM + frag_tri(rr, ri, s) * kFragBytes + lane * 16, o4);
+                }
+                // (the columns of Tril(A_qk) are rows of the transposed tile)
+                for (int idx = wave ^ 2; idx < 6; idx += 4) {
+                    int rr, ri, s;
+                    tile(idx, rr, ri, s);
                     const uint8_t *blk = lds + kAq + ((32 * ri + 16 * s + 4 * hh) * kLdM + 32 * rr + xb) * 2;
                     const u32x2 a = lds_read_tr4(blk, kLdM, lane), b = lds_read_tr4(blk + 8 * kLdM * 2, kLdM, lane);
                     u32x4 o4 = {a[0], a[1], b[0], b[1]};
-                    slot_store16<kPolicy>(out, kOffAqk + frag_aqk(rr, ri, s) * kFragBytes + lane * 16, o4);
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int u = tid + 256 * i, tokv = u >> 4, cg = u & 15;
-                    u32x4 y;
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        float a, b;
-                        unpack_bf16x2(vraw[i][w], a, b);
-                        y[w] = pack_h2(a, b);
-                    }
-                    *reinterpret_cast<u32x4 *>(lds + kV + (tokv * kLdH + 8 * cg) * 2) = y;
-                }
-            }
-            __syncthreads();                                                               // B8
-
-            // ---- W^T = (Gamma.K)^T M^T (wave = d_k tile) and U = M V (wave = d_v tile) ----
-            {
-                // operands with the tokens in the contraction slots: lane (x, hh) wants channel 32 wave + x of
-                // the eight tokens 16 s4 + 8 hh + 0..7 of the [token][channel] tiles: two transposing reads each
-                const int x = lane & 31, hh = lane >> 5, xb = 16 * ((lane >> 4) & 1);
-                h8 mf[2][4], gk[4], vv[4];
-#pragma unroll
-                for (int s4 = 0; s4 < 4; ++s4) {
-#pragma unroll
-                    for (int rho = 0; rho < 2; ++rho)
-                        mf[rho][s4] = *reinterpret_cast<const h8 *>(lds + kM + ((32 * rho + x) * kLdM + 16 * s4 + 8 * hh) * 2);
-                    const int off = ((16 * s4 + 8 * hh) * kLdH + 32 * wave + xb) * 2;
-                    const u32x2 g0 = lds_read_tr4(lds + kGK + off, kLdH, lane), g1 = lds_read_tr4(lds + kGK + off + 4 * kLdH * 2, kLdH, lane);
-                    const u32x2 v0 = lds_read_tr4(lds + kV + off, kLdH, lane), v1 = lds_read_tr4(lds + kV + off + 4 * kLdH * 2, kLdH, lane);
-                    u32x4 pg = {g0[0], g0[1], g1[0], g1[1]}, pv = {v0[0], v0[1], v1[0], v1[1]};
-                    gk[s4] = __builtin_bit_cast(h8, pg);
-                    vv[s4] = __builtin_bit_cast(h8, pv);
-                }
-#pragma unroll
-                for (int rho = 0; rho < 2; ++rho) {
-                    f32x16 wt = {0.f}, u = {0.f};
-#pragma unroll
-                    for (int s4 = 0; s4 < 4; ++s4) {
-                        if (s4 < 2 * (rho + 1)) {            // M is lower triangular: tokens j <= r only
-                            wt = __builtin_amdgcn_mfma_f32_32x32x16_f16(gk[s4], mf[rho][s4], wt, 0, 0, 0);
-                            u = __builtin_amdgcn_mfma_f32_32x32x16_f16(mf[rho][s4], vv[s4], u, 0, 0, 0);
-                        }
-                    }
-                    // -W: registers 8s..8s+7 of a lane are its 8 contraction slots of K-step s
-#pragma unroll
-                    for (int s = 0; s < 2; ++s) {
-                        u32x4 o4;
-#pragma unroll
-                        for (int z = 0; z < 4; ++z) o4[z] = pack_h2(-wt[8 * s + 2 * z], -wt[8 * s + 2 * z + 1]);
-                        slot_store16<kPolicy>(out, kOffWn + frag_rts(rho, wave, s) * kFragBytes + lane * 16, o4);
-                    }
-#pragma unroll
-                    for (int j2 = 0; j2 < 2; ++j2) {            // U as fp16: kda_scan rounds V_new = U - W S to fp16 anyway
-                        u32x4 o4;
-#pragma unroll
-                        for (int z = 0; z < 4; ++z) o4[z] = pack_h2(u[8 * j2 + 2 * z], u[8 * j2 + 2 * z + 1]);
-                        slot_store16<kPolicy>(out, kOffU + (rho * 4 + wave) * kUTileBytes + (j2 * 64 + lane) * 16, o4);
-                    }
+                    slot_store16<kPolicy>(out, kOffAqk + frag_tri(rr, ri, s) * kFragBytes + lane * 16, o4);
                 }
             }
             if (kHandoff) {
@@ -647,21 +592,13 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
                     for (int w = 0; w < 4; ++w) t[w] = pack_h2(qf[2 * w], qf[2 * w + 1]);
                     rowQ[ks] = __builtin_bit_cast(h8, t);
 #pragma unroll
-                    for (int w = 0; w < 4; ++w) t[w] = pack_h2(kf[2 * w] * gam, kf[2 * w + 1] * gam);
-                    *reinterpret_cast<u32x4 *>(lds + kGK + (tok * kLdH + 32 * ks + 8 * g) * 2) = t;
-#pragma unroll
                     for (int w = 0; w < 4; ++w) t[w] = pack_h2(kf[2 * w] * gam_end, kf[2 * w + 1] * gam_end);
                     *reinterpret_cast<u32x4 *>(lds + kKp + (tok * kLdH + 32 * ks + 8 * g) * 2) = t;
-                    {   // Gamma.Q to the workspace in MFMA register order (see the per-channel path)
-                        const uint32_t a0 = pack_h2(qf[0] * gam_q, qf[1] * gam_q), a1 = pack_h2(qf[2] * gam_q, qf[3] * gam_q);
-                        const uint32_t b0 = pack_h2(qf[4] * gam_q, qf[5] * gam_q), b1 = pack_h2(qf[6] * gam_q, qf[7] * gam_q);
-                        const bool odd = g & 1;
-                        const uint32_t r0 = __shfl_xor(odd ? a0 : b0, 16), r1 = __shfl_xor(odd ? a1 : b1, 16);
-                        u32x4 o4;
-                        if (odd) { o4[0] = r0; o4[1] = r1; o4[2] = b0; o4[3] = b1; }
-                        else     { o4[0] = a0; o4[1] = a1; o4[2] = r0; o4[3] = r1; }
-                        slot_store16<kPolicy>(out, kOffQp + frag_rts(tok >> 5, ks, g >> 1) * kFragBytes + ((tok & 31) + 32 * (g & 1)) * 16, o4);
-                    }
+                    float gk[8], qp[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) { gk[e] = -kf[e] * gam; qp[e] = qf[e] * gam_q; }
+                    put_frag(out, kOffKg, ks, tok, g, gk);
+                    put_frag(out, kOffQp, ks, tok, g, qp);
                 }
                 {
                     f32x4 akk = {0.f, 0.f, 0.f, 0.f}, aqk = {0.f, 0.f, 0.f, 0.f};
@@ -861,7 +798,7 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
                     rq[e] = qf[e] * rf;
                     cs[e] = kf[e] * sf;
                     cd[e] = cs[e] * Ti[e];                                // k 2^(-G_i - D/2); 0 for a strong channel
-                    gk[e] = rk[e] * P[e];                                 // Gamma . K
+                    gk[e] = -rk[e] * P[e];                                // -Gamma . K
                     qp[e] = rq[e] * (P[e] * scale);                       // scale * Gamma . Q
                     kp[e] = cs[e] * E[e];                                 // Gamma^{i->C} . K
                 }
@@ -893,23 +830,10 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
                     *reinterpret_cast<u32x4 *>(lds + kColS + ((((R + 3) * (R + 2) / 2 + R) * 4 + ks) * 64 + lane) * 16) = t;
                 }
 #pragma unroll
-                for (int w = 0; w < 4; ++w) t[w] = pack_h2(gk[2 * w], gk[2 * w + 1]);
-                *reinterpret_cast<u32x4 *>(lds + kGK + (tok * kLdH + 32 * ks + 8 * g) * 2) = t;
-#pragma unroll
                 for (int w = 0; w < 4; ++w) t[w] = pack_h2(kp[2 * w], kp[2 * w + 1]);
                 *reinterpret_cast<u32x4 *>(lds + kKp + (tok * kLdH + 32 * ks + 8 * g) * 2) = t;
-                // Gamma.Q goes straight to the workspace in MFMA register order: lanes g and g^1 swap one
-                // 4-channel piece each so that every lane ends up with a complete 16-byte slot
-                {
-                    const uint32_t a0 = pack_h2(qp[0], qp[1]), a1 = pack_h2(qp[2], qp[3]);
-                    const uint32_t b0 = pack_h2(qp[4], qp[5]), b1 = pack_h2(qp[6], qp[7]);
-                    const bool odd = g & 1;
-                    const uint32_t r0 = __shfl_xor(odd ? a0 : b0, 16), r1 = __shfl_xor(odd ? a1 : b1, 16);
-                    u32x4 o4;
-                    if (odd) { o4[0] = r0; o4[1] = r1; o4[2] = b0; o4[3] = b1; }
-                    else     { o4[0] = a0; o4[1] = a1; o4[2] = r0; o4[3] = r1; }
-                    slot_store16<kPolicy>(out, kOffQp + frag_rts(tok >> 5, ks, g >> 1) * kFragBytes + ((tok & 31) + 32 * (g & 1)) * 16, o4);
-                }
+                put_frag(out, kOffKg, ks, tok, g, gk);
+                put_frag(out, kOffQp, ks, tok, g, qp);
             }
             // ---- A_kk, A_qk tiles of sub-chunk row R on the matrix cores (16x16, K = 128) ----
             {

@@ -5,15 +5,20 @@
 // order of the 32x32x16 f16 MFMA so that kda_scan moves them with straight
 // 16-byte copies and never transposes anything:
 //
-//   Wn   -W            A operand [token r][dk]      frags [rho][tau][s]      fp16
+//   Kg   -Gamma.K      A operand [token r][dk]      frags [rho][tau][s]      fp16
 //   Qp   Gamma.Q       A operand [token r][dk]      frags [rho][tau][s]      fp16
 //   Kt   (Gamma^{i->C}.K)^T  A operand [dk][token]  frags [tau][rho][s]      fp16
+//   M    (I + StrictTril(Diag(beta) A_kk))^-1 Diag(beta)
+//                      A operand [token r][token i] frags (0,0,s) (1,0,s) (1,1,s) fp16
 //   Aqk  Tril(A_qk)    A operand [token r][token i] frags (0,0,s) (1,0,s) (1,1,s) fp16
 //   gC   gamma^C       [dk]                                                  fp32
-//   U                  C/D tiles [rho][ct] in accumulator order              fp16
 //
-// rho: 32-token tile, tau: 32-channel d_k tile, ct: 32-column d_v tile, s: one
-// K-step of 16.  A "frag" is 64 lanes x 8 halfs (1 KiB); lane L = (x = L % 32,
+// W = M (Gamma.K) and U = M V are never formed: the sequential stage takes U - W S = M (V - (Gamma.K) S) with V as it
+// stands in the input.  That is six products more in its step, and 20 KiB less through the memory system per chunk (the
+// per-chunk stage neither reads V nor writes U, M is 6 KiB), 217 instead of 237 KiB in all.  2^17 tokens x 32 heads
+// 2987 -> 2749 us, 333 tokens x 32 heads 31.5 -> 29.1, 4 x 4096 x 16 heads 223.3 -> 219.9.
+//
+// rho: 32-token tile, tau: 32-channel d_k tile, s: one K-step of 16.  A "frag" is 64 lanes x 8 halfs (1 KiB); lane L = (x = L % 32,
 // hh = L / 32) holds row x of the tile and the 8 contraction slots e = 0..7 of
 // K-step s, where slot (hh, e) stands for contraction index
 //
@@ -34,32 +39,29 @@ namespace mfma {
 constexpr int D = 128;                        // d_k = d_v of this path
 constexpr int kFragBytes = 1024;
 
-constexpr int kOffWn = 0;                     // 16 frags
-constexpr int kOffQp = kOffWn + 16 * kFragBytes;
+constexpr int kOffKg = 0;                     // 16 frags
+constexpr int kOffQp = kOffKg + 16 * kFragBytes;
 constexpr int kOffKt = kOffQp + 16 * kFragBytes;
-constexpr int kOffAqk = kOffKt + 16 * kFragBytes;   // 6 frags: token tile (0,1) of Tril(A_qk) is zero
+constexpr int kOffM = kOffKt + 16 * kFragBytes;     // 6 frags: token tile (0,1) of M and of Tril(A_qk) is zero
+constexpr int kOffAqk = kOffM + 6 * kFragBytes;
 constexpr int kOffGc = kOffAqk + 6 * kFragBytes;
-constexpr int kLdsBlockBytes = kOffGc + D * 4;      // what kda_scan stages through LDS
-constexpr int kUTileBytes = 64 * 16 * 2;            // one 32x32 tile of U: 16 halfs per lane, two 16-byte units
-constexpr int kOffU = kLdsBlockBytes;               // 8 tiles x 2 KiB
-constexpr int kSlotBytes = kOffU + 8 * kUTileBytes; // 72192
+constexpr int kSlotBytes = 72192;                   // the published size (callers keep workspaces); 10 KiB of it are spare
 // Output gate (fused epilogue): the gate logits of a chunk, bf16, in the accumulator order of the
 // sequential kernel's O tiles: tile (rho, ct) = [2 units][64 lanes][16 B], lane (x, hh) holds the
 // columns 32 ct + 8 q + 4 hh + 0..3 of token 32 rho + x, q = 0..3 (unit q / 2, bytes 8 (q % 2) ..).
 constexpr int kGateTileBytes = 64 * 16 * 2;
 constexpr int kGateSlotBytes = 8 * kGateTileBytes;  // 16384, one per workspace slot when the gate is on
 
-static_assert(kLdsBlockBytes % 16 == 0, "LDS block must be a whole number of 16-byte units");
-static_assert(kSlotBytes % 256 == 0, "slots must stay 256-byte aligned");
+static_assert(kOffGc + D * 4 <= kSlotBytes && kSlotBytes % 256 == 0, "slots must stay 256-byte aligned");
 
 // Contraction index inside a 32-wide tile for K-step s, lane half hh, slot e.
 __host__ __device__ constexpr int kidx(int s, int hh, int e) { return 16 * s + 8 * (e >> 2) + 4 * hh + (e & 3); }
 // Row inside a 32x32 accumulator tile held by register j of a lane in half hh.
 __host__ __device__ constexpr int acc_row(int j, int hh) { return 8 * (j >> 2) + 4 * hh + (j & 3); }
 
-constexpr int frag_rts(int r, int t, int s) { return (r * 4 + t) * 2 + s; }   // Wn, Qp: [rho][tau][s]
+constexpr int frag_rts(int r, int t, int s) { return (r * 4 + t) * 2 + s; }   // Kg, Qp: [rho][tau][s]
 constexpr int frag_trs(int t, int r, int s) { return (t * 2 + r) * 2 + s; }   // Kt: [tau][rho][s]
-constexpr int frag_aqk(int rr, int ri, int s) { return (rr + ri) * 2 + s; }   // (0,0) (1,0) (1,1)
+constexpr int frag_tri(int rr, int ri, int s) { return (rr + ri) * 2 + s; }   // M, Aqk: (0,0) (1,0) (1,1)
 
 // Time-split scan: at most this many ranges per sequence, offered to calls with at most this many
 // (sequence, head) pairs whose longest sequence has at least kSplitMinChunks chunks.  The more pairs, the

@@ -47,7 +47,7 @@ __device__ __forceinline__ int64_t item_index(int64_t wg, int t, int per_wg, int
 }
 template <bool kGate> __device__ __forceinline__ IntraArgs intra_args(const FusedArgs &a)
 {
-    return IntraArgs{a.q, a.k, a.v, a.log_alpha, a.beta, a.cu, a.ws, a.T, a.H, a.seg_chunks, a.seg_index, a.scale,
+    return IntraArgs{a.q, a.k, a.log_alpha, a.beta, a.cu, a.ws, a.T, a.H, a.seg_chunks, a.seg_index, a.scale,
                      a.ready, a.epoch, a.raw, kGate ? a.out_gate : nullptr, kGate ? a.gate_ws : nullptr,
                      kGate ? a.norm_w : nullptr, a.status};
 }
@@ -82,7 +82,7 @@ void kda_prefill_kernel(const FusedArgs a)
             if (nchunks < 0) nchunks = 0;
             if (nchunks > a.seg_chunks) nchunks = a.seg_chunks;
             scan4::split_role<kOutBf16, kGate>(lds, a.split, a.ws + pair * a.seg_chunks * (int64_t)kSlotBytes,
-                                               a.ready + pair * a.seg_chunks, a.state_in, a.state_out, a.o, pair, a.pairs, y,
+                                               a.ready + pair * a.seg_chunks, a.v, a.state_in, a.state_out, a.o, pair, a.pairs, y,
                                                tok_base, len, a.H, h, cbase, nchunks, a.epoch, a.status, a.wait_limit,
                                                kGate ? a.gate_ws + pair * a.seg_chunks * (int64_t)kGateSlotBytes : nullptr,
                                                a.rms_eps);
@@ -139,7 +139,7 @@ void kda_prefill_kernel(const FusedArgs a)
         const int64_t st_base = pair * (int64_t)(D * D) + 32 * wave + (lane & 31);
         const uint8_t *slot0 = a.ws + pair * a.seg_chunks * (int64_t)kSlotBytes;
         const scan4::GateParams gate = {kGate ? a.gate_ws + pair * a.seg_chunks * (int64_t)kGateSlotBytes : nullptr, a.rms_eps};
-        scan4::kda_scan4_body<true, kOutBf16, kRoleFull, kGate>(lds, slot0, (int64_t)kSlotBytes, a.state_in, a.state_out,
+        scan4::kda_scan4_body<true, kOutBf16, kRoleFull, kGate>(lds, slot0, (int64_t)kSlotBytes, a.v, a.state_in, a.state_out,
                                                                 a.o, st_base, tok_base, len, a.H, c_begin, c_end, h,
                                                                 a.ready + pair * a.seg_chunks, a.epoch, a.status,
                                                                 a.wait_limit, false, gate);

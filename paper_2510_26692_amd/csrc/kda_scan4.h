@@ -3,26 +3,26 @@
 // a compute unit (80 KiB of LDS, at most 256 registers per lane), so that it shares a compute unit
 // with a workgroup of the per-chunk stage or with another one of its kind.
 //
-// Per chunk of one (sequence, head), with the operands the per-chunk stage left in the slot:
+// Per chunk of one (sequence, head), with the operands the per-chunk stage left in the slot and V from the input:
 //
-//     V_new = U - W S          O = (Gamma.Q) S + Tril(A_qk) V_new
+//     Y = V - (Gamma.K) S      V_new = M Y      O = (Gamma.Q) S + Tril(A_qk) V_new
 //     S <- Diag(gamma^C) S + (Gamma^{i->C}.K)^T V_new
 //
 // Every column of S is an independent recurrence.  Wave c owns the 32 columns 32 c .. 32 c + 31 of
-// S for ALL of d_k (four 32x32 accumulator tiles), and with them the same columns of V_new and O
+// S for ALL of d_k (four 32x32 accumulator tiles), and with them the same columns of Y, V_new and O
 // for both 32-token tiles: nothing is exchanged between the waves, and the B operands of every
-// product (S, V_new as fp16) come straight out of the wave's own accumulators.  What the waves
-// share is read-only: the A operands W, Gamma.Q, (Gamma^{i->C}.K)^T and Tril(A_qk), 54 fragments of
+// product (S, Y, V_new as fp16) come straight out of the wave's own accumulators.  What the waves
+// share is read-only: the A operands Gamma.K, Gamma.Q, (Gamma^{i->C}.K)^T, M and Tril(A_qk), 60 fragments of
 // 1 KiB per chunk, which all four waves read from LDS.
 //
-// Operand path.  The slot is cut into four pieces in the order a step consumes them: W (16 KiB),
-// Gamma.Q (16 KiB), K^T (16 KiB) and a small one (A_qk and gamma^C, 8 KiB).  LDS holds a ring of
-// four 16 KiB regions and two small ones.  Pieces arrive by LDS-direct loads (global_load_lds:
-// no registers in between); a region is refilled as soon as all waves are through with it, with
-// the piece that is consumed one whole step later, so about 54 KiB are in flight at any time.  A
-// step has three phases (V_new; O; state update) and one workgroup barrier in front of each, which
-// says two things at once: every wave's part of the phase's piece has landed, and every wave is done
-// reading the piece of the phase before.  The wave's own U tile (4 KiB) travels through registers.
+// Operand path.  LDS holds one step's operands: Gamma.K, V, Gamma.Q and K^T, 16 KiB each, and a small piece (M,
+// A_qk and gamma^C, 13 KiB).  All of them arrive by LDS-direct loads (global_load_lds, buffer_load .. lds: no registers
+// in between); a piece's place is refilled for the next step as soon as nobody reads it any more, so every piece has
+// the two phases of a step it is not used in to arrive.  A step has three phases (Y; V_new and O; state update) and
+// one workgroup barrier in front of each, which says two things at once: every wave's part of the phase's pieces has
+// landed, and every wave is done reading the pieces of the phase before.  V is each wave's own affair: its 32 columns
+// (4 KiB, rows of the input) go to its quarter of the region and are turned into accumulator order on the way to
+// registers at the beginning of phase Y; that quarter is refilled as soon as they are there.
 //
 // All vector-memory instructions of the loop are issued from inline assembly in a fixed order
 // and waited for with explicit vmcnt counts (they retire in issue order), because a wait that the
@@ -38,26 +38,25 @@ namespace mfma {
 
 // What one pass over a range of chunks computes (the time-split scan uses the last two):
 //   kRoleFull   the scan itself: state from state_in (zero if NULL), outputs written
-//   kRoleT      the d_k x d_k transition of the range: starts from the identity, drops U (the
+//   kRoleT      the d_k x d_k transition of the range: starts from the identity, drops V (the
 //               recurrence is affine in the state: S_out = T S_in + B), writes no output
-//   kRoleB      the offset of the range: starts from zero, keeps U, writes no output
+//   kRoleB      the offset of the range: starts from zero, keeps V, writes no output
 // A kRoleT pass returns whether the transition it ended with is exactly zero (every other pass: false).
 constexpr int kRoleFull = 0, kRoleT = 1, kRoleB = 2;
 
 namespace scan4 {
 
 
-constexpr int kBig = 16 * kFragBytes;                       // W, Gamma.Q or K^T of one chunk
-constexpr int kSmall = 8 * kFragBytes;                      // Tril(A_qk), gamma^C (and the first bytes of U, unused)
-constexpr int kSmallRegions = 4 * kBig;                     // byte offset of the two small regions
-constexpr int kLds = kSmallRegions + 2 * kSmall;            // 81920
-// The tail of a small region, behind Tril(A_qk) and gamma^C, receives bytes nobody reads; while its step is being
-// worked on it carries the partial mean squares of the output gate: [token tile][wave][32 tokens] fp32.
-constexpr int kGateRed = kOffGc - kOffAqk + D * 4;          // 6656
-static_assert(kGateRed + 2 * 4 * 32 * 4 <= kSmall, "the partial sums fit the tail of the small region");
-static_assert(kOffQp == kBig && kOffKt == 2 * kBig && kOffAqk == 3 * kBig, "pieces follow the slot layout");
-static_assert(kOffAqk + kSmall <= kSlotBytes && kOffGc + D * 4 <= kOffAqk + kSmall, "the small piece stays inside the slot");
-static_assert(kLds <= 80 * 1024, "two workgroups must fit a compute unit");
+constexpr int kBig = 16 * kFragBytes;                       // Gamma.K, V, Gamma.Q or K^T of one chunk
+constexpr int kPlaceK = 0, kPlaceV = kBig, kPlaceQ = 2 * kBig, kPlaceKt = 3 * kBig;
+constexpr int kSmall = 4 * kBig;                            // byte offset of the small piece: M, Tril(A_qk), gamma^C twice
+constexpr int kSmallGc = 12 * kFragBytes;                   // .. gamma^C in it
+// Partial mean squares of the output gate, [token tile][wave][32 tokens] fp32; kRoleT's four flags
+constexpr int kRed = kSmall + kSmallGc + 2 * D * 4;
+constexpr int kLds = 80 * 1024;                             // two workgroups fit a compute unit
+static_assert(kRed + 2 * 4 * 32 * 4 <= kLds - 16, "the last word is the time-split scan's");
+static_assert(kOffAqk == kOffM + 6 * kFragBytes && kOffGc == kOffM + kSmallGc,
+              "pieces follow the slot layout");
 
 // compile-time loop: f(integral_constant<int, I>) for I in [0, N)
 template <int I, int N, typename F>
@@ -83,14 +82,6 @@ __device__ __forceinline__ void dma4(uint32_t m0, uint32_t voff, const uint8_t *
                  "global_load_lds_dwordx4 %1, %2 offset:3072 sc1"
                  :: "s"(m0), "v"(voff), "s"(src) : "memory", "m0");
 }
-__device__ __forceinline__ void dma2(uint32_t m0, uint32_t voff, const uint8_t *src)
-{
-    asm volatile("s_mov_b32 m0, %0\n\t"
-                 "s_nop 0\n\t"
-                 "global_load_lds_dwordx4 %1, %2 sc1\n\t"
-                 "global_load_lds_dwordx4 %1, %2 offset:1024 sc1"
-                 :: "s"(m0), "v"(voff), "s"(src) : "memory", "m0");
-}
 // One LDS-direct load of 16 bytes per lane: LDS byte m0 + 16 L <- src[voff(L)].
 __device__ __forceinline__ void dma1(uint32_t m0, uint32_t voff, const uint8_t *src)
 {
@@ -98,6 +89,22 @@ __device__ __forceinline__ void dma1(uint32_t m0, uint32_t voff, const uint8_t *
                  "s_nop 0\n\t"
                  "global_load_lds_dwordx4 %1, %2 sc1"
                  :: "s"(m0), "v"(voff), "s"(src) : "memory", "m0");
+}
+// The same of 4 bytes per lane: LDS byte m0 + 4 L <- src[voff(L)].
+__device__ __forceinline__ void dma1_word(uint32_t m0, uint32_t voff, const uint8_t *src)
+{
+    asm volatile("s_mov_b32 m0, %0\n\t"
+                 "s_nop 0\n\t"
+                 "global_load_lds_dword %1, %2 sc1"
+                 :: "s"(m0), "v"(voff), "s"(src) : "memory", "m0");
+}
+// One LDS-direct load of 16 bytes per lane through a descriptor (zeros past its end): LDS byte m0 + 16 L <- row byte voff(L).
+__device__ __forceinline__ void dma1_row(uint32_t m0, uint32_t voff, const u32x4 &rsrc)
+{
+    asm volatile("s_mov_b32 m0, %0\n\t"
+                 "s_nop 0\n\t"
+                 "buffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :: "s"(m0), "v"(voff), "s"(rsrc) : "memory", "m0");
 }
 __device__ __forceinline__ void load1(u32x4 &a, uint32_t voff, const uint8_t *src)
 {
@@ -107,6 +114,11 @@ __device__ __forceinline__ void load1(u32x4 &a, uint32_t voff, const uint8_t *sr
 template <int kCtrl> __device__ __forceinline__ float quad_perm(float v)
 {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xf, 0xf, true));
+}
+// every lane of each row of 16 lanes receives the value of the row's lane N
+template <int N> __device__ __forceinline__ float row_broadcast(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + N, 0xf, 0xf, true));
 }
 // 4 x 4 transpose across the four lanes of a quad, one component: on entry r[q] belongs to register
 // group q of this lane, on exit r[i] is what lane 4 (lane / 4) + i held for group lane % 4.
@@ -125,13 +137,6 @@ __device__ __forceinline__ void quad_transpose(float (&r)[4], int lane)
         const float t = quad_perm<0x4E>(l1 ? r[b] : r[b + 2]);
         if (l1) r[b] = t; else r[b + 2] = t;
     }
-}
-// Two 16-byte loads into registers (valid only after the matching wait).
-__device__ __forceinline__ void load2(u32x4 &a, u32x4 &b, uint32_t voff, const uint8_t *src)
-{
-    asm volatile("global_load_dwordx4 %0, %2, %3 sc1\n\t"
-                 "global_load_dwordx4 %1, %2, %3 offset:1024 sc1"
-                 : "=&v"(a), "=&v"(b) : "v"(voff), "s"(src) : "memory");
 }
 __device__ __forceinline__ void load_word(uint32_t &w, uint32_t voff, const uint32_t *src)
 {
@@ -166,6 +171,7 @@ __device__ __noinline__ bool wait_flag(const uint32_t *flag, uint32_t epoch, uin
 
 // One pass over the chunks [c_begin, c_end) of one (sequence, head): 256 threads, kLds bytes at `lds`.
 //   slot0, slot_stride   the slot of chunk c_begin and the byte distance to the next chunk's
+//   v                    the input [tokens][heads][128] bf16
 //   ready                flag of chunk c_begin (consecutive chunks follow); epoch: value of a raised flag
 //   st_base              element offset of this lane's column in the [d_k][d_v] states: pair * D * D + 32 c + x
 //   poisoned             start from NaN instead of state_in (the caller could not obtain the initial state)
@@ -181,7 +187,7 @@ struct GateParams {
     float eps;
 };
 template <bool kFlags, bool kOutBf16, int kRole = kRoleFull, bool kGate = false>
-__device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot0, int64_t slot_stride,
+__device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot0, int64_t slot_stride, const uint16_t *v,
                                                const float *state_in, float *state_out, void *o, int64_t st_base,
                                                int64_t tok_base, int64_t len, int H, int64_t c_begin, int64_t c_end,
                                                int h, const uint32_t *ready, uint32_t epoch, uint32_t *status,
@@ -199,10 +205,14 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
     constexpr bool kFull = kRole == kRoleFull;
 
     // vector-memory instructions per step, in issue order (see the loop)
-    constexpr int nFlag = kFlags ? 1 : 0, nW = 4, nA = 2, nU = (kRole != kRoleT) ? 4 : 0;
-    constexpr int nQ = kFull ? 4 : 0, nSt = kFull ? (kOutBf16 ? 4 : 8) : 0, nK = 4;
-    constexpr int G0 = kGate ? 4 : 0;                             // the step's own gate factors, first thing in phase V
-    constexpr int G1 = nFlag + nW + nA + nU, G2 = nQ, G3 = nSt, G4 = nK;
+    constexpr bool kTakesV = kRole != kRoleT;
+    constexpr bool kRowsOut = kFull && !kOutBf16 && !kGate;       // O in the lanes as it is stored: a column per lane
+    constexpr int nSt = kFull ? (kOutBf16 ? 4 : kRowsOut ? 32 : 8) : 0;
+    constexpr int G0 = kGate ? 4 : 0;                             // phase Y: the step's own gate factors
+    constexpr int G1 = (kFlags ? 1 : 0) + 4;                      //          a flag and K^T of this step
+    constexpr int G2 = kTakesV ? 4 : 0;                           //          V of the next step
+    constexpr int G3 = 4;                                         // phase O: Gamma.K of the next step
+    constexpr int G4 = 4 + (kFull ? 4 : 0), G5 = nSt;             // phase S: the small piece and Gamma.Q of the next step; this step's output
 
     // own state tiles in accumulator order: S[t][j] = S(dk = 32 t + acc_row(j, hh), dv = 32 c + x)
     f32x16 S[4];
@@ -220,34 +230,42 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
 
     if (c_begin < c_end) {
         const uint32_t lds0 = (uint32_t)(uintptr_t)lds;          // LDS byte address of the ring
-        const int64_t nsteps = c_end - c_begin;
-        // this wave's share of a piece: fragments 4 c .. 4 c + 3 of a big one, 2 c, 2 c + 1 of a small one
-        const uint32_t voff_big = lane16 + (uint32_t)c * 4096, voff_small = lane16 + (uint32_t)c * 2048;
-        const uint32_t voff_u = lane16 + (uint32_t)c * kUTileBytes;
+        const int nsteps = (int)(c_end - c_begin);               // (a segment holds at most 65 535 chunk indices)
+        const int64_t tok0 = tok_base + c_begin * kChunk, left64 = len - c_begin * kChunk;
+        const int left = (int)(left64 < (1 << 30) ? left64 : (1 << 30));        // tokens from the pass's first on
+        auto tokens_of = [&](int rel) __attribute__((always_inline)) { const int n = left - rel * kChunk; return n < kChunk ? n : kChunk; };
+        // this wave's share of a piece: fragments 4 c .. 4 c + 3 of a big one, 3 c .. 3 c + 2 of the small one and half of gamma^C
+        const uint32_t voff_big = lane16 + (uint32_t)c * 4096, voff_small = lane16 + (uint32_t)c * 3072;
+        const uint32_t voff_gc = (uint32_t)lane * 4 + (uint32_t)(c & 1) * 256;
+        // its 64 bytes of a row of V: load i takes 16 tokens, four lanes each
+        const uint32_t v_pitch = (uint32_t)H * (D * 2);
+        const uint32_t voff_v = (uint32_t)(lane >> 2) * v_pitch + (uint32_t)c * 64 + (uint32_t)(lane & 3) * 16;
         // gate factors of this wave: tiles (P, c), P = 0, 1, two 16-byte units per lane and tile
         const uint32_t voff_g = lane16 + (uint32_t)c * kGateTileBytes;
         bool gave_up = false;
-        auto gate_of = [&](int64_t rel) __attribute__((always_inline)) {       // clamped past the end
-            return gate.factors + ((rel < nsteps) ? rel : nsteps - 1) * (int64_t)kGateSlotBytes;
+        // (past the end: the last chunk once more)
+        auto gate_of = [&](int rel) __attribute__((always_inline)) { return gate.factors + (int64_t)(rel < nsteps ? rel : nsteps - 1) * kGateSlotBytes; };
+        auto slot_of = [&](int rel) __attribute__((always_inline)) { return slot0 + (int64_t)(rel < nsteps ? rel : nsteps - 1) * slot_stride; };
+        auto flag_of = [&](int rel) __attribute__((always_inline)) { return ready + (rel < nsteps ? rel : nsteps - 1); };
+        // V of a chunk, its real tokens
+        auto rows_of = [&](int rel) __attribute__((always_inline)) {
+            const int r = rel < nsteps ? rel : nsteps - 1;
+            const uint64_t base = (uint64_t)(uintptr_t)(v + ((tok0 + r * kChunk) * H + h) * (int64_t)D);
+            return u32x4{(uint32_t)uni((int)(uint32_t)base), (uint32_t)uni((int)(uint32_t)(base >> 32)) & 0xffffu,
+                         (uint32_t)uni((int)((uint32_t)(tokens_of(r) - 1) * v_pitch + D * 2)), 0x00020000u};
         };
-
-        auto slot_of = [&](int64_t rel) __attribute__((always_inline)) {       // clamped past the end
-            return slot0 + ((rel < nsteps) ? rel : nsteps - 1) * slot_stride;
+        h8 Sb[8];                                                // fp16 copy of S as it enters a step: (tau, s) -> Sb[2 tau + s]
+        auto copy_state = [&](const int t, const int k) __attribute__((always_inline)) {     // a quarter of tile t
+#pragma unroll
+            for (int z = 0; z < 4; ++z) Sb[2 * t + k / 2][4 * (k % 2) + z] = (_Float16)S[t][4 * k + z];
         };
-        auto flag_of = [&](int64_t rel) __attribute__((always_inline)) {
-            return ready + ((rel < nsteps) ? rel : nsteps - 1);
-        };
-        auto issue_w = [&](const uint8_t *slot, int region) __attribute__((always_inline)) {
-            dma4(lds0 + (uint32_t)region * kBig + (uint32_t)c * 4096, voff_big, slot + kOffWn);
-        };
-        auto issue_q = [&](const uint8_t *slot, int region) __attribute__((always_inline)) {
-            if (kFull) dma4(lds0 + (uint32_t)region * kBig + (uint32_t)c * 4096, voff_big, slot + kOffQp);
-        };
-        auto issue_k = [&](const uint8_t *slot, int region) __attribute__((always_inline)) {
-            dma4(lds0 + (uint32_t)region * kBig + (uint32_t)c * 4096, voff_big, slot + kOffKt);
-        };
-        auto issue_a = [&](const uint8_t *slot, int small) __attribute__((always_inline)) {
-            dma2(lds0 + kSmallRegions + (uint32_t)small * kSmall + (uint32_t)c * 2048, voff_small, slot + kOffAqk);
+        // (done here: left to itself the compiler moves the copies to where they are first used, behind the barrier)
+        auto pin_state = [&](const int t) __attribute__((always_inline)) { asm volatile("" : "+v"(Sb[2 * t]), "+v"(Sb[2 * t + 1])); };
+        auto copy_states = [&]() __attribute__((always_inline)) {                            // of what phase Y does not copy itself
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) copy_state(t, k);
         };
         auto poison = [&]() __attribute__((always_inline)) {
             gave_up = true;
@@ -257,60 +275,57 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
             for (int t = 0; t < 4; ++t)
 #pragma unroll
                 for (int j = 0; j < 16; ++j) S[t][j] = bad;
+            if (!kGate) copy_states();
         };
 
+        u32x2 vt[8];                                             // V in accumulator order: registers 4 q .. 4 q + 3 of tile P in vt[4 P + q]
+        // (64 bytes a token: the 32 lanes that go together read 32 different pairs of banks)
+        auto get_v = [&]() __attribute__((always_inline)) {
+            const uint8_t *blk = lds + kPlaceV + c * 4096 + (4 * hh) * 64 + 32 * ((lane >> 4) & 1);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) vt[i] = lds_read_tr4(blk + 8 * i * 64, 32, lane);
+        };
+        // where this wave's part of a piece goes in LDS
+        const uint32_t m0K = lds0 + kPlaceK + (uint32_t)c * 4096, m0V = lds0 + kPlaceV + (uint32_t)c * 4096;
+        const uint32_t m0Q = lds0 + kPlaceQ + (uint32_t)c * 4096, m0Kt = lds0 + kPlaceKt + (uint32_t)c * 4096;
+        const uint32_t m0M = lds0 + kSmall + (uint32_t)c * 3072, m0Gc = lds0 + kSmall + kSmallGc + (uint32_t)c * 256;
+
         // ---- prologue: the whole first slot, waited for in full ----
-        u32x4 ur[4];                                             // U tiles (0, c), (1, c): two 16-byte units each
         uint32_t seen = epoch;
         if (kFlags && !wait_flag(flag_of(0), epoch, wait_limit)) poison();
         {
             const uint8_t *s0 = slot_of(0);
             if (kFlags) load_word(seen, 0u, flag_of(1));
-            issue_w(s0, 0);
-            issue_a(s0, 0);
-            if (kRole != kRoleT) {
-                load2(ur[0], ur[1], voff_u, s0 + kOffU);
-                load2(ur[2], ur[3], voff_u, s0 + kOffU + 4 * kUTileBytes);
+            dma4(m0K, voff_big, s0 + kOffKg);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) dma1(m0M + j * 1024, voff_small, s0 + kOffM + j * 1024);
+            dma1_word(m0Gc, voff_gc, s0 + kOffGc);
+            if (kTakesV) {
+                const u32x4 rows = rows_of(0);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) dma1_row(m0V + j * 1024, voff_v + (uint32_t)(16 * j) * v_pitch, rows);
             }
-            issue_q(s0, 1);
-            issue_k(s0, 2);
+            if (kFull) dma4(m0Q, voff_big, s0 + kOffQp);
         }
         phase_barrier<0>();
+        if (!kGate) copy_states();
         bool next_ok = !kFlags || (uint32_t)__builtin_amdgcn_readfirstlane((int)seen) == epoch;
-
-        f32x16 av[2];                                            // V_new tiles (token tile P, columns of this wave)
-        auto take_u = [&]() __attribute__((always_inline)) {
-#pragma unroll
-            for (int P = 0; P < 2; ++P)
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int z = 0; z < 4; ++z) {
-                        const uint32_t w2 = ur[2 * P + i][z];
-                        const h2 pr = __builtin_bit_cast(h2, w2);
-                        av[P][8 * i + 2 * z] = (kRole == kRoleT) ? 0.f : (float)pr[0];
-                        av[P][8 * i + 2 * z + 1] = (kRole == kRoleT) ? 0.f : (float)pr[1];
-                    }
-        };
-        take_u();
 
         const uint32_t o_rstride = (uint32_t)H * D * (kOutBf16 ? 2 : 4);   // bytes between consecutive tokens of o
         constexpr int LA = 4, RING = LA + 2;                     // operand fragments read ahead of the product that uses them
         // Vector-memory instructions are handed to the memory pipe one at a time between the matrix
         // products (a burst of them stalls the wave at issue, and the products behind it), in this order:
-        //   phase V  (gate: the factors of this step, G0,) the flag of the step after next, then W, the small piece and
-        //            U of the next step                                                                 (G1)
-        //   phase O  Gamma.Q of the next step                                                          (G2)
-        //   phase S  K^T of the next step (G4), then this step's output stores                         (G3)
-        constexpr int kStores = nSt;
+        //   phase Y  (gate: the factors of this step, G0,) the flag of the step after next, K^T of this step (G1), V of the next (G2)
+        //   phase O  Gamma.K of the next step (G3)
+        //   phase S  the small piece and Gamma.Q of the next step (G4), then this step's output stores (G5)
+        // Where the next step's operands are, moved on in phase S, where the scalar instructions hide behind the products
+        const uint8_t *cur = slot0, *nxt = slot_of(1), *gate_cur = kGate ? gate_of(0) : nullptr;
+        u32x4 rows = kTakesV ? rows_of(1) : u32x4{0u, 0u, 0u, 0u};
+        uint8_t *obase = static_cast<uint8_t *>(o) + (tok0 * H + h) * (int64_t)(D * (kOutBf16 ? 2 : 4));
 
-        for (int64_t rel = 0; rel < nsteps; ++rel) {
-            // pieces of this step sit in regions rW (W), rQ (Gamma.Q), rK (K^T); the region after them takes W of the next step
-            const int p3 = (int)((3 * rel) & 3);
-            const int rW = p3, rQ = (p3 + 1) & 3, rK = (p3 + 2) & 3, rN = (p3 + 3) & 3;
-            const int sm = (int)(rel & 1);
-            const uint8_t *ldsW = lds + rW * kBig + lane16, *ldsQ = lds + rQ * kBig + lane16, *ldsK = lds + rK * kBig + lane16;
-            const uint8_t *ldsA = lds + kSmallRegions + sm * kSmall + lane16;
+        for (int rel = 0; rel < nsteps; ++rel) {
+            const uint8_t *ldsY = lds + kPlaceK + lane16, *ldsQ = lds + kPlaceQ + lane16, *ldsK = lds + kPlaceKt + lane16;
+            const uint8_t *ldsM = lds + kSmall + lane16, *ldsA = ldsM + 6 * kFragBytes;
             // (kGate: what depends on the lane number is formed afresh in every step: carried in registers across the loop
             // these were the values too many, and a reload from scratch memory waits for every load in flight, once per
             // step; a volatile statement, or the compiler forms them once ahead of the loop all the same)
@@ -320,100 +335,147 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                 return l;
             };
             const int hh_step = kGate ? (lane_now() >> 5) : hh;
-            const float *gc = reinterpret_cast<const float *>(lds + kSmallRegions + sm * kSmall + (kOffGc - kOffAqk)) + 4 * hh_step;
-            const uint8_t *nxt = slot_of(rel + 1);
-            const uint8_t *gate_cur = kGate ? gate_of(rel) : nullptr;
+            // gamma^C: lane l of a row of 16 lanes holds that of the row its register l of a tile stands for
+            const float *gc = reinterpret_cast<const float *>(lds + kSmall + kSmallGc) + (kGate ? acc_row(lane_now() & 15, hh_step) : acc_row(lane & 15, hh));
             u32x4 gr[4];                                         // kGate: gate factors of tiles (0, c), (1, c), two 16-byte units each
-            float *red = reinterpret_cast<float *>(lds + kSmallRegions + sm * kSmall + kGateRed);   // idle tail of the small region: kGate's partial mean squares, kRoleT's flags
-            const uint32_t m0W = lds0 + (uint32_t)rN * kBig + (uint32_t)c * 4096;      // W of the next step
-            const uint32_t m0Q = lds0 + (uint32_t)rW * kBig + (uint32_t)c * 4096;      // Gamma.Q of the next step (over this step's W)
-            const uint32_t m0K = lds0 + (uint32_t)rQ * kBig + (uint32_t)c * 4096;      // K^T of the next step (over this step's Gamma.Q)
-            const uint32_t m0A = lds0 + kSmallRegions + (uint32_t)(sm ^ 1) * kSmall + (uint32_t)c * 2048;
-
+            float *red = reinterpret_cast<float *>(lds + kRed);
             if (kFlags && !next_ok && !gave_up) {
                 if (!wait_flag(flag_of(rel + 1), epoch, wait_limit)) poison();
             }
-            const uint32_t *flag2 = kFlags ? flag_of(rel + 2) : nullptr;
             __builtin_amdgcn_sched_barrier(0);
 
-            // ---- phase V: V_new[P] = U[P] + (-W)(P, tau, s) S(tau, s), slot i: P = i % 2, (tau, s) = i / 2 ----
-            h8 Sb[8];                                            // fp16 copy of S as it enters the step: (tau, s) -> Sb[2 tau + s]
+            // ---- phase Y: Y[P] = V[P] + (-Gamma.K)(P, tau, s) S(tau, s), slot i: P = i / 8, (tau, s) = i % 8.  Tile 0 starts from
+            // zero and has its V added at the end, by which time V has come through the LDS; tile 1 starts from V ----
+            h8 Yb[2][2];                                         // fp16 copy of Y: registers 8 s .. 8 s + 7 of a tile are its slots of K-step s as a B operand
+            f32x16 av[2];                                        // Y, then V_new: token tile P, columns of this wave
+            auto v_of = [&](const int P, const int j) __attribute__((always_inline)) {
+                const uint32_t w = vt[4 * P + j / 4][(j % 4) / 2];
+                return kTakesV ? __uint_as_float((j & 1) ? (w & 0xffff0000u) : (w << 16)) : 0.f;
+            };
             {
                 h8 ring[RING];
                 auto frag = [&](const int i) __attribute__((always_inline)) {
-                    return *reinterpret_cast<const h8 *>(ldsW + frag_rts(i % 2, (i / 2) / 2, (i / 2) % 2) * kFragBytes);
+                    return *reinterpret_cast<const h8 *>(ldsY + frag_rts(i / 8, (i % 8) / 2, i % 2) * kFragBytes);
                 };
                 static_for<0, LA>([&](auto ic) __attribute__((always_inline)) { ring[decltype(ic)::value % RING] = frag(decltype(ic)::value); });
+                if (kTakesV) get_v();
+                if (kGate) { copy_state(0, 0); copy_state(0, 1); }
+                av[0] = f32x16{0.f};
                 static_for<0, 16>([&](auto ic) __attribute__((always_inline)) {
-                    constexpr int i = decltype(ic)::value, P = i % 2, tau = (i / 2) / 2, s = (i / 2) % 2;
+                    constexpr int i = decltype(ic)::value, P = i / 8, ks = i % 8;
                     if constexpr (i + LA < 16) ring[(i + LA) % RING] = frag(i + LA);
-                    if constexpr (P == 0) {
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) Sb[i / 2][e] = (_Float16)S[tau][8 * s + e];
+                    if constexpr (kGate ? P == 0 && ks < 7 : i == 2 || i == 4) {                         // (for the slot after the next, or the next)
+                        constexpr int t = kGate ? (ks + 1) / 2 : 3, k = kGate ? 2 * ((ks + 1) % 2) : i - 2;
+                        copy_state(t, k); copy_state(t, k + 1);
                     }
-                    av[P] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], Sb[i / 2], av[P], 0, 0, 0);
-                    // G0 (this step's gate factors), then G1, one instruction per slot
-                    constexpr int j = i - G0;
+                    av[P] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], Sb[ks], av[P], 0, 0, 0);
+                    // tile 1 of V (slots 4 .. 7), and Y of tile 0 (slots 9 .. 12)
+                    if constexpr (i >= 4 && i < 8) {
+#pragma unroll
+                        for (int z = 0; z < 4; ++z) av[1][4 * (i - 4) + z] = v_of(1, 4 * (i - 4) + z);
+                    }
+                    if constexpr (i >= 9 && i < 13) {
+                        constexpr int q = i - 9;
+#pragma unroll
+                        for (int z = 0; z < 4; ++z) Yb[0][q / 2][4 * (q % 2) + z] = (_Float16)(av[0][4 * q + z] + v_of(0, 4 * q + z));
+                    }
+                    // G0 (this step's gate factors), G1 and G2, one instruction per slot; V of the next step goes over that of this one,
+                    // which has to be in registers first
+                    constexpr int y = i - G0;
                     if constexpr (i < G0) load1(gr[i], voff_g, gate_cur + (i / 2) * 4 * kGateTileBytes + (i % 2) * 1024);
-                    else if constexpr (j == 0) { if (kFlags) load_word(seen, 0u, flag2); }
-                    else if constexpr (j >= 1 && j <= 4) dma1(m0W + (j - 1) * 1024, voff_big, nxt + kOffWn + (j - 1) * 1024);
-                    else if constexpr (j >= 5 && j <= 6) dma1(m0A + (j - 5) * 1024, voff_small, nxt + kOffAqk + (j - 5) * 1024);
-                    else if constexpr (j >= 7 && j <= 10) {
-                        if (kRole != kRoleT)
-                            load1(ur[j - 7], voff_u, nxt + kOffU + ((j - 7) / 2) * 4 * kUTileBytes + ((j - 7) % 2) * 1024);
+                    else if constexpr (y == 0) { if (kFlags) load_word(seen, (uint32_t)(rel + 2 < nsteps ? rel + 2 : nsteps - 1) * 4u, ready); }
+                    else if constexpr (y <= 4) dma1(m0Kt + (y - 1) * 1024, voff_big, cur + kOffKt + (y - 1) * 1024);
+                    else if constexpr (y <= 8 && kTakesV) {
+                        if constexpr (y == 5) {
+#pragma unroll
+                            for (int z = 0; z < 8; ++z) asm volatile("" :: "v"(vt[z]));
+                        }
+                        dma1_row(m0V + (y - 5) * 1024, voff_v + (uint32_t)(16 * (y - 5)) * v_pitch, rows);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 });
             }
-            // fp16 copy of V_new: registers 8 s .. 8 s + 7 of a tile are its slots of K-step s as a B operand
-            h8 Vb[2][2];
-#pragma unroll
-            for (int P = 0; P < 2; ++P)
-#pragma unroll
-                for (int s = 0; s < 2; ++s)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) Vb[P][s][e] = (_Float16)av[P][8 * s + e];
-            phase_barrier<G3 + G4 + G0 + G1>();                  // Gamma.Q (and the small piece) of this step
+            phase_barrier<G5 + G0 + G1 + G2>();                  // Gamma.Q and the small piece of this step
 
-            // ---- phase O: O^T[P] = S^T (Gamma.Q)(P)^T + V_new^T Tril(A_qk)(P, rho)^T; between the products the
-            // state is scaled, S <- Diag(gamma^C) S (the products read the fp16 copy taken in phase V) ----
+            // ---- phase O: V_new = M Y and O^T[P] = S^T (Gamma.Q)(P)^T + V_new^T Tril(A_qk)(P, rho)^T; between the products the
+            // state is scaled, S <- Diag(gamma^C) S (the products read the fp16 copy taken in phase Y), and Y of tile 1 and V_new
+            // become operands, each while products that do not need it are under way ----
+            h8 Vb[2][2];                                         // fp16 copy of V_new
             f32x16 ao[2] = {{0.f}, {0.f}};
-            auto scale_state = [&](const int t, const int q4) __attribute__((always_inline)) {
-                const f32x4 gv = *reinterpret_cast<const f32x4 *>(gc + 32 * t + 8 * q4);
+            av[0] = f32x16{0.f};
+            float gcv[4];
 #pragma unroll
-                for (int z = 0; z < 4; ++z) S[t][4 * q4 + z] *= gv[z];
+            for (int t = 0; t < 4; ++t) gcv[t] = gc[32 * t];
+            auto scale_state = [&](auto tc, auto qc) __attribute__((always_inline)) {
+                constexpr int t = decltype(tc)::value, q4 = decltype(qc)::value;
+                static_for<0, 4>([&](auto zc) __attribute__((always_inline)) {
+                    constexpr int j = 4 * q4 + decltype(zc)::value;
+                    S[t][j] *= row_broadcast<j>(gcv[t]);
+                });
             };
+            auto take_y1 = [&](const int q) __attribute__((always_inline)) {
+#pragma unroll
+                for (int z = 0; z < 4; ++z) Yb[1][q / 2][4 * (q % 2) + z] = (_Float16)av[1][4 * q + z];
+            };
+            auto take_v = [&](const int i) __attribute__((always_inline)) {
+#pragma unroll
+                for (int z = 0; z < 4; ++z) Vb[i / 4][(i % 4) / 2][4 * (i % 2) + z] = (_Float16)av[i / 4][4 * (i % 4) + z];
+            };
+            // fragment (rr, ri, s) = j of M or Tril(A_qk): output token tile rr, contraction token tile ri
+            constexpr auto row_of = [](int j) { return (j < 2) ? 0 : 1; };
+            constexpr auto col_of = [](int j) { return (j < 4) ? 0 : 1; };
+            // (V_new of tile 1 starts where Y of tile 1 was, which is read up to slot 3)
+            // (kGate: M first, the gate's factors take the registers)
+            constexpr int kM0 = kGate ? 0 : 4, kQ1 = kM0 + 6, kA0 = kQ1 + 16 - kM0, kSlots = kA0 + 6;
+            auto m_product = [&](auto jc, const h8 &m) __attribute__((always_inline)) {
+                constexpr int j = decltype(jc)::value, rr = row_of(j), ri = col_of(j);
+                if constexpr (j == 2) av[1] = f32x16{0.f};
+                av[rr] = __builtin_amdgcn_mfma_f32_32x32x16_f16(m, Yb[ri][j % 2], av[rr], 0, 0, 0);
+            };
+            if constexpr (kM0 == 0 || !kFull) static_for<0, 4>([&](auto ic) __attribute__((always_inline)) { take_y1(decltype(ic)::value); });
             if constexpr (kFull) {
                 h8 ring[RING];
-                // slots 0..15: Gamma.Q (P, tau, s) as in phase V; 16..21: A_qk (0,0,s) (1,0,s) (1,1,s)
+                // slots kM0 .. kQ1 - 1: M; the last six: A_qk; the others: Gamma.Q (P, tau, s), alternating tiles
                 auto frag = [&](const int i) __attribute__((always_inline)) {
-                    if (i < 16) return *reinterpret_cast<const h8 *>(ldsQ + frag_rts(i % 2, (i / 2) / 2, (i / 2) % 2) * kFragBytes);
-                    return *reinterpret_cast<const h8 *>(ldsA + (i - 16) * kFragBytes);
+                    if (i >= kA0) return *reinterpret_cast<const h8 *>(ldsA + (i - kA0) * kFragBytes);
+                    if (i >= kM0 && i < kQ1) return *reinterpret_cast<const h8 *>(ldsM + (i - kM0) * kFragBytes);
+                    const int qi = i < kM0 ? i : i - 6;
+                    return *reinterpret_cast<const h8 *>(ldsQ + frag_rts(qi % 2, (qi / 2) / 2, (qi / 2) % 2) * kFragBytes);
                 };
                 static_for<0, LA>([&](auto ic) __attribute__((always_inline)) { ring[decltype(ic)::value % RING] = frag(decltype(ic)::value); });
-                static_for<0, 22>([&](auto ic) __attribute__((always_inline)) {
+                static_for<0, kSlots>([&](auto ic) __attribute__((always_inline)) {
                     constexpr int i = decltype(ic)::value;
-                    if constexpr (i + LA < 22) ring[(i + LA) % RING] = frag(i + LA);
-                    if constexpr (i < 16) {
-                        constexpr int P = i % 2;
-                        ao[P] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Sb[i / 2], ring[i % RING], ao[P], 0, 0, 0);
-                        scale_state(i / 4, i % 4);
+                    if constexpr (i + LA < kSlots) ring[(i + LA) % RING] = frag(i + LA);
+                    if constexpr (i >= kA0) {
+                        constexpr int j = i - kA0, rr = row_of(j), ri = col_of(j);
+                        ao[rr] = kRowsOut ? __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], Vb[ri][j % 2], ao[rr], 0, 0, 0)
+                                          : __builtin_amdgcn_mfma_f32_32x32x16_f16(Vb[ri][j % 2], ring[i % RING], ao[rr], 0, 0, 0);
+                    } else if constexpr (i >= kM0 && i < kQ1) {
+                        m_product(std::integral_constant<int, i - kM0>{}, ring[i % RING]);
                     } else {
-                        // fragment (rr, ri, s) of Tril(A_qk): output token tile rr, V_new token tile ri
-                        constexpr int j = i - 16, rr = (j < 2) ? 0 : 1, ri = (j < 4) ? 0 : 1, s = j % 2;
-                        ao[rr] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Vb[ri][s], ring[i % RING], ao[rr], 0, 0, 0);
+                        constexpr int qi = i < kM0 ? i : i - 6;
+                        ao[qi % 2] = kRowsOut ? __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], Sb[qi / 2], ao[qi % 2], 0, 0, 0)
+                                              : __builtin_amdgcn_mfma_f32_32x32x16_f16(Sb[qi / 2], ring[i % RING], ao[qi % 2], 0, 0, 0);
+                        scale_state(std::integral_constant<int, qi / 4>{}, std::integral_constant<int, qi % 4>{});
                     }
-                    if constexpr (i < 4) dma1(m0Q + i * 1024, voff_big, nxt + kOffQp + i * 1024);      // G2
+                    if constexpr (i < kM0) take_y1(i);
+                    if constexpr (i >= kQ1 + 2 && i < kQ1 + 10) take_v(i - kQ1 - 2);
+                    if constexpr (i < 4) dma1(m0K + i * 1024, voff_big, nxt + kOffKg + i * 1024);      // G3
                     __builtin_amdgcn_sched_barrier(0);
                 });
             } else {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) scale_state(i / 4, i % 4);
+                dma4(m0K, voff_big, nxt + kOffKg);               // G3
+                static_for<0, 6>([&](auto ic) __attribute__((always_inline)) {
+                    m_product(ic, *reinterpret_cast<const h8 *>(ldsM + decltype(ic)::value * kFragBytes));
+                });
+                static_for<0, 16>([&](auto ic) __attribute__((always_inline)) {
+                    scale_state(std::integral_constant<int, decltype(ic)::value / 4>{}, std::integral_constant<int, decltype(ic)::value % 4>{});
+                });
+                static_for<0, 8>([&](auto ic) __attribute__((always_inline)) { take_v(decltype(ic)::value); });
             }
             if (kGate) {
                 // A token's 128 outputs sit in two lanes of each of the four waves: lane-local sum of squares, the
-                // two lanes by a swap, the four waves through the unused tail of this step's small region (the
-                // barrier that ends the phase publishes it).
+                // two lanes by a swap, the four waves through LDS (the barrier that ends the phase publishes it).
                 const int ln = lane_now();
 #pragma unroll
                 for (int P = 0; P < 2; ++P) {
@@ -483,51 +545,80 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
             // The stores go through a buffer descriptor that covers the chunk's real tokens: rows of
             // tokens past the end of the sequence are dropped by the hardware, and the number of
             // store instructions does not depend on the data.
-            const int64_t t0 = (c_begin + rel) * kChunk;
-            const int64_t left = len - t0;
-            const uint32_t nvalid = (uint32_t)(left < kChunk ? left : kChunk);
-            uint8_t *obase = static_cast<uint8_t *>(o) + ((tok_base + t0) * H + h) * (int64_t)(D * (kOutBf16 ? 2 : 4));
-            const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc(obase, 0, (int)(nvalid * o_rstride), 0x00020000);
+            const uint32_t nvalid = (uint32_t)tokens_of(rel);
+            // (kRowsOut: one descriptor for each of four consecutive rows, so that the lanes' offsets are the same in every step)
+            __amdgpu_buffer_rsrc_t orsrc[kRowsOut ? 4 : 1];
+#pragma unroll
+            for (int z = 0; z < (kRowsOut ? 4 : 1); ++z)
+                orsrc[z] = __builtin_amdgcn_make_buffer_rsrc(obase + z * o_rstride, 0, nvalid > (uint32_t)z ? (int)((nvalid - z) * o_rstride) : 0, 0x00020000);
             // fp32: store i of tile P: token 32 P + 4 (x / 4) + i, columns 32 c + 8 (x % 4) + 4 hh + 0..3
             // bf16: store qq of tile P: token 32 P + x, columns 32 c + 8 (qq + 2 hh) + 0..7
-            const uint32_t ol = kOutBf16 ? (uint32_t)x * o_rstride + (uint32_t)(32 * c + 16 * hh) * 2
+            // kRowsOut: group q of tile P, register z: token 32 P + 8 q + 4 hh + z, column 32 c + x
+            const uint32_t ol = kRowsOut ? (uint32_t)(4 * hh) * o_rstride + (uint32_t)(32 * c + x) * 4
+                                : kOutBf16 ? (uint32_t)x * o_rstride + (uint32_t)(32 * c + 16 * hh) * 2
                                          : (uint32_t)(x & ~3) * o_rstride + (uint32_t)(32 * c + 8 * (x & 3) + 4 * hh) * 4;
-            // K^T of this step; with the gate also its factors, which were issued after the stores of the step before:
-            // those stores are then waited for as well
-            phase_barrier<kGate ? G1 + G2 : G1 + G2 + G3>();
+            phase_barrier<G2 + G3>();                            // K^T of this step (kGate: and its factors)
 
-            // ---- phase S: S += (Gamma^{i->C}.K)^T V_new (S is already scaled), slot i: tau = i % 4, (rho, s) = i / 4.
-            // Slots 0..3 also issue K^T of the next step and turn output tile 0 into store order, 4..7 store it
-            // and turn tile 1, 8..11 store tile 1 ----
+            // ---- phase S: S += (Gamma^{i->C}.K)^T V_new (S is already scaled), slot i: tau = i / 4, (rho, s) = i % 4, so that
+            // a tile that is done becomes an operand of the next step while the next ones are formed.  The small piece and
+            // Gamma.Q of the next step go out first, then this step's output ----
             {
                 h8 ring[RING];
                 auto frag = [&](const int i) __attribute__((always_inline)) {
-                    return *reinterpret_cast<const h8 *>(ldsK + frag_trs(i % 4, (i / 4) / 2, (i / 4) % 2) * kFragBytes);
+                    return *reinterpret_cast<const h8 *>(ldsK + frag_trs(i / 4, (i % 4) / 2, i % 2) * kFragBytes);
                 };
                 static_for<0, LA>([&](auto ic) __attribute__((always_inline)) { ring[decltype(ic)::value % RING] = frag(decltype(ic)::value); });
                 static_for<0, 16>([&](auto ic) __attribute__((always_inline)) {
-                    constexpr int i = decltype(ic)::value, tau = i % 4, rho = (i / 4) / 2, s = (i / 4) % 2;
+                    constexpr int i = decltype(ic)::value, tau = i / 4, rho = (i % 4) / 2, s = i % 2;
                     if constexpr (i + LA < 16) ring[(i + LA) % RING] = frag(i + LA);
                     S[tau] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], Vb[rho][s], S[tau], 0, 0, 0);
-                    if constexpr (i < 4) dma1(m0K + i * 1024, voff_big, nxt + kOffKt + i * 1024);      // G4
+                    if constexpr (i < 3) dma1(m0M + i * 1024, voff_small, nxt + kOffM + i * 1024);     // G4
+                    else if constexpr (i == 3) dma1_word(m0Gc, voff_gc, nxt + kOffGc);
+                    if constexpr (kFull && (kRowsOut ? i < 4 : i >= 4 && i < 8)) dma1(m0Q + (i % 4) * 1024, voff_big, nxt + kOffQp + (i % 4) * 1024);
                     if constexpr (kGate && (i == 0 || i == 4)) apply_gate(i / 4);
-                    if constexpr (kFull && i < 8) prepare_out(i / 4, i % 4);
-                    if constexpr (kFull && i >= 4 && i < 12) {                                          // G3
-                        constexpr int P = (i - 4) / 4, k = (i - 4) % 4;
-                        if constexpr (k < kStores / 2) {
-                            const uint32_t off = ol + (uint32_t)(32 * P) * o_rstride + (kOutBf16 ? (uint32_t)k * 16 : (uint32_t)k * o_rstride);
-                            __builtin_amdgcn_raw_buffer_store_b128(ot[P][k], orsrc, (int)off, 0, 0);
+                    if constexpr (kRowsOut) {                                                           // G5
+                        static_for<0, 3>([&](auto yc) __attribute__((always_inline)) {
+                            constexpr int y = 3 * (i - 4) + decltype(yc)::value, P = y / 16, q = (y / 4) % 4, z = y % 4;
+                            if constexpr (i >= 4 && y < 32)
+                                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ao[P][4 * q + z]), orsrc[z], (int)(ol + (uint32_t)(32 * P + 8 * q) * o_rstride), 0, 0);
+                        });
+                    } else if constexpr (kFull) {
+                        if constexpr (i < 8) prepare_out(i / 4, i % 4);
+                        if constexpr (i >= 8) {
+                            constexpr int P = (i - 8) / 4, k = (i - 8) % 4;
+                            if constexpr (k < nSt / 2) {
+                                const uint32_t off = ol + (uint32_t)(32 * P) * o_rstride + (kOutBf16 ? (uint32_t)k * 16 : (uint32_t)k * o_rstride);
+                                __builtin_amdgcn_raw_buffer_store_b128(ot[P][k], orsrc[0], (int)off, 0, 0);
+                            }
+                        }
+                    }
+                    if constexpr (!kGate && i >= 6) {
+                        if constexpr (i < 14) copy_state((i - 6) / 4, (i - 6) % 4);
+                        else { copy_state(2, 2 * (i - 14)); copy_state(2, 2 * (i - 14) + 1); }
+                        if constexpr (i == 9 || i == 13 || i == 15) pin_state((i - 6) / 4);
+                    }
+                    if constexpr (i == 8) {
+                        // (past the last step but one, the last chunk's again)
+                        const bool more = rel + 2 < nsteps;
+                        cur = nxt;
+                        nxt += more ? slot_stride : 0;
+                        if (kGate) gate_cur += kGateSlotBytes;
+                        if (kTakesV && more) {
+                            const uint64_t base = ((uint64_t)rows[1] << 32 | rows[0]) + (uint64_t)v_pitch * kChunk;
+                            rows[0] = (uint32_t)base; rows[1] = (uint32_t)(base >> 32);
+                            rows[2] = (uint32_t)(tokens_of(rel + 2) - 1) * v_pitch + D * 2;
                         }
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 });
+                if (kFull) obase += (int64_t)o_rstride * kChunk;
             }
 
             // kRoleT, every eighth step: has this wave's slice of the transition vanished, bit for bit?  Decay takes a
             // range's transition to exact zero within a few chunks (S is scaled by gamma^C every step and what the
             // products add is formed from it), and zero stays zero under every further step, so the rest of the range
             // need not be walked.  Every wave still loads its share of the operands for the others, so the four
-            // waves leave together: flags through the idle tail of this step's small region.
+            // waves leave together: flags through LDS.
             const bool probe = kRole == kRoleT && (rel & 7) == 7;
             if (probe) {
                 uint32_t bits = 0;
@@ -540,15 +631,13 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             }
 
-            // ---- the next step's W and U are here: take U, note whether the flag read in phase V was up ----
-            phase_barrier<G2 + G3 + G4>();
-            take_u();
+            // ---- the next step's Gamma.K and V are here; note whether the flag read in phase Y was up ----
+            phase_barrier<G4 + G5>();
             if (kFlags) next_ok = (uint32_t)__builtin_amdgcn_readfirstlane((int)seen) == epoch;
             if (probe) {
                 const uint32_t *zf = reinterpret_cast<const uint32_t *>(red);
                 const bool all_zero = (zf[0] & zf[1] & zf[2] & zf[3]) != 0;
-                // (nobody's next loads may land on the flags before everybody has read them)
-                __builtin_amdgcn_s_barrier();
+                // (nobody writes the next flags before everybody has read these: eight steps of barriers lie between)
                 if (all_zero) break;                             // the same answer in every thread of the workgroup
             }
         }

@@ -160,7 +160,7 @@ __device__ __forceinline__ bool fold_slices(float *sE, float *E, const float *Tm
 // the RMSNorm (see kda_scan4_body).
 template <bool kOutBf16, bool kGate = false>
 __device__ __forceinline__ void split_role(uint8_t *lds, const SplitArgs &sp, const uint8_t *ws_pair, const uint32_t *ready_pair,
-                                           const float *h0, float *state_final, void *o, int64_t pair, int64_t pairs, int y,
+                                           const uint16_t *v, const float *h0, float *state_final, void *o, int64_t pair, int64_t pairs, int y,
                                            int64_t tok_base, int64_t len, int H, int h, int64_t cbase, int64_t nchunks,
                                            uint32_t epoch, uint32_t *status, uint64_t wait_limit,
                                            const uint8_t *gate_pair = nullptr, float gate_eps = 0.f)
@@ -207,11 +207,11 @@ __device__ __forceinline__ void split_role(uint8_t *lds, const SplitArgs &sp, co
             bool vanished = false;
             if (is_t)
                 vanished = kda_scan4_body<true, kOutBf16, kRoleT>(
-                    lds, ws_pair + c_begin * (int64_t)kSlotBytes, (int64_t)kSlotBytes, nullptr, state_out, o, st_base, tok_base,
+                    lds, ws_pair + c_begin * (int64_t)kSlotBytes, (int64_t)kSlotBytes, v, nullptr, state_out, o, st_base, tok_base,
                     len, H, cbase + c_begin, cbase + c_end, h, ready_pair + c_begin, epoch, status, wait_limit);
             else
                 kda_scan4_body<true, kOutBf16, kRoleB>(
-                    lds, ws_pair + c_begin * (int64_t)kSlotBytes, (int64_t)kSlotBytes, nullptr, state_out, o, st_base, tok_base,
+                    lds, ws_pair + c_begin * (int64_t)kSlotBytes, (int64_t)kSlotBytes, v, nullptr, state_out, o, st_base, tok_base,
                     len, H, cbase + c_begin, cbase + c_end, h, ready_pair + c_begin, epoch, status, wait_limit);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
             __syncthreads();
@@ -301,7 +301,7 @@ __device__ __forceinline__ void split_role(uint8_t *lds, const SplitArgs &sp, co
     float *state_out = (range == 0) ? sp.E : last ? (detour ? sp.E + (int64_t)(parts - 1) * pair_states : state_final) : nullptr;
     const int64_t c_begin = clip(begin_of(range)), c_end = clip(end_of(range));
     kda_scan4_body<true, kOutBf16, kRoleFull, kGate>(
-        lds, ws_pair + c_begin * (int64_t)kSlotBytes, (int64_t)kSlotBytes, state_in, state_out, o, st_base, tok_base, len, H,
+        lds, ws_pair + c_begin * (int64_t)kSlotBytes, (int64_t)kSlotBytes, v, state_in, state_out, o, st_base, tok_base, len, H,
         cbase + c_begin, cbase + c_end, h, ready_pair + c_begin, epoch, status, wait_limit, poisoned,
         GateParams{kGate ? gate_pair + c_begin * (int64_t)kGateSlotBytes : nullptr, gate_eps});
     if (range == 0) {
