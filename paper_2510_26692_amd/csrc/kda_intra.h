@@ -2,8 +2,8 @@
 // that a kernel calls with the (head, sequence, chunk) of its workgroup.  It forms the running
 // log-decay G, the two intra-chunk matrices A_kk and A_qk, the UT transform
 // M = (I + StrictTril(Diag(beta) A_kk))^-1 Diag(beta) by forward substitution and the decay-scaled operands
-// Gamma.K, Gamma.Q and Gamma^{i->C}.K, and leaves them in the chunk's workspace slot in MFMA register order
-// (kda_mfma_layout.h).  V is not touched: the sequential stage reads it where it stands.
+// Gamma.K, Gamma.Q and Gamma^{i->C}.K, and leaves Gamma.K, Gamma.Q, M^T (Gamma^{i->C}.K) and Tril(A_qk) M in the chunk's
+// workspace slot in MFMA register order (kda_mfma_layout.h).  V is not touched: the sequential stage reads it where it stands.
 //
 // Matrix-core operands are fp16 (unit roundoff 2^-11), accumulation is fp32.  bf16 inputs convert
 // to fp16 exactly while their magnitude lies in [2^-14, 65504] (or is zero); derived operands are rounded.
@@ -403,21 +403,6 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
                     for (int r = 0; r < 16; ++r) sX[(16 * w + r) * kLdF + 16 * w + j] = x[r];
                 }
             }
-            // ---- copy (Gamma^{i->C}.K)^T out in MFMA register order ----
-            {
-                // lane (x = lane % 32, hh): channel 32 tau + x, tokens 32 rho + kidx(s, hh, 0..7), which are two
-                // runs of four consecutive tokens: two transposing reads per fragment
-                const int hh = lane >> 5, xb = 16 * ((lane >> 4) & 1);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int f = wave * 4 + i;                     // Kt frag f = (tau*2 + rho)*2 + s
-                    const int tau = f >> 2, rho = (f >> 1) & 1, s = f & 1;
-                    const uint8_t *blk = lds + kKp + ((32 * rho + kidx(s, hh, 0)) * kLdH + 32 * tau + xb) * 2;
-                    const u32x2 lo = lds_read_tr4(blk, kLdH, lane), hi = lds_read_tr4(blk + 8 * kLdH * 2, kLdH, lane);
-                    u32x4 o4 = {lo[0], lo[1], hi[0], hi[1]};
-                    slot_store16<kPolicy>(out, kOffKt + f * kFragBytes + lane * 16, o4);
-                }
-            }
             __syncthreads();                                                               // B6
 
             // ---- UT transform, off-diagonal blocks (fp32 MFMA).  First X_10 and X_32, then the lower left quarter of blocks:
@@ -456,6 +441,10 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
                     const int I = 2 * (wave - 2);                           // 0 and 2
                     const f32x4 d = row(I + 1, I + 1);
                     put(I + 1, I, mul(d, mul(left(I + 1, I), right(I, I), none), none));
+                } else {
+                    // the blocks above the diagonal in the 32-token tiles on it: read as part of M below
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) sX[(32 * wave + 4 * g + z) * kLdF + 32 * wave + 16 + m] = 0.f;
                 }
                 __syncthreads();                                                           // B7
                 const int I = wave & 1;
@@ -472,40 +461,69 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
                 }
                 __syncthreads();
             }
-            // ---- M = X Diag(beta) and Tril(A_qk) out in MFMA register order, three fragments a wave ----
+            // ---- M^T (Gamma^{i->C}.K) and Tril(A_qk) M, M = X Diag(beta): formed with the roles of rows and columns such that an
+            // accumulator is the fragment to be stored, 32 channels of the one a wave, a 32x32 tile of the other ----
             {
-                // lane (x, hh) of fragment (rr, ri, s): row token 32 rr + x, column tokens 32 ri + 16 s + 4 hh + 0..3 and + 8..11
                 const float *sX = reinterpret_cast<const float *>(lds + kX);
                 const int x = lane & 31, hh = lane >> 5, xb = 16 * ((lane >> 4) & 1);
-                auto tile = [](int idx, int &rr, int &ri, int &s) { const int p = idx >> 1; s = idx & 1; rr = (p == 0) ? 0 : 1; ri = (p == 2) ? 1 : 0; };
-                for (int idx = wave; idx < 6; idx += 4) {
-                    int rr, ri, s;
-                    tile(idx, rr, ri, s);
-                    const int r = 32 * rr + x, j0 = 32 * ri + 16 * s + 4 * hh;
-                    u32x4 o4;
+                // M^T as A operand, (ri, rj) = (0,0) (1,0) (1,1): lane (x, hh) holds column 32 rj + x, rows 32 ri + kidx(s, hh, 0..7)
+                h8 mt[6];
 #pragma unroll
-                    for (int half = 0; half < 2; ++half) {
-                        const f32x4 xr = *reinterpret_cast<const f32x4 *>(sX + r * kLdF + j0 + 8 * half);
-                        const f32x4 br = *reinterpret_cast<const f32x4 *>(sBeta + j0 + 8 * half);
-                        float val[4];
+                for (int f = 0; f < 6; ++f) {
+                    const int ri = (f < 2) ? 0 : 1, rj = (f < 4) ? 0 : 1;
+                    const float b = sBeta[32 * rj + x];
+                    const float *col = sX + (32 * ri + 16 * (f & 1) + 4 * hh) * kLdF + 32 * rj + x;
+                    u32x4 w;
 #pragma unroll
-                        for (int z = 0; z < 4; ++z) {
-                            const int j = j0 + 8 * half + z;
-                            val[z] = (j < r) ? xr[z] * br[z] : ((j == r) ? br[z] : 0.f);
-                        }
-                        o4[2 * half] = pack_h2(val[0], val[1]); o4[2 * half + 1] = pack_h2(val[2], val[3]);
+                    for (int e = 0; e < 4; ++e) {
+                        const int row = 8 * (e >> 1) + 2 * (e & 1);
+                        w[e] = pack_h2(col[row * kLdF] * b, col[(row + 1) * kLdF] * b);
                     }
-                    slot_store16<kPolicy>(out, kOffM + frag_tri(rr, ri, s) * kFragBytes + lane * 16, o4);
+                    mt[f] = __builtin_bit_cast(h8, w);
                 }
-                // (the columns of Tril(A_qk) are rows of the transposed tile)
-                for (int idx = wave ^ 2; idx < 6; idx += 4) {
-                    int rr, ri, s;
-                    tile(idx, rr, ri, s);
-                    const uint8_t *blk = lds + kAq + ((32 * ri + 16 * s + 4 * hh) * kLdM + 32 * rr + xb) * 2;
-                    const u32x2 a = lds_read_tr4(blk, kLdM, lane), b = lds_read_tr4(blk + 8 * kLdM * 2, kLdM, lane);
-                    u32x4 o4 = {a[0], a[1], b[0], b[1]};
-                    slot_store16<kPolicy>(out, kOffAqk + frag_tri(rr, ri, s) * kFragBytes + lane * 16, o4);
+                auto put_tile = [&](const f32x16 &acc, const int off0, const int off1) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int s = 0; s < 2; ++s) {
+                        u32x4 o4;
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) o4[w] = pack_h2(acc[8 * s + 2 * w], acc[8 * s + 2 * w + 1]);
+                        slot_store16<kPolicy>(out, (s ? off1 : off0) + lane * 16, o4);
+                    }
+                };
+                // B operands: lane (x, hh) holds channel 32 wave + x of Gamma^{i->C}.K, or row 32 rr + x of Tril(A_qk) (whose columns
+                // are rows of the transposed tile), tokens 32 ri + kidx(s, hh, 0..7): two transposing reads a fragment
+                auto turned = [&](const uint8_t *blk, const int pitch) __attribute__((always_inline)) {
+                    const u32x2 lo = lds_read_tr4(blk, pitch, lane), hi = lds_read_tr4(blk + 8 * pitch * 2, pitch, lane);
+                    const u32x4 v = {lo[0], lo[1], hi[0], hi[1]};
+                    return __builtin_bit_cast(h8, v);
+                };
+                f32x16 kt[2] = {{0.f}, {0.f}};
+#pragma unroll
+                for (int f = 0; f < 4; ++f) {
+                    const int ri = f >> 1, s = f & 1;
+                    const h8 b = turned(lds + kKp + ((32 * ri + 16 * s + 4 * hh) * kLdH + 32 * wave + xb) * 2, kLdH);
+                    kt[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(mt[f], b, kt[0], 0, 0, 0);
+                    if (ri == 1) kt[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(mt[4 + s], b, kt[1], 0, 0, 0);
                 }
+#pragma unroll
+                for (int rho = 0; rho < 2; ++rho)
+                    put_tile(kt[rho], kOffKt + frag_trs(wave, rho, 0) * kFragBytes, kOffKt + frag_trs(wave, rho, 1) * kFragBytes);
+                __builtin_amdgcn_sched_barrier(0);
+                auto aqk = [&](const int rr, const int ri, const int s) __attribute__((always_inline)) {
+                    return turned(lds + kAq + ((32 * ri + 16 * s + 4 * hh) * kLdM + 32 * rr + xb) * 2, kLdM);
+                };
+                auto p_tile = [&](const int rr, const int rj) __attribute__((always_inline)) {
+                    f32x16 pt = {0.f};
+#pragma unroll
+                    for (int f = 0; f < 4; ++f) {
+                        const int ri = f >> 1, s = f & 1;
+                        if (ri >= rj && ri <= rr) pt = __builtin_amdgcn_mfma_f32_32x32x16_f16(mt[frag_tri(ri, rj, s)], aqk(rr, ri, s), pt, 0, 0, 0);
+                    }
+                    put_tile(pt, kOffP + frag_tri(rr, rj, 0) * kFragBytes, kOffP + frag_tri(rr, rj, 1) * kFragBytes);
+                };
+                if (wave == 0) p_tile(0, 0);
+                else if (wave == 1) p_tile(1, 0);
+                else if (wave == 2) p_tile(1, 1);
             }
             if (kHandoff) {
                 // Hand the finished slot to kda_scan.  Every store to the slot is a write-through store;

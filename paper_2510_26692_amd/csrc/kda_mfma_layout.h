@@ -7,16 +7,15 @@
 //
 //   Kg   -Gamma.K      A operand [token r][dk]      frags [rho][tau][s]      fp16
 //   Qp   Gamma.Q       A operand [token r][dk]      frags [rho][tau][s]      fp16
-//   Kt   (Gamma^{i->C}.K)^T  A operand [dk][token]  frags [tau][rho][s]      fp16
-//   M    (I + StrictTril(Diag(beta) A_kk))^-1 Diag(beta)
-//                      A operand [token r][token i] frags (0,0,s) (1,0,s) (1,1,s) fp16
-//   Aqk  Tril(A_qk)    A operand [token r][token i] frags (0,0,s) (1,0,s) (1,1,s) fp16
+//   Kt   (M^T (Gamma^{i->C}.K))^T    A operand [dk][token]   frags [tau][rho][s]    fp16
+//   P    Tril(A_qk) M  A operand [token r][token j] frags (0,0,s) (1,0,s) (1,1,s) fp16
 //   gC   gamma^C       [dk]                                                  fp32
 //
-// W = M (Gamma.K) and U = M V are never formed: the sequential stage takes U - W S = M (V - (Gamma.K) S) with V as it
-// stands in the input.  That is six products more in its step, and 20 KiB less through the memory system per chunk (the
-// per-chunk stage neither reads V nor writes U, M is 6 KiB), 217 instead of 237 KiB in all.  2^17 tokens x 32 heads
-// 2987 -> 2749 us, 333 tokens x 32 heads 31.5 -> 29.1, 4 x 4096 x 16 heads 223.3 -> 219.9.
+// M = (I + StrictTril(Diag(beta) A_kk))^-1 Diag(beta).  With Y = V - (Gamma.K) S the pseudo-value is U - W S = M Y, and it is met only
+// by Tril(A_qk) and (Gamma^{i->C}.K)^T: M goes into those two, and W = M (Gamma.K), U = M V and the pseudo-value are never formed.
+// V is read by the sequential stage where it stands.  A chunk and head moves 205 KiB; with W and U in the slot it was 237, with M and
+// Tril(A_qk) one by one 217.  us with 237 / 217 / 205 KiB: 2^17 tokens x 32 heads 2920-2987 / 2716-2749 / 2640, eight packed
+// sequences (20 000 chunks and heads) 926 / 929 / 890, 4 x 4096 x 16 heads 219-223 / 220 / 208, 333 tokens x 32 heads 31.5 / 29.1 / 28.4.
 //
 // rho: 32-token tile, tau: 32-channel d_k tile, s: one K-step of 16.  A "frag" is 64 lanes x 8 halfs (1 KiB); lane L = (x = L % 32,
 // hh = L / 32) holds row x of the tile and the 8 contraction slots e = 0..7 of
@@ -27,7 +26,7 @@
 // inside the 32-wide tile.  This is the order in which a 32x32 accumulator tile
 // (register j of lane (x, hh) holds row 8 (j/4) + 4 hh + j%4, column x) turns
 // into a B operand with no data movement: registers 8 s .. 8 s + 7 of a lane are
-// exactly its 8 slots of K-step s.  The state S and the pseudo-value V_new live
+// exactly its 8 slots of K-step s.  The state S and Y live
 // in accumulators and are fed back as B operands that way.
 #pragma once
 #include <stddef.h>
@@ -42,10 +41,9 @@ constexpr int kFragBytes = 1024;
 constexpr int kOffKg = 0;                     // 16 frags
 constexpr int kOffQp = kOffKg + 16 * kFragBytes;
 constexpr int kOffKt = kOffQp + 16 * kFragBytes;
-constexpr int kOffM = kOffKt + 16 * kFragBytes;     // 6 frags: token tile (0,1) of M and of Tril(A_qk) is zero
-constexpr int kOffAqk = kOffM + 6 * kFragBytes;
-constexpr int kOffGc = kOffAqk + 6 * kFragBytes;
-constexpr int kSlotBytes = 72192;                   // the published size (callers keep workspaces); 10 KiB of it are spare
+constexpr int kOffP = kOffKt + 16 * kFragBytes;     // 6 frags: token tile (0,1) of P is zero
+constexpr int kOffGc = kOffP + 6 * kFragBytes;
+constexpr int kSlotBytes = 72192;                   // the published size (callers keep workspaces); 16 KiB of it are spare
 // Output gate (fused epilogue): the gate logits of a chunk, bf16, in the accumulator order of the
 // sequential kernel's O tiles: tile (rho, ct) = [2 units][64 lanes][16 B], lane (x, hh) holds the
 // columns 32 ct + 8 q + 4 hh + 0..3 of token 32 rho + x, q = 0..3 (unit q / 2, bytes 8 (q % 2) ..).
@@ -61,7 +59,7 @@ __host__ __device__ constexpr int acc_row(int j, int hh) { return 8 * (j >> 2) +
 
 constexpr int frag_rts(int r, int t, int s) { return (r * 4 + t) * 2 + s; }   // Kg, Qp: [rho][tau][s]
 constexpr int frag_trs(int t, int r, int s) { return (t * 2 + r) * 2 + s; }   // Kt: [tau][rho][s]
-constexpr int frag_tri(int rr, int ri, int s) { return (rr + ri) * 2 + s; }   // M, Aqk: (0,0) (1,0) (1,1)
+constexpr int frag_tri(int rr, int ri, int s) { return (rr + ri) * 2 + s; }   // M, P: (0,0) (1,0) (1,1)
 
 // Time-split scan: at most this many ranges per sequence, offered to calls with at most this many
 // (sequence, head) pairs whose longest sequence has at least kSplitMinChunks chunks.  The more pairs, the

@@ -5,20 +5,20 @@
 //
 // Per chunk of one (sequence, head), with the operands the per-chunk stage left in the slot and V from the input:
 //
-//     Y = V - (Gamma.K) S      V_new = M Y      O = (Gamma.Q) S + Tril(A_qk) V_new
-//     S <- Diag(gamma^C) S + (Gamma^{i->C}.K)^T V_new
+//     Y = V - (Gamma.K) S      O = (Gamma.Q) S + P Y      S <- Diag(gamma^C) S + K~^T Y
+//     (P = Tril(A_qk) M, K~ = M^T (Gamma^{i->C}.K): the pseudo-value M Y is not formed)
 //
 // Every column of S is an independent recurrence.  Wave c owns the 32 columns 32 c .. 32 c + 31 of
-// S for ALL of d_k (four 32x32 accumulator tiles), and with them the same columns of Y, V_new and O
+// S for ALL of d_k (four 32x32 accumulator tiles), and with them the same columns of Y and O
 // for both 32-token tiles: nothing is exchanged between the waves, and the B operands of every
-// product (S, Y, V_new as fp16) come straight out of the wave's own accumulators.  What the waves
-// share is read-only: the A operands Gamma.K, Gamma.Q, (Gamma^{i->C}.K)^T, M and Tril(A_qk), 60 fragments of
+// product (S and Y as fp16) come straight out of the wave's own accumulators.  What the waves
+// share is read-only: the A operands Gamma.K, Gamma.Q, K~^T and P, 54 fragments of
 // 1 KiB per chunk, which all four waves read from LDS.
 //
-// Operand path.  LDS holds one step's operands: Gamma.K, V, Gamma.Q and K^T, 16 KiB each, and a small piece (M,
-// A_qk and gamma^C, 13 KiB).  All of them arrive by LDS-direct loads (global_load_lds, buffer_load .. lds: no registers
+// Operand path.  LDS holds one step's operands: Gamma.K, V, Gamma.Q and K~^T, 16 KiB each, and a small piece (P
+// and gamma^C, 6.5 KiB).  All of them arrive by LDS-direct loads (global_load_lds, buffer_load .. lds: no registers
 // in between); a piece's place is refilled for the next step as soon as nobody reads it any more, so every piece has
-// the two phases of a step it is not used in to arrive.  A step has three phases (Y; V_new and O; state update) and
+// the two phases of a step it is not used in to arrive.  A step has three phases (Y; O; state update) and
 // one workgroup barrier in front of each, which says two things at once: every wave's part of the phase's pieces has
 // landed, and every wave is done reading the pieces of the phase before.  V is each wave's own affair: its 32 columns
 // (4 KiB, rows of the input) go to its quarter of the region and are turned into accumulator order on the way to
@@ -47,16 +47,15 @@ constexpr int kRoleFull = 0, kRoleT = 1, kRoleB = 2;
 namespace scan4 {
 
 
-constexpr int kBig = 16 * kFragBytes;                       // Gamma.K, V, Gamma.Q or K^T of one chunk
+constexpr int kBig = 16 * kFragBytes;                       // Gamma.K, V, Gamma.Q or K~^T of one chunk
 constexpr int kPlaceK = 0, kPlaceV = kBig, kPlaceQ = 2 * kBig, kPlaceKt = 3 * kBig;
-constexpr int kSmall = 4 * kBig;                            // byte offset of the small piece: M, Tril(A_qk), gamma^C twice
-constexpr int kSmallGc = 12 * kFragBytes;                   // .. gamma^C in it
+constexpr int kSmall = 4 * kBig;                            // byte offset of the small piece: P, gamma^C twice
+constexpr int kSmallGc = 6 * kFragBytes;                    // .. gamma^C in it
 // Partial mean squares of the output gate, [token tile][wave][32 tokens] fp32; kRoleT's four flags
 constexpr int kRed = kSmall + kSmallGc + 2 * D * 4;
 constexpr int kLds = 80 * 1024;                             // two workgroups fit a compute unit
 static_assert(kRed + 2 * 4 * 32 * 4 <= kLds - 16, "the last word is the time-split scan's");
-static_assert(kOffAqk == kOffM + 6 * kFragBytes && kOffGc == kOffM + kSmallGc,
-              "pieces follow the slot layout");
+static_assert(kOffGc == kOffP + kSmallGc, "the small piece follows the slot layout");
 
 // compile-time loop: f(integral_constant<int, I>) for I in [0, N)
 template <int I, int N, typename F>
@@ -196,7 +195,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
 {
     static_assert(!kGate || kRole == kRoleFull, "only a pass that writes outputs has a gate to apply");
     const int tid = threadIdx.x, lane = tid & 63;
-    const int c = __builtin_amdgcn_readfirstlane(tid >> 6);       // the wave: column slice of S, V_new, O
+    const int c = __builtin_amdgcn_readfirstlane(tid >> 6);       // the wave: column slice of S, Y, O
     // The chain of steps is the critical path of the whole prefill, the per-chunk workgroups that share the
     // compute unit are throughput work: the waves of this role go first where both want to issue.
     __builtin_amdgcn_s_setprio(3);
@@ -209,10 +208,10 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
     constexpr bool kRowsOut = kFull && !kOutBf16 && !kGate;       // O in the lanes as it is stored: a column per lane
     constexpr int nSt = kFull ? (kOutBf16 ? 4 : kRowsOut ? 32 : 8) : 0;
     constexpr int G0 = kGate ? 4 : 0;                             // phase Y: the step's own gate factors
-    constexpr int G1 = (kFlags ? 1 : 0) + 4;                      //          a flag and K^T of this step
+    constexpr int G1 = (kFlags ? 1 : 0) + 4;                      //          a flag and K~^T of this step
     constexpr int G2 = kTakesV ? 4 : 0;                           //          V of the next step
     constexpr int G3 = 4;                                         // phase O: Gamma.K of the next step
-    constexpr int G4 = 4 + (kFull ? 4 : 0), G5 = nSt;             // phase S: the small piece and Gamma.Q of the next step; this step's output
+    constexpr int G4 = 3 + (kFull ? 4 : 0), G5 = nSt;             // phase S: the small piece and Gamma.Q of the next step; this step's output
 
     // own state tiles in accumulator order: S[t][j] = S(dk = 32 t + acc_row(j, hh), dv = 32 c + x)
     f32x16 S[4];
@@ -234,8 +233,9 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
         const int64_t tok0 = tok_base + c_begin * kChunk, left64 = len - c_begin * kChunk;
         const int left = (int)(left64 < (1 << 30) ? left64 : (1 << 30));        // tokens from the pass's first on
         auto tokens_of = [&](int rel) __attribute__((always_inline)) { const int n = left - rel * kChunk; return n < kChunk ? n : kChunk; };
-        // this wave's share of a piece: fragments 4 c .. 4 c + 3 of a big one, 3 c .. 3 c + 2 of the small one and half of gamma^C
-        const uint32_t voff_big = lane16 + (uint32_t)c * 4096, voff_small = lane16 + (uint32_t)c * 3072;
+        // this wave's share of a piece: fragments 4 c .. 4 c + 3 of a big one, c and 4 + c % 2 of P and half of gamma^C
+        const uint32_t voff_big = lane16 + (uint32_t)c * 4096;
+        const int off_p0 = kOffP + c * 1024, off_p1 = kOffP + (4 + (c & 1)) * 1024;
         const uint32_t voff_gc = (uint32_t)lane * 4 + (uint32_t)(c & 1) * 256;
         // its 64 bytes of a row of V: load i takes 16 tokens, four lanes each
         const uint32_t v_pitch = (uint32_t)H * (D * 2);
@@ -278,17 +278,26 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
             if (!kGate) copy_states();
         };
 
+        // (kGate, and a pass without outputs: what depends on the lane number is formed afresh in every step: carried in registers across the loop
+        // these were the values too many, and a reload from scratch memory waits for every load in flight, once per
+        // step; a volatile statement, or the compiler forms them once ahead of the loop all the same)
+        auto lane_now = [&]() __attribute__((always_inline)) {
+            int l;
+            asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+            return l;
+        };
         u32x2 vt[8];                                             // V in accumulator order: registers 4 q .. 4 q + 3 of tile P in vt[4 P + q]
         // (64 bytes a token: the 32 lanes that go together read 32 different pairs of banks)
         auto get_v = [&]() __attribute__((always_inline)) {
-            const uint8_t *blk = lds + kPlaceV + c * 4096 + (4 * hh) * 64 + 32 * ((lane >> 4) & 1);
+            const int l = kFull ? lane : lane_now();
+            const uint8_t *blk = lds + kPlaceV + c * 4096 + (4 * (l >> 5)) * 64 + 32 * ((l >> 4) & 1);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) vt[i] = lds_read_tr4(blk + 8 * i * 64, 32, lane);
+            for (int i = 0; i < 8; ++i) vt[i] = lds_read_tr4(blk + 8 * i * 64, 32, l);
         };
         // where this wave's part of a piece goes in LDS
         const uint32_t m0K = lds0 + kPlaceK + (uint32_t)c * 4096, m0V = lds0 + kPlaceV + (uint32_t)c * 4096;
         const uint32_t m0Q = lds0 + kPlaceQ + (uint32_t)c * 4096, m0Kt = lds0 + kPlaceKt + (uint32_t)c * 4096;
-        const uint32_t m0M = lds0 + kSmall + (uint32_t)c * 3072, m0Gc = lds0 + kSmall + kSmallGc + (uint32_t)c * 256;
+        const uint32_t m0P0 = lds0 + kSmall + (uint32_t)c * 1024, m0P1 = lds0 + kSmall + (uint32_t)(4 + (c & 1)) * 1024, m0Gc = lds0 + kSmall + kSmallGc + (uint32_t)c * 256;
 
         // ---- prologue: the whole first slot, waited for in full ----
         uint32_t seen = epoch;
@@ -297,8 +306,8 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
             const uint8_t *s0 = slot_of(0);
             if (kFlags) load_word(seen, 0u, flag_of(1));
             dma4(m0K, voff_big, s0 + kOffKg);
-#pragma unroll
-            for (int j = 0; j < 3; ++j) dma1(m0M + j * 1024, voff_small, s0 + kOffM + j * 1024);
+            dma1(m0P0, lane16, s0 + off_p0);
+            dma1(m0P1, lane16, s0 + off_p1);
             dma1_word(m0Gc, voff_gc, s0 + kOffGc);
             if (kTakesV) {
                 const u32x4 rows = rows_of(0);
@@ -315,7 +324,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
         constexpr int LA = 4, RING = LA + 2;                     // operand fragments read ahead of the product that uses them
         // Vector-memory instructions are handed to the memory pipe one at a time between the matrix
         // products (a burst of them stalls the wave at issue, and the products behind it), in this order:
-        //   phase Y  (gate: the factors of this step, G0,) the flag of the step after next, K^T of this step (G1), V of the next (G2)
+        //   phase Y  (gate: the factors of this step, G0,) the flag of the step after next, K~^T of this step (G1), V of the next (G2)
         //   phase O  Gamma.K of the next step (G3)
         //   phase S  the small piece and Gamma.Q of the next step (G4), then this step's output stores (G5)
         // Where the next step's operands are, moved on in phase S, where the scalar instructions hide behind the products
@@ -325,15 +334,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
 
         for (int rel = 0; rel < nsteps; ++rel) {
             const uint8_t *ldsY = lds + kPlaceK + lane16, *ldsQ = lds + kPlaceQ + lane16, *ldsK = lds + kPlaceKt + lane16;
-            const uint8_t *ldsM = lds + kSmall + lane16, *ldsA = ldsM + 6 * kFragBytes;
-            // (kGate: what depends on the lane number is formed afresh in every step: carried in registers across the loop
-            // these were the values too many, and a reload from scratch memory waits for every load in flight, once per
-            // step; a volatile statement, or the compiler forms them once ahead of the loop all the same)
-            auto lane_now = [&]() __attribute__((always_inline)) {
-                int l;
-                asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-                return l;
-            };
+            const uint8_t *ldsP = lds + kSmall + lane16;
             const int hh_step = kGate ? (lane_now() >> 5) : hh;
             // gamma^C: lane l of a row of 16 lanes holds that of the row its register l of a tile stands for
             const float *gc = reinterpret_cast<const float *>(lds + kSmall + kSmallGc) + (kGate ? acc_row(lane_now() & 15, hh_step) : acc_row(lane & 15, hh));
@@ -347,7 +348,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
             // ---- phase Y: Y[P] = V[P] + (-Gamma.K)(P, tau, s) S(tau, s), slot i: P = i / 8, (tau, s) = i % 8.  Tile 0 starts from
             // zero and has its V added at the end, by which time V has come through the LDS; tile 1 starts from V ----
             h8 Yb[2][2];                                         // fp16 copy of Y: registers 8 s .. 8 s + 7 of a tile are its slots of K-step s as a B operand
-            f32x16 av[2];                                        // Y, then V_new: token tile P, columns of this wave
+            f32x16 av[2];                                        // Y: token tile P, columns of this wave
             auto v_of = [&](const int P, const int j) __attribute__((always_inline)) {
                 const uint32_t w = vt[4 * P + j / 4][(j % 4) / 2];
                 return kTakesV ? __uint_as_float((j & 1) ? (w & 0xffff0000u) : (w << 16)) : 0.f;
@@ -397,12 +398,9 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
             }
             phase_barrier<G5 + G0 + G1 + G2>();                  // Gamma.Q and the small piece of this step
 
-            // ---- phase O: V_new = M Y and O^T[P] = S^T (Gamma.Q)(P)^T + V_new^T Tril(A_qk)(P, rho)^T; between the products the
-            // state is scaled, S <- Diag(gamma^C) S (the products read the fp16 copy taken in phase Y), and Y of tile 1 and V_new
-            // become operands, each while products that do not need it are under way ----
-            h8 Vb[2][2];                                         // fp16 copy of V_new
+            // ---- phase O: O^T[P] = S^T (Gamma.Q)(P)^T + Y^T P(P, rho)^T; between the products the state is scaled,
+            // S <- Diag(gamma^C) S (the products read the fp16 copy taken in phase Y), and Y of tile 1 becomes an operand ----
             f32x16 ao[2] = {{0.f}, {0.f}};
-            av[0] = f32x16{0.f};
             float gcv[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) gcv[t] = gc[32 * t];
@@ -417,61 +415,33 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
 #pragma unroll
                 for (int z = 0; z < 4; ++z) Yb[1][q / 2][4 * (q % 2) + z] = (_Float16)av[1][4 * q + z];
             };
-            auto take_v = [&](const int i) __attribute__((always_inline)) {
-#pragma unroll
-                for (int z = 0; z < 4; ++z) Vb[i / 4][(i % 4) / 2][4 * (i % 2) + z] = (_Float16)av[i / 4][4 * (i % 4) + z];
-            };
-            // fragment (rr, ri, s) = j of M or Tril(A_qk): output token tile rr, contraction token tile ri
-            constexpr auto row_of = [](int j) { return (j < 2) ? 0 : 1; };
-            constexpr auto col_of = [](int j) { return (j < 4) ? 0 : 1; };
-            // (V_new of tile 1 starts where Y of tile 1 was, which is read up to slot 3)
-            // (kGate: M first, the gate's factors take the registers)
-            constexpr int kM0 = kGate ? 0 : 4, kQ1 = kM0 + 6, kA0 = kQ1 + 16 - kM0, kSlots = kA0 + 6;
-            auto m_product = [&](auto jc, const h8 &m) __attribute__((always_inline)) {
-                constexpr int j = decltype(jc)::value, rr = row_of(j), ri = col_of(j);
-                if constexpr (j == 2) av[1] = f32x16{0.f};
-                av[rr] = __builtin_amdgcn_mfma_f32_32x32x16_f16(m, Yb[ri][j % 2], av[rr], 0, 0, 0);
-            };
-            if constexpr (kM0 == 0 || !kFull) static_for<0, 4>([&](auto ic) __attribute__((always_inline)) { take_y1(decltype(ic)::value); });
             if constexpr (kFull) {
                 h8 ring[RING];
-                // slots kM0 .. kQ1 - 1: M; the last six: A_qk; the others: Gamma.Q (P, tau, s), alternating tiles
+                // slots 0 .. 15: Gamma.Q (P, tau, s), alternating tiles; 16 .. 21: P (0,0,s) (1,0,s) (1,1,s)
                 auto frag = [&](const int i) __attribute__((always_inline)) {
-                    if (i >= kA0) return *reinterpret_cast<const h8 *>(ldsA + (i - kA0) * kFragBytes);
-                    if (i >= kM0 && i < kQ1) return *reinterpret_cast<const h8 *>(ldsM + (i - kM0) * kFragBytes);
-                    const int qi = i < kM0 ? i : i - 6;
-                    return *reinterpret_cast<const h8 *>(ldsQ + frag_rts(qi % 2, (qi / 2) / 2, (qi / 2) % 2) * kFragBytes);
+                    if (i >= 16) return *reinterpret_cast<const h8 *>(ldsP + (i - 16) * kFragBytes);
+                    return *reinterpret_cast<const h8 *>(ldsQ + frag_rts(i % 2, (i / 2) / 2, (i / 2) % 2) * kFragBytes);
                 };
                 static_for<0, LA>([&](auto ic) __attribute__((always_inline)) { ring[decltype(ic)::value % RING] = frag(decltype(ic)::value); });
-                static_for<0, kSlots>([&](auto ic) __attribute__((always_inline)) {
-                    constexpr int i = decltype(ic)::value;
-                    if constexpr (i + LA < kSlots) ring[(i + LA) % RING] = frag(i + LA);
-                    if constexpr (i >= kA0) {
-                        constexpr int j = i - kA0, rr = row_of(j), ri = col_of(j);
-                        ao[rr] = kRowsOut ? __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], Vb[ri][j % 2], ao[rr], 0, 0, 0)
-                                          : __builtin_amdgcn_mfma_f32_32x32x16_f16(Vb[ri][j % 2], ring[i % RING], ao[rr], 0, 0, 0);
-                    } else if constexpr (i >= kM0 && i < kQ1) {
-                        m_product(std::integral_constant<int, i - kM0>{}, ring[i % RING]);
-                    } else {
-                        constexpr int qi = i < kM0 ? i : i - 6;
-                        ao[qi % 2] = kRowsOut ? __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], Sb[qi / 2], ao[qi % 2], 0, 0, 0)
-                                              : __builtin_amdgcn_mfma_f32_32x32x16_f16(Sb[qi / 2], ring[i % RING], ao[qi % 2], 0, 0, 0);
-                        scale_state(std::integral_constant<int, qi / 4>{}, std::integral_constant<int, qi % 4>{});
-                    }
-                    if constexpr (i < kM0) take_y1(i);
-                    if constexpr (i >= kQ1 + 2 && i < kQ1 + 10) take_v(i - kQ1 - 2);
+                static_for<0, 22>([&](auto ic) __attribute__((always_inline)) {
+                    constexpr int i = decltype(ic)::value, j = i - 16;
+                    // fragment (rr, ri, s) = j of P: output token tile rr, contraction token tile ri
+                    constexpr int rr = i < 16 ? i % 2 : j < 2 ? 0 : 1, ri = j < 4 ? 0 : 1;
+                    if constexpr (i + LA < 22) ring[(i + LA) % RING] = frag(i + LA);
+                    const h8 &b = i < 16 ? Sb[(i / 2) % 8] : Yb[ri][i % 2];
+                    ao[rr] = kRowsOut ? __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], b, ao[rr], 0, 0, 0)
+                                      : __builtin_amdgcn_mfma_f32_32x32x16_f16(b, ring[i % RING], ao[rr], 0, 0, 0);
+                    if constexpr (i < 16) scale_state(std::integral_constant<int, i / 4>{}, std::integral_constant<int, i % 4>{});
+                    if constexpr (i < 4) take_y1(i);
                     if constexpr (i < 4) dma1(m0K + i * 1024, voff_big, nxt + kOffKg + i * 1024);      // G3
                     __builtin_amdgcn_sched_barrier(0);
                 });
             } else {
                 dma4(m0K, voff_big, nxt + kOffKg);               // G3
-                static_for<0, 6>([&](auto ic) __attribute__((always_inline)) {
-                    m_product(ic, *reinterpret_cast<const h8 *>(ldsM + decltype(ic)::value * kFragBytes));
-                });
+                static_for<0, 4>([&](auto ic) __attribute__((always_inline)) { take_y1(decltype(ic)::value); });
                 static_for<0, 16>([&](auto ic) __attribute__((always_inline)) {
                     scale_state(std::integral_constant<int, decltype(ic)::value / 4>{}, std::integral_constant<int, decltype(ic)::value % 4>{});
                 });
-                static_for<0, 8>([&](auto ic) __attribute__((always_inline)) { take_v(decltype(ic)::value); });
             }
             if (kGate) {
                 // A token's 128 outputs sit in two lanes of each of the four waves: lane-local sum of squares, the
@@ -557,9 +527,9 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
             const uint32_t ol = kRowsOut ? (uint32_t)(4 * hh) * o_rstride + (uint32_t)(32 * c + x) * 4
                                 : kOutBf16 ? (uint32_t)x * o_rstride + (uint32_t)(32 * c + 16 * hh) * 2
                                          : (uint32_t)(x & ~3) * o_rstride + (uint32_t)(32 * c + 8 * (x & 3) + 4 * hh) * 4;
-            phase_barrier<G2 + G3>();                            // K^T of this step (kGate: and its factors)
+            phase_barrier<G2 + G3>();                            // K~^T of this step (kGate: and its factors)
 
-            // ---- phase S: S += (Gamma^{i->C}.K)^T V_new (S is already scaled), slot i: tau = i / 4, (rho, s) = i % 4, so that
+            // ---- phase S: S += K~^T Y (S is already scaled), slot i: tau = i / 4, (rho, s) = i % 4, so that
             // a tile that is done becomes an operand of the next step while the next ones are formed.  The small piece and
             // Gamma.Q of the next step go out first, then this step's output ----
             {
@@ -571,9 +541,10 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                 static_for<0, 16>([&](auto ic) __attribute__((always_inline)) {
                     constexpr int i = decltype(ic)::value, tau = i / 4, rho = (i % 4) / 2, s = i % 2;
                     if constexpr (i + LA < 16) ring[(i + LA) % RING] = frag(i + LA);
-                    S[tau] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], Vb[rho][s], S[tau], 0, 0, 0);
-                    if constexpr (i < 3) dma1(m0M + i * 1024, voff_small, nxt + kOffM + i * 1024);     // G4
-                    else if constexpr (i == 3) dma1_word(m0Gc, voff_gc, nxt + kOffGc);
+                    S[tau] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], Yb[rho][s], S[tau], 0, 0, 0);
+                    if constexpr (i == 0) dma1(m0P0, lane16, nxt + off_p0);                            // G4
+                    else if constexpr (i == 1) dma1(m0P1, lane16, nxt + off_p1);
+                    else if constexpr (i == 2) dma1_word(m0Gc, voff_gc, nxt + kOffGc);
                     if constexpr (kFull && (kRowsOut ? i < 4 : i >= 4 && i < 8)) dma1(m0Q + (i % 4) * 1024, voff_big, nxt + kOffQp + (i % 4) * 1024);
                     if constexpr (kGate && (i == 0 || i == 4)) apply_gate(i / 4);
                     if constexpr (kRowsOut) {                                                           // G5
