@@ -68,17 +68,21 @@ __device__ __forceinline__ void static_for(F &&f)
 }
 
 // ---- vector memory from inline assembly (device-scope policy sc1: the slots are written by
-// workgroups of the same launch, on any die) ----
+// workgroups of the same launch, on any die).  A slot is read once, and o is written once: both marked nt, so that they
+// leave the L2 to the input rows, which are fetched by half lines and so wanted twice.  us without / with: 4 x 4096 x 16 heads
+// 217 / 205, eight packed sequences (20 000 chunks and heads) 894 / 840, gated layer 449 / 441, 2^17 tokens x 32 heads 2625 / 2588.
+// (nt on the input rows, too: 194, 883, 463 and 2717; on the slot's stores: worse everywhere, 226 for the first.) ----
+constexpr int kCacheStream = 2;                              // nt, for stores
 // Four LDS-direct loads: lane L of the wave moves 16 bytes from src + voff + 1024 j to LDS byte
 // m0 + 1024 j + 16 L, j = 0..3 (the instruction offset applies to both addresses).
 __device__ __forceinline__ void dma4(uint32_t m0, uint32_t voff, const uint8_t *src)
 {
     asm volatile("s_mov_b32 m0, %0\n\t"
                  "s_nop 0\n\t"
-                 "global_load_lds_dwordx4 %1, %2 sc1\n\t"
-                 "global_load_lds_dwordx4 %1, %2 offset:1024 sc1\n\t"
-                 "global_load_lds_dwordx4 %1, %2 offset:2048 sc1\n\t"
-                 "global_load_lds_dwordx4 %1, %2 offset:3072 sc1"
+                 "global_load_lds_dwordx4 %1, %2 sc1 nt\n\t"
+                 "global_load_lds_dwordx4 %1, %2 offset:1024 sc1 nt\n\t"
+                 "global_load_lds_dwordx4 %1, %2 offset:2048 sc1 nt\n\t"
+                 "global_load_lds_dwordx4 %1, %2 offset:3072 sc1 nt"
                  :: "s"(m0), "v"(voff), "s"(src) : "memory", "m0");
 }
 // One LDS-direct load of 16 bytes per lane: LDS byte m0 + 16 L <- src[voff(L)].
@@ -86,7 +90,7 @@ __device__ __forceinline__ void dma1(uint32_t m0, uint32_t voff, const uint8_t *
 {
     asm volatile("s_mov_b32 m0, %0\n\t"
                  "s_nop 0\n\t"
-                 "global_load_lds_dwordx4 %1, %2 sc1"
+                 "global_load_lds_dwordx4 %1, %2 sc1 nt"
                  :: "s"(m0), "v"(voff), "s"(src) : "memory", "m0");
 }
 // The same of 4 bytes per lane: LDS byte m0 + 4 L <- src[voff(L)].
@@ -94,7 +98,7 @@ __device__ __forceinline__ void dma1_word(uint32_t m0, uint32_t voff, const uint
 {
     asm volatile("s_mov_b32 m0, %0\n\t"
                  "s_nop 0\n\t"
-                 "global_load_lds_dword %1, %2 sc1"
+                 "global_load_lds_dword %1, %2 sc1 nt"
                  :: "s"(m0), "v"(voff), "s"(src) : "memory", "m0");
 }
 // One LDS-direct load of 16 bytes per lane through a descriptor (zeros past its end): LDS byte m0 + 16 L <- row byte voff(L).
@@ -107,7 +111,7 @@ __device__ __forceinline__ void dma1_row(uint32_t m0, uint32_t voff, const u32x4
 }
 __device__ __forceinline__ void load1(u32x4 &a, uint32_t voff, const uint8_t *src)
 {
-    asm volatile("global_load_dwordx4 %0, %1, %2 sc1" : "=&v"(a) : "v"(voff), "s"(src) : "memory");
+    asm volatile("global_load_dwordx4 %0, %1, %2 sc1 nt" : "=&v"(a) : "v"(voff), "s"(src) : "memory");
 }
 // lane i of each quad of four lanes receives the value of lane kSel[i] of the quad
 template <int kCtrl> __device__ __forceinline__ float quad_perm(float v)
@@ -210,8 +214,8 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
     constexpr int G0 = kGate ? 4 : 0;                             // phase Y: the step's own gate factors
     constexpr int G1 = (kFlags ? 1 : 0) + 4;                      //          a flag and K~^T of this step
     constexpr int G2 = kTakesV ? 4 : 0;                           //          V of the next step
-    constexpr int G3 = 4;                                         // phase O: Gamma.K of the next step
-    constexpr int G4 = 3 + (kFull ? 4 : 0), G5 = nSt;             // phase S: the small piece and Gamma.Q of the next step; this step's output
+    constexpr int G3 = 4, G5a = kGate ? 0 : nSt / 2;              // phase O: Gamma.K of the next step; the first half of this step's output
+    constexpr int G4 = 3 + (kFull ? 4 : 0), G5b = nSt - G5a;      // phase S: the small piece and Gamma.Q of the next step; the other half, or all of it
 
     // own state tiles in accumulator order: S[t][j] = S(dk = 32 t + acc_row(j, hh), dv = 32 c + x)
     f32x16 S[4];
@@ -325,8 +329,8 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
         // Vector-memory instructions are handed to the memory pipe one at a time between the matrix
         // products (a burst of them stalls the wave at issue, and the products behind it), in this order:
         //   phase Y  (gate: the factors of this step, G0,) the flag of the step after next, K~^T of this step (G1), V of the next (G2)
-        //   phase O  Gamma.K of the next step (G3)
-        //   phase S  the small piece and Gamma.Q of the next step (G4), then this step's output stores (G5)
+        //   phase O  Gamma.K of the next step (G3), then the stores of output tile 0 (G5a; not with the gate, which needs all of it first)
+        //   phase S  the small piece and Gamma.Q of the next step (G4), then the stores of tile 1, or of both (G5b)
         // Where the next step's operands are, moved on in phase S, where the scalar instructions hide behind the products
         const uint8_t *cur = slot0, *nxt = slot_of(1), *gate_cur = kGate ? gate_of(0) : nullptr;
         u32x4 rows = kTakesV ? rows_of(1) : u32x4{0u, 0u, 0u, 0u};
@@ -396,7 +400,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                     __builtin_amdgcn_sched_barrier(0);
                 });
             }
-            phase_barrier<G5 + G0 + G1 + G2>();                  // Gamma.Q and the small piece of this step
+            phase_barrier<G5b + G0 + G1 + G2>();                  // Gamma.Q and the small piece of this step
 
             // ---- phase O: O^T[P] = S^T (Gamma.Q)(P)^T + Y^T P(P, rho)^T; between the products the state is scaled,
             // S <- Diag(gamma^C) S (the products read the fp16 copy taken in phase Y), and Y of tile 1 becomes an operand ----
@@ -415,25 +419,97 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
 #pragma unroll
                 for (int z = 0; z < 4; ++z) Yb[1][q / 2][4 * (q % 2) + z] = (_Float16)av[1][4 * q + z];
             };
+            // O^T accumulator: lane (token 32 P + x, hh), registers 4 q .. 4 q + 3 = columns 32 c + 8 q + 4 hh + 0..3:
+            // a token's 128 bytes of this wave's columns sit in two lanes, 16 bytes per register group.  Stored
+            // that way, one instruction touches 32 cache lines and every line is written four times over; the
+            // memory pipe pays per line.  The four lanes of a quad therefore transpose their 4 x 4 register
+            // groups (between the products): afterwards lane (x, hh) holds group x % 4 of the tokens
+            // 4 (x / 4) + 0..3, so that store i writes the whole line of token 4 (x / 4) + i from eight lanes:
+            // eight lines per instruction, each once.
+            u32x4 ot[2][4];
+            auto prepare_out = [&](const int P, const int z) __attribute__((always_inline)) {
+                if constexpr (!kOutBf16) {
+                    float r[4] = {ao[P][z], ao[P][4 + z], ao[P][8 + z], ao[P][12 + z]};
+                    quad_transpose(r, lane);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) ot[P][i][z] = __float_as_uint(r[i]);
+                } else if (z == 0) {
+                    // bf16: w[2 q4 + z] = columns 8 q4 + 4 hh + 2 z, + 1.  The two lanes of a token trade
+                    // halves, so each ends up with two runs of eight consecutive columns: two stores.
+                    uint32_t w[8];
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        w[2 * q4] = pack_bf16x2(ao[P][4 * q4], ao[P][4 * q4 + 1]);
+                        w[2 * q4 + 1] = pack_bf16x2(ao[P][4 * q4 + 2], ao[P][4 * q4 + 3]);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const auto sw = __builtin_amdgcn_permlane32_swap(w[i], w[4 + i], false, false);
+                        w[i] = sw[0]; w[4 + i] = sw[1];
+                    }
+#pragma unroll
+                    for (int qq = 0; qq < 2; ++qq) {
+                        u32x4 val = {w[2 * qq], w[2 * qq + 1], w[4 + 2 * qq], w[4 + 2 * qq + 1]};
+                        ot[P][qq] = val;
+                    }
+                }
+            };
+            // The stores go through a buffer descriptor that covers the chunk's real tokens: rows of
+            // tokens past the end of the sequence are dropped by the hardware, and the number of
+            // store instructions does not depend on the data.
+            const uint32_t nvalid = (uint32_t)tokens_of(rel);
+            // (kRowsOut: one descriptor for each of four consecutive rows, so that the lanes' offsets are the same in every step)
+            __amdgpu_buffer_rsrc_t orsrc[kRowsOut ? 4 : 1];
+#pragma unroll
+            for (int z = 0; z < (kRowsOut ? 4 : 1); ++z)
+                orsrc[z] = __builtin_amdgcn_make_buffer_rsrc(obase + z * o_rstride, 0, nvalid > (uint32_t)z ? (int)((nvalid - z) * o_rstride) : 0, 0x00020000);
+            // fp32: store i of tile P: token 32 P + 4 (x / 4) + i, columns 32 c + 8 (x % 4) + 4 hh + 0..3
+            // bf16: store qq of tile P: token 32 P + x, columns 32 c + 8 (qq + 2 hh) + 0..7
+            // kRowsOut: group q of tile P, register z: token 32 P + 8 q + 4 hh + z, column 32 c + x
+            auto out_offset = [&](const int l) __attribute__((always_inline)) {
+                const int xl = l & 31, hl = l >> 5;
+                return kRowsOut ? (uint32_t)(4 * hl) * o_rstride + (uint32_t)(32 * c + xl) * 4
+                       : kOutBf16 ? (uint32_t)xl * o_rstride + (uint32_t)(32 * c + 16 * hl) * 2
+                                  : (uint32_t)(xl & ~3) * o_rstride + (uint32_t)(32 * c + 8 * (xl & 3) + 4 * hl) * 4;
+            };
+            uint32_t ol = kGate ? 0u : out_offset(lane);
+            // store k of tile P, k = 0 .. nSt / 2 - 1
+            auto put_out = [&](auto Pc, auto kc) __attribute__((always_inline)) {
+                constexpr int P = decltype(Pc)::value, k = decltype(kc)::value;
+                if constexpr (kRowsOut)
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ao[P][k]), orsrc[k % 4], (int)(ol + (uint32_t)(32 * P + 8 * (k / 4)) * o_rstride), 0, kCacheStream);
+                else
+                    __builtin_amdgcn_raw_buffer_store_b128(ot[P][k], orsrc[0], (int)(ol + (uint32_t)(32 * P) * o_rstride + (kOutBf16 ? (uint32_t)k * 16 : (uint32_t)k * o_rstride)), 0, kCacheStream);
+            };
+            // those of tile P whose turn is slot i when they are spread over slots first .. last
+            auto put_share = [&](auto Pc, auto ic, auto firstc, auto lastc) __attribute__((always_inline)) {
+                constexpr int i = decltype(ic)::value, first = decltype(firstc)::value, n = decltype(lastc)::value - first + 1, all = nSt / 2;
+                if constexpr (i >= first && i < first + n)
+                    static_for<(i - first) * all / n, (i - first + 1) * all / n>([&](auto kc) __attribute__((always_inline)) { put_out(Pc, kc); });
+            };
             if constexpr (kFull) {
                 h8 ring[RING];
-                // slots 0 .. 15: Gamma.Q (P, tau, s), alternating tiles; 16 .. 21: P (0,0,s) (1,0,s) (1,1,s)
+                // output tile 0, then tile 1: Gamma.Q (P, tau, s), slots 0 .. 7 and 10 .. 17, and P (0,0,s), slots 8 .. 9, (1,0,s) (1,1,s), 18 .. 21
+                constexpr auto q_of = [](int i) { return i < 8 ? i : i >= 10 && i < 18 ? i - 2 : -1; };
                 auto frag = [&](const int i) __attribute__((always_inline)) {
-                    if (i >= 16) return *reinterpret_cast<const h8 *>(ldsP + (i - 16) * kFragBytes);
-                    return *reinterpret_cast<const h8 *>(ldsQ + frag_rts(i % 2, (i / 2) / 2, (i / 2) % 2) * kFragBytes);
+                    const int qi = q_of(i);
+                    if (qi < 0) return *reinterpret_cast<const h8 *>(ldsP + (i < 10 ? i - 8 : i - 16) * kFragBytes);
+                    return *reinterpret_cast<const h8 *>(ldsQ + frag_rts(qi / 8, (qi % 8) / 2, qi % 2) * kFragBytes);
                 };
                 static_for<0, LA>([&](auto ic) __attribute__((always_inline)) { ring[decltype(ic)::value % RING] = frag(decltype(ic)::value); });
                 static_for<0, 22>([&](auto ic) __attribute__((always_inline)) {
-                    constexpr int i = decltype(ic)::value, j = i - 16;
-                    // fragment (rr, ri, s) = j of P: output token tile rr, contraction token tile ri
-                    constexpr int rr = i < 16 ? i % 2 : j < 2 ? 0 : 1, ri = j < 4 ? 0 : 1;
+                    constexpr int i = decltype(ic)::value, qi = q_of(i), rr = i < 10 ? 0 : 1, ri = i < 20 ? 0 : 1;
                     if constexpr (i + LA < 22) ring[(i + LA) % RING] = frag(i + LA);
-                    const h8 &b = i < 16 ? Sb[(i / 2) % 8] : Yb[ri][i % 2];
+                    const h8 &b = qi >= 0 ? Sb[qi & 7] : Yb[ri][i % 2];
                     ao[rr] = kRowsOut ? __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], b, ao[rr], 0, 0, 0)
                                       : __builtin_amdgcn_mfma_f32_32x32x16_f16(b, ring[i % RING], ao[rr], 0, 0, 0);
-                    if constexpr (i < 16) scale_state(std::integral_constant<int, i / 4>{}, std::integral_constant<int, i % 4>{});
+                    if constexpr (qi >= 0) scale_state(std::integral_constant<int, qi / 4>{}, std::integral_constant<int, qi % 4>{});
                     if constexpr (i < 4) take_y1(i);
                     if constexpr (i < 4) dma1(m0K + i * 1024, voff_big, nxt + kOffKg + i * 1024);      // G3
+                    if constexpr (G5a > 0) {                                                           // G5a
+                        if constexpr (!kRowsOut && i == 11) prepare_out(0, 0);
+                        put_share(std::integral_constant<int, 0>{}, ic, std::integral_constant<int, 12>{}, std::integral_constant<int, 21>{});
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                 });
             } else {
@@ -477,57 +553,8 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                         ao[P][idx + 1] *= rstd * (float)pr[1];
                     }
             };
-            // O^T accumulator: lane (token 32 P + x, hh), registers 4 q .. 4 q + 3 = columns 32 c + 8 q + 4 hh + 0..3:
-            // a token's 128 bytes of this wave's columns sit in two lanes, 16 bytes per register group.  Stored
-            // that way, one instruction touches 32 cache lines and every line is written four times over; the
-            // memory pipe pays per line.  The four lanes of a quad therefore transpose their 4 x 4 register
-            // groups (in phase S, between the products): afterwards lane (x, hh) holds group x % 4 of the tokens
-            // 4 (x / 4) + 0..3, so that store i writes the whole line of token 4 (x / 4) + i from eight lanes:
-            // eight lines per instruction, each once.
-            u32x4 ot[2][4];
-            auto prepare_out = [&](const int P, const int z) __attribute__((always_inline)) {
-                if constexpr (!kOutBf16) {
-                    float r[4] = {ao[P][z], ao[P][4 + z], ao[P][8 + z], ao[P][12 + z]};
-                    quad_transpose(r, lane);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) ot[P][i][z] = __float_as_uint(r[i]);
-                } else if (z == 0) {
-                    // bf16: w[2 q4 + z] = columns 8 q4 + 4 hh + 2 z, + 1.  The two lanes of a token trade
-                    // halves, so each ends up with two runs of eight consecutive columns: two stores.
-                    uint32_t w[8];
-#pragma unroll
-                    for (int q4 = 0; q4 < 4; ++q4) {
-                        w[2 * q4] = pack_bf16x2(ao[P][4 * q4], ao[P][4 * q4 + 1]);
-                        w[2 * q4 + 1] = pack_bf16x2(ao[P][4 * q4 + 2], ao[P][4 * q4 + 3]);
-                    }
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const auto sw = __builtin_amdgcn_permlane32_swap(w[i], w[4 + i], false, false);
-                        w[i] = sw[0]; w[4 + i] = sw[1];
-                    }
-#pragma unroll
-                    for (int qq = 0; qq < 2; ++qq) {
-                        u32x4 val = {w[2 * qq], w[2 * qq + 1], w[4 + 2 * qq], w[4 + 2 * qq + 1]};
-                        ot[P][qq] = val;
-                    }
-                }
-            };
-            // The stores go through a buffer descriptor that covers the chunk's real tokens: rows of
-            // tokens past the end of the sequence are dropped by the hardware, and the number of
-            // store instructions does not depend on the data.
-            const uint32_t nvalid = (uint32_t)tokens_of(rel);
-            // (kRowsOut: one descriptor for each of four consecutive rows, so that the lanes' offsets are the same in every step)
-            __amdgpu_buffer_rsrc_t orsrc[kRowsOut ? 4 : 1];
-#pragma unroll
-            for (int z = 0; z < (kRowsOut ? 4 : 1); ++z)
-                orsrc[z] = __builtin_amdgcn_make_buffer_rsrc(obase + z * o_rstride, 0, nvalid > (uint32_t)z ? (int)((nvalid - z) * o_rstride) : 0, 0x00020000);
-            // fp32: store i of tile P: token 32 P + 4 (x / 4) + i, columns 32 c + 8 (x % 4) + 4 hh + 0..3
-            // bf16: store qq of tile P: token 32 P + x, columns 32 c + 8 (qq + 2 hh) + 0..7
-            // kRowsOut: group q of tile P, register z: token 32 P + 8 q + 4 hh + z, column 32 c + x
-            const uint32_t ol = kRowsOut ? (uint32_t)(4 * hh) * o_rstride + (uint32_t)(32 * c + x) * 4
-                                : kOutBf16 ? (uint32_t)x * o_rstride + (uint32_t)(32 * c + 16 * hh) * 2
-                                         : (uint32_t)(x & ~3) * o_rstride + (uint32_t)(32 * c + 8 * (x & 3) + 4 * hh) * 4;
-            phase_barrier<G2 + G3>();                            // K~^T of this step (kGate: and its factors)
+            if (kGate) ol = out_offset(lane_now());
+            phase_barrier<G2 + G3 + G5a>();                      // K~^T of this step (kGate: and its factors)
 
             // ---- phase S: S += K~^T Y (S is already scaled), slot i: tau = i / 4, (rho, s) = i % 4, so that
             // a tile that is done becomes an operand of the next step while the next ones are formed.  The small piece and
@@ -547,21 +574,13 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                     else if constexpr (i == 2) dma1_word(m0Gc, voff_gc, nxt + kOffGc);
                     if constexpr (kFull && (kRowsOut ? i < 4 : i >= 4 && i < 8)) dma1(m0Q + (i % 4) * 1024, voff_big, nxt + kOffQp + (i % 4) * 1024);
                     if constexpr (kGate && (i == 0 || i == 4)) apply_gate(i / 4);
-                    if constexpr (kRowsOut) {                                                           // G5
-                        static_for<0, 3>([&](auto yc) __attribute__((always_inline)) {
-                            constexpr int y = 3 * (i - 4) + decltype(yc)::value, P = y / 16, q = (y / 4) % 4, z = y % 4;
-                            if constexpr (i >= 4 && y < 32)
-                                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ao[P][4 * q + z]), orsrc[z], (int)(ol + (uint32_t)(32 * P + 8 * q) * o_rstride), 0, 0);
-                        });
-                    } else if constexpr (kFull) {
+                    if constexpr (kGate) {                                                             // G5b
                         if constexpr (i < 8) prepare_out(i / 4, i % 4);
-                        if constexpr (i >= 8) {
-                            constexpr int P = (i - 8) / 4, k = (i - 8) % 4;
-                            if constexpr (k < nSt / 2) {
-                                const uint32_t off = ol + (uint32_t)(32 * P) * o_rstride + (kOutBf16 ? (uint32_t)k * 16 : (uint32_t)k * o_rstride);
-                                __builtin_amdgcn_raw_buffer_store_b128(ot[P][k], orsrc[0], (int)off, 0, 0);
-                            }
-                        }
+                        put_share(std::integral_constant<int, 0>{}, ic, std::integral_constant<int, 8>{}, std::integral_constant<int, 11>{});
+                        put_share(std::integral_constant<int, 1>{}, ic, std::integral_constant<int, 12>{}, std::integral_constant<int, 15>{});
+                    } else if constexpr (kFull) {
+                        if constexpr (!kRowsOut && i == 7) prepare_out(1, 0);
+                        put_share(std::integral_constant<int, 1>{}, ic, std::integral_constant<int, kRowsOut ? 4 : 8>{}, std::integral_constant<int, 15>{});
                     }
                     if constexpr (!kGate && i >= 6) {
                         if constexpr (i < 14) copy_state((i - 6) / 4, (i - 6) % 4);
@@ -603,7 +622,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
             }
 
             // ---- the next step's Gamma.K and V are here; note whether the flag read in phase Y was up ----
-            phase_barrier<G4 + G5>();
+            phase_barrier<G5a + G4 + G5b>();
             if (kFlags) next_ok = (uint32_t)__builtin_amdgcn_readfirstlane((int)seen) == epoch;
             if (probe) {
                 const uint32_t *zf = reinterpret_cast<const uint32_t *>(red);
