@@ -73,6 +73,30 @@ __device__ __forceinline__ uint32_t pack_h2(float a, float b)
     return __builtin_bit_cast(uint32_t, v);
 }
 
+// A pair of lanes (i, i ^ 1) trades: the even lane keeps a and gets its partner's a for b, the odd one keeps b and gets its partner's b
+// for a, four words at a time.  (As moves and selects the compiler takes two instructions a word.)
+__device__ __forceinline__ void trade4(u32x4 &a, u32x4 &b)
+{
+    u32x4 x, y;
+    asm("s_mov_b32 vcc_lo, 0x55555555\n\t"
+        "s_mov_b32 vcc_hi, vcc_lo\n\t"
+        "s_nop 1\n\t"                                       // (a lane swap reads registers two wait states after they are written)
+        "v_cndmask_b32_dpp %0, %12, %8, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_cndmask_b32_dpp %1, %13, %9, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_cndmask_b32_dpp %2, %14, %10, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_cndmask_b32_dpp %3, %15, %11, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_mov_b32 vcc_lo, 0xaaaaaaaa\n\t"                   // (no instruction here writes SCC, which the compiler may hold across)
+        "s_mov_b32 vcc_hi, vcc_lo\n\t"
+        "v_cndmask_b32_dpp %4, %8, %12, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_cndmask_b32_dpp %5, %9, %13, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_cndmask_b32_dpp %6, %10, %14, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_cndmask_b32_dpp %7, %11, %15, vcc quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+        : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3])
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3])
+        : "vcc");
+    a = x; b = y;
+}
+
 // lane i of each row of 16 lanes receives the value of lane i - N (0 when there is none)
 template <int N> __device__ __forceinline__ float row_shr(float x)
 {
@@ -86,12 +110,15 @@ template <int N> __device__ __forceinline__ float row_shr(float x)
 // address of row p / 4, columns 4 (p % 4) .. + 3; it returns to lane c element c % 4 of the four
 // rows handed in by lanes c / 4, 4 + c / 4, 8 + c / 4, 12 + c / 4.)
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x2 lds_read_tr(const uint8_t *a)
+{
+    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)a);
+    return __builtin_bit_cast(u32x2, v);
+}
 __device__ __forceinline__ u32x2 lds_read_tr4(const uint8_t *block, int ld, int lane)
 {
     const int p = lane & 15;
-    const uint8_t *a = block + ((p >> 2) * ld + 4 * (p & 3)) * 2;
-    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)a);
-    return __builtin_bit_cast(u32x2, v);
+    return lds_read_tr(block + ((p >> 2) * ld + 4 * (p & 3)) * 2);
 }
 
 // Workspace slots are written and read through buffer instructions with the device-scope cache
@@ -125,9 +152,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_resource(const void *base
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
 }
-__device__ __forceinline__ u32x4 rows_load16(__amdgpu_buffer_rsrc_t rs, int off)
+template <int kPolicy = 0> __device__ __forceinline__ u32x4 rows_load16(__amdgpu_buffer_rsrc_t rs, int off)
 {
-    return __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+    return __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kPolicy);
 }
 __device__ __forceinline__ uint16_t rows_load2(__amdgpu_buffer_rsrc_t rs, int off)
 {
@@ -205,7 +232,7 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
 {
     // (the wave index is the same in all lanes: telling the compiler so turns the per-wave cases
     // below into scalar branches instead of masked vector code)
-    constexpr int kPolicy = kHandoff ? kCacheDevice : 0;
+    constexpr int kPolicy = kHandoff ? kCacheDevice : 0, kOnce = kRaw ? 0 : 2;
     const uint16_t *__restrict__ q = A.q, *__restrict__ k = A.k;
     const uint16_t *__restrict__ log_alpha = A.log_alpha, *__restrict__ beta = A.beta, *__restrict__ out_gate = A.out_gate;
     uint8_t *__restrict__ ws = A.ws, *__restrict__ gate_ws = A.gate_ws;
@@ -255,22 +282,31 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
     // end with the chunk's last valid token: a token beyond it (and every token of an item that does not
     // exist) reads as zeros, with no branch around a load and nothing for a load to wait for.
     // (log_alpha first: the running sum waits for it, k and q are needed later)
+    // Load 2 l + p of a tensor takes line l (128 bytes) of eight rows, those of parity p in the wave's 16 tokens: the even and the odd lane of
+    // a pair bring one half of it each, and own_rows() hands the pair their own rows.  (A lane fetching its own row asks for half a line
+    // at a time, and every line twice.)  A line is then read once and marked nt.  us before / as whole
+    // lines / marked too: 4 x 4096 x 16 heads 204 / 201 / 185, eight packed sequences (20 000 chunks and heads) 835 / 825 / 818, 2^17 tokens x 32
+    // heads 2550 / 2500 / 2507.  (Raw projections with the output gate are not marked: 439 / 434 / 448.)
     u32x4 kraw[4], qraw[4], graw[4];
     uint32_t beta_raw = 0, gscalar_raw = 0;                  // beta of token tid % 64; kScalar: log alpha of this lane's token
     auto fetch = [&](const Loc &L, const int tid) __attribute__((always_inline)) {
         const int tok = (tid & 63 & 15) + 16 * (tid >> 6), g = (tid & 63) >> 4;
-        const int off = tok * row_pitch + 16 * g;
+        const int off = (tok & ~1) * row_pitch + 64 * (tok & 1) + 16 * g;
+        auto at = [&](const int i) { return off + (i & 1) * row_pitch + 128 * (i >> 1); };
         const __amdgpu_buffer_rsrc_t rg = rows_resource(log_alpha + L.row0, kScalar ? 0 : L.row_bytes);
         const __amdgpu_buffer_rsrc_t rk = rows_resource(k + L.row0, L.row_bytes), rq = rows_resource(q + L.row0, L.row_bytes);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) graw[ks] = rows_load16(rg, off + 64 * ks);
+        for (int i = 0; i < 4; ++i) graw[i] = rows_load16<kOnce>(rg, at(i));
         if (kScalar) gscalar_raw = rows_load2(rows_resource(log_alpha + (L.tok0 * H + L.h), L.head_bytes), tok * H * 2);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) kraw[ks] = rows_load16(rk, off + 64 * ks);
+        for (int i = 0; i < 4; ++i) kraw[i] = rows_load16<kOnce>(rk, at(i));
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) qraw[ks] = rows_load16(rq, off + 64 * ks);
+        for (int i = 0; i < 4; ++i) qraw[i] = rows_load16<kOnce>(rq, at(i));
         beta_raw = rows_load2(rows_resource(beta + (L.tok0 * H + L.h), L.head_bytes), (tid & 63) * H * 2);
     };
+
+    // What fetch brought, to the lanes of its tokens: [ks] holds channels 32 ks + 8 g + 0..7 of this lane's token.
+    auto own_rows = [](u32x4 (&x)[4]) __attribute__((always_inline)) { trade4(x[0], x[1]); trade4(x[2], x[3]); };
 
     // Eight values of this lane's token, channels 32 ks + 8 g + 0..7, to the workspace in MFMA register order as fp16: lanes g and
     // g ^ 1 swap one 4-channel piece each so that every lane ends up with a complete 16-byte slot.  off: kOffKg or kOffQp.
@@ -554,6 +590,7 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
             }
             // kRaw: 1 / |q|, 1 / |k| of this lane's token (the four lanes g = 0..3 of a token hold 32 channels each)
             float invq = 1.f, invk = 1.f;
+            if (kRaw || kScalar) { own_rows(kraw); own_rows(qraw); }
             if (kRaw) {
                 float sq = 0.f, sk = 0.f;
 #pragma unroll
@@ -668,6 +705,7 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
                 __syncthreads();                                                           // B4 (early aliases dead)
             } else {
             // ---- G: running sum of log2(alpha) over the 16 tokens of the sub-chunk (lanes of a row) ----
+            own_rows(graw);
             float G[32];
             f32x4 bias[8];                                           // kRaw: dt_bias of this lane's 32 channels
             float a_scale = 1.f;
@@ -770,6 +808,7 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
                 for (int z = 0; z < 4; ++z) G[4 * i + z] += x[z];
             }
 
+            if (!kRaw) { own_rows(kraw); own_rows(qraw); }
             // ---- operands, built in registers ----
             h8 rowK[4], rowQ[4], colKd[4];
 #pragma unroll
