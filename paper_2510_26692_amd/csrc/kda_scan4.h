@@ -22,7 +22,9 @@
 // one workgroup barrier in front of each, which says two things at once: every wave's part of the phase's pieces has
 // landed, and every wave is done reading the pieces of the phase before.  V is each wave's own affair: its 32 columns
 // (4 KiB, rows of the input) go to its quarter of the region and are turned into accumulator order on the way to
-// registers at the beginning of phase Y; that quarter is refilled as soon as they are there.
+// registers at the beginning of phase Y; that quarter is refilled as soon as they are there.  A pass without outputs has
+// hardly any phase O, and no Gamma.Q: Gamma.K and K~^T go round the three places the latter leaves, each fetched a step ahead.
+// (16 pairs x 47 chunks, whose ranges take the general way: 99 us with a place each, 91 so.)
 //
 // All vector-memory instructions of the loop are issued from inline assembly in a fixed order
 // and waited for with explicit vmcnt counts (they retire in issue order), because a wait that the
@@ -69,9 +71,10 @@ __device__ __forceinline__ void static_for(F &&f)
 
 // ---- vector memory from inline assembly (device-scope policy sc1: the slots are written by
 // workgroups of the same launch, on any die).  A slot is read once, and o is written once: both marked nt, so that they
-// leave the L2 to the input rows, which are fetched by half lines and so wanted twice.  us without / with: 4 x 4096 x 16 heads
+// leave the L2 to what is wanted again.  us without / with: 4 x 4096 x 16 heads
 // 217 / 205, eight packed sequences (20 000 chunks and heads) 894 / 840, gated layer 449 / 441, 2^17 tokens x 32 heads 2625 / 2588.
-// (nt on the input rows, too: 194, 883, 463 and 2717; on the slot's stores: worse everywhere, 226 for the first.) ----
+// (nt on the slot's stores: worse everywhere, 226 for
+// the first.  On o in bf16, of whose lines an instruction writes pieces: 4 x 4096 x 16 heads 174, without 170, 8 x 2048 x 16 171 / 168.) ----
 constexpr int kCacheStream = 2;                              // nt, for stores
 // Four LDS-direct loads: lane L of the wave moves 16 bytes from src + voff + 1024 j to LDS byte
 // m0 + 1024 j + 16 L, j = 0..3 (the instruction offset applies to both addresses).
@@ -212,10 +215,11 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
     constexpr bool kRowsOut = kFull && !kOutBf16 && !kGate;       // O in the lanes as it is stored: a column per lane
     constexpr int nSt = kFull ? (kOutBf16 ? 4 : kRowsOut ? 32 : 8) : 0;
     constexpr int G0 = kGate ? 4 : 0;                             // phase Y: the step's own gate factors
-    constexpr int G1 = (kFlags ? 1 : 0) + 4;                      //          a flag and K~^T of this step
+    constexpr int G1 = (kFlags ? 1 : 0) + 4;                      //          K~^T of this step (no outputs: Gamma.K of the next) and a flag
     constexpr int G2 = kTakesV ? 4 : 0;                           //          V of the next step
-    constexpr int G3 = 4, G5a = kGate ? 0 : nSt / 2;              // phase O: Gamma.K of the next step; the first half of this step's output
-    constexpr int G4 = 3 + (kFull ? 4 : 0), G5b = nSt - G5a;      // phase S: the small piece and Gamma.Q of the next step; the other half, or all of it
+    constexpr int G3 = kFull ? 4 : 0, G5a = kGate ? 0 : nSt / 2;  // phase O: Gamma.K of the next step; the first half of this step's output
+    constexpr int G4a = kFull ? 3 : 1, G4 = G4a + 4;              // phase S: the small piece, then Gamma.Q (no outputs: K~^T) of the next step;
+    constexpr int G5b = nSt - G5a;                                //          the other half of the output, or all of it
 
     // own state tiles in accumulator order: S[t][j] = S(dk = 32 t + acc_row(j, hh), dv = 32 c + x)
     f32x16 S[4];
@@ -301,6 +305,8 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
         // where this wave's part of a piece goes in LDS
         const uint32_t m0K = lds0 + kPlaceK + (uint32_t)c * 4096, m0V = lds0 + kPlaceV + (uint32_t)c * 4096;
         const uint32_t m0Q = lds0 + kPlaceQ + (uint32_t)c * 4096, m0Kt = lds0 + kPlaceKt + (uint32_t)c * 4096;
+        // no outputs: place of Gamma.K of step n is 2 n % 3 of these, of K~^T the next one
+        auto place_of = [](int i) __attribute__((always_inline)) { return (uint32_t)(i == 0 ? kPlaceK : i == 1 ? kPlaceQ : kPlaceKt); };
         const uint32_t m0P0 = lds0 + kSmall + (uint32_t)c * 1024, m0P1 = lds0 + kSmall + (uint32_t)(4 + (c & 1)) * 1024, m0Gc = lds0 + kSmall + kSmallGc + (uint32_t)c * 256;
 
         // ---- prologue: the whole first slot, waited for in full ----
@@ -310,8 +316,12 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
             const uint8_t *s0 = slot_of(0);
             if (kFlags) load_word(seen, 0u, flag_of(1));
             dma4(m0K, voff_big, s0 + kOffKg);
-            dma1(m0P0, lane16, s0 + off_p0);
-            dma1(m0P1, lane16, s0 + off_p1);
+            if (kFull) {
+                dma1(m0P0, lane16, s0 + off_p0);
+                dma1(m0P1, lane16, s0 + off_p1);
+            } else {
+                dma4(place_of(1) + m0K, voff_big, s0 + kOffKt);
+            }
             dma1_word(m0Gc, voff_gc, s0 + kOffGc);
             if (kTakesV) {
                 const u32x4 rows = rows_of(0);
@@ -328,16 +338,20 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
         constexpr int LA = 4, RING = LA + 2;                     // operand fragments read ahead of the product that uses them
         // Vector-memory instructions are handed to the memory pipe one at a time between the matrix
         // products (a burst of them stalls the wave at issue, and the products behind it), in this order:
-        //   phase Y  (gate: the factors of this step, G0,) the flag of the step after next, K~^T of this step (G1), V of the next (G2)
+        //   phase Y  K~^T of this step, (gate: the factors of this step, G0,) the flag of the step after next (G1), V of the next (G2)
         //   phase O  Gamma.K of the next step (G3), then the stores of output tile 0 (G5a; not with the gate, which needs all of it first)
         //   phase S  the small piece and Gamma.Q of the next step (G4), then the stores of tile 1, or of both (G5b)
+        // (no outputs: Gamma.K of the next step in phase Y, K~^T of the next in phase S)
         // Where the next step's operands are, moved on in phase S, where the scalar instructions hide behind the products
+        int turn = 0;                                            // no outputs: 2 rel % 3
         const uint8_t *cur = slot0, *nxt = slot_of(1), *gate_cur = kGate ? gate_of(0) : nullptr;
         u32x4 rows = kTakesV ? rows_of(1) : u32x4{0u, 0u, 0u, 0u};
         uint8_t *obase = static_cast<uint8_t *>(o) + (tok0 * H + h) * (int64_t)(D * (kOutBf16 ? 2 : 4));
 
         for (int rel = 0; rel < nsteps; ++rel) {
-            const uint8_t *ldsY = lds + kPlaceK + lane16, *ldsQ = lds + kPlaceQ + lane16, *ldsK = lds + kPlaceKt + lane16;
+            const uint32_t at_k = kFull ? kPlaceK : place_of(turn), at_kt = kFull ? kPlaceKt : place_of(turn == 2 ? 0 : turn + 1);
+            const uint32_t at_next = place_of(turn == 0 ? 2 : turn - 1);          // no outputs: of Gamma.K of the next step
+            const uint8_t *ldsY = lds + at_k + lane16, *ldsQ = lds + kPlaceQ + lane16, *ldsK = lds + at_kt + lane16;
             const uint8_t *ldsP = lds + kSmall + lane16;
             const int hh_step = kGate ? (lane_now() >> 5) : hh;
             // gamma^C: lane l of a row of 16 lanes holds that of the row its register l of a tile stands for
@@ -384,23 +398,26 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
 #pragma unroll
                         for (int z = 0; z < 4; ++z) Yb[0][q / 2][4 * (q % 2) + z] = (_Float16)(av[0][4 * q + z] + v_of(0, 4 * q + z));
                     }
-                    // G0 (this step's gate factors), G1 and G2, one instruction per slot; V of the next step goes over that of this one,
-                    // which has to be in registers first
-                    constexpr int y = i - G0;
-                    if constexpr (i < G0) load1(gr[i], voff_g, gate_cur + (i / 2) * 4 * kGateTileBytes + (i % 2) * 1024);
+                    // G1 (and G0, this step's gate factors) and G2, one instruction per slot; V of the next step goes over that of this
+                    // one, which has to be in registers first
+                    constexpr int y = i - 4 - G0;
+                    if constexpr (i < 4) {
+                        if (kFull) dma1(m0Kt + i * 1024, voff_big, cur + kOffKt + i * 1024);
+                        else dma1(m0K + at_next + i * 1024, voff_big, nxt + kOffKg + i * 1024);
+                    }
+                    else if constexpr (y < 0) load1(gr[i - 4], voff_g, gate_cur + ((i - 4) / 2) * 4 * kGateTileBytes + ((i - 4) % 2) * 1024);
                     else if constexpr (y == 0) { if (kFlags) load_word(seen, (uint32_t)(rel + 2 < nsteps ? rel + 2 : nsteps - 1) * 4u, ready); }
-                    else if constexpr (y <= 4) dma1(m0Kt + (y - 1) * 1024, voff_big, cur + kOffKt + (y - 1) * 1024);
-                    else if constexpr (y <= 8 && kTakesV) {
-                        if constexpr (y == 5) {
+                    else if constexpr (y <= 4 && kTakesV) {
+                        if constexpr (y == 1) {
 #pragma unroll
                             for (int z = 0; z < 8; ++z) asm volatile("" :: "v"(vt[z]));
                         }
-                        dma1_row(m0V + (y - 5) * 1024, voff_v + (uint32_t)(16 * (y - 5)) * v_pitch, rows);
+                        dma1_row(m0V + (y - 1) * 1024, voff_v + (uint32_t)(16 * (y - 1)) * v_pitch, rows);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 });
             }
-            phase_barrier<G5b + G0 + G1 + G2>();                  // Gamma.Q and the small piece of this step
+            phase_barrier<(kFull ? G5b : G4 - G4a) + G0 + G1 + G2>();                  // Gamma.Q and the small piece of this step
 
             // ---- phase O: O^T[P] = S^T (Gamma.Q)(P)^T + Y^T P(P, rho)^T; between the products the state is scaled,
             // S <- Diag(gamma^C) S (the products read the fp16 copy taken in phase Y), and Y of tile 1 becomes an operand ----
@@ -479,7 +496,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                 if constexpr (kRowsOut)
                     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ao[P][k]), orsrc[k % 4], (int)(ol + (uint32_t)(32 * P + 8 * (k / 4)) * o_rstride), 0, kCacheStream);
                 else
-                    __builtin_amdgcn_raw_buffer_store_b128(ot[P][k], orsrc[0], (int)(ol + (uint32_t)(32 * P) * o_rstride + (kOutBf16 ? (uint32_t)k * 16 : (uint32_t)k * o_rstride)), 0, kCacheStream);
+                    __builtin_amdgcn_raw_buffer_store_b128(ot[P][k], orsrc[0], (int)(ol + (uint32_t)(32 * P) * o_rstride + (kOutBf16 ? (uint32_t)k * 16 : (uint32_t)k * o_rstride)), 0, kOutBf16 ? 0 : kCacheStream);
             };
             // those of tile P whose turn is slot i when they are spread over slots first .. last
             auto put_share = [&](auto Pc, auto ic, auto firstc, auto lastc) __attribute__((always_inline)) {
@@ -513,7 +530,6 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                     __builtin_amdgcn_sched_barrier(0);
                 });
             } else {
-                dma4(m0K, voff_big, nxt + kOffKg);               // G3
                 static_for<0, 4>([&](auto ic) __attribute__((always_inline)) { take_y1(decltype(ic)::value); });
                 static_for<0, 16>([&](auto ic) __attribute__((always_inline)) {
                     scale_state(std::integral_constant<int, decltype(ic)::value / 4>{}, std::integral_constant<int, decltype(ic)::value % 4>{});
@@ -554,7 +570,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                     }
             };
             if (kGate) ol = out_offset(lane_now());
-            phase_barrier<G2 + G3 + G5a>();                      // K~^T of this step (kGate: and its factors)
+            phase_barrier<(kFull ? 0 : G1) + G2 + G3 + G5a>();                      // K~^T of this step (kGate: and its factors)
 
             // ---- phase S: S += K~^T Y (S is already scaled), slot i: tau = i / 4, (rho, s) = i % 4, so that
             // a tile that is done becomes an operand of the next step while the next ones are formed.  The small piece and
@@ -569,9 +585,10 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                     constexpr int i = decltype(ic)::value, tau = i / 4, rho = (i % 4) / 2, s = i % 2;
                     if constexpr (i + LA < 16) ring[(i + LA) % RING] = frag(i + LA);
                     S[tau] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], Yb[rho][s], S[tau], 0, 0, 0);
-                    if constexpr (i == 0) dma1(m0P0, lane16, nxt + off_p0);                            // G4
-                    else if constexpr (i == 1) dma1(m0P1, lane16, nxt + off_p1);
+                    if constexpr (kFull && i == 0) dma1(m0P0, lane16, nxt + off_p0);                   // G4
+                    else if constexpr (kFull && i == 1) dma1(m0P1, lane16, nxt + off_p1);
                     else if constexpr (i == 2) dma1_word(m0Gc, voff_gc, nxt + kOffGc);
+                    if constexpr (!kFull && i >= 4 && i < 8) dma1(m0K + at_k + (i - 4) * 1024, voff_big, nxt + kOffKt + (i - 4) * 1024);
                     if constexpr (kFull && (kRowsOut ? i < 4 : i >= 4 && i < 8)) dma1(m0Q + (i % 4) * 1024, voff_big, nxt + kOffQp + (i % 4) * 1024);
                     if constexpr (kGate && (i == 0 || i == 4)) apply_gate(i / 4);
                     if constexpr (kGate) {                                                             // G5b
@@ -601,6 +618,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 });
+                turn = turn == 0 ? 2 : turn - 1;
                 if (kFull) obase += (int64_t)o_rstride * kChunk;
             }
 
