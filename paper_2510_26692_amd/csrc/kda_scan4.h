@@ -341,6 +341,8 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
         //   phase Y  K~^T of this step, (gate: the factors of this step, G0,) the flag of the step after next (G1), V of the next (G2)
         //   phase O  Gamma.K of the next step (G3), then the stores of output tile 0 (G5a; not with the gate, which needs all of it first)
         //   phase S  the small piece and Gamma.Q of the next step (G4), then the stores of tile 1, or of both (G5b)
+        // (gate: the stores, all of them in phase S, ahead of the loads there: behind them they hold up the phase's end, a store of
+        // bf16 rows touching 32 lines: 8 pairs x 24 chunks with the gate 77.5 -> 74.0 us, 32 pairs x 15 62.4 -> 60.9)
         // (no outputs: Gamma.K of the next step in phase Y, K~^T of the next in phase S)
         // Where the next step's operands are, moved on in phase S, where the scalar instructions hide behind the products
         int turn = 0;                                            // no outputs: 2 rel % 3
@@ -417,7 +419,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                     __builtin_amdgcn_sched_barrier(0);
                 });
             }
-            phase_barrier<(kFull ? G5b : G4 - G4a) + G0 + G1 + G2>();                  // Gamma.Q and the small piece of this step
+            phase_barrier<(kGate ? 0 : kFull ? G5b : G4 - G4a) + G0 + G1 + G2>();                  // Gamma.Q and the small piece of this step
 
             // ---- phase O: O^T[P] = S^T (Gamma.Q)(P)^T + Y^T P(P, rho)^T; between the products the state is scaled,
             // S <- Diag(gamma^C) S (the products read the fp16 copy taken in phase Y), and Y of tile 1 becomes an operand ----
@@ -585,16 +587,18 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                     constexpr int i = decltype(ic)::value, tau = i / 4, rho = (i % 4) / 2, s = i % 2;
                     if constexpr (i + LA < 16) ring[(i + LA) % RING] = frag(i + LA);
                     S[tau] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], Yb[rho][s], S[tau], 0, 0, 0);
-                    if constexpr (kFull && i == 0) dma1(m0P0, lane16, nxt + off_p0);                   // G4
-                    else if constexpr (kFull && i == 1) dma1(m0P1, lane16, nxt + off_p1);
-                    else if constexpr (i == 2) dma1_word(m0Gc, voff_gc, nxt + kOffGc);
-                    if constexpr (!kFull && i >= 4 && i < 8) dma1(m0K + at_k + (i - 4) * 1024, voff_big, nxt + kOffKt + (i - 4) * 1024);
-                    if constexpr (kFull && (kRowsOut ? i < 4 : i >= 4 && i < 8)) dma1(m0Q + (i % 4) * 1024, voff_big, nxt + kOffQp + (i % 4) * 1024);
+                    constexpr int z = kGate ? i - 9 : i;                                               // G4
+                    const uint8_t *ahead = kGate ? cur : nxt;                                          // (slot 8 moves them on)
+                    if constexpr (kFull && z == 0) dma1(m0P0, lane16, ahead + off_p0);
+                    else if constexpr (kFull && z == 1) dma1(m0P1, lane16, ahead + off_p1);
+                    else if constexpr (z == 2) dma1_word(m0Gc, voff_gc, ahead + kOffGc);
+                    if constexpr (!kFull && i >= 4 && i < 8) dma1(m0K + at_k + (i - 4) * 1024, voff_big, ahead + kOffKt + (i - 4) * 1024);
+                    if constexpr (kGate ? i >= 12 : kFull && (kRowsOut ? i < 4 : i >= 4 && i < 8)) dma1(m0Q + (i % 4) * 1024, voff_big, ahead + kOffQp + (i % 4) * 1024);
                     if constexpr (kGate && (i == 0 || i == 4)) apply_gate(i / 4);
                     if constexpr (kGate) {                                                             // G5b
                         if constexpr (i < 8) prepare_out(i / 4, i % 4);
-                        put_share(std::integral_constant<int, 0>{}, ic, std::integral_constant<int, 8>{}, std::integral_constant<int, 11>{});
-                        put_share(std::integral_constant<int, 1>{}, ic, std::integral_constant<int, 12>{}, std::integral_constant<int, 15>{});
+                        put_share(std::integral_constant<int, 0>{}, ic, std::integral_constant<int, kOutBf16 ? 1 : 4>{}, std::integral_constant<int, kOutBf16 ? 4 : 7>{});
+                        put_share(std::integral_constant<int, 1>{}, ic, std::integral_constant<int, kOutBf16 ? 5 : 8>{}, std::integral_constant<int, kOutBf16 ? 8 : 11>{});
                     } else if constexpr (kFull) {
                         if constexpr (!kRowsOut && i == 7) prepare_out(1, 0);
                         put_share(std::integral_constant<int, 1>{}, ic, std::integral_constant<int, kRowsOut ? 4 : 8>{}, std::integral_constant<int, 15>{});
