@@ -141,10 +141,6 @@ template <int kPolicy, typename V> __device__ __forceinline__ void slot_store8(_
     static_assert(sizeof(V) == 8, "8-byte store");
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, val), rs, off, 0, kPolicy);
 }
-template <int kPolicy> __device__ __forceinline__ u32x4 slot_load16(__amdgpu_buffer_rsrc_t rs, int off)
-{
-    return __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kPolicy);
-}
 
 // Input rows are read through a descriptor that covers exactly the bytes that may be read: the hardware
 // returns zeros for an offset beyond it (a padding token of a ragged chunk).
