@@ -1,7 +1,7 @@
 // kda_intra: the per-chunk stage of the matrix-core prefill (Section 3.1), as a device function
 // that a kernel calls with the (head, sequence, chunk) of its workgroup.  It forms the running
 // log-decay G, the two intra-chunk matrices A_kk and A_qk, the UT transform
-// M = (I + StrictTril(Diag(beta) A_kk))^-1 Diag(beta) by forward substitution and the decay-scaled operands
+// M = (I + StrictTril(Diag(beta) A_kk))^-1 Diag(beta / bY) by forward substitution (bY: the factor of beta that is left to the sequential stage) and the decay-scaled operands
 // Gamma.K, Gamma.Q and Gamma^{i->C}.K, and leaves Gamma.K, Gamma.Q, M^T (Gamma^{i->C}.K) and Tril(A_qk) M in the chunk's
 // workspace slot in MFMA register order (kda_mfma_layout.h).  V is not touched: the sequential stage reads it where it stands.
 //
@@ -73,6 +73,21 @@ __device__ __forceinline__ uint32_t pack_h2(float a, float b)
     return __builtin_bit_cast(uint32_t, v);
 }
 
+// beta is cut in two factors.  One, a power of two, meets the residual V - (Gamma.K) S in the sequential stage; the other goes with the
+// inverse into Tril(A_qk) M and M^T (Gamma^{i->C}.K).  Both sides are rounded to fp16, and a beta of 2^-e takes e / 2 binades off either: all of it on the
+// products (k of unit norm is near 2^-3.5, scale * A_qk near 2^-7) sends them into the subnormals from e = 7 on, all of it on the
+// residual does so to small values.  A beta up to 1 leaves at most 1/2 for the residual, which then stays finite while both
+// its terms are at most 65504.  Errors (2-norm of o against fp64, unit q and k, scale 128^-1/2, logits of beta near 0 / -6 / -8 / -10 / -12):
+// 3.3e-4 / 2.9e-4 / 3.1e-4 / 4.2e-4 / 1.6e-3; all on the products 3.3e-4 / 1.2e-3 / 7.6e-3 / 4.8e-2 / 2.4e-1; all on the residual
+// 3.4e-4 / 3.3e-4 / 3.0e-4 / 3.7e-4 / 1.9e-3, but 1.2 times the error of the final state at the first and 3 to 5 times at v near 1e-3 and logits near -4.
+// 0 and subnormals: 2^-64 and what is left; infinity and NaN stay in the second factor.
+// (us with all of beta on the products / cut in two, 32 more multiplications a lane and step of the scan: 333 tokens x 32 heads 29.1 / 29.6, 4 x 4096 x 16 heads
+// 182.3 / 184.9, eight packed sequences (20 000 chunks and heads) 812.6 / 820.4, 2^17 tokens x 32 heads 2480 / 2497.  With bY on Gamma.K in
+// this stage and on V in the scan, 16 there and 32 here: 29.9 / 186.3 / 825.0 / 2500.)
+__device__ __forceinline__ int beta_exponent(float b) { return (((int)((__float_as_uint(b) >> 23) & 0xffu) - 126) >> 1) - 1; }
+__device__ __forceinline__ float beta_on_y(float b) { return __uint_as_float((uint32_t)(127 + beta_exponent(b)) << 23); }
+__device__ __forceinline__ float beta_on_m(float b) { return b * __uint_as_float((uint32_t)(127 - beta_exponent(b)) << 23); }
+
 // A pair of lanes (i, i ^ 1) trades: the even lane keeps a and gets its partner's a for b, the odd one keeps b and gets its partner's b
 // for a, four words at a time.  (As moves and selects the compiler takes two instructions a word.)
 __device__ __forceinline__ void trade4(u32x4 &a, u32x4 &b)
@@ -135,6 +150,10 @@ template <int kPolicy, typename V> __device__ __forceinline__ void slot_store16(
 {
     static_assert(sizeof(V) == 16, "16-byte store");
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, val), rs, off, 0, kPolicy);
+}
+template <int kPolicy> __device__ __forceinline__ void slot_store4(__amdgpu_buffer_rsrc_t rs, int off, float val)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val), rs, off, 0, kPolicy);
 }
 template <int kPolicy, typename V> __device__ __forceinline__ void slot_store8(__amdgpu_buffer_rsrc_t rs, int off, V val)
 {
@@ -493,7 +512,7 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
                 }
                 __syncthreads();
             }
-            // ---- M^T (Gamma^{i->C}.K) and Tril(A_qk) M, M = X Diag(beta): formed with the roles of rows and columns such that an
+            // ---- M^T (Gamma^{i->C}.K) and Tril(A_qk) M, M = X Diag(beta / bY): formed with the roles of rows and columns such that an
             // accumulator is the fragment to be stored, 32 channels of the one a wave, a 32x32 tile of the other ----
             {
                 const float *sX = reinterpret_cast<const float *>(lds + kX);
@@ -503,7 +522,7 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
 #pragma unroll
                 for (int f = 0; f < 6; ++f) {
                     const int ri = (f < 2) ? 0 : 1, rj = (f < 4) ? 0 : 1;
-                    const float b = sBeta[32 * rj + x];
+                    const float b = beta_on_m(sBeta[32 * rj + x]);
                     const float *col = sX + (32 * ri + 16 * (f & 1) + 4 * hh) * kLdF + 32 * rj + x;
                     u32x4 w;
 #pragma unroll
@@ -583,6 +602,7 @@ void kda_intra_items(uint8_t *lds, const IntraArgs &A, int count, ItemAt item_at
                 float b = beta_tok;
                 if (kRaw) b = (tid < nv) ? __builtin_amdgcn_rcpf(1.f + fast_exp2(-b * kLog2e)) : 0.f;   // Sigmoid
                 sBeta[tid] = b;
+                slot_store4<kPolicy>(out, kOffBy + tid * 4, beta_on_y(b));
             }
             // kRaw: 1 / |q|, 1 / |k| of this lane's token (the four lanes g = 0..3 of a token hold 32 channels each)
             float invq = 1.f, invk = 1.f;

@@ -10,9 +10,12 @@
 //   Kt   (M^T (Gamma^{i->C}.K))^T    A operand [dk][token]   frags [tau][rho][s]    fp16
 //   P    Tril(A_qk) M  A operand [token r][token j] frags (0,0,s) (1,0,s) (1,1,s) fp16
 //   gC   gamma^C       [dk]                                                  fp32
+//   bY   the other factor of beta    [token]                                 fp32
 //
-// M = (I + StrictTril(Diag(beta) A_kk))^-1 Diag(beta).  With Y = V - (Gamma.K) S the pseudo-value is U - W S = M Y, and it is met only
-// by Tril(A_qk) and (Gamma^{i->C}.K)^T: M goes into those two, and W = M (Gamma.K), U = M V and the pseudo-value are never formed.
+// M bY = (I + StrictTril(Diag(beta) A_kk))^-1 Diag(beta).  With Y = Diag(bY) (V - (Gamma.K) S) the pseudo-value is U - W S = M Y, and it is met
+// only by Tril(A_qk) and (Gamma^{i->C}.K)^T: M goes into those two, and W = M (Gamma.K), U = M V and the pseudo-value are never formed.
+// beta is cut in two (beta_on_y, kda_intra.h), so that neither those products, whose other factors are small already, nor Y have to take
+// all of a small beta in fp16.
 // V is read by the sequential stage where it stands.  A chunk and head moves 205 KiB; with W and U in the slot it was 237, with M and
 // Tril(A_qk) one by one 217.  us with 237 / 217 / 205 KiB: 2^17 tokens x 32 heads 2920-2987 / 2716-2749 / 2640, eight packed
 // sequences (20 000 chunks and heads) 926 / 929 / 890, 4 x 4096 x 16 heads 219-223 / 220 / 208, 333 tokens x 32 heads 31.5 / 29.1 / 28.4.
@@ -43,6 +46,7 @@ constexpr int kOffQp = kOffKg + 16 * kFragBytes;
 constexpr int kOffKt = kOffQp + 16 * kFragBytes;
 constexpr int kOffP = kOffKt + 16 * kFragBytes;     // 6 frags: token tile (0,1) of P is zero
 constexpr int kOffGc = kOffP + 6 * kFragBytes;
+constexpr int kOffBy = kOffGc + D * 4;
 constexpr int kSlotBytes = 72192;                   // the published size (callers keep workspaces); 16 KiB of it are spare
 // Output gate (fused epilogue): the gate logits of a chunk, bf16, in the accumulator order of the
 // sequential kernel's O tiles: tile (rho, ct) = [2 units][64 lanes][16 B], lane (x, hh) holds the
@@ -50,7 +54,7 @@ constexpr int kSlotBytes = 72192;                   // the published size (calle
 constexpr int kGateTileBytes = 64 * 16 * 2;
 constexpr int kGateSlotBytes = 8 * kGateTileBytes;  // 16384, one per workspace slot when the gate is on
 
-static_assert(kOffGc + D * 4 <= kSlotBytes && kSlotBytes % 256 == 0, "slots must stay 256-byte aligned");
+static_assert(kOffBy + kChunk * 4 <= kSlotBytes && kSlotBytes % 256 == 0, "slots must stay 256-byte aligned");
 
 // Contraction index inside a 32-wide tile for K-step s, lane half hh, slot e.
 __host__ __device__ constexpr int kidx(int s, int hh, int e) { return 16 * s + 8 * (e >> 2) + 4 * hh + (e & 3); }

@@ -5,7 +5,7 @@
 //
 // Per chunk of one (sequence, head), with the operands the per-chunk stage left in the slot and V from the input:
 //
-//     Y = V - (Gamma.K) S      O = (Gamma.Q) S + P Y      S <- Diag(gamma^C) S + K~^T Y
+//     Y = Diag(bY) (V - (Gamma.K) S)      O = (Gamma.Q) S + P Y      S <- Diag(gamma^C) S + K~^T Y
 //     (P = Tril(A_qk) M, K~ = M^T (Gamma^{i->C}.K): the pseudo-value M Y is not formed)
 //
 // Every column of S is an independent recurrence.  Wave c owns the 32 columns 32 c .. 32 c + 31 of
@@ -55,8 +55,9 @@ constexpr int kSmall = 4 * kBig;                            // byte offset of th
 constexpr int kSmallGc = 6 * kFragBytes;                    // .. gamma^C in it
 // Partial mean squares of the output gate, [token tile][wave][32 tokens] fp32; kRoleT's four flags
 constexpr int kRed = kSmall + kSmallGc + 2 * D * 4;
+constexpr int kBy = kRed + 2 * 4 * 32 * 4;                  // bY, one copy per wave
 constexpr int kLds = 80 * 1024;                             // two workgroups fit a compute unit
-static_assert(kRed + 2 * 4 * 32 * 4 <= kLds - 16, "the last word is the time-split scan's");
+static_assert(kBy + 4 * kChunk * 4 <= kLds - 16, "the last word is the time-split scan's");
 static_assert(kOffGc == kOffP + kSmallGc, "the small piece follows the slot layout");
 
 // compile-time loop: f(integral_constant<int, I>) for I in [0, N)
@@ -216,7 +217,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
     constexpr int nSt = kFull ? (kOutBf16 ? 4 : kRowsOut ? 32 : 8) : 0;
     constexpr int G0 = kGate ? 4 : 0;                             // phase Y: the step's own gate factors
     constexpr int G1 = (kFlags ? 1 : 0) + 4;                      //          K~^T of this step (no outputs: Gamma.K of the next) and a flag
-    constexpr int G2 = kTakesV ? 4 : 0;                           //          V of the next step
+    constexpr int G2 = kTakesV ? 5 : 1;                           //          V and bY of the next step
     constexpr int G3 = kFull ? 4 : 0, G5a = kGate ? 0 : nSt / 2;  // phase O: Gamma.K of the next step; the first half of this step's output
     constexpr int G4a = kFull ? 3 : 1, G4 = G4a + 4;              // phase S: the small piece, then Gamma.Q (no outputs: K~^T) of the next step;
     constexpr int G5b = nSt - G5a;                                //          the other half of the output, or all of it
@@ -294,6 +295,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
             asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
             return l;
         };
+        float by[2];                                             // bY: lane l of a row of 16 lanes holds that of the token its register l of tile P stands for
         u32x2 vt[8];                                             // V in accumulator order: registers 4 q .. 4 q + 3 of tile P in vt[4 P + q]
         // (64 bytes a token: the 32 lanes that go together read 32 different pairs of banks)
         auto get_v = [&]() __attribute__((always_inline)) {
@@ -302,11 +304,17 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
 #pragma unroll
             for (int i = 0; i < 8; ++i) vt[i] = lds_read_tr4(blk + 8 * i * 64, 32, l);
         };
+        auto get_by = [&]() __attribute__((always_inline)) {
+            const int l = kFull ? lane : lane_now();
+            const float *b = reinterpret_cast<const float *>(lds + kBy + c * 256) + acc_row(l & 15, l >> 5);
+            by[0] = b[0]; by[1] = b[32];
+        };
         // where this wave's part of a piece goes in LDS
         const uint32_t m0K = lds0 + kPlaceK + (uint32_t)c * 4096, m0V = lds0 + kPlaceV + (uint32_t)c * 4096;
         const uint32_t m0Q = lds0 + kPlaceQ + (uint32_t)c * 4096, m0Kt = lds0 + kPlaceKt + (uint32_t)c * 4096;
         // no outputs: place of Gamma.K of step n is 2 n % 3 of these, of K~^T the next one
         auto place_of = [](int i) __attribute__((always_inline)) { return (uint32_t)(i == 0 ? kPlaceK : i == 1 ? kPlaceQ : kPlaceKt); };
+        const uint32_t m0By = lds0 + kBy + (uint32_t)c * 256;
         const uint32_t m0P0 = lds0 + kSmall + (uint32_t)c * 1024, m0P1 = lds0 + kSmall + (uint32_t)(4 + (c & 1)) * 1024, m0Gc = lds0 + kSmall + kSmallGc + (uint32_t)c * 256;
 
         // ---- prologue: the whole first slot, waited for in full ----
@@ -323,6 +331,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                 dma4(place_of(1) + m0K, voff_big, s0 + kOffKt);
             }
             dma1_word(m0Gc, voff_gc, s0 + kOffGc);
+            dma1_word(m0By, (uint32_t)lane * 4, s0 + kOffBy);
             if (kTakesV) {
                 const u32x4 rows = rows_of(0);
 #pragma unroll
@@ -338,7 +347,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
         constexpr int LA = 4, RING = LA + 2;                     // operand fragments read ahead of the product that uses them
         // Vector-memory instructions are handed to the memory pipe one at a time between the matrix
         // products (a burst of them stalls the wave at issue, and the products behind it), in this order:
-        //   phase Y  K~^T of this step, (gate: the factors of this step, G0,) the flag of the step after next (G1), V of the next (G2)
+        //   phase Y  K~^T of this step, (gate: the factors of this step, G0,) the flag of the step after next (G1), V and bY of the next (G2)
         //   phase O  Gamma.K of the next step (G3), then the stores of output tile 0 (G5a; not with the gate, which needs all of it first)
         //   phase S  the small piece and Gamma.Q of the next step (G4), then the stores of tile 1, or of both (G5b)
         // (gate: the stores, all of them in phase S, ahead of the loads there: behind them they hold up the phase's end, a store of
@@ -365,10 +374,10 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
             }
             __builtin_amdgcn_sched_barrier(0);
 
-            // ---- phase Y: Y[P] = V[P] + (-Gamma.K)(P, tau, s) S(tau, s), slot i: P = i / 8, (tau, s) = i % 8.  Tile 0 starts from
+            // ---- phase Y: Y[P] = bY (V[P] + (-Gamma.K)(P, tau, s) S(tau, s)), slot i: P = i / 8, (tau, s) = i % 8.  Tile 0 starts from
             // zero and has its V added at the end, by which time V has come through the LDS; tile 1 starts from V ----
             h8 Yb[2][2];                                         // fp16 copy of Y: registers 8 s .. 8 s + 7 of a tile are its slots of K-step s as a B operand
-            f32x16 av[2];                                        // Y: token tile P, columns of this wave
+            f32x16 av[2];                                        // Y / bY: token tile P, columns of this wave
             auto v_of = [&](const int P, const int j) __attribute__((always_inline)) {
                 const uint32_t w = vt[4 * P + j / 4][(j % 4) / 2];
                 return kTakesV ? __uint_as_float((j & 1) ? (w & 0xffff0000u) : (w << 16)) : 0.f;
@@ -380,6 +389,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                 };
                 static_for<0, LA>([&](auto ic) __attribute__((always_inline)) { ring[decltype(ic)::value % RING] = frag(decltype(ic)::value); });
                 if (kTakesV) get_v();
+                get_by();
                 if (kGate) { copy_state(0, 0); copy_state(0, 1); }
                 av[0] = f32x16{0.f};
                 static_for<0, 16>([&](auto ic) __attribute__((always_inline)) {
@@ -396,9 +406,10 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                         for (int z = 0; z < 4; ++z) av[1][4 * (i - 4) + z] = v_of(1, 4 * (i - 4) + z);
                     }
                     if constexpr (i >= 9 && i < 13) {
-                        constexpr int q = i - 9;
-#pragma unroll
-                        for (int z = 0; z < 4; ++z) Yb[0][q / 2][4 * (q % 2) + z] = (_Float16)(av[0][4 * q + z] + v_of(0, 4 * q + z));
+                        static_for<4 * (i - 9), 4 * (i - 8)>([&](auto jc) __attribute__((always_inline)) {
+                            constexpr int j = decltype(jc)::value;
+                            Yb[0][j / 8][j % 8] = (_Float16)((av[0][j] + v_of(0, j)) * row_broadcast<j>(by[0]));
+                        });
                     }
                     // G1 (and G0, this step's gate factors) and G2, one instruction per slot; V of the next step goes over that of this
                     // one, which has to be in registers first
@@ -415,6 +426,9 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                             for (int z = 0; z < 8; ++z) asm volatile("" :: "v"(vt[z]));
                         }
                         dma1_row(m0V + (y - 1) * 1024, voff_v + (uint32_t)(16 * (y - 1)) * v_pitch, rows);
+                    } else if constexpr (y == 5) {
+                        asm volatile("" :: "v"(by[0]), "v"(by[1]));
+                        dma1_word(m0By, (uint32_t)(kFull ? lane : lane_now()) * 4, nxt + kOffBy);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 });
@@ -434,9 +448,11 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                     S[t][j] *= row_broadcast<j>(gcv[t]);
                 });
             };
-            auto take_y1 = [&](const int q) __attribute__((always_inline)) {
-#pragma unroll
-                for (int z = 0; z < 4; ++z) Yb[1][q / 2][4 * (q % 2) + z] = (_Float16)av[1][4 * q + z];
+            auto take_y1 = [&](auto pc) __attribute__((always_inline)) {                         // a pair
+                static_for<2 * decltype(pc)::value, 2 * decltype(pc)::value + 2>([&](auto jc) __attribute__((always_inline)) {
+                    constexpr int j = decltype(jc)::value;
+                    Yb[1][j / 8][j % 8] = (_Float16)(av[1][j] * row_broadcast<j>(by[1]));
+                });
             };
             // O^T accumulator: lane (token 32 P + x, hh), registers 4 q .. 4 q + 3 = columns 32 c + 8 q + 4 hh + 0..3:
             // a token's 128 bytes of this wave's columns sit in two lanes, 16 bytes per register group.  Stored
@@ -523,7 +539,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                     ao[rr] = kRowsOut ? __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[i % RING], b, ao[rr], 0, 0, 0)
                                       : __builtin_amdgcn_mfma_f32_32x32x16_f16(b, ring[i % RING], ao[rr], 0, 0, 0);
                     if constexpr (qi >= 0) scale_state(std::integral_constant<int, qi / 4>{}, std::integral_constant<int, qi % 4>{});
-                    if constexpr (i < 4) take_y1(i);
+                    if constexpr (i < 8) take_y1(ic);
                     if constexpr (i < 4) dma1(m0K + i * 1024, voff_big, nxt + kOffKg + i * 1024);      // G3
                     if constexpr (G5a > 0) {                                                           // G5a
                         if constexpr (!kRowsOut && i == 11) prepare_out(0, 0);
@@ -532,7 +548,7 @@ __device__ __forceinline__ bool kda_scan4_body(uint8_t *lds, const uint8_t *slot
                     __builtin_amdgcn_sched_barrier(0);
                 });
             } else {
-                static_for<0, 4>([&](auto ic) __attribute__((always_inline)) { take_y1(decltype(ic)::value); });
+                static_for<0, 8>([&](auto ic) __attribute__((always_inline)) { take_y1(ic); });
                 static_for<0, 16>([&](auto ic) __attribute__((always_inline)) {
                     scale_state(std::integral_constant<int, decltype(ic)::value / 4>{}, std::integral_constant<int, decltype(ic)::value % 4>{});
                 });
