@@ -134,7 +134,8 @@ size_t kda_chunk_fwd_min_workspace_size(const kda_dims *dims);
  * throughout; KDA_BF16 inputs use fp16 matrix-core operands with fp32
  * accumulation, fp32 cumulative decay and an fp32 state.  Domain of the KDA_BF16
  * path: |k_t| <= 4 and entries of q within +-3.9 (the paper's q and k are
- * L2-normalised, Section 4), and states, values and pseudo-values small enough for
+ * L2-normalised, Section 4), and states, values, pseudo-values and k_t^T S (what the
+ * key of a token reads of the state that its chunk starts from) small enough for
  * fp16 (below 65504 in magnitude).  bf16 inputs convert to fp16 exactly while their magnitude is
  * zero or within [2^-14, 65504]; smaller ones lose bits or flush, larger ones
  * become infinite.  Beyond the domain an fp16 operand overflows to infinity and

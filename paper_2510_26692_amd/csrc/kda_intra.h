@@ -74,17 +74,23 @@ __device__ __forceinline__ uint32_t pack_h2(float a, float b)
 }
 
 // beta is cut in two factors.  One, a power of two, meets the residual V - (Gamma.K) S in the sequential stage; the other goes with the
-// inverse into Tril(A_qk) M and M^T (Gamma^{i->C}.K).  Both sides are rounded to fp16, and a beta of 2^-e takes e / 2 binades off either: all of it on the
-// products (k of unit norm is near 2^-3.5, scale * A_qk near 2^-7) sends them into the subnormals from e = 7 on, all of it on the
-// residual does so to small values.  A beta up to 1 leaves at most 1/2 for the residual, which then stays finite while both
-// its terms are at most 65504.  Errors (2-norm of o against fp64, unit q and k, scale 128^-1/2, logits of beta near 0 / -6 / -8 / -10 / -12):
-// 3.3e-4 / 2.9e-4 / 3.1e-4 / 4.2e-4 / 1.6e-3; all on the products 3.3e-4 / 1.2e-3 / 7.6e-3 / 4.8e-2 / 2.4e-1; all on the residual
-// 3.4e-4 / 3.3e-4 / 3.0e-4 / 3.7e-4 / 1.9e-3, but 1.2 times the error of the final state at the first and 3 to 5 times at v near 1e-3 and logits near -4.
-// 0 and subnormals: 2^-64 and what is left; infinity and NaN stay in the second factor.
+// inverse into Tril(A_qk) M and M^T (Gamma^{i->C}.K).  Both sides are rounded to fp16.
+//   A weak beta: all of it on the products (k of unit norm is near 2^-3.5, scale * A_qk near 2^-7) sends them into the subnormals from 2^-7 on, all of it
+//   on the residual does so to small values.  Below 2^-4 each side takes half of the binades.
+//   A beta of 2^-4 and more: the residual takes its exponent, at most 1/2, so that it stays finite wherever the pseudo-value beta (v - S^T k) of
+//   a first token does, and wherever v and S^T k are at most 65504.
+// Errors (2-norm of o against fp64, unit q and k, scale 128^-1/2, logits of beta near 0 / -6 / -8 / -10 / -12):
+// 3.3e-4 / 2.9e-4 / 3.0e-4 / 3.6e-4 / 1.4e-3; all on the products 3.3e-4 / 1.2e-3 / 7.6e-3 / 4.8e-2 / 2.4e-1; all on the residual
+// 3.4e-4 / 3.3e-4 / 3.0e-4 / 3.7e-4 / 1.9e-3, but 1.2 times the error of the final state at the first and 2 to 6 times at v near 1e-3 and logits from -4 on.
+// 0 and subnormals: 2^-65 and what is left; infinity and NaN stay in the second factor.
 // (us with all of beta on the products / cut in two, 32 more multiplications a lane and step of the scan: 333 tokens x 32 heads 29.1 / 29.6, 4 x 4096 x 16 heads
 // 182.3 / 184.9, eight packed sequences (20 000 chunks and heads) 812.6 / 820.4, 2^17 tokens x 32 heads 2480 / 2497.  With bY on Gamma.K in
 // this stage and on V in the scan, 16 there and 32 here: 29.9 / 186.3 / 825.0 / 2500.)
-__device__ __forceinline__ int beta_exponent(float b) { return (((int)((__float_as_uint(b) >> 23) & 0xffu) - 126) >> 1) - 1; }
+__device__ __forceinline__ int beta_exponent(float b)
+{
+    const int e = (int)((__float_as_uint(b) >> 23) & 0xffu) - 127;               // floor of log2 |b|
+    return e >= -4 ? (e < -1 ? e : -1) : ((e + 5) >> 1) - 4;
+}
 __device__ __forceinline__ float beta_on_y(float b) { return __uint_as_float((uint32_t)(127 + beta_exponent(b)) << 23); }
 __device__ __forceinline__ float beta_on_m(float b) { return b * __uint_as_float((uint32_t)(127 - beta_exponent(b)) << 23); }
 

@@ -63,10 +63,12 @@ def test_weak_beta_through_ranges():
     print("ranges: err_o %.2e err_hT %.2e" % (eo, eh))
 
 
-@pytest.mark.parametrize("beta", [0.0, 2.0 ** -130, 2.0 ** -126, 2.0 ** -24, 0.25, 0.25 - 2.0 ** -10, 0.5, 0.5 + 2.0 ** -8, 1.0, 1.5])
+@pytest.mark.parametrize("beta", [0.0, 2.0 ** -130, 2.0 ** -126, 2.0 ** -24, 2.0 ** -6, 2.0 ** -5, 2.0 ** -4 - 2.0 ** -12, 2.0 ** -4, 0.25 - 2.0 ** -10, 0.25,
+                                  0.5, 0.5 + 2.0 ** -8, 1.0, 1.5, 2.0, 6.0])
 def test_beta_at_the_edges_of_its_factors(beta):
-    """One and the same beta for every token: zero, a subnormal, powers of two of odd and even exponent and their neighbours."""
-    x = si.make_prefill(1, 150, 2, D, D, "bf16", -2.0, 41, 0.5)
+    """One and the same beta for every token: zero, a subnormal, powers of two of odd and even exponent, their neighbours, and one
+    above 1 (few tokens then: the recurrence itself grows)."""
+    x = si.make_prefill(1, 150 if beta < 2.0 else 20, 2, D, D, "bf16", -2.0, 41, 0.5)
     x["beta"] = torch.full_like(x["beta"], beta)
     assert beta == 0.0 or float(x["beta"].float().max()) == beta
     eo, eh = check_prefill(x, TOL)
