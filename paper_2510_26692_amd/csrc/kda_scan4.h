@@ -76,46 +76,55 @@ __device__ __forceinline__ void static_for(F &&f)
 // 217 / 205, eight packed sequences (20 000 chunks and heads) 894 / 840, gated layer 449 / 441, 2^17 tokens x 32 heads 2625 / 2588.
 // (nt on the slot's stores: worse everywhere, 226 for
 // the first.  On o in bf16, of whose lines an instruction writes pieces: 4 x 4096 x 16 heads 174, without 170, 8 x 2048 x 16 171 / 168.) ----
+// A memory instruction may read a scalar register five wait states after a vector instruction wrote it, not before, and the compiler, which
+// brings spilled scalar registers back with v_readlane, keeps that distance for its own instructions and not for
+// text.  Every address therefore passes through a scalar move here (whose read is interlocked), and a descriptor, of four registers, is waited for.  (A flag load right behind
+// the v_readlane of its base's upper half read from 4 GiB multiples away.  us before / now: 333 tokens x 32 heads 28.3 / 28.8, 16 pairs x 47 chunks with
+// slow decay 125.8 / 126.7, 8 pairs x 24 chunks with the gate 75.8 / 76.2, 4 x 4096 x 16 heads 166, 4 x 8192 x 32 613 either way; with waits everywhere 29.3, 128.0, 78.7.)
 constexpr int kCacheStream = 2;                              // nt, for stores
 // Four LDS-direct loads: lane L of the wave moves 16 bytes from src + voff + 1024 j to LDS byte
 // m0 + 1024 j + 16 L, j = 0..3 (the instruction offset applies to both addresses).
 __device__ __forceinline__ void dma4(uint32_t m0, uint32_t voff, const uint8_t *src)
 {
-    asm volatile("s_mov_b32 m0, %0\n\t"
-                 "s_nop 0\n\t"
-                 "global_load_lds_dwordx4 %1, %2 sc1 nt\n\t"
-                 "global_load_lds_dwordx4 %1, %2 offset:1024 sc1 nt\n\t"
-                 "global_load_lds_dwordx4 %1, %2 offset:2048 sc1 nt\n\t"
-                 "global_load_lds_dwordx4 %1, %2 offset:3072 sc1 nt"
-                 :: "s"(m0), "v"(voff), "s"(src) : "memory", "m0");
+    const uint8_t *at;
+    asm volatile("s_mov_b32 m0, %1\n\t"
+                 "s_mov_b64 %0, %3\n\t"
+                 "global_load_lds_dwordx4 %2, %0 sc1 nt\n\t"
+                 "global_load_lds_dwordx4 %2, %0 offset:1024 sc1 nt\n\t"
+                 "global_load_lds_dwordx4 %2, %0 offset:2048 sc1 nt\n\t"
+                 "global_load_lds_dwordx4 %2, %0 offset:3072 sc1 nt"
+                 : "=&s"(at) : "s"(m0), "v"(voff), "s"(src) : "memory", "m0");
 }
 // One LDS-direct load of 16 bytes per lane: LDS byte m0 + 16 L <- src[voff(L)].
 __device__ __forceinline__ void dma1(uint32_t m0, uint32_t voff, const uint8_t *src)
 {
-    asm volatile("s_mov_b32 m0, %0\n\t"
-                 "s_nop 0\n\t"
-                 "global_load_lds_dwordx4 %1, %2 sc1 nt"
-                 :: "s"(m0), "v"(voff), "s"(src) : "memory", "m0");
+    const uint8_t *at;
+    asm volatile("s_mov_b32 m0, %1\n\t"
+                 "s_mov_b64 %0, %3\n\t"
+                 "global_load_lds_dwordx4 %2, %0 sc1 nt"
+                 : "=&s"(at) : "s"(m0), "v"(voff), "s"(src) : "memory", "m0");
 }
 // The same of 4 bytes per lane: LDS byte m0 + 4 L <- src[voff(L)].
 __device__ __forceinline__ void dma1_word(uint32_t m0, uint32_t voff, const uint8_t *src)
 {
-    asm volatile("s_mov_b32 m0, %0\n\t"
-                 "s_nop 0\n\t"
-                 "global_load_lds_dword %1, %2 sc1 nt"
-                 :: "s"(m0), "v"(voff), "s"(src) : "memory", "m0");
+    const uint8_t *at;
+    asm volatile("s_mov_b32 m0, %1\n\t"
+                 "s_mov_b64 %0, %3\n\t"
+                 "global_load_lds_dword %2, %0 sc1 nt"
+                 : "=&s"(at) : "s"(m0), "v"(voff), "s"(src) : "memory", "m0");
 }
 // One LDS-direct load of 16 bytes per lane through a descriptor (zeros past its end): LDS byte m0 + 16 L <- row byte voff(L).
 __device__ __forceinline__ void dma1_row(uint32_t m0, uint32_t voff, const u32x4 &rsrc)
 {
     asm volatile("s_mov_b32 m0, %0\n\t"
-                 "s_nop 0\n\t"
+                 "s_nop 3\n\t"
                  "buffer_load_dwordx4 %1, %2, 0 offen lds"
                  :: "s"(m0), "v"(voff), "s"(rsrc) : "memory", "m0");
 }
 __device__ __forceinline__ void load1(u32x4 &a, uint32_t voff, const uint8_t *src)
 {
-    asm volatile("global_load_dwordx4 %0, %1, %2 sc1 nt" : "=&v"(a) : "v"(voff), "s"(src) : "memory");
+    const uint8_t *at;
+    asm volatile("s_mov_b64 %1, %3\n\tglobal_load_dwordx4 %0, %2, %1 sc1 nt" : "=&v"(a), "=&s"(at) : "v"(voff), "s"(src) : "memory");
 }
 // lane i of each quad of four lanes receives the value of lane kSel[i] of the quad
 template <int kCtrl> __device__ __forceinline__ float quad_perm(float v)
@@ -147,7 +156,8 @@ __device__ __forceinline__ void quad_transpose(float (&r)[4], int lane)
 }
 __device__ __forceinline__ void load_word(uint32_t &w, uint32_t voff, const uint32_t *src)
 {
-    asm volatile("global_load_dword %0, %1, %2 sc1" : "=&v"(w) : "v"(voff), "s"(src) : "memory");
+    const uint32_t *at;
+    asm volatile("s_mov_b64 %1, %3\n\tglobal_load_dword %0, %2, %1 sc1" : "=&v"(w), "=&s"(at) : "v"(voff), "s"(src) : "memory");
 }
 template <int N> __device__ __forceinline__ void wait_vm()
 {

@@ -115,3 +115,59 @@ def test_no_prefill_kernel_waits_for_each_load_of_a_state_before_the_next(tmp_pa
             elif ins.startswith(("global_store", "flat_store", "v_mfma", "s_barrier", "ds_")):
                 run, waited = 0, False
         assert longest < 8, (name, longest)
+
+
+def _scalar_registers(operands):
+    found = set()
+    for first, last, one in re.findall(r"\bs\[(\d+):(\d+)\]|\bs(\d+)\b", operands):
+        found |= {int(one)} if one else set(range(int(first), int(last) + 1))
+    return found
+
+
+def _written_by_vector(ins):
+    """Scalar registers that a vector instruction writes."""
+    op, _, rest = ins.partition(" ")
+    operands = rest.split(",")
+    if op in ("v_readlane_b32", "v_readfirstlane_b32") or op.startswith("v_cmp"):
+        return _scalar_registers(operands[0])
+    return _scalar_registers(operands[1]) if "_co_" in op and len(operands) > 1 else set()
+
+
+def early_scalar_reads(code):
+    """Memory instructions that read a scalar register less than five wait states after a vector instruction wrote it: they read
+    the register as it was before.  [(position, instruction that wrote, memory instruction), ..]"""
+    found = []
+    for i, ins in enumerate(code):
+        if not ins.startswith(("buffer_", "global_", "flat_", "scratch_")):
+            continue
+        open_, states, j = _scalar_registers(ins), 0, i - 1
+        while open_ and j >= 0 and states < 5:
+            before = code[j]
+            if before.startswith("v_") and _written_by_vector(before) & open_:
+                found.append((i, before, ins))
+                break
+            if before.startswith("s_") and not before.startswith(("s_cmp", "s_bitcmp", "s_waitcnt", "s_nop", "s_barrier", "s_cbranch", "s_branch")):
+                open_ -= _scalar_registers(before.partition(" ")[2].split(",")[0])       # (written again by a scalar instruction: no wait needed)
+            states += int(before.split()[1]) + 1 if before.startswith("s_nop") else 1
+            j -= 1
+    return found
+
+
+def test_early_scalar_reads_are_found():
+    base = ["v_readlane_b32 s3, v255, 21"]
+    load = ["global_load_dword v73, v78, s[2:3] sc1"]
+    assert len(early_scalar_reads(base + load)) == 1
+    assert len(early_scalar_reads(base + ["s_mov_b32 m0, s5", "s_nop 0"] + load)) == 1
+    assert not early_scalar_reads(base + ["s_nop 4"] + load)
+    assert not early_scalar_reads(base + ["s_mov_b64 s[2:3], s[2:3]"] + load)
+    assert len(early_scalar_reads(["v_cmp_eq_u32_e64 s[4:5], v0, v1", "buffer_load_dwordx4 v177, s[4:7], 0 offen lds"])) == 1
+
+
+@pytest.mark.skipif(not os.path.exists(_OBJDUMP), reason="needs llvm-objdump")
+def test_no_memory_instruction_reads_a_scalar_register_too_early(tmp_path):
+    """The compiler keeps the distance for the instructions it makes; those written as text have to keep it themselves."""
+    lib = os.path.join(ROOT, "paper_2510_26692_amd", "libkda.so")
+    if not os.path.exists(lib):
+        pytest.skip("no library: build it first (python -m paper_2510_26692_amd.build)")
+    for name, code in _kernel_code(lib, tmp_path, "kda_").items():
+        assert early_scalar_reads(code) == [], name
