@@ -144,3 +144,33 @@ def check_prefill(d, tol, scale=1.0, **kw):
     assert eo <= tol, "o error %.3e exceeds %.1e" % (eo, tol)
     assert eh <= tol, "hT error %.3e exceeds %.1e" % (eh, tol)
     return eo, eh
+
+
+def check_form(form, lens, H, tol, seed, scale=1.0, beta_mean=0.0, h0_std=0.0, out_dtype=torch.float32):
+    """One of the bf16 prefill's forms ("plain": decay per channel, "scalar": per head, "raw": projections) on packed sequences of
+    128-channel heads, beta = Sigmoid(N(beta_mean, 1)), against the oracle; returns (err_o, err_hT).  tol: of both; out_dtype bf16 adds
+    half a unit in the last place of o, at most 2^-8 of the value (8 significant bits)."""
+    import paper_2510_26692_amd as kda
+    d = 128
+    gen = torch.Generator().manual_seed(seed + 7)
+    logit = (torch.randn(1, int(sum(lens)), H, generator=gen) + beta_mean).to(torch.bfloat16)
+    x = si.make_varlen(lens, H, d, d, "bf16", -2.0, seed, h0_std)
+    cu = x["cu_seqlens"].numpy().astype(np.int64)
+    beta = torch.sigmoid(logit.float()).to(torch.bfloat16)
+    if form == "raw":
+        r = si.make_raw_tokens(1, int(sum(lens)), H, d, d, "bf16", -2.0, seed)
+        args, run, ref = [r["q_raw"], r["k_raw"], r["v"], r["gate"], logit], kda.kda_chunk_fwd_fused, oracle.kda_forward_raw
+    elif form == "scalar":
+        args = [x["q"], x["k"], x["v"], x["log_alpha"][..., 0].contiguous(), beta]
+        run, ref = kda.kda_chunk_fwd_scalar_gate, oracle.kda_forward_scalar_gate
+    else:
+        args, run, ref = [x["q"], x["k"], x["v"], x["log_alpha"], beta], kda.kda_chunk_fwd, oracle.kda_forward
+    o, hT = run(*(t.cuda() for t in args), h0=None if x["h0"] is None else x["h0"].cuda(), cu_seqlens=x["cu_seqlens"].cuda(), scale=scale,
+                out_dtype=out_dtype, check=True)
+    torch.cuda.synchronize()
+    o_ref, h_ref = ref(*(si.to_np32(t) for t in args), h0=None if x["h0"] is None else x["h0"].numpy().astype(np.float64), cu_seqlens=cu, scale=scale)
+    eo = worst_slice_err(o.float().cpu().numpy(), o_ref, o_slices(1, H, cu))
+    eh = worst_slice_err(hT.cpu().numpy(), h_ref, state_slices(len(lens), H))
+    assert eo <= tol + (2.0 ** -8 if out_dtype == torch.bfloat16 else 0.0), "o error %.3e" % eo
+    assert eh <= tol, "hT error %.3e" % eh
+    return eo, eh

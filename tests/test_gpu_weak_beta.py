@@ -1,13 +1,11 @@
 """bf16 prefill with write gates that are nearly shut.  What a small beta multiplies is rounded to fp16 on its way through the matrix
 cores, and keys of unit norm and scale * A_qk are small already: beta must not take them into the subnormals.  Against the
 fp64 oracle, at the tolerance of every other bf16 prefill; the factors that beta is cut into keep the error near that of open gates (4.5e-4)."""
-import numpy as np
 import pytest
 import torch
 
-import oracle
 import synth_inputs as si
-from helpers import check_prefill, o_slices, state_slices, worst_slice_err
+from helpers import check_form, check_prefill
 
 pytestmark = pytest.mark.gpu
 
@@ -15,46 +13,19 @@ TOL = 2e-3
 D = 128
 
 
-def _beta(shape, mean, seed):
-    """Sigmoid(N(mean, 1)) as logits and as values, bf16."""
-    logit = (torch.randn(*shape, generator=torch.Generator().manual_seed(seed)) + mean).to(torch.bfloat16)
-    return logit, torch.sigmoid(logit.float()).to(torch.bfloat16)
-
-
 @pytest.mark.parametrize("scale", [1.0, D ** -0.5])
 @pytest.mark.parametrize("mean", [-4.0, -6.0, -8.0, -10.0])
 @pytest.mark.parametrize("form", ["plain", "scalar", "raw"])
 def test_weak_beta(form, mean, scale):
-    import paper_2510_26692_amd as kda
-    H, T, seed = 3, 333, int(-10 * mean) + len(form)
-    logit, beta = _beta((1, T, H), mean, seed)
-    if form == "plain":
-        x = si.make_prefill(1, T, H, D, D, "bf16", -2.0, seed, 0.0)
-        x["beta"] = beta
-        eo, eh = check_prefill(x, TOL, scale=scale)
-    elif form == "scalar":
-        x = si.make_prefill(1, T, H, D, D, "bf16", -2.0, seed, 0.0)
-        args = [x["q"], x["k"], x["v"], x["log_alpha"][..., 0].contiguous(), beta]
-        o, hT = kda.kda_chunk_fwd_scalar_gate(*(t.cuda() for t in args), scale=scale, check=True)
-        o_ref, h_ref = oracle.kda_forward_scalar_gate(*(si.to_np32(t) for t in args), scale=scale)
-    else:
-        x = si.make_raw_tokens(1, T, H, D, D, "bf16", -2.0, seed)
-        args = [x["q_raw"], x["k_raw"], x["v"], x["gate"], logit]
-        o, hT = kda.kda_chunk_fwd_fused(*(t.cuda() for t in args), scale=scale, check=True)
-        o_ref, h_ref = oracle.kda_forward_raw(*(si.to_np32(t) for t in args), scale=scale)
-    if form != "plain":
-        torch.cuda.synchronize()
-        eo = worst_slice_err(o.cpu().numpy(), o_ref, o_slices(1, H))
-        eh = worst_slice_err(hT.cpu().numpy(), h_ref, state_slices(1, H))
+    eo, eh = check_form(form, [333], 3, TOL, int(-10 * mean) + len(form), scale=scale, beta_mean=mean)
     print("%s mean %g scale %.2f: err_o %.2e err_hT %.2e" % (form, mean, scale, eo, eh))
-    assert eo <= TOL and eh <= TOL
 
 
 def test_weak_beta_through_ranges():
     """The passes without outputs apply the factor of beta themselves: slow decay, so that their results count."""
     import paper_2510_26692_amd as kda
     x = si.make_prefill(1, 64 * 60 - 11, 2, D, D, "bf16", -6.0, 31, 0.0)
-    x["beta"] = _beta(x["beta"].shape, -8.0, 32)[1]
+    x["beta"] = torch.sigmoid(torch.randn(x["beta"].shape, generator=torch.Generator().manual_seed(32)) - 8.0).to(torch.bfloat16)
     try:
         kda.kda_debug_set_time_split(8)
         eo, eh = check_prefill(x, TOL, scale=D ** -0.5)
