@@ -373,10 +373,11 @@ def main():
         ms_mfma = _time_region(torch, lambda: kda.kda_debug_mfma_probe(sink, wgs, 2000), 5)
         head["roofline"]["measured_mfma_f16_TFLOPs"] = flops / (ms_mfma * 1e-3) / 1e12
         head["roofline"]["mfma_peak_TFLOPs"] = MFMA_PEAK_TFLOPS
-        # the data movement of the two-stage design per (chunk, head) and nothing else (64 KiB in, a 72 KiB slot
-        # written and read back, 32 KiB out), by a plain kernel on 65 536 items (the item count of a prefill of
-        # 2^17 tokens x 32 heads): the level a prefill that is bound by its own traffic is read against
-        tbuf = torch.empty(65536 * 172032, dtype=torch.uint8, device=dev)
+        # the data movement of the two-stage design per (chunk, head) and nothing else (64 KiB in, 54.75 KiB of a slot
+        # written and read back from memory, 32 KiB out), by a plain kernel on 65 536 items (the item count of a prefill of
+        # 2^17 tokens x 32 heads): what a prefill that is bound by its own traffic is read against (it may take less,
+        # where slots are read back from the caches)
+        tbuf = torch.empty(65536 * 154368, dtype=torch.uint8, device=dev)
         items, moved = kda.kda_debug_prefill_traffic_probe(tbuf)
         ms_t = _time_region(torch, lambda: kda.kda_debug_prefill_traffic_probe(tbuf), 5)
         del tbuf

@@ -3,6 +3,7 @@
 // what this device delivers as well as against its data-sheet peaks.
 #include "kda_common.h"
 #include "kda_debug.h"
+#include "kda_mfma_layout.h"
 
 namespace kda {
 
@@ -30,25 +31,35 @@ __global__ __launch_bounds__(256) void kda_stream_probe_kernel(float *buf, float
     }
 }
 
-// mode 3: the data movement of the two-stage prefill and nothing else.  Item i (one chunk of one head) reads 64 KiB of
-// streamed input, writes a 72 KiB slot, reads the slot of another item (written by another workgroup) and writes
-// 32 KiB of streamed output: 240 KiB through the memory system per item, as kda_prefill_kernel moves per chunk with
-// bf16 inputs and fp32 o.  The buffer holds `items` records of 168 KiB: [64 KiB in][72 KiB slot][32 KiB out].
-constexpr int kItemIn = 65536, kItemSlot = 73728, kItemOut = 32768, kItemBytes = kItemIn + kItemSlot + kItemOut;
+// The data movement of the two-stage prefill and nothing else.  Item i (one chunk of one head) reads 48 KiB of streamed input (q, k, log
+// alpha), writes what a slot holds, reads the slot of another item (written by another workgroup) and 16 KiB of streamed input (V), and
+// writes 32 KiB of streamed output: 205.5 KiB through the memory system per item, as kda_prefill_kernel moves per chunk with
+// bf16 inputs and fp32 o.  The buffer holds `items` records [48 KiB in][slot][16 KiB V][32 KiB out].
+constexpr int kItemIn = 49152, kItemSlot = mfma::kOffBy + kChunk * 4, kItemV = 16384, kItemOut = 32768;
+constexpr int kItemBytes = kItemIn + kItemSlot + kItemV + kItemOut;
+constexpr int kSlotRest = kItemSlot % 4096 / 16;              // threads that take part in a slot's last round
+static_assert(kItemSlot == 56064 && kItemBytes == 154368, "the sizes that kda_debug.h states");
 __global__ __launch_bounds__(256) void kda_prefill_traffic_probe_kernel(uint8_t *buf, unsigned items, float a)
 {
     const unsigned i = blockIdx.x, j = (i + items / 2) % items;
-    const f32x4 *in = reinterpret_cast<const f32x4 *>(buf + (size_t)i * kItemBytes) + threadIdx.x;
-    f32x4 *slot = reinterpret_cast<f32x4 *>(buf + (size_t)i * kItemBytes + kItemIn) + threadIdx.x;
+    uint8_t *item = buf + (size_t)i * kItemBytes;
+    const f32x4 *in = reinterpret_cast<const f32x4 *>(item) + threadIdx.x;
+    f32x4 *slot = reinterpret_cast<f32x4 *>(item + kItemIn) + threadIdx.x;
     const f32x4 *other = reinterpret_cast<const f32x4 *>(buf + (size_t)j * kItemBytes + kItemIn) + threadIdx.x;
-    f32x4 *out = reinterpret_cast<f32x4 *>(buf + (size_t)i * kItemBytes + kItemIn + kItemSlot) + threadIdx.x;
+    const f32x4 *v = reinterpret_cast<const f32x4 *>(item + kItemIn + kItemSlot) + threadIdx.x;
+    f32x4 *out = reinterpret_cast<f32x4 *>(item + kItemIn + kItemSlot + kItemV) + threadIdx.x;
+    const bool rest = threadIdx.x < kSlotRest;
     f32x4 acc = {a, a, a, a};
 #pragma unroll
     for (int m = 0; m < kItemIn / 4096; ++m) acc += __builtin_nontemporal_load(in + m * 256);
 #pragma unroll
     for (int m = 0; m < kItemSlot / 4096; ++m) __builtin_nontemporal_store(acc, slot + m * 256);
+    if (rest) __builtin_nontemporal_store(acc, slot + kItemSlot / 4096 * 256);
 #pragma unroll
     for (int m = 0; m < kItemSlot / 4096; ++m) acc += __builtin_nontemporal_load(other + m * 256);
+    if (rest) acc += __builtin_nontemporal_load(other + kItemSlot / 4096 * 256);
+#pragma unroll
+    for (int m = 0; m < kItemV / 4096; ++m) acc += __builtin_nontemporal_load(v + m * 256);
 #pragma unroll
     for (int m = 0; m < kItemOut / 4096; ++m) __builtin_nontemporal_store(acc, out + m * 256);
 }
@@ -106,7 +117,7 @@ extern "C" kda_status kda_debug_prefill_traffic_probe(void *buffer, size_t bytes
                        static_cast<uint8_t *>(buffer), (unsigned)items, 0.5f);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(KDA_ERR_LAUNCH, "kda_prefill_traffic_probe_kernel: %s", hipGetErrorString(e));
-    if (moved) *moved = items * (size_t)(kItemIn + 2 * kItemSlot + kItemOut);
+    if (moved) *moved = items * (size_t)(kItemIn + 2 * kItemSlot + kItemV + kItemOut);
     return KDA_OK;
 }
 

@@ -47,7 +47,9 @@ constexpr int kOffKt = kOffQp + 16 * kFragBytes;
 constexpr int kOffP = kOffKt + 16 * kFragBytes;     // 6 frags: token tile (0,1) of P is zero
 constexpr int kOffGc = kOffP + 6 * kFragBytes;
 constexpr int kOffBy = kOffGc + D * 4;
-constexpr int kSlotBytes = 72192;                   // the published size (callers keep workspaces); 16 KiB of it are spare
+// The distance from slot to slot, of which 15.75 KiB are spare: what a call asks for, and into how many time segments a smaller workspace
+// cuts it, follow from it, and callers (and tests) that work with these sizes are to find them as they were.
+constexpr int kSlotBytes = 72192;
 // Output gate (fused epilogue): the gate logits of a chunk, bf16, in the accumulator order of the
 // sequential kernel's O tiles: tile (rho, ct) = [2 units][64 lanes][16 B], lane (x, hh) holds the
 // columns 32 ct + 8 q + 4 hh + 0..3 of token 32 rho + x, q = 0..3 (unit q / 2, bytes 8 (q % 2) ..).
