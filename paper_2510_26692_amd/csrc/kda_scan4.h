@@ -15,8 +15,8 @@
 // share is read-only: the A operands Gamma.K, Gamma.Q, K~^T and P, 54 fragments of
 // 1 KiB per chunk, which all four waves read from LDS.
 //
-// Operand path.  LDS holds one step's operands: Gamma.K, V, Gamma.Q and K~^T, 16 KiB each, and a small piece (P
-// and gamma^C, 6.5 KiB).  All of them arrive by LDS-direct loads (global_load_lds, buffer_load .. lds: no registers
+// Operand path.  LDS holds one step's operands: Gamma.K, V, Gamma.Q and K~^T, 16 KiB each, a small piece (P
+// and gamma^C, 6.5 KiB) and bY, a copy for each wave.  All of them arrive by LDS-direct loads (global_load_lds, buffer_load .. lds: no registers
 // in between); a piece's place is refilled for the next step as soon as nobody reads it any more, so every piece has
 // the two phases of a step it is not used in to arrive.  A step has three phases (Y; O; state update) and
 // one workgroup barrier in front of each, which says two things at once: every wave's part of the phase's pieces has
