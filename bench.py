@@ -377,7 +377,7 @@ def main():
         # written and read back from memory, 32 KiB out), by a plain kernel on 65 536 items (the item count of a prefill of
         # 2^17 tokens x 32 heads): what a prefill that is bound by its own traffic is read against (it may take less,
         # where slots are read back from the caches)
-        tbuf = torch.empty(65536 * 154368, dtype=torch.uint8, device=dev)
+        tbuf = torch.empty(65536 * 172032, dtype=torch.uint8, device=dev)
         items, moved = kda.kda_debug_prefill_traffic_probe(tbuf)
         ms_t = _time_region(torch, lambda: kda.kda_debug_prefill_traffic_probe(tbuf), 5)
         del tbuf

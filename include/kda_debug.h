@@ -83,13 +83,13 @@ kda_status kda_debug_chunk_fwd_status(const kda_dims *dims, const void *workspac
 kda_status kda_debug_stream_probe(int mode, float *buffer, size_t bytes, void *hip_stream);
 /*
  * kda_debug_prefill_traffic_probe: the data movement of the two-stage matrix-core prefill and nothing else.  `buffer`
- * (device, 16-byte aligned, overwritten) holds bytes / 154 368 items of [48 KiB in][56 064 bytes of a slot][16 KiB V]
- * [32 KiB out]; one workgroup per item reads its input, writes its slot, reads the slot of the item half the buffer away
+ * (device, 16-byte aligned, overwritten) holds bytes / 172 032 items of [48 KiB in][56 064 bytes of a slot][16 KiB V]
+ * [32 KiB out][spare]; one workgroup per item reads its input, writes its slot, reads the slot of the item half the buffer away
  * (written by another workgroup of the launch or an earlier one) and its V and writes its output: 205.5 KiB through the
  * memory system per item, which is what kda_chunk_fwd moves per chunk and head with bf16 inputs and fp32 o.  *moved (may
  * be NULL) receives the bytes the launch moves.  The time of a launch is that of so many chunks whose slots all travel through
  * memory and back; a prefill, which picks a slot up soon after it was written, finds some of them in the caches and may
- * take less (2^20 tokens x 32 heads: 37.0 ns a chunk and head, the probe 40.4; with the slot of 2048 items before, 30.4).
+ * take less (2^20 tokens x 32 heads: 37.0 ns a chunk and head, the probe 39 to 41; with the slot of 2048 items before, 30.4).
  */
 kda_status kda_debug_prefill_traffic_probe(void *buffer, size_t bytes, size_t *moved, void *hip_stream);
 kda_status kda_debug_mfma_probe(float *sink, int workgroups, int iters, double *flops, void *hip_stream);

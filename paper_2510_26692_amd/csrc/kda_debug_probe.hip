@@ -34,11 +34,11 @@ __global__ __launch_bounds__(256) void kda_stream_probe_kernel(float *buf, float
 // The data movement of the two-stage prefill and nothing else.  Item i (one chunk of one head) reads 48 KiB of streamed input (q, k, log
 // alpha), writes what a slot holds, reads the slot of another item (written by another workgroup) and 16 KiB of streamed input (V), and
 // writes 32 KiB of streamed output: 205.5 KiB through the memory system per item, as kda_prefill_kernel moves per chunk with
-// bf16 inputs and fp32 o.  The buffer holds `items` records [48 KiB in][slot][16 KiB V][32 KiB out].
+// bf16 inputs and fp32 o.  The buffer holds `items` records of 168 KiB: [48 KiB in][slot][16 KiB V][32 KiB out][spare].
 constexpr int kItemIn = 49152, kItemSlot = mfma::kOffBy + kChunk * 4, kItemV = 16384, kItemOut = 32768;
-constexpr int kItemBytes = kItemIn + kItemSlot + kItemV + kItemOut;
+constexpr int kItemBytes = 172032;
 constexpr int kSlotRest = kItemSlot % 4096 / 16;              // threads that take part in a slot's last round
-static_assert(kItemSlot == 56064 && kItemBytes == 154368, "the sizes that kda_debug.h states");
+static_assert(kItemSlot == 56064 && kItemIn + kItemSlot + kItemV + kItemOut <= kItemBytes, "the sizes that kda_debug.h states");
 __global__ __launch_bounds__(256) void kda_prefill_traffic_probe_kernel(uint8_t *buf, unsigned items, float a)
 {
     const unsigned i = blockIdx.x, j = (i + items / 2) % items;

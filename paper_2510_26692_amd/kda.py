@@ -198,7 +198,7 @@ def kda_debug_stream_probe(mode, buffer):
 
 
 def kda_debug_prefill_traffic_probe(buffer):
-    """One launch of the prefill traffic probe over the uint8 device tensor `buffer` (a multiple of 154368 bytes,
+    """One launch of the prefill traffic probe over the uint8 device tensor `buffer` (a multiple of 172032 bytes,
     overwritten) on the current stream; returns (items, bytes moved)."""
     _check_dev(buffer)
     nbytes = buffer.numel() * buffer.element_size()
@@ -207,7 +207,7 @@ def kda_debug_prefill_traffic_probe(buffer):
                                                         _stream_ptr(buffer.device))
     if st != 0:
         raise KdaError(st, kda_last_error())
-    return nbytes // 154368, int(moved.value)
+    return nbytes // 172032, int(moved.value)
 
 
 def kda_debug_mfma_probe(sink, workgroups, iters):
